@@ -176,7 +176,7 @@ def bench_linear(args):
         "config": {"workload": f"{args.workload}: T={T} d_in={di} d_out={dn} r={r} bf16 forward+backward",
                    "algorithmic_tflop_per_step": step_flops / 1e12,
                    "mfma_frac_whole_step": step_flops / (ms_per_step / 1e3) / MFMA_BF16_PEAK},
-        "roofline": {"bound": "mfma", "kernel": "gemm_bf16_dl_kernel<256,256,64,2 stages,8 waves>",
+        "roofline": {"bound": "mfma", "kernel": "gemm_bf16_pp_kernel<256>",
                      "achieved": achieved / 1e12, "peak": MFMA_BF16_PEAK / 1e12, "unit": "TFLOP/s",
                      "frac": achieved / MFMA_BF16_PEAK, "launches_per_step": k_launches / args.steps,
                      "avg_launch_ms": avg_launch_s * 1e3, "traffic": None},
@@ -427,7 +427,7 @@ def main():
     else:
         alg_flops_per_launch = units_per_step * unit / max(launches_per_step, 1e-9)
         achieved = alg_flops_per_launch / avg_launch_s if launches_per_step else 0.0
-        roofline = {"bound": "mfma", "kernel": "gemm_bf16_dl_kernel<256,256,64,2 stages,8 waves>",
+        roofline = {"bound": "mfma", "kernel": "gemm_bf16_pp_kernel<256>",
                     "achieved": achieved / 1e12, "peak": MFMA_BF16_PEAK / 1e12,
                     "unit": "TFLOP/s", "frac": achieved / MFMA_BF16_PEAK,
                     "launches_per_step": launches_per_step,

@@ -123,12 +123,13 @@ MIXLORA_API int mixlora_ffn_forward(const mixlora_dims *dims, const mixlora_weig
  * code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Every
  * buffer that mixlora_ffn_forward takes from the caller's workspace (routing tables, grouped
  * activations, partial results of the split down projection, ...) lives instead in a device
- * array inside the library, MIXLORA_STATIC_SCRATCH_BYTES large, one copy per GPU, held until the
- * process ends.  The call allocates nothing and frees nothing; inputs and outputs are the
- * caller's as before, results are bit-identical to mixlora_ffn_forward.  Forward only: the
- * array is not a handle for mixlora_ffn_backward.
- *   - dims whose mixlora_workspace_bytes(dims, 0) exceeds MIXLORA_STATIC_SCRATCH_BYTES return
- *     MIXLORA_E_SCRATCH (checked on the host, nothing enqueued).  40 MiB covers the LLaMA-2 7B /
+ * array inside the library, one copy per GPU, held until the process ends:
+ * MIXLORA_STATIC_SCRATCH_BYTES, and 64 MiB for the partial tiles of matrix products cut along
+ * their contraction (calls of more than 128 tokens).  The call allocates nothing and frees
+ * nothing; inputs and outputs are the caller's as before, results are bit-identical to
+ * mixlora_ffn_forward.  Forward only: the array is not a handle for mixlora_ffn_backward.
+ *   - dims whose forward workspace, the partial tiles apart, exceeds MIXLORA_STATIC_SCRATCH_BYTES
+ *     return MIXLORA_E_SCRATCH (checked on the host, nothing enqueued).  40 MiB covers the LLaMA-2 7B /
  *     13B and LLaMA-3 8B shapes of this block up to 128 tokens per call (decode batches).
  *   - All calls on one GPU share that GPU's array and it keeps the previous call's contents; the
  *     call itself clears what has to start at zero.  Calls that overlap on one GPU (two streams,

@@ -31,7 +31,9 @@ struct Layout {
   size_t pg_tok, pg_tiles, pg_ntiles;   // tokens grouped by expert pair (csrc/fused_pg.hip)
   size_t G, U, Pg_all, Pu_all, a_grp, Q_all;
   // forward scratch
-  size_t a_comb, Qw, Bd_cat, rank_part, splitk, gp_scratch;
+  size_t a_comb, Qw, Bd_cat, rank_part, splitk, gp_scratch, gemm_part;
+  size_t gemm_floats;   // floats at gemm_part: partial tiles of GEMM launches cut along K
+  size_t base_end;      // forward workspace without them
   size_t fwd_end;
   // backward scratch
   size_t WdT, WgT, WuT, H, Bd_T, VB_all, dg_grp, du_grp, dgsum, dusum, dw_part, dw, Bg_T, Bu_T, AdT,
@@ -123,8 +125,18 @@ Layout make_layout(const mixlora_dims &D, int schedule = MIXLORA_SCHEDULE_LINEAR
   // few tokens (decode-shaped calls): partial outputs of the K-split down projection
   L.splitk = take(T <= SPLITK_MAX_ROWS ? (size_t)GEMM_MAX_PROBLEMS * T * d * 4 : 0);
   L.gp_scratch = take(kT > GROUP_SINGLE_WG_PAIRS ? group_pairs_scratch_bytes((int)T, (int)k) : 0);
-  L.fwd_end = o;
   L.Kx = up64((int)(2 * R) + (int)N);   // whole K tiles of the GEMM's DMA path
+  {   // scratch of both passes' GEMM launches: at most one partial tile per CU, none where no K range is long
+    // enough to cut (the longest is that of the input-gradient product)
+    const size_t slices = (2 * f + (size_t)L.Kx) / 64 / 4, rows = (pair_down ? kT : T) / 192 + 1;
+    const size_t tiles = rows * (2 * (f / 256 + 1) + d / 256 + 4) * slices;
+    size_t bytes = E == 2 && T > SPLITK_MAX_ROWS && slices >= 2 ? GEMM_SCRATCH_FLOATS * 4 : 0;
+    if (tiles < 256) bytes = bytes / 256 * tiles;
+    L.gemm_floats = bytes / 4;
+    L.base_end = o;
+    L.gemm_part = take(bytes);
+  }
+  L.fwd_end = o;
   L.nct = swiglu_col_tiles((int)f);
   L.WdT = take(f * d * E);
   L.WgT = take(f * d * E);
@@ -294,14 +306,16 @@ static int forward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mod
                         float *topk_w, int32_t *expert_counts, float *aux_loss, void *workspace,
                         size_t workspace_bytes, void *stream,
                         int schedule = MIXLORA_SCHEDULE_LINEAR_DOWN,
-                        const mixlora_dora *dora = nullptr) {
+                        const mixlora_dora *dora = nullptr,
+                        float *gemm_part = nullptr) {   // partial tiles elsewhere than in the workspace
   const Layout L = make_layout(Du, schedule, dora != nullptr);
   const bool pair_down = schedule != MIXLORA_SCHEDULE_LINEAR_DOWN;   // down projection per pair
   const bool vanilla = schedule == MIXLORA_SCHEDULE_VANILLA;         // gate/up per pair as well
-  if (workspace_bytes < L.fwd_end) return MIXLORA_E_WORKSPACE;
+  if (workspace_bytes < (gemm_part ? L.base_end : L.fwd_end)) return MIXLORA_E_WORKSPACE;
 
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   char *ws = reinterpret_cast<char *>(workspace);
+  const GemmScratch gs{gemm_part ? gemm_part : (float *)(ws + L.gemm_part), L.gemm_floats};
   mixlora_dims D = Du;   // the pass runs on the rank-padded banks
   D.r = L.rp;
   mixlora_weights wpad;
@@ -339,20 +353,24 @@ static int forward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mod
     add_seg(p[6], w->W_up, d, w->A_up, d, d);
     add_seg(p[7], w->W_down, f, w->A_down, f, f);
     if (vanilla) {   // unshared schedule: the frozen gate/up products follow the routing, per pair;
-      HIP_TRY(launch_gemm(dt, p + 4, 1, st));   // only the router logits are needed up front
+      HIP_TRY(launch_gemm(dt, p + 4, 1, st, gs));   // only the router logits are needed up front
     } else if (dora) {
       // the W_down product has the longest K range: its tiles go first so that they do not
       // trail the launch
-      const GemmProblem q[8] = {p[7], p[0], p[1], p[2], p[3], p[4], p[5], p[6]};
+      const GemmProblem q[8] = {p[7], p[2], p[3], p[4], p[5], p[6], p[0], p[1]};
       if (gemm_mixed_rows_ok(dt, q, 8)) {
-        HIP_TRY(launch_gemm(dt, q, 8, st));
+        HIP_TRY(launch_gemm(dt, q, 8, st, gs));
       } else {   // shapes outside the large-tile kernel: problems of different M go separately
-        HIP_TRY(launch_gemm(dt, p, 5, st));
-        HIP_TRY(launch_gemm(dt, p + 5, 2, st));
-        HIP_TRY(launch_gemm(dt, p + 7, 1, st));
+        HIP_TRY(launch_gemm(dt, p, 5, st, gs));
+        HIP_TRY(launch_gemm(dt, p + 5, 2, st, gs));
+        HIP_TRY(launch_gemm(dt, p + 7, 1, st, gs));
       }
     } else {
-      HIP_TRY(launch_gemm(dt, p, dt == MIXLORA_BF16 ? 5 : 4, st));
+      // the narrow problems go first: where the launch's last round is cut along K, it is frozen
+      // tiles that are cut, not the router's (whose logits then are summed in one order at every
+      // schedule)
+      const GemmProblem q[5] = {p[2], p[3], p[4], p[0], p[1]};
+      HIP_TRY(dt == MIXLORA_BF16 ? launch_gemm(dt, q, 5, st, gs) : launch_gemm(dt, p, 4, st));
     }
   }
   DoraArgs dargs{};
@@ -434,10 +452,10 @@ static int forward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mod
       add_seg(p[2], x, d, w->A_gate, d, d);
       add_seg(p[3], x, d, w->A_up, d, d);
       if (gemm_mixed_rows_ok(dt, p, 4)) {
-        HIP_TRY(launch_gemm(dt, p, 4, st));
+        HIP_TRY(launch_gemm(dt, p, 4, st, gs));
       } else {   // shapes outside the large-tile kernel: problems of different M go separately
-        HIP_TRY(launch_gemm(dt, p, 2, st));
-        HIP_TRY(launch_gemm(dt, p + 2, 2, st));
+        HIP_TRY(launch_gemm(dt, p, 2, st, gs));
+        HIP_TRY(launch_gemm(dt, p + 2, 2, st, gs));
       }
       Gsrc = ws + L.Gp;
       Usrc = ws + L.Up;
@@ -451,7 +469,7 @@ static int forward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mod
     GemmProblem p = problem(kT, d, ws + L.Op, d, 0);
     add_seg(p, ws + L.a_grp, f, w->W_down, f, f);
     add_seg(p, ws + L.Qp, R, ws + L.Bd_cat, R, R);
-    HIP_TRY(launch_gemm(dt, &p, 1, st));
+    HIP_TRY(launch_gemm(dt, &p, 1, st, gs));
     if (!dora) {
       HIP_TRY_AS(PROF_COMBINE, (double)(k + 1) * T * d * Eb, launch_pair_combine(dt, pc, d, ws + L.Op, y, 1, st));
       return MIXLORA_OK;
@@ -475,7 +493,7 @@ static int forward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mod
     GemmProblem p = problem(T, d, y, d, 0);
     add_seg(p, ws + L.a_comb, f, w->W_down, f, f);
     add_seg(p, ws + L.Qw, R, ws + L.Bd_cat, R, R);
-    HIP_TRY(launch_gemm(dt, &p, 1, st));
+    HIP_TRY(launch_gemm(dt, &p, 1, st, gs));
     return MIXLORA_OK;
   }
   // Algorithm 1 lines 11-13 on the routed pairs, expert-grouped rows
@@ -495,7 +513,7 @@ static int forward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mod
     // A_down of every expert on the grouped activations
     GemmProblem p = problem(kT, R, ws + L.Q_all, R, 1);
     add_seg(p, ws + L.a_grp, f, w->A_down, f, f);
-    HIP_TRY(launch_gemm(dt, &p, 1, st));
+    HIP_TRY(launch_gemm(dt, &p, 1, st, gs));
     // the block-sparse low-rank operand
     HIP_TRY_AS(PROF_OTHER, 0, launch_scatter_blocks(dt, pc, (float *)(ws + L.Q_all), 0, 1, R, 1, 1, ws + L.Qw, R, 0, st));
   }
@@ -528,13 +546,13 @@ static int forward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mod
       add_seg(p[used], ws + L.a_comb + (size_t)k0 * E, f, (const char *)w->W_down + (size_t)k0 * E, f, klen);
       if (used == 0) add_seg(p[0], ws + L.Qw, R, ws + L.Bd_cat, R, R);
     }
-    HIP_TRY(launch_gemm(dt, p, used, st));
+    HIP_TRY(launch_gemm(dt, p, used, st, gs));
     HIP_TRY_AS(PROF_OTHER, 0, launch_splitk_reduce(dt, part, used, (int64_t)T * d, y, st));
   } else {
     GemmProblem p = problem(T, d, y, d, 0);
     add_seg(p, ws + L.a_comb, f, w->W_down, f, f);
     add_seg(p, ws + L.Qw, R, ws + L.Bd_cat, R, R);
-    HIP_TRY(launch_gemm(dt, &p, 1, st));
+    HIP_TRY(launch_gemm(dt, &p, 1, st, gs));
   }
   return MIXLORA_OK;
 }
@@ -629,6 +647,7 @@ static int backward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mo
 
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   char *ws = reinterpret_cast<char *>(workspace);
+  const GemmScratch gs{(float *)(ws + L.gemm_part), L.gemm_floats};
   mixlora_dims D = Du;   // rank-padded banks (the forward pass left them in the workspace) and
   D.r = L.rp;            // rank-padded gradients, cut back to r entries at the end
   mixlora_weights wpad;
@@ -686,16 +705,16 @@ static int backward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mo
     add_seg(p[0], ws + L.dYp, d, WdT, d, d);
     add_seg(p[1], dy, d, ws + L.Bd_T, d, d);
     if (gemm_mixed_rows_ok(dt, p, 2)) {
-      HIP_TRY(launch_gemm(dt, p, 2, st));
+      HIP_TRY(launch_gemm(dt, p, 2, st, gs));
     } else {   // shapes outside the large-tile kernel: problems of different M go separately
-      HIP_TRY(launch_gemm(dt, p, 1, st));
-      HIP_TRY(launch_gemm(dt, p + 1, 1, st));
+      HIP_TRY(launch_gemm(dt, p, 1, st, gs));
+      HIP_TRY(launch_gemm(dt, p + 1, 1, st, gs));
     }
   } else {
     GemmProblem p[2] = {problem(T, f, ws + L.H, f, 0), problem(T, R, ws + L.VB_all, R, 1)};
     add_seg(p[0], dy, d, WdT, d, d);
     add_seg(p[1], dy, d, ws + L.Bd_T, d, d);
-    HIP_TRY(launch_gemm(dt, p, 2, st));
+    HIP_TRY(launch_gemm(dt, p, 2, st, gs));
   }
   const int rows_mode = (pair_down ? ROWS_H : 0) | (vanilla ? ROWS_GU | ROWS_SPARSE : 0);
   DoraArgs dargs{};
@@ -741,7 +760,7 @@ static int backward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mo
     GemmProblem p[2] = {problem(kT, R, ws + L.TG_all, R, 1), problem(kT, R, ws + L.TU_all, R, 1)};
     add_seg(p[0], ws + L.dg_grp, f, ws + L.Bg_T, f, f);
     add_seg(p[1], ws + L.du_grp, f, ws + L.Bu_T, f, f);
-    HIP_TRY(launch_gemm(dt, p, 2, st));
+    HIP_TRY(launch_gemm(dt, p, 2, st, gs));
   }
   if (!vanilla && !use_pg) {   // shared gate/up: their input gradient needs the per-token sums only
     HIP_TRY_AS(PROF_COMBINE, 2.0 * (k + 1) * T * f * Eb, launch_pair_combine2(dt, pc, f, ws + L.dg_grp, ws + L.dgsum, ws + L.du_grp,
@@ -791,14 +810,14 @@ static int backward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mo
     add_seg(p, ws + L.dg_grp, f, WgT, f, f);
     add_seg(p, ws + L.du_grp, f, WuT, f, f);
     add_seg(p, ws + L.Sp, Kx, ws + L.Bx, Kx, Kx);
-    HIP_TRY(launch_gemm(dt, &p, 1, st));
+    HIP_TRY(launch_gemm(dt, &p, 1, st, gs));
     HIP_TRY_AS(PROF_COMBINE, (double)(k + 1) * T * d * Eb, launch_pair_combine(dt, pc, d, ws + L.dXp, dx, 0, st));
   } else {
     GemmProblem p = problem(T, d, dx, d, 0);
     add_seg(p, ws + L.dgsum, f, WgT, f, f);
     add_seg(p, ws + L.dusum, f, WuT, f, f);
     add_seg(p, ws + L.S, Kx, ws + L.Bx, Kx, Kx);
-    HIP_TRY(launch_gemm(dt, &p, 1, st));
+    HIP_TRY(launch_gemm(dt, &p, 1, st, gs));
   }
   if (dt == MIXLORA_BF16) {
     GatherJob gj[6];
@@ -979,7 +998,8 @@ int mixlora_dora_backward(const mixlora_dims *dims, const mixlora_weights *w,
 }  // extern "C"
 
 namespace {
-static __device__ __align__(256) unsigned char scratch[MIXLORA_STATIC_SCRATCH_BYTES];
+// the workspace, and behind it the partial tiles of GEMM launches cut along K
+static __device__ __align__(256) unsigned char scratch[MIXLORA_STATIC_SCRATCH_BYTES + GEMM_SCRATCH_FLOATS * 4];
 constexpr int STATIC_MAX_DEVICES = 64;
 void *g_scratch_ptr[STATIC_MAX_DEVICES] = {};
 std::mutex g_scratch_mutex;
@@ -1008,11 +1028,12 @@ int mixlora_ffn_forward_static(const mixlora_dims *dims, const mixlora_weights *
                                     reinterpret_cast<const void *>(uintptr_t{256}));
   if (rc) return rc;
   const Layout L = make_layout(*dims);
-  if (L.fwd_end > (size_t)MIXLORA_STATIC_SCRATCH_BYTES) return MIXLORA_E_SCRATCH;
+  if (L.base_end > (size_t)MIXLORA_STATIC_SCRATCH_BYTES) return MIXLORA_E_SCRATCH;
   void *ws = static_scratch_ptr();
   if (!ws) return MIXLORA_E_HIP;
   return forward_impl(*dims, dims->N, nullptr, w, x, y, topk_idx, topk_w, expert_counts, aux_loss,
-                      ws, (size_t)MIXLORA_STATIC_SCRATCH_BYTES, stream);
+                      ws, (size_t)MIXLORA_STATIC_SCRATCH_BYTES, stream, MIXLORA_SCHEDULE_LINEAR_DOWN, nullptr,
+                      (float *)((char *)ws + MIXLORA_STATIC_SCRATCH_BYTES));
 }
 
 int mixlora_aux_loss(const float *probs, const int32_t *topk_idx, int32_t T, int32_t N,

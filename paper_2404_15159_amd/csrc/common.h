@@ -67,9 +67,17 @@ struct GemmProblem {
 };
 // Enqueue up to GEMM_MAX_PROBLEMS independent problems in one launch (N and the output type may
 // differ per problem; M too when the launch qualifies for the large-tile bf16 kernel, i.e. every
-// M > 128, some N > 128 and every K a multiple of 64 - otherwise differing M is an error).
+// M > 128, some N > 128 and every operand below 4 GiB - otherwise differing M is an error).
+// scratch (may be empty): room for the fp32 partial tiles of a launch whose last round of tiles is
+// cut along K; more than GEMM_SCRATCH_FLOATS is never used, with less fewer cuts are made.
 constexpr int GEMM_MAX_PROBLEMS = 8;
-hipError_t launch_gemm(int dtype, const GemmProblem *probs, int nprob, hipStream_t st);
+constexpr size_t GEMM_SCRATCH_FLOATS = (size_t)256 * 256 * 256;   // one 256 x 256 tile per CU
+struct GemmScratch {
+  float *part;
+  size_t floats;
+};
+hipError_t launch_gemm(int dtype, const GemmProblem *probs, int nprob, hipStream_t st,
+                       const GemmScratch &scratch = GemmScratch{nullptr, 0});
 // whether problems of different M may share one launch_gemm call
 bool gemm_mixed_rows_ok(int dtype, const GemmProblem *probs, int nprob);
 

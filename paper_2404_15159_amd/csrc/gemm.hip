@@ -1,9 +1,10 @@
 // GEMM engine of libmixlora:  C[M,N] = sum_s A_s[M,K_s] * B_s[N,K_s]^T  ("NT", K contiguous).
 //
-// bf16 storage: MFMA 32x32x16 bf16 -> fp32 tiles, 64-wide wavefronts, operands staged through
-// padded LDS tiles with register prefetch of the next K tile (double-buffered LDS, one barrier
-// per K tile), XCD-aware + grouped tile order so that the tiles resident on one XCD share
-// operand rows in that XCD's L2.
+// bf16 storage: the frozen projections of more than 128 rows run on gemm_bf16_pp_kernel (256-wide
+// tiles, two groups of four waves taking turns at the matrix pipe and at memory, trailing tiles
+// cut along K); few rows (decode) on gemm_bf16_dl_kernel's narrow tiles; what neither takes on
+// the register-staged gemm_bf16_kernel.  XCD-aware + grouped tile order everywhere, so that the
+// tiles resident on one XCD share operand rows in that XCD's L2.
 // fp32 storage: plain FMA tiles (the fp32 configuration is a small parity case).
 //
 // Every frozen projection of the block (shared gate/up: Algorithm 1 lines 7-8; down: line 14)
@@ -19,15 +20,15 @@ struct GemmBatch {
   GemmProblem p[GEMM_MAX_PROBLEMS];
 };
 
-constexpr int GEMM_LONG_K = 8192;   // summed K of a problem from which the half-slot ring is used
-
-// Map the hardware block id to a tile so that (a) blocks that land on the same XCD (id % 8)
-// get consecutive logical ids and (b) consecutive logical ids walk GROUP tile-rows at a time.
-__device__ __forceinline__ void tile_of_block(int bid, int tiles_m, int tiles_n, int &tm, int &tn) {
-  const int nb = tiles_m * tiles_n;
+// Logical id of hardware block `bid` of `nb`: blocks that land on the same XCD (bid % 8) get
+// consecutive logical ids.
+__device__ __forceinline__ int xcd_order(int bid, int nb) {
   const int q = nb >> 3, rem = nb & 7;
   const int xcd = bid & 7, local = bid >> 3;
-  const int lid = xcd * q + (xcd < rem ? xcd : rem) + local;
+  return xcd * q + (xcd < rem ? xcd : rem) + local;
+}
+// Tile of a logical id: consecutive ids walk GROUP tile-rows at a time.
+__device__ __forceinline__ void tile_of_lid(int lid, int tiles_m, int tiles_n, int &tm, int &tn) {
   constexpr int GROUP = 4;   // measured: 4 slightly ahead of 2, 8, 16 (all within 3 %)
   const int width = GROUP * tiles_n;
   const int group_id = lid / width;
@@ -36,6 +37,11 @@ __device__ __forceinline__ void tile_of_block(int bid, int tiles_m, int tiles_n,
   const int in_group = lid - group_id * width;
   tm = first_m + in_group % gsz;
   tn = in_group / gsz;
+}
+
+// Both steps for a grid that holds the tiles of one problem only.
+__device__ __forceinline__ void tile_of_block(int bid, int tiles_m, int tiles_n, int &tm, int &tn) {
+  tile_of_lid(xcd_order(bid, tiles_m * tiles_n), tiles_m, tiles_n, tm, tn);
 }
 
 template <typename OutT> __device__ __forceinline__ void store_c(OutT *p, float v);
@@ -212,18 +218,6 @@ __global__ __launch_bounds__(WGM *WGN * 64) void gemm_bf16_kernel(GemmBatch args
 // The loads and their s_waitcnt are inline asm: the compiler's own bookkeeping would wait for
 // all outstanding LDS DMA before every LDS read and collapse the ring to depth one.
 // Requires every K_s % BK == 0 and operands below 4 GiB (32-bit lane offsets).
-// PW > 0 makes only the first PW waves issue the copies (all of them, IA + IB instructions each).
-// A compute unit's vector-memory front end takes one 1 KiB copy instruction per ~16 cycles, so
-// the 64 instructions of a 256x256x64 tile keep their issuing waves stalled for ~1000 cycles
-// right after the barrier.  If every wave issues its share, both waves of each SIMD stall
-// together and the matrix pipe runs dry; with one issuing wave per SIMD (PW = 4 of 8 waves)
-// the other wave works through its MFMAs meanwhile, and the issuing wave follows with its own.
-// H5 replaces the two whole stages by five half-slots of one operand's K tile each (all 160 KB
-// of LDS).  A and B tiles rotate through them separately, so the A tile of step t+3 is requested
-// together with the B tile of step t+2: a barrier still frees and refills 64 KB, but the half
-// needed at the next barrier is first in the burst and the other half has one tile longer to
-// arrive.  That pays where the copies come from HBM rather than from L2 (one round of tiles over
-// a long K, operands last touched by other kernels); over short K it costs a few percent.
 __device__ __forceinline__ void dma16(uint32_t voff, const void *sbase, uint32_t lds_addr) {
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                :
@@ -241,19 +235,18 @@ __device__ __forceinline__ const void *uniform_ptr(const void *p) {
   return reinterpret_cast<const void *>(((uint64_t)hi << 32) | lo);
 }
 
-template <int BM, int BN, int BK, int STAGES, int WGM, int WGN, bool PIPE = false, int PW = 0, bool H5 = false>
+template <int BM, int BN, int BK, int STAGES, int WGM, int WGN>
 __global__ __launch_bounds__(WGM *WGN * 64) void gemm_bf16_dl_kernel(GemmBatch args) {
   constexpr int NW = WGM * WGN;
-  constexpr int NPW = PW > 0 ? PW : NW;   // waves that issue the copies
   constexpr int ROWB = BK * 2;            // bytes per tile row in LDS
   constexpr int CPR = BK / 8;             // 16-byte chunks per row
   constexpr int RPI = 64 / CPR;           // rows covered by one wave-wide DMA instruction
   constexpr int RPB = 256 / ROWB;         // rows per 256-byte bank row
-  constexpr int IA = BM / RPI / NPW, IB = BN / RPI / NPW;   // DMA instructions per issuing wave per tile
+  constexpr int IA = BM / RPI / NW, IB = BN / RPI / NW;   // DMA instructions per wave per tile
   constexpr int IPW = IA + IB;
   constexpr int STAGE_BYTES = (BM + BN) * ROWB;
   constexpr int TM = BM / WGM, TN = BN / WGN, MI = TM / 32, NI = TN / 32, KS = BK / 16;
-  static_assert(NPW <= NW && BM % (RPI * NPW) == 0 && BN % (RPI * NPW) == 0, "tile/waves mismatch");
+  static_assert(BM % (RPI * NW) == 0 && BN % (RPI * NW) == 0, "tile/waves mismatch");
   static_assert((STAGES - 2) * IPW < 64 && STAGES >= 2, "ring depth");
 
   extern __shared__ __align__(16) unsigned char smem[];
@@ -310,12 +303,10 @@ __global__ __launch_bounds__(WGM *WGN * 64) void gemm_bf16_dl_kernel(GemmBatch a
     const void *gb = uniform_ptr(baseB + (size_t)k0 * 2);
     const uint32_t la = lds0 + stage * STAGE_BYTES + wave * IA * 1024;
     const uint32_t lb = lds0 + stage * STAGE_BYTES + BM * ROWB + wave * IB * 1024;
-    if (NPW == NW || wave < NPW) {   // the other waves' offsets point past the tile and are never used
 #pragma unroll
-      for (int j = 0; j < IA; j++) dma16(offA[j], ga, la + j * 1024);
+    for (int j = 0; j < IA; j++) dma16(offA[j], ga, la + j * 1024);
 #pragma unroll
-      for (int j = 0; j < IB; j++) dma16(offB[j], gb, lb + j * 1024);
-    }
+    for (int j = 0; j < IB; j++) dma16(offB[j], gb, lb + j * 1024);
   };
 
   int total_tiles = 0;
@@ -335,10 +326,8 @@ __global__ __launch_bounds__(WGM *WGN * 64) void gemm_bf16_dl_kernel(GemmBatch a
     }
     issued++;
   };
-  if constexpr (!H5) {
 #pragma unroll
-    for (int s0 = 0; s0 < STAGES - 1; s0++) issue_next();
-  }
+  for (int s0 = 0; s0 < STAGES - 1; s0++) issue_next();
 
   // --- consumer side: swizzled fragment addresses -------------------------------------------
   const int l31 = lane & 31, hi = lane >> 5;
@@ -351,225 +340,33 @@ __global__ __launch_bounds__(WGM *WGN * 64) void gemm_bf16_dl_kernel(GemmBatch a
 
   auto wait_tile = [&](int it) {
     // tiles it+1 .. min(it+STAGES-2, last) may stay in flight; tile `it` must have landed
-    // (a wave that issues no copies has nothing outstanding: it learns of the tile at the barrier)
     const int newer = total_tiles - 1 - it;
     if (newer >= STAGES - 2) wait_vmcnt<(STAGES - 2) * IPW>();
     else if (STAGES > 3 && newer == 1) wait_vmcnt<IPW>();
     else if (STAGES > 4 && newer == 2) wait_vmcnt<2 * IPW>();
     else wait_vmcnt<0>();
   };
-  if constexpr (H5) {
-    static_assert(BM == BN && IA == IB && KS == 4 && PIPE, "half-slot ring shape");
-    constexpr int HS = BM * ROWB, NSLOT = 5;
-    // the two operands advance through the K segments separately
-    int segA = 0, segB = 0, k0A = 0, k0B = 0, KA = Kcur, KB = Kcur, nA = 0, nB = 0;
-    const unsigned char *bA = baseA, *bB = baseB;
-    const void *gA = uniform_ptr(bA), *gB = uniform_ptr(bB);   // also the source of copies issued past the end
-    auto setupA = [&](int sgi) {
-      const GemmSeg &S = P.seg[sgi];
-#pragma unroll
-      for (int j = 0; j < IA; j++) {
-        const int rt = (wave * IA + j) * RPI + lrow;
-        const int kc = lpos ^ ((rt / RPB) % CPR);
-        int r = row0 + rt;
-        r = r < M ? r : M - 1;
-        offA[j] = (uint32_t)r * (uint32_t)S.lda * 2u + kc * 16;
-      }
-      bA = reinterpret_cast<const unsigned char *>(S.A);
-      KA = S.K;
-    };
-    auto setupB = [&](int sgi) {
-      const GemmSeg &S = P.seg[sgi];
-#pragma unroll
-      for (int j = 0; j < IB; j++) {
-        const int rt = (wave * IB + j) * RPI + lrow;
-        const int kc = lpos ^ ((rt / RPB) % CPR);
-        int c = col0 + rt;
-        c = c < N ? c : N - 1;
-        offB[j] = (uint32_t)c * (uint32_t)S.ldb * 2u + kc * 16;
-      }
-      bB = reinterpret_cast<const unsigned char *>(S.B);
-      KB = S.K;
-    };
-    // Past the last tile the previous address is copied again into the slot that is free anyway,
-    // so that the number of copies in flight at every wait is the same constant.
-    auto issueA = [&]() {
-      if (nA < total_tiles) {
-        if (k0A >= KA) {
-          segA++;
-          setupA(segA);
-          k0A = 0;
-        }
-        gA = uniform_ptr(bA + (size_t)k0A * 2);
-        k0A += BK;
-      }
-      const uint32_t l = lds0 + ((2 * nA) % NSLOT) * HS + wave * IA * 1024;
-      if (NPW == NW || wave < NPW) {
-#pragma unroll
-        for (int j = 0; j < IA; j++) dma16(offA[j], gA, l + j * 1024);
-      }
-      nA++;
-    };
-    auto issueB = [&]() {
-      if (nB < total_tiles) {
-        if (k0B >= KB) {
-          segB++;
-          setupB(segB);
-          k0B = 0;
-        }
-        gB = uniform_ptr(bB + (size_t)k0B * 2);
-        k0B += BK;
-      }
-      const uint32_t l = lds0 + ((2 * nB + 1) % NSLOT) * HS + wave * IB * 1024;
-      if (NPW == NW || wave < NPW) {
-#pragma unroll
-        for (int j = 0; j < IB; j++) dma16(offB[j], gB, l + j * 1024);
-      }
-      nB++;
-    };
-    bf16x8_t af[2][MI], bfr[2][NI];
-    const unsigned char *a5 = smem + (wm * TM + l31) * ROWB, *b5 = smem + (wn * TN + l31) * ROWB;
-    auto load_frags = [&](int buf, int sa, int sb, int ks) {
-      const unsigned char *a = a5 + sa * HS + koff[ks];
-      const unsigned char *b = b5 + sb * HS + koff[ks];
-#pragma unroll
-      for (int i = 0; i < MI; i++) af[buf][i] = *reinterpret_cast<const bf16x8_t *>(a + i * 32 * ROWB);
-#pragma unroll
-      for (int j = 0; j < NI; j++) bfr[buf][j] = *reinterpret_cast<const bf16x8_t *>(b + j * 32 * ROWB);
-    };
-    auto mfma_step = [&](int cur) {
-#pragma unroll
-      for (int i = 0; i < MI; i++)
-#pragma unroll
-        for (int j = 0; j < NI; j++)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[cur][j], af[cur][i], acc[i][j], 0, 0, 0);
-    };
-    issueA(); issueB(); issueA(); issueB(); issueA();    // A0 B0 A1 B1 A2
-    wait_vmcnt<3 * IA>();                                // A0 and B0 have landed
+  for (int it = 0; it < total_tiles; it++) {
+    wait_tile(it);
     __syncthreads();
-    int sa = 0, sb = 1;                                  // half-slots of the tile being consumed
-    load_frags(0, sa, sb, 0);
-    for (int t = 0; t + 1 < total_tiles; t++) {
-      const int sa1 = sa + 2 >= NSLOT ? sa + 2 - NSLOT : sa + 2;
-      const int sb1 = sb + 2 >= NSLOT ? sb + 2 - NSLOT : sb + 2;
-#pragma unroll
-      for (int ks = 0; ks < KS; ks++) {
-        const int cur = ks & 1, nxt = cur ^ 1;
-        if (ks + 1 < KS) {
-          load_frags(nxt, sa, sb, ks + 1);
-        } else {
-          wait_vmcnt<IA>();     // A(t+2) may be in flight; A(t+1) and B(t+1) have landed
-          __syncthreads();      // ... for every wave, and the half-slots of A(t) and B(t) are free
-          issueB();             // B(t+2) into A(t)'s half-slot: needed at the next barrier
-          issueA();             // A(t+3) into B(t)'s: needed one barrier later
-          load_frags(nxt, sa1, sb1, 0);
-        }
-        mfma_step(cur);
-#pragma unroll
-        for (int q = 0; q < MI + NI; q++) {
-          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // one LDS read ...
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // ... then one MFMA
-        }
-        __builtin_amdgcn_sched_group_barrier(0x008, MI * NI - MI - NI, 0);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      sa = sa1;
-      sb = sb1;
-    }
+    issue_next();   // refills the slot that tile it-1 occupied: every wave is past reading it
+    const int st = it % STAGES;
+    const unsigned char *a = a_rd + st * STAGE_BYTES;
+    const unsigned char *b = b_rd + st * STAGE_BYTES;
 #pragma unroll
     for (int ks = 0; ks < KS; ks++) {
-      const int cur = ks & 1;
-      if (ks + 1 < KS) load_frags(cur ^ 1, sa, sb, ks + 1);
-      __builtin_amdgcn_sched_barrier(0);
-      mfma_step(cur);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    wait_vmcnt<0>();            // the copies issued past the end have to be out of the ring
-  } else if constexpr (!PIPE) {
-    for (int it = 0; it < total_tiles; it++) {
-      wait_tile(it);
-      __syncthreads();
-      issue_next();   // refills the slot that tile it-1 occupied: every wave is past reading it
-      const int st = it % STAGES;
-      const unsigned char *a = a_rd + st * STAGE_BYTES;
-      const unsigned char *b = b_rd + st * STAGE_BYTES;
+      bf16x8_t af[MI], bfr[NI];
 #pragma unroll
-      for (int ks = 0; ks < KS; ks++) {
-        bf16x8_t af[MI], bfr[NI];
+      for (int i = 0; i < MI; i++)
+        af[i] = *reinterpret_cast<const bf16x8_t *>(a + i * 32 * ROWB + koff[ks]);
 #pragma unroll
-        for (int i = 0; i < MI; i++)
-          af[i] = *reinterpret_cast<const bf16x8_t *>(a + i * 32 * ROWB + koff[ks]);
-#pragma unroll
-        for (int j = 0; j < NI; j++)
-          bfr[j] = *reinterpret_cast<const bf16x8_t *>(b + j * 32 * ROWB + koff[ks]);
-#pragma unroll
-        for (int i = 0; i < MI; i++)
-#pragma unroll
-          for (int j = 0; j < NI; j++)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[j], af[i], acc[i][j], 0, 0, 0);
-      }
-    }
-  } else {
-    // Register double-buffered fragments: the LDS reads of K step s+1 (or of the next tile's
-    // first step, right after its barrier) are issued before the MFMAs of step s.
-    bf16x8_t af[2][MI], bfr[2][NI];
-    auto load_frags = [&](int buf, int st, int ks) {
-      const unsigned char *a = a_rd + st * STAGE_BYTES + koff[ks];
-      const unsigned char *b = b_rd + st * STAGE_BYTES + koff[ks];
-#pragma unroll
-      for (int i = 0; i < MI; i++) af[buf][i] = *reinterpret_cast<const bf16x8_t *>(a + i * 32 * ROWB);
-#pragma unroll
-      for (int j = 0; j < NI; j++) bfr[buf][j] = *reinterpret_cast<const bf16x8_t *>(b + j * 32 * ROWB);
-    };
-    auto mfma_step = [&](int cur) {
+      for (int j = 0; j < NI; j++)
+        bfr[j] = *reinterpret_cast<const bf16x8_t *>(b + j * 32 * ROWB + koff[ks]);
 #pragma unroll
       for (int i = 0; i < MI; i++)
 #pragma unroll
         for (int j = 0; j < NI; j++)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[cur][j], af[cur][i], acc[i][j], 0, 0, 0);
-    };
-    wait_tile(0);
-    __syncthreads();
-    issue_next();
-    load_frags(0, 0, 0);
-    // All tiles but the last: no data-dependent branch inside, so that the wait counts the
-    // compiler derives for the fragment reads are exact (a merge with a path that skips the
-    // tile switch would make every post-barrier MFMA wait for the reads just issued).
-    for (int it = 0; it + 1 < total_tiles; it++) {
-      const int st = it % STAGES;
-#pragma unroll
-      for (int ks = 0; ks < KS; ks++) {
-        const int cur = ks & 1, nxt = cur ^ 1;   // KS is even, so step 0 always uses buffer 0
-        if (ks + 1 < KS) {
-          load_frags(nxt, st, ks + 1);
-        } else {
-          wait_tile(it + 1);
-          __syncthreads();
-          issue_next();
-          load_frags(nxt, (it + 1) % STAGES, 0);
-        }
-        // issue order within the step: one LDS read between consecutive MFMAs, so the reads of
-        // the next step trickle out while the matrix pipe is busy
-        mfma_step(cur);
-#pragma unroll
-        for (int q = 0; q < MI + NI; q++) {
-          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // one LDS read ...
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // ... then one MFMA
-        }
-        __builtin_amdgcn_sched_group_barrier(0x008, MI * NI - MI - NI, 0);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-    {
-      const int st = (total_tiles - 1) % STAGES;
-#pragma unroll
-      for (int ks = 0; ks < KS; ks++) {
-        const int cur = ks & 1;
-        if (ks + 1 < KS) load_frags(cur ^ 1, st, ks + 1);
-        __builtin_amdgcn_sched_barrier(0);
-        mfma_step(cur);
-        __builtin_amdgcn_sched_barrier(0);
-      }
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[j], af[i], acc[i][j], 0, 0, 0);
     }
   }
 
@@ -649,6 +446,376 @@ __global__ __launch_bounds__(WGM *WGN * 64) void gemm_bf16_dl_kernel(GemmBatch a
   }
   if (P.c_f32) store_all(reinterpret_cast<float *>(P.C));
   else store_all(reinterpret_cast<bf16_t *>(P.C));
+}
+
+// ---- bf16, large tiles: two wave groups in turns -------------------------------------------------
+// What bounds it: the chip's power.  At full matrix load on real (toggling) data the clock drops
+// to ~1.7 GHz, so what counts is energy per product and a matrix pipe that never idles.
+//  - MFMA 16x16x32 instead of 32x32x16: same rate per cycle, but a product moves a fifth less
+//    operand and accumulator data through the registers (4 KB against 5 KB per 16 kFLOP), and the
+//    clock settles higher: 526 -> 461 us on 4096 x 4096 x 22272, 575 -> 530 us on
+//    4096 x 22016 x 4096 with everything else equal (1.42 -> 1.62 and 1.28 -> 1.39 PFLOP/s).
+//    Consecutive MFMAs share one operand (serpentine order; the other order costs 2 %).
+//  - Eight waves, two per SIMD: waves 0-3 and 4-7 (the upper and lower half of the tile's rows) do
+//    the same phases half a phase apart, so that one wave of every SIMD issues MFMAs while the
+//    other reads fragments and issues copies.  A barrier ends each half phase.  Against a two-
+//    stage ring with the copies in one burst after a barrier: 3-5 % at equal MFMA shape.
+//  - A K tile is four phases, one quarter (2 x 2) of the wave's output each; both operand tiles are
+//    copied in halves (the rows the first / second quarter pair needs), one half per phase, five
+//    halves (80 KB of 128 KB LDS) in flight behind the one being waited for.
+//  - The fragment reads of a phase are waited for behind its barrier, by the MFMAs that use them,
+//    not in front of it: 518 -> 493 us on 4096 x 4096 x 22272 and 101 -> 88 us on
+//    300 x 22016 x 4096 on one box.
+// A phase: issue the copies of one half tile, start this phase's fragment reads, wait for the half
+// that the NEXT phase reads, barrier, MFMAs, barrier.  The waits are counted: half tiles are
+// requested in the order B0 A0 B1 A1 of each K tile, IA or IB instructions per wave.
+//  - Read after copy: a wave waits for its own share of a half tile in front of a barrier; the
+//    second group does so one half phase after the first, still one barrier before the first
+//    group's reads.
+//  - Copy after read: the reads of a phase are complete before its closing barrier, and the copies
+//    that refill a slot are issued at the earliest two half phases after its last reader's.
+// Copies past the last tile repeat the last address into the slot that is free anyway, so that
+// the counts stay constant.
+// BM = 192 is for row counts that need no more tiles of 192 than of 256 (a quarter less padding).
+// The last K tile of a segment may be ragged (K % 8 == 0): lanes past the end copy zeros.
+// Trailing tiles that would fill less than half of a last round of workgroups are cut along K
+// into S slices each (plan_tail below); a slice writes its fp32 partial tile to scratch and
+// gemm_tail_reduce_kernel adds the slices in order.
+struct GemmPlan {
+  int nprob, tail_start, ntail, S;
+  int start[GEMM_MAX_PROBLEMS];   // first block of problem p's whole tiles (a multiple of 8)
+  int whole[GEMM_MAX_PROBLEMS];   // number of them: tiles [0, whole) in tile_of_lid's order
+  int tail0[GEMM_MAX_PROBLEMS];   // first split tile of problem p among all split tiles
+  float *part;                    // [S][ntail][BM][256]
+};
+__device__ __align__(16) const unsigned char gemm_zero16[16] = {};   // source of ragged-K zeros
+
+__device__ __forceinline__ void dma16_at(const void *p, uint32_t lds_addr) {
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
+               :
+               : "v"(p), "s"(lds_addr)
+               : "memory", "m0");
+}
+
+// problem and tile of split tile tt
+__device__ __forceinline__ int tail_tile(const GemmPlan &plan, int tt, int &lid) {
+  int pi = 0;
+  while (pi + 1 < plan.nprob && plan.tail0[pi + 1] <= tt) pi++;
+  lid = plan.whole[pi] + tt - plan.tail0[pi];
+  return pi;
+}
+
+constexpr int PP_BN = 256, PP_BK = 64;
+constexpr size_t pp_lds_bytes(int BM) { return (size_t)2 * (BM + PP_BN) * PP_BK * sizeof(bf16_t); }
+
+template <int BM>
+__global__ __launch_bounds__(512) void gemm_bf16_pp_kernel(GemmBatch args, GemmPlan plan) {
+  constexpr int BN = PP_BN, BK = PP_BK, ROWB = BK * 2;
+  constexpr int HA = BM / 2 * ROWB, HB = BN / 2 * ROWB, STAGE = 2 * (HA + HB);   // half tiles in bytes
+  constexpr int HM = BM / 4, MH = HM / 16, NH = 2;   // a wave's rows / 16-row blocks per half
+  constexpr int PA = BM / 16, PB = BN / 16;          // 1 KiB pieces of a half tile
+  constexpr int IA = (PA + 7) / 8, IB = (PB + 7) / 8;
+  static_assert(BM % 64 == 0 && PB % 8 == 0, "tile shape");
+
+  extern __shared__ __align__(16) unsigned char smem[];
+  const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) unsigned char *)smem;
+
+  // block -> problem, tile and K slice
+  int bid = blockIdx.x, pi = 0, lid, slice = 0, S = 1, tt = 0;
+  if (bid < plan.tail_start) {
+    while (pi + 1 < plan.nprob && plan.start[pi + 1] <= bid) pi++;
+    bid -= plan.start[pi];
+    if (bid >= plan.whole[pi]) return;
+    lid = xcd_order(bid, plan.whole[pi]);
+  } else {
+    bid -= plan.tail_start;
+    S = plan.S;
+    if (bid >= plan.ntail * S) return;
+    const int l = xcd_order(bid, plan.ntail * S);
+    slice = l / plan.ntail;
+    tt = l - slice * plan.ntail;
+    pi = tail_tile(plan, tt, lid);
+  }
+  const GemmProblem &P = args.p[pi];
+  const int M = P.M, N = P.N;
+  int tm, tn;
+  tile_of_lid(lid, (M + BM - 1) / BM, (N + BN - 1) / BN, tm, tn);
+  const int row0 = tm * BM, col0 = tn * BN;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 2, wn = wave & 3;
+
+  f32x4_t acc[2 * MH][2 * NH];
+#pragma unroll
+  for (int i = 0; i < 2 * MH; i++)
+#pragma unroll
+    for (int j = 0; j < 2 * NH; j++) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+  // --- producer side ----------------------------------------------------------------------
+  int all_tiles = 0;
+  for (int sgi = 0; sgi < P.nseg; sgi++) all_tiles += (P.seg[sgi].K + BK - 1) / BK;
+  const int t_first = (int)((int64_t)all_tiles * slice / S);
+  const int total = (int)((int64_t)all_tiles * (slice + 1) / S) - t_first;
+  const int lrow = lane >> 3, lpos = lane & 7;
+  // piece j of this wave; with PA = 12 pieces the last four waves repeat other waves' pieces
+  auto piece = [&](int j, int pieces) { return wave + 8 * j < pieces ? wave + 8 * j : 8 * j + (wave & 3); };
+  uint32_t offA[2][IA], offB[2][IB];
+  const unsigned char *baseA = nullptr, *baseB = nullptr;
+  int seg = 0, k0, Kcur = 0, valid = 8;   // valid: 16-byte chunks of a row inside K
+  auto setup = [&]() {
+    const GemmSeg &Sg = P.seg[seg];
+#pragma unroll
+    for (int h = 0; h < 2; h++) {
+#pragma unroll
+      for (int j = 0; j < IA; j++) {
+        const int q = piece(j, PA) * 8 + lrow;               // row of the half tile
+        int r = row0 + (q / HM) * (BM / 2) + h * HM + q % HM;
+        r = r < M ? r : M - 1;
+        offA[h][j] = (uint32_t)r * (uint32_t)Sg.lda * 2u + (lpos ^ ((q >> 1) & 7)) * 16;
+      }
+#pragma unroll
+      for (int j = 0; j < IB; j++) {
+        const int q = piece(j, PB) * 8 + lrow;
+        int c = col0 + (q >> 5) * 64 + h * 32 + (q & 31);
+        c = c < N ? c : N - 1;
+        offB[h][j] = (uint32_t)c * (uint32_t)Sg.ldb * 2u + (lpos ^ ((q >> 1) & 7)) * 16;
+      }
+    }
+    baseA = reinterpret_cast<const unsigned char *>(Sg.A);
+    baseB = reinterpret_cast<const unsigned char *>(Sg.B);
+    Kcur = Sg.K;
+  };
+  {
+    int skip = t_first;
+    for (;;) {
+      const int kt = (P.seg[seg].K + BK - 1) / BK;
+      if (skip < kt) break;
+      skip -= kt;
+      seg++;
+    }
+    k0 = skip * BK;
+  }
+  setup();
+  const void *ga, *gb;
+  auto point = [&]() {
+    ga = uniform_ptr(baseA + (size_t)k0 * 2);
+    gb = uniform_ptr(baseB + (size_t)k0 * 2);
+    valid = Kcur - k0 >= BK ? 8 : (Kcur - k0) >> 3;
+  };
+  point();
+  int issued = 0;   // the tile the producer points at
+  auto advance = [&]() {
+    issued++;
+    if (issued < total) {
+      k0 += BK;
+      if (k0 >= Kcur) {
+        seg++;
+        k0 = 0;
+        setup();
+      }
+      point();
+    }
+  };
+  auto issue = [&](const uint32_t *off, const void *base, int n, int pieces, uint32_t l) {
+    if (valid == 8) {
+#pragma unroll
+      for (int j = 0; j < n; j++) dma16(off[j], base, l + piece(j, pieces) * 1024);
+    } else {
+#pragma unroll
+      for (int j = 0; j < n; j++) {
+        const int q = piece(j, pieces) * 8 + lrow;
+        const unsigned char *p = reinterpret_cast<const unsigned char *>(base) + off[j];
+        dma16_at((lpos ^ ((q >> 1) & 7)) < valid ? p : gemm_zero16, l + piece(j, pieces) * 1024);
+      }
+    }
+  };
+  auto issueA = [&](int h) { issue(offA[h], ga, IA, PA, lds0 + (issued & 1) * STAGE + h * HA); };
+  auto issueB = [&](int h) { issue(offB[h], gb, IB, PB, lds0 + (issued & 1) * STAGE + 2 * HA + h * HB); };
+
+  // --- consumer side ----------------------------------------------------------------------
+  const int l15 = lane & 15, hi = lane >> 4;
+  const int koff[2] = {(hi ^ (l15 >> 1)) * 16, ((4 + hi) ^ (l15 >> 1)) * 16};   // swizzled chunks
+  const unsigned char *a_rd = smem + (wm * HM + l15) * ROWB;
+  const unsigned char *b_rd = smem + 2 * HA + (wn * 32 + l15) * ROWB;
+  bf16x8_t fa[2][MH], fb0[2][NH], fb1[2][NH];
+  auto readA = [&](int st, int h) {
+    const unsigned char *p = a_rd + st * STAGE + h * HA;
+#pragma unroll
+    for (int ks = 0; ks < 2; ks++)
+#pragma unroll
+      for (int i = 0; i < MH; i++)
+        fa[ks][i] = *reinterpret_cast<const bf16x8_t *>(p + i * 16 * ROWB + koff[ks]);
+  };
+  auto readB = [&](int st, int h, bf16x8_t (&fb)[2][NH]) {
+    const unsigned char *p = b_rd + st * STAGE + h * HB;
+#pragma unroll
+    for (int ks = 0; ks < 2; ks++)
+#pragma unroll
+      for (int j = 0; j < NH; j++)
+        fb[ks][j] = *reinterpret_cast<const bf16x8_t *>(p + j * 16 * ROWB + koff[ks]);
+  };
+  auto barrier = [&]() {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto mfmas = [&](int h, int j, const bf16x8_t (&fb)[2][NH]) {
+#pragma unroll
+    for (int ks = 0; ks < 2; ks++)
+#pragma unroll
+      for (int i = 0; i < MH; i++)
+#pragma unroll
+        for (int q = 0; q < NH; q++) {
+          const int jj = q ^ (i & 1);
+          acc[h * MH + i][j * NH + jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+              fb[ks][jj], fa[ks][i], acc[h * MH + i][j * NH + jj], 0, 0, 0);
+        }
+    // every fragment read of the phase is complete before its closing barrier (those the MFMAs did
+    // not need as well: B0 of the next tile)
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  };
+
+  issueB(0); issueA(0); issueB(1); issueA(1);
+  advance();
+  issueB(0); issueA(0); issueB(1);
+  wait_vmcnt<2 * IA + 3 * IB>();     // B0 and A0 of tile 0
+  barrier();
+  if (wm == 1) barrier();            // the second group runs half a phase behind the first
+  readB(0, 0, fb0);
+  for (int t = 0; t < total; t++) {
+    const int st = t & 1;
+    issueA(1);                       // A1(t+1)
+    readA(st, 0);
+    wait_vmcnt<3 * IA + 2 * IB>();   // B1(t)
+    barrier();
+    mfmas(0, 0, fb0);
+    barrier();
+    advance();
+    issueB(0);                       // B0(t+2)
+    readB(st, 1, fb1);
+    wait_vmcnt<2 * IA + 3 * IB>();   // A1(t)
+    barrier();
+    mfmas(0, 1, fb1);
+    barrier();
+    issueA(0);                       // A0(t+2)
+    readA(st, 1);
+    wait_vmcnt<3 * IA + 2 * IB>();   // B0(t+1)
+    barrier();
+    mfmas(1, 0, fb0);
+    barrier();
+    issueB(1);                       // B1(t+2)
+    readB(st ^ 1, 0, fb0);           // B0(t+1)
+    wait_vmcnt<2 * IA + 3 * IB>();   // A0(t+1)
+    barrier();
+    mfmas(1, 1, fb1);
+    barrier();
+  }
+  wait_vmcnt<0>();                   // the copies issued past the end have to be out of the ring
+  if (wm == 0) barrier();
+
+  // --- epilogue: through per-wave LDS tiles of 32 rows x 64 columns, so that every global store is
+  // 16 bytes per lane and whole 128-byte (or longer) row segments; streaming stores, an output
+  // tile is never read again by this launch
+  __syncthreads();
+  auto store_rows = [&](auto *C, int64_t ldc, int r0, int c0, int rows, int cols) {
+    typedef typename std::remove_pointer<decltype(C)>::type OutT;
+    constexpr int PER = 16 / (int)sizeof(OutT), TN = 64, EP = TN + PER;
+    constexpr int CPW = TN / PER, RPW = 64 / CPW;
+    static_assert(8 * 32 * EP * sizeof(OutT) <= pp_lds_bytes(BM), "epilogue tiles fit");
+    typedef OutT out4_t __attribute__((ext_vector_type(4)));
+    typedef OutT outp_t __attribute__((ext_vector_type(PER)));
+    OutT *tile = reinterpret_cast<OutT *>(smem) + wave * 32 * EP;
+    const int rr = lane / CPW, cc = lane % CPW;
+    const int c = c0 + wn * TN + cc * PER;
+#pragma unroll
+    for (int i = 0; i < MH; i++) {
+#pragma unroll
+      for (int ii = 0; ii < 2; ii++)
+#pragma unroll
+        for (int j = 0; j < 2 * NH; j++) {
+          out4_t v;
+#pragma unroll
+          for (int m = 0; m < 4; m++) v[m] = (OutT)acc[i * 2 + ii][j][m];
+          *reinterpret_cast<out4_t *>(tile + (ii * 16 + l15) * EP + j * 16 + hi * 4) = v;
+        }
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int p = 0; p < 32 / RPW; p++) {
+        const int rl = p * RPW + rr;
+        const int r = r0 + wm * (BM / 2) + i * 32 + rl;
+        const outp_t v = *reinterpret_cast<const outp_t *>(tile + rl * EP + cc * PER);
+        if (r < rows && c < cols) __builtin_nontemporal_store(v, reinterpret_cast<outp_t *>(C + r * ldc + c));
+      }
+      __builtin_amdgcn_wave_barrier();
+    }
+  };
+  if (S > 1) {
+    store_rows(plan.part + ((int64_t)slice * plan.ntail + tt) * (BM * BN), BN, 0, 0, BM, BN);
+    return;
+  }
+  const int per = P.c_f32 ? 4 : 8;
+  if ((N % per) == 0 && (P.ldc % per) == 0 && (reinterpret_cast<uintptr_t>(P.C) & 15) == 0) {
+    if (P.c_f32) store_rows(reinterpret_cast<float *>(P.C), P.ldc, row0, col0, M, N);
+    else store_rows(reinterpret_cast<bf16_t *>(P.C), P.ldc, row0, col0, M, N);
+    return;
+  }
+  // outputs whose rows are not whole 16-byte pieces (an odd number of experts, say)
+#pragma unroll
+  for (int i = 0; i < 2 * MH; i++) {
+    const int r = row0 + wm * (BM / 2) + i * 16 + l15;
+    if (r >= M) continue;
+#pragma unroll
+    for (int j = 0; j < 2 * NH; j++)
+#pragma unroll
+      for (int m = 0; m < 4; m++) {
+        const int c = col0 + wn * 64 + j * 16 + hi * 4 + m;
+        if (c >= N) continue;
+        if (P.c_f32) store_c<float>(reinterpret_cast<float *>(P.C) + r * P.ldc + c, acc[i][j][m]);
+        else store_c<bf16_t>(reinterpret_cast<bf16_t *>(P.C) + r * P.ldc + c, acc[i][j][m]);
+      }
+  }
+}
+
+// Adds the S partial tiles of every split tile in slice order and writes them out: one workgroup
+// per 8 rows of a tile, 8 columns per thread.
+template <int BM>
+__global__ __launch_bounds__(256) void gemm_tail_reduce_kernel(GemmBatch args, GemmPlan plan) {
+  constexpr int BN = PP_BN;
+  const int tt = blockIdx.x;
+  int lid;
+  const GemmProblem &P = args.p[tail_tile(plan, tt, lid)];
+  int tm, tn;
+  tile_of_lid(lid, (P.M + BM - 1) / BM, (P.N + BN - 1) / BN, tm, tn);
+  const int rt = blockIdx.y * 8 + (threadIdx.x >> 5), ct = (threadIdx.x & 31) * 8;
+  const int r = tm * BM + rt, c = tn * BN + ct;
+  if (r >= P.M || c >= P.N) return;
+  const float *src = plan.part + (int64_t)tt * (BM * BN) + rt * BN + ct;
+  const int64_t step = (int64_t)plan.ntail * (BM * BN);
+  Vec8<float> a;
+  a.load(src);
+#pragma unroll 4
+  for (int sp = 1; sp < plan.S; sp++) {
+    Vec8<float> b;
+    b.load(src + sp * step);
+#pragma unroll
+    for (int i = 0; i < 8; i++) a.set(i, a.get(i) + b.get(i));
+  }
+  const int per = P.c_f32 ? 4 : 8;
+  if (c + 8 <= P.N && (P.ldc % per) == 0 && (reinterpret_cast<uintptr_t>(P.C) & 15) == 0) {
+    if (P.c_f32) {
+      a.store(reinterpret_cast<float *>(P.C) + r * P.ldc + c);
+    } else {
+      Vec8<bf16_t> o;
+#pragma unroll
+      for (int i = 0; i < 8; i++) o.set(i, a.get(i));
+      o.store(reinterpret_cast<bf16_t *>(P.C) + r * P.ldc + c);
+    }
+    return;
+  }
+  for (int i = 0; i < 8 && c + i < P.N; i++) {
+    if (P.c_f32) reinterpret_cast<float *>(P.C)[r * P.ldc + c + i] = a.get(i);
+    else reinterpret_cast<bf16_t *>(P.C)[r * P.ldc + c + i] = (bf16_t)a.get(i);
+  }
 }
 
 // ---- fp32 storage: 64x64 tile, 256 threads, 4x4 outputs per thread ----------------------
@@ -735,10 +902,10 @@ static hipError_t launch_bf16(const GemmBatch &b, int nprob, hipStream_t st) {
   return hipGetLastError();
 }
 
-template <int BM, int BN, int BK, int STAGES, int WGM, int WGN, bool PIPE = false, int PW = 0, bool H5 = false>
+template <int BM, int BN, int BK, int STAGES, int WGM, int WGN>
 static hipError_t launch_bf16_dl(const GemmBatch &b, int nprob, hipStream_t st) {
-  constexpr size_t smem = H5 ? (size_t)5 * BM * BK * sizeof(bf16_t) : (size_t)STAGES * (BM + BN) * BK * sizeof(bf16_t);
-  auto kern = gemm_bf16_dl_kernel<BM, BN, BK, STAGES, WGM, WGN, PIPE, PW, H5>;
+  constexpr size_t smem = (size_t)STAGES * (BM + BN) * BK * sizeof(bf16_t);
+  auto kern = gemm_bf16_dl_kernel<BM, BN, BK, STAGES, WGM, WGN>;
   static bool attr_set = false;
   if (!attr_set) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
@@ -759,7 +926,7 @@ static hipError_t launch_bf16_dl(const GemmBatch &b, int nprob, hipStream_t st) 
   return hipGetLastError();
 }
 
-// The direct-to-LDS kernel needs whole K tiles and 32-bit operand offsets.
+// The direct-to-LDS kernels need 32-bit operand offsets, and (the narrow-tile one) whole K tiles.
 static bool dl_eligible(const GemmBatch &b, int nprob, int BK) {
   for (int i = 0; i < nprob; i++) {
     const GemmProblem &p = b.p[i];
@@ -773,6 +940,94 @@ static bool dl_eligible(const GemmBatch &b, int nprob, int BK) {
   return true;
 }
 
+// How many trailing tiles of a launch of `tiles` to cut along K, and into how many slices.  The
+// last round of workgroups (one per CU) takes as long as a full one however few tiles it holds;
+// with S slices per tile it takes 1/S of that, plus the partial tiles' way through memory.
+// Per K tile a tile needs ~1.2 us (0.9 alone on the chip, 1.5 with all CUs at work), partial
+// tiles are written and read at ~4 TB/s, and the second launch costs ~6 us.
+static void plan_tail(int tiles, int ktiles, int BM, size_t part_floats, int &ntail, int &S) {
+  constexpr int CUS = 256;
+  ntail = 0;
+  S = 1;
+  const int tail = tiles % CUS;
+  if (tail == 0 || tail > CUS / 2) return;
+  const double tile_mb = BM * PP_BN * 8e-6;   // MB written and read again per partial tile
+  double best = 0.0;
+  for (int n = 2; n <= 32 && n * tail <= CUS && ktiles / n >= 4 && (size_t)n * tail * BM * PP_BN <= part_floats; n++) {
+    const double gain = 1.2 * ktiles * (1.0 - 1.0 / n) - (tail * n * tile_mb / 4.0 + 6.0);
+    if (gain > best) {
+      best = gain;
+      ntail = tail;
+      S = n;
+    }
+  }
+}
+
+static int pp_tiles(const GemmProblem &p, int BM) {
+  return ((p.M + BM - 1) / BM) * ((p.N + PP_BN - 1) / PP_BN);
+}
+
+template <int BM>
+static hipError_t launch_pp(const GemmBatch &b, int nprob, int ntail, int S, float *part, hipStream_t st) {
+  constexpr size_t smem = pp_lds_bytes(BM);
+  auto kern = gemm_bf16_pp_kernel<BM>;
+  static bool attr_set = false;
+  if (!attr_set) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    if (e != hipSuccess) return e;
+    attr_set = true;
+  }
+  GemmPlan plan{};
+  plan.nprob = nprob;
+  plan.ntail = ntail;
+  plan.S = S;
+  plan.part = part;
+  int total = 0, at = 0, before = 0;
+  for (int i = 0; i < nprob; i++) total += pp_tiles(b.p[i], BM);
+  const int whole_all = total - ntail;
+  for (int i = 0; i < GEMM_MAX_PROBLEMS; i++) {
+    const int n = i < nprob ? pp_tiles(b.p[i], BM) : 0;
+    int w = whole_all - before;                  // whole tiles left for this problem
+    w = w < 0 ? 0 : (w > n ? n : w);
+    plan.start[i] = at;
+    plan.whole[i] = w;
+    plan.tail0[i] = before + w - whole_all;      // <= 0 up to the first problem with split tiles
+    if (plan.tail0[i] < 0) plan.tail0[i] = 0;
+    at += (w + 7) & ~7;
+    before += n;
+  }
+  plan.tail_start = at;
+  const int slot = prof_on() ? prof_mark_begin(PROF_GEMM, st) : -1;
+  hipLaunchKernelGGL(kern, dim3(at + ntail * S), dim3(512), smem, st, b, plan);
+  if (slot >= 0) prof_mark_end(slot, st, batch_flops(b, nprob));
+  if (ntail > 0) {
+    const int s2 = prof_on() ? prof_mark_begin(PROF_OTHER, st) : -1;
+    hipLaunchKernelGGL(gemm_tail_reduce_kernel<BM>, dim3(ntail, BM / 8), dim3(256), 0, st, b, plan);
+    if (s2 >= 0) prof_mark_end(s2, st, 0.0);
+  }
+  return hipGetLastError();
+}
+
+// Large-tile launch of any number of problems (row counts may differ).
+static hipError_t launch_large(const GemmBatch &b, int nprob, const GemmScratch &scratch, hipStream_t st) {
+  // 192 rows per tile where that needs no more tiles than 256 (129-192, 257-384, 513-576 rows)
+  bool m192 = true;
+  int ktiles = 1 << 30;
+  for (int i = 0; i < nprob; i++) {
+    if ((b.p[i].M + 191) / 192 != (b.p[i].M + 255) / 256) m192 = false;
+    int kt = 0;
+    for (int sgi = 0; sgi < b.p[i].nseg; sgi++) kt += (b.p[i].seg[sgi].K + PP_BK - 1) / PP_BK;
+    ktiles = kt < ktiles ? kt : ktiles;
+  }
+  const int BM = m192 ? 192 : 256;
+  int tiles = 0, ntail, S;
+  for (int i = 0; i < nprob; i++) tiles += pp_tiles(b.p[i], BM);
+  plan_tail(tiles, ktiles, BM, scratch.part ? scratch.floats : 0, ntail, S);
+  return m192 ? launch_pp<192>(b, nprob, ntail, S, scratch.part, st)
+              : launch_pp<256>(b, nprob, ntail, S, scratch.part, st);
+}
+
 bool gemm_mixed_rows_ok(int dtype, const GemmProblem *probs, int nprob) {
   if (dtype != MIXLORA_BF16 || nprob < 1 || nprob > GEMM_MAX_PROBLEMS) return false;
   GemmBatch b;
@@ -782,10 +1037,11 @@ bool gemm_mixed_rows_ok(int dtype, const GemmProblem *probs, int nprob) {
     if (probs[i].M <= 128 || probs[i].N <= 0) return false;
     if (probs[i].N > 128) any_big = true;
   }
-  return any_big && dl_eligible(b, nprob, 64);
+  return any_big && dl_eligible(b, nprob, 8);
 }
 
-hipError_t launch_gemm(int dtype, const GemmProblem *probs, int nprob, hipStream_t st) {
+hipError_t launch_gemm(int dtype, const GemmProblem *probs, int nprob, hipStream_t st,
+                       const GemmScratch &scratch) {
   if (nprob < 1 || nprob > GEMM_MAX_PROBLEMS) return hipErrorInvalidValue;
   GemmBatch b;
   for (int i = 0; i < GEMM_MAX_PROBLEMS; i++) b.p[i] = probs[i < nprob ? i : 0];
@@ -801,36 +1057,23 @@ hipError_t launch_gemm(int dtype, const GemmProblem *probs, int nprob, hipStream
     // problems of different row counts (per-token and per-pair operands) can share a launch of
     // the large-tile kernel only: every tile takes M from its own problem
     if (!gemm_mixed_rows_ok(dtype, probs, nprob)) return hipErrorInvalidValue;
-    return launch_bf16_dl<256, 256, 64, 2, 2, 4, true, 4>(b, nprob, st);
+    return launch_large(b, nprob, scratch, st);
   }
   if (M <= 0) return hipSuccess;
-  if (dtype == MIXLORA_BF16 && M > 128 && any_big) {
-    // large tiles: direct-to-LDS ring; BK = 64 needs whole 64-wide K tiles, else BK = 32.
-    // Problems of one launch may differ in N and output type (narrow ones ride in the slack
-    // of the last, partially filled round of workgroups).
-    if (dl_eligible(b, nprob, 64)) {
-      // long K (the down projection and the input-gradient products): the half-slot ring
-      bool long_k = true;
-      for (int i = 0; i < nprob; i++) {
-        int64_t kt = 0;
-        for (int sgi = 0; sgi < probs[i].nseg; sgi++) kt += probs[i].seg[sgi].K;
-        if (kt < GEMM_LONG_K) long_k = false;
-      }
-      if (long_k) return launch_bf16_dl<256, 256, 64, 2, 2, 4, true, 4, true>(b, nprob, st);
-      return launch_bf16_dl<256, 256, 64, 2, 2, 4, true, 4>(b, nprob, st);
-    }
-    if (dl_eligible(b, nprob, 32)) return launch_bf16_dl<256, 256, 32, 4, 2, 4, false>(b, nprob, st);
-  }
+  // Large tiles.  Problems of one launch may differ in N and output type (narrow ones ride in the
+  // slack of the last, partially filled round of workgroups).
+  if (dtype == MIXLORA_BF16 && M > 128 && any_big && dl_eligible(b, nprob, 8))
+    return launch_large(b, nprob, scratch, st);
   if (dtype == MIXLORA_BF16 && M <= 128 && any_big && dl_eligible(b, nprob, 64)) {
     // few rows (decode-shaped calls): the launch is bound by streaming the weights once, so the
     // tiles are narrow (64 output columns: enough workgroups to cover the chip) and the ring is
     // deep (4 K tiles in flight per workgroup, 2 workgroups per CU)
-    if (M <= 64) return launch_bf16_dl<64, 64, 64, 4, 1, 2, false>(b, nprob, st);
-    return launch_bf16_dl<128, 64, 64, 4, 2, 2, false>(b, nprob, st);
+    if (M <= 64) return launch_bf16_dl<64, 64, 64, 4, 1, 2>(b, nprob, st);
+    return launch_bf16_dl<128, 64, 64, 4, 2, 2>(b, nprob, st);
   }
   if (!uniform || nprob > 2) {   // the generic kernels take uniform batches of at most two
     for (int i = 0; i < nprob; i++) {
-      const hipError_t e = launch_gemm(dtype, probs + i, 1, st);
+      const hipError_t e = launch_gemm(dtype, probs + i, 1, st, scratch);
       if (e != hipSuccess) return e;
     }
     return hipSuccess;

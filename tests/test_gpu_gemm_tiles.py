@@ -1,0 +1,51 @@
+"""GPU parity at the edges of the large-tile GEMM: row counts on both sides of its tile heights (192
+and 256), contraction lengths that end inside a 64-wide K tile, output rows that are not whole
+16-byte pieces, and K ranges long enough that the last round of tiles is cut into slices.
+
+Forward and backward of the whole block against the oracle; tolerance as everywhere for bf16
+storage (2e-2: a handful of bf16 roundings of 2^-9 each between an input and an output)."""
+import numpy as np
+import pytest
+
+from oracle import mixlora_oracle as orc
+from paper_2404_15159_amd import synth
+from paper_2404_15159_amd.runner import MixLoraFFN
+
+import parity_utils as pu
+
+pytestmark = pytest.mark.gpu
+
+# T, d, d_ff, N: one row tile of 192 / of 256, two of 192 / of 256, three of 192, four of 256
+SHAPES = [(129, 512, 1400, 8), (192, 1024, 2744, 8), (193, 1032, 2048, 5), (256, 1024, 1416, 8),
+          (257, 1024, 2744, 5), (384, 520, 2056, 8), (385, 1024, 2816, 8), (513, 776, 1544, 3),
+          (577, 1024, 1032, 8)]
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "T%d_d%d_f%d_N%d" % s)
+def test_tile_edges_match_oracle(shape):
+    T, d, f, N = shape
+    cfg = synth.scaled(synth.CONFIGS["llama2_7b"], name="tiles", T=T, d=d, d_ff=f, N=N)
+    print(f"case T={T} d={d} f={f} N={N}", flush=True)
+    host = synth.make_inputs(cfg)
+    m = MixLoraFFN(cfg, host)
+    m.workspace.fill_(0xFF)          # NaN patterns: nothing may be read before it is written
+    m.forward()
+    m.backward(d_aux=1.0)
+    res = m.results()
+    W = {n: host[n] for n in synth.WEIGHT_NAMES}
+    bw = orc.backward(host["x"], W, cfg.k, cfg.lora_scale, host["dy"], 1.0, cfg.aux_coeff, "top1")
+    pu.compare_all(res, bw["forward"], bw, cfg)
+
+
+def test_repeated_passes_are_bit_identical():
+    """Slices are added in a fixed order."""
+    cfg = synth.scaled(synth.CONFIGS["llama2_7b"], name="tiles_rerun", T=300, d=1024, d_ff=2744)
+    host = synth.make_inputs(cfg)
+    m = MixLoraFFN(cfg, host)
+    runs = []
+    for _ in range(2):
+        m.forward()
+        m.backward(d_aux=1.0)
+        runs.append(m.results())
+    for n in ("y", "dx") + pu.GRAD_NAMES:
+        assert np.array_equal(runs[0][n], runs[1][n]), n
