@@ -20,8 +20,8 @@ struct GemmBatch {
   GemmProblem p[GEMM_MAX_PROBLEMS];
 };
 
-// Logical id of hardware block `bid` of `nb`: blocks that land on the same XCD (bid % 8) get
-// consecutive logical ids.
+// Logical id of block `bid` of a run of `nb` consecutive blocks: blocks that land on the same XCD
+// (the hardware deals them out in turn, so equal bid % 8) get consecutive logical ids.
 __device__ __forceinline__ int xcd_order(int bid, int nb) {
   const int q = nb >> 3, rem = nb & 7;
   const int xcd = bid & 7, local = bid >> 3;
@@ -480,10 +480,11 @@ __global__ __launch_bounds__(WGM *WGN * 64) void gemm_bf16_dl_kernel(GemmBatch a
 // The last K tile of a segment may be ragged (K % 8 == 0): lanes past the end copy zeros.
 // Trailing tiles that would fill less than half of a last round of workgroups are cut along K
 // into S slices each (plan_tail below); a slice writes its fp32 partial tile to scratch and
-// gemm_tail_reduce_kernel adds the slices in order.
+// gemm_tail_reduce_kernel adds the slices in order.  Partial tiles are stored through the caches (the
+// other outputs stream past them): the reduction reads them back at once, 5-6 us sooner over 50 MB.
 struct GemmPlan {
   int nprob, tail_start, ntail, S;
-  int start[GEMM_MAX_PROBLEMS];   // first block of problem p's whole tiles (a multiple of 8)
+  int start[GEMM_MAX_PROBLEMS];   // first block of problem p's whole tiles
   int whole[GEMM_MAX_PROBLEMS];   // number of them: tiles [0, whole) in tile_of_lid's order
   int tail0[GEMM_MAX_PROBLEMS];   // first split tile of problem p among all split tiles
   float *part;                    // [S][ntail][BM][256]
@@ -524,14 +525,10 @@ __global__ __launch_bounds__(512) void gemm_bf16_pp_kernel(GemmBatch args, GemmP
   int bid = blockIdx.x, pi = 0, lid, slice = 0, S = 1, tt = 0;
   if (bid < plan.tail_start) {
     while (pi + 1 < plan.nprob && plan.start[pi + 1] <= bid) pi++;
-    bid -= plan.start[pi];
-    if (bid >= plan.whole[pi]) return;
-    lid = xcd_order(bid, plan.whole[pi]);
+    lid = xcd_order(bid - plan.start[pi], plan.whole[pi]);
   } else {
-    bid -= plan.tail_start;
     S = plan.S;
-    if (bid >= plan.ntail * S) return;
-    const int l = xcd_order(bid, plan.ntail * S);
+    const int l = xcd_order(bid - plan.tail_start, plan.ntail * S);
     slice = l / plan.ntail;
     tt = l - slice * plan.ntail;
     pi = tail_tile(plan, tt, lid);
@@ -717,7 +714,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_pp_kernel(GemmBatch args, GemmP
   // 16 bytes per lane and whole 128-byte (or longer) row segments; streaming stores, an output
   // tile is never read again by this launch
   __syncthreads();
-  auto store_rows = [&](auto *C, int64_t ldc, int r0, int c0, int rows, int cols) {
+  auto store_rows = [&](auto *C, int64_t ldc, int r0, int c0, int rows, int cols, bool streaming) {
     typedef typename std::remove_pointer<decltype(C)>::type OutT;
     constexpr int PER = 16 / (int)sizeof(OutT), TN = 64, EP = TN + PER;
     constexpr int CPW = TN / PER, RPW = 64 / CPW;
@@ -744,19 +741,22 @@ __global__ __launch_bounds__(512) void gemm_bf16_pp_kernel(GemmBatch args, GemmP
         const int rl = p * RPW + rr;
         const int r = r0 + wm * (BM / 2) + i * 32 + rl;
         const outp_t v = *reinterpret_cast<const outp_t *>(tile + rl * EP + cc * PER);
-        if (r < rows && c < cols) __builtin_nontemporal_store(v, reinterpret_cast<outp_t *>(C + r * ldc + c));
+        if (r < rows && c < cols) {
+          if (streaming) __builtin_nontemporal_store(v, reinterpret_cast<outp_t *>(C + r * ldc + c));
+          else *reinterpret_cast<outp_t *>(C + r * ldc + c) = v;
+        }
       }
       __builtin_amdgcn_wave_barrier();
     }
   };
   if (S > 1) {
-    store_rows(plan.part + ((int64_t)slice * plan.ntail + tt) * (BM * BN), BN, 0, 0, BM, BN);
+    store_rows(plan.part + ((int64_t)slice * plan.ntail + tt) * (BM * BN), BN, 0, 0, BM, BN, false);
     return;
   }
   const int per = P.c_f32 ? 4 : 8;
   if ((N % per) == 0 && (P.ldc % per) == 0 && (reinterpret_cast<uintptr_t>(P.C) & 15) == 0) {
-    if (P.c_f32) store_rows(reinterpret_cast<float *>(P.C), P.ldc, row0, col0, M, N);
-    else store_rows(reinterpret_cast<bf16_t *>(P.C), P.ldc, row0, col0, M, N);
+    if (P.c_f32) store_rows(reinterpret_cast<float *>(P.C), P.ldc, row0, col0, M, N, true);
+    else store_rows(reinterpret_cast<bf16_t *>(P.C), P.ldc, row0, col0, M, N, true);
     return;
   }
   // outputs whose rows are not whole 16-byte pieces (an odd number of experts, say)
@@ -776,45 +776,40 @@ __global__ __launch_bounds__(512) void gemm_bf16_pp_kernel(GemmBatch args, GemmP
   }
 }
 
-// Adds the S partial tiles of every split tile in slice order and writes them out: one workgroup
-// per 8 rows of a tile, 8 columns per thread.
+// Adds the S partial tiles of every split tile in slice order and writes them out.  Bound by the
+// partials' latency and rate: a thread owns 4 columns of a row (4 rows per workgroup), and requests
+// up to 8 slices before it adds the first.
 template <int BM>
 __global__ __launch_bounds__(256) void gemm_tail_reduce_kernel(GemmBatch args, GemmPlan plan) {
-  constexpr int BN = PP_BN;
+  constexpr int BN = PP_BN, INFLIGHT = 8;
   const int tt = blockIdx.x;
   int lid;
   const GemmProblem &P = args.p[tail_tile(plan, tt, lid)];
   int tm, tn;
   tile_of_lid(lid, (P.M + BM - 1) / BM, (P.N + BN - 1) / BN, tm, tn);
-  const int rt = blockIdx.y * 8 + (threadIdx.x >> 5), ct = (threadIdx.x & 31) * 8;
+  const int rt = blockIdx.y * 4 + (threadIdx.x >> 6), ct = (threadIdx.x & 63) * 4;
   const int r = tm * BM + rt, c = tn * BN + ct;
   if (r >= P.M || c >= P.N) return;
   const float *src = plan.part + (int64_t)tt * (BM * BN) + rt * BN + ct;
   const int64_t step = (int64_t)plan.ntail * (BM * BN);
-  Vec8<float> a;
-  a.load(src);
-#pragma unroll 4
-  for (int sp = 1; sp < plan.S; sp++) {
-    Vec8<float> b;
-    b.load(src + sp * step);
+  f32x4_t a = {0.f, 0.f, 0.f, 0.f};
+  for (int s0 = 0; s0 < plan.S; s0 += INFLIGHT) {
+    f32x4_t v[INFLIGHT];
 #pragma unroll
-    for (int i = 0; i < 8; i++) a.set(i, a.get(i) + b.get(i));
+    for (int i = 0; i < INFLIGHT; i++)   // (a slice past the last one is read again and not added)
+      v[i] = *reinterpret_cast<const f32x4_t *>(src + (s0 + i < plan.S ? s0 + i : s0) * step);
+#pragma unroll
+    for (int i = 0; i < INFLIGHT; i++)
+      if (s0 + i < plan.S) a += v[i];
   }
-  const int per = P.c_f32 ? 4 : 8;
-  if (c + 8 <= P.N && (P.ldc % per) == 0 && (reinterpret_cast<uintptr_t>(P.C) & 15) == 0) {
-    if (P.c_f32) {
-      a.store(reinterpret_cast<float *>(P.C) + r * P.ldc + c);
-    } else {
-      Vec8<bf16_t> o;
-#pragma unroll
-      for (int i = 0; i < 8; i++) o.set(i, a.get(i));
-      o.store(reinterpret_cast<bf16_t *>(P.C) + r * P.ldc + c);
-    }
+  if (c + 4 <= P.N && (P.ldc & 3) == 0 && (reinterpret_cast<uintptr_t>(P.C) & 15) == 0) {
+    if (P.c_f32) store_c4<float>(reinterpret_cast<float *>(P.C) + r * P.ldc + c, a[0], a[1], a[2], a[3]);
+    else store_c4<bf16_t>(reinterpret_cast<bf16_t *>(P.C) + r * P.ldc + c, a[0], a[1], a[2], a[3]);
     return;
   }
-  for (int i = 0; i < 8 && c + i < P.N; i++) {
-    if (P.c_f32) reinterpret_cast<float *>(P.C)[r * P.ldc + c + i] = a.get(i);
-    else reinterpret_cast<bf16_t *>(P.C)[r * P.ldc + c + i] = (bf16_t)a.get(i);
+  for (int i = 0; i < 4 && c + i < P.N; i++) {
+    if (P.c_f32) reinterpret_cast<float *>(P.C)[r * P.ldc + c + i] = a[i];
+    else reinterpret_cast<bf16_t *>(P.C)[r * P.ldc + c + i] = (bf16_t)a[i];
   }
 }
 
@@ -943,8 +938,11 @@ static bool dl_eligible(const GemmBatch &b, int nprob, int BK) {
 // How many trailing tiles of a launch of `tiles` to cut along K, and into how many slices.  The
 // last round of workgroups (one per CU) takes as long as a full one however few tiles it holds;
 // with S slices per tile it takes 1/S of that, plus the partial tiles' way through memory.
-// Per K tile a tile needs ~1.2 us (0.9 alone on the chip, 1.5 with all CUs at work), partial
-// tiles are written and read at ~4 TB/s, and the second launch costs ~6 us.
+// Per K tile a tile needs ~1.2 us (1.3 with few CUs at work, 1.5 with all of them and less clock),
+// partial tiles are written and read at ~6 TB/s, and the second launch costs ~5 us.  Measured
+// (us, uncut / cut, operands in HBM): 300 x 4096 x 11136 209 / 62 (7 slices), 300 x 11008 x 4096
+// 88 / 68 (2), 517 x 22016 x 4096 171 / 113 (2 of 258 tiles in 16), 1999 x 4096 x 22272 425 / 277 (2),
+// 236 x 1024 x 4096 85 / 23 (12).
 static void plan_tail(int tiles, int ktiles, int BM, size_t part_floats, int &ntail, int &S) {
   constexpr int CUS = 256;
   ntail = 0;
@@ -954,7 +952,7 @@ static void plan_tail(int tiles, int ktiles, int BM, size_t part_floats, int &nt
   const double tile_mb = BM * PP_BN * 8e-6;   // MB written and read again per partial tile
   double best = 0.0;
   for (int n = 2; n <= 32 && n * tail <= CUS && ktiles / n >= 4 && (size_t)n * tail * BM * PP_BN <= part_floats; n++) {
-    const double gain = 1.2 * ktiles * (1.0 - 1.0 / n) - (tail * n * tile_mb / 4.0 + 6.0);
+    const double gain = 1.2 * ktiles * (1.0 - 1.0 / n) - (tail * n * tile_mb / 6.0 + 5.0);
     if (gain > best) {
       best = gain;
       ntail = tail;
@@ -994,7 +992,7 @@ static hipError_t launch_pp(const GemmBatch &b, int nprob, int ntail, int S, flo
     plan.whole[i] = w;
     plan.tail0[i] = before + w - whole_all;      // <= 0 up to the first problem with split tiles
     if (plan.tail0[i] < 0) plan.tail0[i] = 0;
-    at += (w + 7) & ~7;
+    at += w;   // no padding between problems: 256 tiles are 32 per XCD, one round
     before += n;
   }
   plan.tail_start = at;
@@ -1003,7 +1001,7 @@ static hipError_t launch_pp(const GemmBatch &b, int nprob, int ntail, int S, flo
   if (slot >= 0) prof_mark_end(slot, st, batch_flops(b, nprob));
   if (ntail > 0) {
     const int s2 = prof_on() ? prof_mark_begin(PROF_OTHER, st) : -1;
-    hipLaunchKernelGGL(gemm_tail_reduce_kernel<BM>, dim3(ntail, BM / 8), dim3(256), 0, st, b, plan);
+    hipLaunchKernelGGL(gemm_tail_reduce_kernel<BM>, dim3(ntail, BM / 4), dim3(256), 0, st, b, plan);
     if (s2 >= 0) prof_mark_end(s2, st, 0.0);
   }
   return hipGetLastError();
