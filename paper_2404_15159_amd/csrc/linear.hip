@@ -1,8 +1,10 @@
 // Plain LoRA linear (Eq. 1 with the scale alpha / r), the form the method puts on the attention
 // projections (Section 3.2):  y = x W^T + s (x A^T) B^T  with W frozen.  Built from the same
-// pieces as the feed-forward block: the frozen product and the rank-r projection share one GEMM
-// launch, the rank-r update is added in place in fp32 before the result is rounded, and the
-// gradients of A and B are outer-product sums over all tokens as one group.
+// pieces as the feed-forward block.  bf16 with more than 128 rows: the rank-r projection s x A^T
+// is made first (rank_project_kernel) and enters the frozen product as two extra K segments, its
+// bf16 value and the bf16 rounding residue of it.  Otherwise the frozen product and the projection
+// share one GEMM launch and the rank-r update is added in place in fp32.  The gradients of A and B
+// are outer-product sums over all tokens as one group.
 #include "common.h"
 
 using namespace mixlora;
@@ -18,10 +20,11 @@ inline int pad_rank(int r) { return (r + 7) & ~7; }
 struct LinLayout {
   int rp;                         // rank entries the pass runs on: r rounded up to a multiple of 8
   size_t padA, padB, padgA, padgB;   // zero-padded copies of A, B (kept for the backward) and of dA, dB
-  size_t P, tok_offs, slices, fwd_end;
-  size_t W_T, Bt, At, VB, VB_T, P_T, partials, bwd_end;
-  size_t partial_floats;
+  size_t P, P_T, tok_offs, ext, gemm_part, fwd_end;
+  size_t W_T, Bt, At, VB, VB_T, partials, bwd_end;
+  size_t partial_floats, gemm_floats;
   int ldT;
+  bool extend;                    // the rank-r term rides in the frozen product
 };
 
 LinLayout make_layout(const mixlora_linear_dims &D) {
@@ -35,16 +38,23 @@ LinLayout make_layout(const mixlora_linear_dims &D) {
   L.padA = take(padded ? r * di * E : 0);
   L.padB = take(padded ? dn * r * E : 0);
   L.P = take(T * r * 4);
+  L.extend = E == 2 && T > 128;
+  L.ldT = (int)((T + 15) / 16 * 16 + 16);
+  L.P_T = take((size_t)L.ldT * r * 2);
   L.tok_offs = take(2 * 4);
-  L.slices = take((size_t)(GEMM_MAX_PROBLEMS - 1) * T * r * 4);   // K-slice partial sums of a rank-r projection
+  L.ext = take(L.extend ? T * 2 * r * 2 : 0);
+  {   // partial tiles of products cut along K: at most one tile per CU
+    const size_t slices = (di > dn ? di : dn) / 64 / 4;
+    const size_t tiles = (T / 192 + 1) * ((di > dn ? di : dn) / 256 + 1) * slices;
+    L.gemm_floats = L.extend && slices >= 2 ? GEMM_SCRATCH_FLOATS / 256 * (tiles < 256 ? tiles : 256) : 0;
+    L.gemm_part = take(L.gemm_floats * 4);
+  }
   L.fwd_end = o;
   L.W_T = take(di * dn * E);
   L.Bt = take(r * dn * E);
   L.At = take(di * r * E);
   L.VB = take(T * r * 4);
-  L.ldT = (int)((T + 15) / 16 * 16 + 16);
   L.VB_T = take((size_t)L.ldT * r * 2);
-  L.P_T = take((size_t)L.ldT * r * 2);
   const int big = (int)(di > dn ? di : dn);
   size_t pf = group_outer_partial_floats(1, (int)r, big);
   const size_t pm = group_outer_mfma_partial_floats(1, (int)r, big);
@@ -52,6 +62,7 @@ LinLayout make_layout(const mixlora_linear_dims &D) {
                    group_outer_mfma_partial_floats(1, (int)r, (int)di),
                    group_outer_mfma_partial_floats(1, (int)r, (int)dn), pm})
     pf = v > pf ? v : pf;
+  if (di == dn) pf *= 2;   // both sums in one launch
   L.partial_floats = pf;
   L.partials = take(pf * 4);
   L.padgA = take(padded ? r * di * 4 : 0);
@@ -87,35 +98,114 @@ GemmProblem problem(int M, int N, void *C, int64_t ldc, int c_f32, const void *A
   return p;
 }
 
-// One launch for  C_main = X Wmain^T  (storage dtype)  and the rank-r projection
-// C_small = X Wsmall^T  (float32, r columns), both with contraction length K.  The frozen product of
-// a square projection fills the chip exactly once, so a second problem whose few tiles run the
-// whole K range would add a second round almost as long as the first; the small problem is
-// therefore cut into K slices (one problem each, fp32 partial outputs) that finish in a fraction
-// of a round, and the slices are added in order afterwards.
-int gemm_with_sliced_projection(int dtype, int T, int Nmain, int r, int K, const void *X,
-                                const void *Wmain, void *Cmain, const void *Wsmall, float *Csmall,
-                                float *slices, hipStream_t st) {
-  const size_t E = dtype == MIXLORA_BF16 ? 2 : 4;
-  const int ktiles = (K + 63) / 64;
-  int S = GEMM_MAX_PROBLEMS - 1;
-  if (dtype != MIXLORA_BF16 || T <= 128 || ktiles < 2 * S) S = 1;
-  GemmProblem p[GEMM_MAX_PROBLEMS];
-  p[0] = problem(T, Nmain, Cmain, Nmain, 0, X, K, Wmain, K, K);
-  if (S == 1) {
-    p[1] = problem(T, r, Csmall, r, 1, X, K, Wsmall, K, K);
-    HIP_TRY(launch_gemm(dtype, p, 2, st));
-    return MIXLORA_OK;
+// P[t, q] = sum_c X[t, c] * Wq[q, c]  (r <= 64 columns), in three forms: fp32, transposed bf16 (the
+// row factor of the gradient sums) and s * P split into a bf16 value and its bf16 residue,
+// ext[t] = [hi(r) | lo(r)]: hi + lo carries s * P to 2^-17, far below the rounding of the product
+// that it is added to.  Bound by reading X once (33 MB at 4096 x 4096: 9 us); a workgroup owns 16
+// rows, its eight waves every eighth 128-column run of them, so that 256 workgroups have 2 waves
+// per SIMD with 4 KB each in flight; fragments come straight from memory (whole 128-byte lines over
+// four MFMA steps), Wq from the caches.  The waves' sums are added in a fixed order.
+template <int NQ>
+__global__ __launch_bounds__(512) void rank_project_kernel(const bf16_t *__restrict__ X,
+                                                           const bf16_t *__restrict__ Wq, int T, int K,
+                                                           int r, float s, float *__restrict__ P,
+                                                           bf16_t *__restrict__ PT, int ldT,
+                                                           bf16_t *__restrict__ ext,
+                                                           int32_t *__restrict__ tok_offs) {
+  __shared__ float red[8][NQ][64][4];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int l15 = lane & 15, hi = lane >> 4;
+  const int t0 = blockIdx.x * 16;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {   // all tokens are one group of the gradient sums
+    tok_offs[0] = 0;
+    tok_offs[1] = T;
   }
-  const int chunk = ((ktiles + S - 1) / S) * 64;
-  int used = 0;
-  for (int k0 = 0; k0 < K; k0 += chunk, used++) {
-    const int klen = K - k0 < chunk ? K - k0 : chunk;
-    p[1 + used] = problem(T, r, slices + (size_t)used * T * r, r, 1, (const char *)X + (size_t)k0 * E, K,
-                          (const char *)Wsmall + (size_t)k0 * E, K, klen);
+  const int row = t0 + l15 < T ? t0 + l15 : T - 1;
+  const bf16_t *xr = X + (int64_t)row * K;
+  const bf16_t *wr[NQ];
+#pragma unroll
+  for (int j = 0; j < NQ; j++) wr[j] = Wq + (int64_t)(j * 16 + l15 < r ? j * 16 + l15 : r - 1) * K;
+  f32x4_t acc[NQ];
+#pragma unroll
+  for (int j = 0; j < NQ; j++) acc[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  for (int k0 = wave * 128; k0 < K; k0 += 8 * 128) {
+    bf16x8_t fx[4], fw[NQ][4];
+#pragma unroll
+    for (int ks = 0; ks < 4; ks++) {
+      const int k = k0 + ks * 32 + hi * 8;
+      const int kc = k < K ? k : 0;
+      fx[ks] = *reinterpret_cast<const bf16x8_t *>(xr + kc);
+#pragma unroll
+      for (int j = 0; j < NQ; j++) fw[j][ks] = *reinterpret_cast<const bf16x8_t *>(wr[j] + kc);
+    }
+#pragma unroll
+    for (int ks = 0; ks < 4; ks++) {
+      if (k0 + ks * 32 + hi * 8 >= K) {   // past the end: zeros on both sides
+#pragma unroll
+        for (int m = 0; m < 8; m++) fx[ks][m] = (bf16_t)0.f;
+#pragma unroll
+        for (int j = 0; j < NQ; j++)
+#pragma unroll
+          for (int m = 0; m < 8; m++) fw[j][ks][m] = (bf16_t)0.f;
+      }
+#pragma unroll
+      for (int j = 0; j < NQ; j++)
+        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[j][ks], fx[ks], acc[j], 0, 0, 0);
+    }
   }
-  HIP_TRY(launch_gemm(dtype, p, 1 + used, st));
-  HIP_TRY(launch_splitk_reduce(MIXLORA_F32, slices, used, (int64_t)T * r, Csmall, st));
+#pragma unroll
+  for (int j = 0; j < NQ; j++) *reinterpret_cast<f32x4_t *>(red[wave][j][lane]) = acc[j];
+  __syncthreads();
+  // acc[j][m] of lane (l15, hi): row l15, q = 16 j + 4 hi + m
+  for (int i = threadIdx.x; i < NQ * 256; i += 512) {
+    const int j = i >> 8, q = j * 16 + (i & 15), t = t0 + ((i >> 4) & 15);
+    if (q >= r || t >= T) continue;
+    const int ln = ((i >> 2) & 3) * 16 + ((i >> 4) & 15), m = i & 3;
+    float v = red[0][j][ln][m];
+#pragma unroll
+    for (int w = 1; w < 8; w++) v += red[w][j][ln][m];
+    P[(int64_t)t * r + q] = v;
+    PT[(int64_t)q * ldT + t] = (bf16_t)v;
+    const float sv = s * v;
+    const bf16_t h = (bf16_t)sv;
+    ext[(int64_t)t * 2 * r + q] = h;
+    ext[(int64_t)t * 2 * r + r + q] = (bf16_t)(__builtin_isinf((float)h) ? 0.f : sv - (float)h);
+  }
+}
+
+// C = X Wmain^T + s (X Wq^T) Wr^T for bf16 and more than 128 rows: the projection, then one product
+// over the K segments [X | hi | lo] x [Wmain | Wr | Wr].  P and PT keep the projection (unscaled).
+// Against the product beside an unextended projection, its slices' sum and an in-place update of C:
+// 4096 x 4096 x 4096, rank 16, 157 -> 108 us, and one rounding of C less.
+int extended_product(const LinLayout &L, char *ws, int T, int Nmain, int r, int K, float s, const void *X,
+                     const void *Wmain, void *C, const void *Wq, const void *Wr, float *P, void *PT,
+                     hipStream_t st) {
+  const dim3 grid((T + 15) / 16), block(512);
+#define MIXLORA_RANKP(NQ_)                                                                          \
+  hipLaunchKernelGGL(rank_project_kernel<NQ_>, grid, block, 0, st, (const bf16_t *)X,               \
+                     (const bf16_t *)Wq, T, K, r, s, P, (bf16_t *)PT, L.ldT, (bf16_t *)(ws + L.ext), \
+                     (int32_t *)(ws + L.tok_offs))
+  if (r <= 16) MIXLORA_RANKP(1);
+  else if (r <= 32) MIXLORA_RANKP(2);
+  else MIXLORA_RANKP(4);
+#undef MIXLORA_RANKP
+  HIP_TRY(hipGetLastError());
+  GemmProblem p = problem(T, Nmain, C, Nmain, 0, X, K, Wmain, K, K);
+  const bf16_t *ext = (const bf16_t *)(ws + L.ext);
+  p.seg[1] = GemmSeg{ext, Wr, 2 * r, r, r};
+  p.seg[2] = GemmSeg{ext + r, Wr, 2 * r, r, r};
+  p.nseg = 3;
+  HIP_TRY(launch_gemm(MIXLORA_BF16, &p, 1, st, GemmScratch{(float *)(ws + L.gemm_part), L.gemm_floats}));
+  return MIXLORA_OK;
+}
+
+// C_main = X Wmain^T  (storage dtype)  and the rank-r projection  C_small = X Wsmall^T  (float32, r
+// columns), one launch where both have a kernel in common.
+int product_and_projection(int dtype, int T, int Nmain, int r, int K, const void *X, const void *Wmain,
+                           void *Cmain, const void *Wsmall, float *Csmall, hipStream_t st) {
+  const GemmProblem p[2] = {problem(T, Nmain, Cmain, Nmain, 0, X, K, Wmain, K, K),
+                            problem(T, r, Csmall, r, 1, X, K, Wsmall, K, K)};
+  HIP_TRY(launch_gemm(dtype, p, 2, st));
   return MIXLORA_OK;
 }
 
@@ -150,9 +240,12 @@ int mixlora_lora_linear_forward(const mixlora_linear_dims *dims, const void *W, 
     B = ws + L.padB;
     D.r = L.rp;
   }
+  if (L.extend)
+    return extended_product(L, ws, D.T, D.d_out, D.r, D.d_in, D.lora_scale, x, W, y, A, B,
+                            (float *)(ws + L.P), ws + L.P_T, st);
   // y0 = x W^T and P = x A^T in one launch (both read x), then y = y0 + s P B^T in place
-  const int grc = gemm_with_sliced_projection(D.dtype, D.T, D.d_out, D.r, D.d_in, x, W, y, A,
-                                              (float *)(ws + L.P), (float *)(ws + L.slices), st);
+  const int grc = product_and_projection(D.dtype, D.T, D.d_out, D.r, D.d_in, x, W, y, A,
+                                         (float *)(ws + L.P), st);
   if (grc) return grc;
   HIP_TRY(launch_lowrank_add(D.dtype, y, (const float *)(ws + L.P), B, D.T, D.d_out, D.r,
                              D.lora_scale, st));
@@ -193,25 +286,37 @@ int mixlora_lora_linear_backward(const mixlora_linear_dims *dims, const void *W,
                                  job_bank_T(A, 1, r, di, ws + L.At)};    // [r, d_in]  -> [d_in, r]
     HIP_TRY(launch_relayout(dt, jobs, 2, st));
   }
-  hipLaunchKernelGGL(set_pair_kernel, dim3(1), dim3(64), 0, st, (int32_t *)(ws + L.tok_offs), 0, T);
-  HIP_TRY(hipGetLastError());
-  // dx0 = dy W and VB = dy B in one launch (both read dy), then dx = dx0 + s VB A in place
-  const int grc = gemm_with_sliced_projection(dt, T, di, r, dn, dy, W_T, dx, ws + L.Bt,
-                                              (float *)(ws + L.VB), (float *)(ws + L.slices), st);
-  if (grc) return grc;
-  HIP_TRY(launch_lowrank_add(dt, dx, (const float *)(ws + L.VB), ws + L.At, T, di, r, s, st));
+  if (L.extend) {
+    const int erc = extended_product(L, ws, T, di, r, dn, s, dy, W_T, dx, ws + L.Bt, ws + L.At,
+                                     (float *)(ws + L.VB), ws + L.VB_T, st);
+    if (erc) return erc;
+  } else {
+    hipLaunchKernelGGL(set_pair_kernel, dim3(1), dim3(64), 0, st, (int32_t *)(ws + L.tok_offs), 0, T);
+    HIP_TRY(hipGetLastError());
+    // dx0 = dy W and VB = dy B in one launch (both read dy), then dx = dx0 + s VB A in place
+    const int grc = product_and_projection(dt, T, di, r, dn, dy, W_T, dx, ws + L.Bt,
+                                           (float *)(ws + L.VB), st);
+    if (grc) return grc;
+    HIP_TRY(launch_lowrank_add(dt, dx, (const float *)(ws + L.VB), ws + L.At, T, di, r, s, st));
+    if (dt == MIXLORA_BF16) {
+      HIP_TRY(launch_f32_to_bf16T((const float *)(ws + L.VB), T, r, ws + L.VB_T, L.ldT, st));
+      HIP_TRY(launch_f32_to_bf16T((const float *)(ws + L.P), T, r, ws + L.P_T, L.ldT, st));
+    }
+  }
   // dA = s VB^T x  [r, d_in];  dB = s dy^T P  [d_out, r]: outer-product sums over all tokens
   const int32_t *tok = (const int32_t *)(ws + L.tok_offs);
   float *part = (float *)(ws + L.partials);
   if (dt == MIXLORA_BF16) {
-    HIP_TRY(launch_f32_to_bf16T((const float *)(ws + L.VB), T, r, ws + L.VB_T, L.ldT, st));
-    const GomJob ja{ws + L.VB_T, x, dA, 1};
-    HIP_TRY(launch_group_outer_mfma(tok, 1, T, nullptr, 1, &ja, 1, L.ldT, r, di, s, part,
-                                    L.partial_floats, st));
-    HIP_TRY(launch_f32_to_bf16T((const float *)(ws + L.P), T, r, ws + L.P_T, L.ldT, st));
-    const GomJob jb{ws + L.P_T, dy, dB, 0};
-    HIP_TRY(launch_group_outer_mfma(tok, 1, T, nullptr, 1, &jb, 1, L.ldT, r, dn, s, part,
-                                    L.partial_floats, st));
+    const GomJob j2[2] = {GomJob{ws + L.VB_T, x, dA, 1}, GomJob{ws + L.P_T, dy, dB, 0}};
+    if (di == dn) {   // same width: one launch
+      HIP_TRY(launch_group_outer_mfma(tok, 1, T, nullptr, 1, j2, 2, L.ldT, r, di, s, part,
+                                      L.partial_floats, st));
+    } else {
+      HIP_TRY(launch_group_outer_mfma(tok, 1, T, nullptr, 1, j2, 1, L.ldT, r, di, s, part,
+                                      L.partial_floats, st));
+      HIP_TRY(launch_group_outer_mfma(tok, 1, T, nullptr, 1, j2 + 1, 1, L.ldT, r, dn, s, part,
+                                      L.partial_floats, st));
+    }
   } else {
     HIP_TRY(launch_group_outer(dt, tok, 1, T, nullptr, 1, (const float *)(ws + L.VB), r, x, di, s, 1,
                                dA, part, L.partial_floats, st));

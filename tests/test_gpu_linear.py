@@ -20,6 +20,12 @@ CASES = [
     ("bf16_multi_tile", 1000, 512, 1288, 8, "bf16", True),
     ("bf16_few_rows", 17, 512, 704, 16, "bf16", True),
     ("bf16_one_row", 1, 64, 128, 8, "bf16", True),
+    # both sides of the row count from which the rank-r term rides in the frozen product; square
+    # (one launch for both gradient sums), column blocks of 16 that are not full, cut K ranges
+    ("bf16_128_rows", 128, 264, 264, 40, "bf16", True),
+    ("bf16_129_rows", 129, 264, 264, 40, "bf16", True),
+    ("bf16_square_split", 200, 1024, 1024, 8, "bf16", True),
+    ("bf16_r12_square", 331, 1032, 1032, 12, "bf16", False),
 ]
 
 
