@@ -170,11 +170,10 @@ Layout make_layout(const mixlora_dims &D, int schedule = MIXLORA_SCHEDULE_LINEAR
   L.Bx = take(d * (size_t)L.Kx * E);
   for (int i = 0; i < 6; i++) L.pad_g[i] = take((int)r != D.r ? bank_elems(i, N, r, d, f) * 4 : 0);
   L.dz = take(T * N * 4);
-  size_t pf = group_outer_partial_floats((int)N, (int)r, (int)f);
-  size_t pd = group_outer_partial_floats((int)N, (int)r, (int)d);
-  size_t pr = group_outer_partial_floats(1, (int)N, (int)d);
-  L.partial_floats = pf > pd ? pf : pd;
-  if (pr > L.partial_floats) L.partial_floats = pr;
+  if (E == 4)   // all seven sums of the pass at once
+    L.partial_floats = 3 * group_outer_partial_floats((int)N, (int)r, (int)f, (int)kT) +
+                       3 * group_outer_partial_floats((int)N, (int)r, (int)d, (int)kT) +
+                       group_outer_partial_floats(1, (int)N, (int)d, (int)T);
   for (size_t v : {GOM_MAX_JOBS * group_outer_mfma_partial_floats((int)N, (int)r, (int)f),
                    GOM_MAX_JOBS * group_outer_mfma_partial_floats((int)N, (int)r, (int)d),
                    group_outer_mfma_partial_floats(1, (int)N, (int)d)})
@@ -507,7 +506,7 @@ static int forward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mod
                                    w->B_up, w->A_down, ws + L.a_grp, (float *)(ws + L.rank_part),
                                    (float *)(ws + L.Q_all), ws + L.Qw, R, st, 0, nullptr, !merge_tail));
   } else {
-    HIP_TRY_AS(PROF_FUSED_FWD, 3.0 * kT * f * Eb, launch_swiglu_fwd(dt, pc, f, D.lora_scale, ws + L.G, ws + L.U,
+    HIP_TRY_AS(PROF_FUSED_FWD, 3.0 * kT * f * Eb, launch_swiglu_fwd(pc, f, D.lora_scale, ws + L.G, ws + L.U,
                               (float *)(ws + L.Pg_all), (float *)(ws + L.Pu_all), w->B_gate,
                               w->B_up, ws + L.a_grp, st));
     // A_down of every expert on the grouped activations
@@ -753,7 +752,7 @@ static int backward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mo
                                    (float *)(ws + L.TU_all), Sop, Kx, st, rows_mode,
                                    dora ? &dargs : nullptr));
   } else {
-    HIP_TRY_AS(PROF_FUSED_BWD, 5.0 * kT * f * Eb, launch_swiglu_bwd(dt, pc, f, s, ws + L.G, ws + L.U, (float *)(ws + L.Pg_all),
+    HIP_TRY_AS(PROF_FUSED_BWD, 5.0 * kT * f * Eb, launch_swiglu_bwd(pc, f, s, ws + L.G, ws + L.U, (float *)(ws + L.Pg_all),
                               (float *)(ws + L.Pu_all), w->B_gate, w->B_up, ws + L.H,
                               (float *)(ws + L.VB_all), w->A_down, ws + L.dg_grp, ws + L.du_grp,
                               (float *)(ws + L.dw_part), L.nct, st));
@@ -850,15 +849,18 @@ static int backward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mo
                launch_group_outer_mfma((int32_t *)(ws + L.tok_offs), 1, T, nullptr, 1, &jr, 1, L.ldTz,
                                        N, d, 1.f, part, pfl, st));
   } else {
+    GatherJob gj[6];
+    GoJob go[GO_MAX_JOBS];
     for (int i = 0; i < 6; i++) {
-      HIP_TRY_AS(PROF_OTHER, 0, launch_gather_small(pc, fsrc[i], by_token[i], weighted[i], (float *)(ws + L.small[i]), st));
-      HIP_TRY_AS(PROF_GRAD_SUMS, (double)kT * width[i] * Eb,
-                 launch_group_outer(dt, offs, N, kT, gat[i], k, (float *)(ws + L.small[i]), r, wide[i],
-                                    width[i], s, layout_qc[i], gout[i], part, pfl, st));
+      gj[i] = GatherJob{fsrc[i], ws + L.small[i], by_token[i], weighted[i]};
+      go[i] = GoJob{offs, gat[i], (float *)(ws + L.small[i]), (const float *)wide[i], gout[i],
+                    N, r, width[i], k, (int)kT, layout_qc[i], s};
     }
-    HIP_TRY_AS(PROF_GRAD_SUMS, (double)T * d * Eb,
-               launch_group_outer(dt, (int32_t *)(ws + L.tok_offs), 1, T, nullptr, 1,
-                                  (float *)(ws + L.dz), N, x, d, 1.f, 1, grads->dW_router, part, pfl, st));
+    go[6] = GoJob{(int32_t *)(ws + L.tok_offs), nullptr, (float *)(ws + L.dz), (const float *)x,
+                  grads->dW_router, 1, N, d, 1, T, 1, 1.f};
+    HIP_TRY_AS(PROF_OTHER, 0, launch_gather_small(pc, gj, 6, st));
+    HIP_TRY_AS(PROF_GRAD_SUMS, (3.0 * kT * f + 3.0 * kT * d + (double)T * d) * Eb,
+               launch_group_outer(go, GO_MAX_JOBS, part, pfl, st));
   }
   if (L.rp != Du.r) {
     float *dst[6] = {grads_user->dA_gate, grads_user->dB_gate, grads_user->dA_up,

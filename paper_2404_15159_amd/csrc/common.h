@@ -161,12 +161,13 @@ struct PairCtx {  // device pointers describing the grouped pairs
 };
 
 // a_grp[row,:] = SiLU(G[t] + s B_gate[e] Pg[t,e]) * (U[t] + s B_up[e] Pu[t,e]),  rows grouped
-hipError_t launch_swiglu_fwd(int dtype, const PairCtx &pc, int f, float s, const void *G,
+// (fp32 storage, as the next one)
+hipError_t launch_swiglu_fwd(const PairCtx &pc, int f, float s, const void *G,
                              const void *U, const float *Pg_all, const float *Pu_all,
                              const void *B_gate, const void *B_up, void *a_grp,
                              hipStream_t st);
 // backward of the above; also the per-(row, column tile) partial sums of <H[t], a_row>
-hipError_t launch_swiglu_bwd(int dtype, const PairCtx &pc, int f, float s, const void *G,
+hipError_t launch_swiglu_bwd(const PairCtx &pc, int f, float s, const void *G,
                              const void *U, const float *Pg_all, const float *Pu_all,
                              const void *B_gate, const void *B_up, const void *H,
                              const float *VB_all, const void *A_down, void *dg_grp,
@@ -267,10 +268,6 @@ hipError_t launch_gather_rows(int dtype, const PairCtx &pc, int width, const voi
 hipError_t launch_scatter_blocks(int dtype, const PairCtx &pc, const float *src, int64_t src_stride,
                                  int nsrc, int lds_, int src_dense, int weighted, void *dst,
                                  int ldd, int col0, hipStream_t st);
-// small_grp[row, q] = scale * src[(by_token ? t(row) : row), e(row)*r + q]   (float32)
-hipError_t launch_gather_small(const PairCtx &pc, const float *src, int by_token, int weighted,
-                               float *small_grp, hipStream_t st);
-
 // io[t, c] += s * sum_q P[t, q] * Wt[c, q]   (io [T,C] storage dtype, P [T,r] f32, Wt [C,r])
 hipError_t launch_lowrank_add(int dtype, void *io, const float *P, const void *Wt, int T, int C,
                               int r, float s, hipStream_t st);
@@ -318,12 +315,20 @@ hipError_t launch_transpose(int dtype, const void *in, void *out, int rows, int 
 
 // ---- gradients --------------------------------------------------------------------------
 // out[g][q][c] (layout_qc = 1) or out[g][c][q] (0) = scale * sum over rows of group g of
-//   small[row, q] * wide[(tok_of_row ? tok(row) : row), c];   groups from offs[0..G].
-hipError_t launch_group_outer(int dtype, const int32_t *offs, int G, int max_rows,
-                              const int32_t *pair_of_row, int k, const float *small, int r,
-                              const void *wide, int C, float scale, int layout_qc, float *out,
-                              float *partials, size_t partial_floats, hipStream_t st);
-size_t group_outer_partial_floats(int G, int r, int C);
+//   small[row, q] * wide[(pair_of_row ? pair_of_row[row] / k : row), c];   groups from offs[0..G].
+// fp32 storage; rows is the number of rows of all groups together.  Up to GO_MAX_JOBS sums of any
+// shapes in one launch; partials holds the sum of their group_outer_partial_floats.
+struct GoJob {
+  const int32_t *offs, *pair_of_row;
+  const float *small, *wide;
+  float *out;
+  int G, r, C, k, rows, layout_qc;
+  float scale;
+};
+constexpr int GO_MAX_JOBS = 7;
+hipError_t launch_group_outer(const GoJob *jobs, int njobs, float *partials, size_t partial_floats,
+                              hipStream_t st);
+size_t group_outer_partial_floats(int G, int r, int C, int rows);
 
 // bf16 MFMA version: smallT is the transposed bf16 factor [r][ldT] (ldT % 8 == 0, readable up to
 // the next multiple of 16 rows past the last group), wide is bf16 with C % 8 == 0.  Up to
@@ -349,6 +354,8 @@ struct GatherJob {
   int by_token, weighted;
 };
 constexpr int GATHER_MAX_JOBS = 6;
+// the same untransposed in float32:  out[row, q]
+hipError_t launch_gather_small(const PairCtx &pc, const GatherJob *jobs, int njobs, hipStream_t st);
 hipError_t launch_gather_small_T(const PairCtx &pc, const GatherJob *jobs, int njobs, int ldT,
                                  hipStream_t st);
 hipError_t launch_f32_to_bf16T(const float *src, int rows, int r, void *outT, int ldT,

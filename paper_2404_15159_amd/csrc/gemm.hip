@@ -813,57 +813,87 @@ __global__ __launch_bounds__(256) void gemm_tail_reduce_kernel(GemmBatch args, G
   }
 }
 
-// ---- fp32 storage: 64x64 tile, 256 threads, 4x4 outputs per thread ----------------------
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmBatch args) {
-  constexpr int BM = 64, BN = 64, BK = 16;
-  __shared__ float As[BK][BM + 4];
-  __shared__ float Bs[BK][BN + 4];
+// ---- fp32 storage ---------------------------------------------------------------------------
+// MFMA 16x16x4 fp32 (each product and sum rounded to fp32) on a TB x TB tile; the waves of a
+// workgroup take every NWV-th 16-wide run of K (of all segments in a row) and their sums are added
+// in wave order through LDS.  Fragments come straight from memory as 16-byte loads: lane (l15, hi)
+// holds elements 4 hi .. 4 hi + 3 of a row's run, i.e. four MFMA steps whose K order is permuted
+// alike on both sides.  fp32 problems here are small (the configuration the numerics are checked
+// on: 256 x 344 x 128 and the like), so what bounds them is the latency of a chain of loads: eight
+// waves on a 32 x 32 tile walk K in an eighth of the steps and cover the chip with tiles, where a
+// 64 x 64 tile staged through LDS left most of it idle (256 x 128 x 824: 64 -> 11 us).  Where 64 x 64
+// tiles are many enough for every CU, they halve the loads per product.
+template <int TB, int NWV>
+__global__ __launch_bounds__(NWV * 64) void gemm_f32_kernel(GemmBatch args) {
+  constexpr int NB = TB / 16;
+  __shared__ float red[NWV][TB][TB + (TB == 64 ? 0 : 4)];   // 64 KB at most
   const GemmProblem &P = args.p[blockIdx.z];
   const int M = P.M, N = P.N;
-  const int tiles_n = (N + BN - 1) / BN;
-  const int tm = blockIdx.x / tiles_n, tn = blockIdx.x % tiles_n;
-  const int row0 = tm * BM, col0 = tn * BN;
-  const int tid = threadIdx.x;
-  const int tx = tid & 15, ty = tid >> 4;
-  float acc[4][4] = {};
-  const int lr = tid >> 2, lk = (tid & 3) * 4;   // 64 rows x 4 float4 chunks
-  for (int s = 0; s < P.nseg; s++) {
-    const GemmSeg &S = P.seg[s];
-    const float *A = reinterpret_cast<const float *>(S.A);
-    const float *B = reinterpret_cast<const float *>(S.B);
-    for (int k0 = 0; k0 < S.K; k0 += BK) {
-      float4 va = make_float4(0, 0, 0, 0), vb = va;
-      if (k0 + lk < S.K) {   // K % 8 == 0, so a float4 chunk is entirely in or out
-        if (row0 + lr < M) va = *reinterpret_cast<const float4 *>(A + (int64_t)(row0 + lr) * S.lda + k0 + lk);
-        if (col0 + lr < N) vb = *reinterpret_cast<const float4 *>(B + (int64_t)(col0 + lr) * S.ldb + k0 + lk);
-      }
-      __syncthreads();
-      As[lk + 0][lr] = va.x; As[lk + 1][lr] = va.y; As[lk + 2][lr] = va.z; As[lk + 3][lr] = va.w;
-      Bs[lk + 0][lr] = vb.x; Bs[lk + 1][lr] = vb.y; Bs[lk + 2][lr] = vb.z; Bs[lk + 3][lr] = vb.w;
-      __syncthreads();
+  const int tiles_m = (M + TB - 1) / TB, tiles_n = (N + TB - 1) / TB;
+  if ((int)blockIdx.x >= tiles_m * tiles_n) return;   // problems of one launch may differ in shape
+  const int row0 = blockIdx.x / tiles_n * TB, col0 = blockIdx.x % tiles_n * TB;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int l15 = lane & 15, hi = lane >> 4;
+  int arow[NB], bcol[NB];
 #pragma unroll
-      for (int kk = 0; kk < BK; kk++) {
-        float a[4], b[4];
-#pragma unroll
-        for (int i = 0; i < 4; i++) a[i] = As[kk][ty * 4 + i];
-#pragma unroll
-        for (int j = 0; j < 4; j++) b[j] = Bs[kk][tx * 4 + j];
-#pragma unroll
-        for (int i = 0; i < 4; i++)
-#pragma unroll
-          for (int j = 0; j < 4; j++) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-      }
-    }
+  for (int i = 0; i < NB; i++) {   // rows past the edge: the last one again, never stored
+    arow[i] = row0 + i * 16 + l15 < M ? row0 + i * 16 + l15 : M - 1;
+    bcol[i] = col0 + i * 16 + l15 < N ? col0 + i * 16 + l15 : N - 1;
   }
+  f32x4_t acc[NB][NB];
+#pragma unroll
+  for (int i = 0; i < NB; i++)
+#pragma unroll
+    for (int j = 0; j < NB; j++) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  int turn = wave;   // runs until this wave's next one
+  for (int sgi = 0; sgi < P.nseg; sgi++) {
+    const GemmSeg &S = P.seg[sgi];
+    const float *A = reinterpret_cast<const float *>(S.A), *B = reinterpret_cast<const float *>(S.B);
+    const int runs = (S.K + 15) >> 4;
+    const int mine = turn < runs ? (runs - turn + NWV - 1) / NWV : 0;
+    for (int it = 0; it < mine; it++) {   // (two runs in flight per wave measured slower: 1200 -> 1660 us
+                                          // per step at 2048 x 1024 x 2752, 102 -> 106 at the small one)
+      const int k = (turn + it * NWV) * 16 + hi * 4;
+      const bool in = k < S.K;   // K % 8 == 0: a lane's four elements are all in or all out
+      f32x4_t fa[NB], fb[NB];
+#pragma unroll
+      for (int i = 0; i < NB; i++) {
+        fa[i] = *reinterpret_cast<const f32x4_t *>(A + (int64_t)arow[i] * S.lda + (in ? k : 0));
+        fb[i] = *reinterpret_cast<const f32x4_t *>(B + (int64_t)bcol[i] * S.ldb + (in ? k : 0));
+      }
+      if (!in) {
+#pragma unroll
+        for (int i = 0; i < NB; i++) fa[i] = fb[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+      }
+#pragma unroll
+      for (int m = 0; m < 4; m++)
+#pragma unroll
+        for (int i = 0; i < NB; i++)
+#pragma unroll
+          for (int j = 0; j < NB; j++)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[j][m], fa[i][m], acc[i][j], 0, 0, 0);
+    }
+    turn += mine * NWV - runs;
+  }
+#pragma unroll
+  for (int i = 0; i < NB; i++)
+#pragma unroll
+    for (int j = 0; j < NB; j++)
+      *reinterpret_cast<f32x4_t *>(&red[wave][i * 16 + l15][j * 16 + hi * 4]) = acc[i][j];
+  __syncthreads();
   float *C = reinterpret_cast<float *>(P.C);
+  const bool vec = (P.ldc & 3) == 0 && (reinterpret_cast<uintptr_t>(C) & 15) == 0;
+  for (int x = threadIdx.x; x < TB * TB / 4; x += NWV * 64) {
+    const int rl = x / (TB / 4), cl = x % (TB / 4) * 4;
+    const int r = row0 + rl, c = col0 + cl;
+    if (r >= M || c >= N) continue;
+    f32x4_t v = *reinterpret_cast<const f32x4_t *>(&red[0][rl][cl]);
 #pragma unroll
-  for (int i = 0; i < 4; i++) {
-    const int r = row0 + ty * 4 + i;
-    if (r >= M) continue;
-#pragma unroll
-    for (int j = 0; j < 4; j++) {
-      const int c = col0 + tx * 4 + j;
-      if (c < N) C[(int64_t)r * P.ldc + c] = acc[i][j];
+    for (int w = 1; w < NWV; w++) v += *reinterpret_cast<const f32x4_t *>(&red[w][rl][cl]);
+    if (vec && c + 4 <= N) {
+      *reinterpret_cast<f32x4_t *>(C + (int64_t)r * P.ldc + c) = v;
+    } else {
+      for (int m = 0; m < 4 && c + m < N; m++) C[(int64_t)r * P.ldc + c + m] = v[m];
     }
   }
 }
@@ -1043,6 +1073,22 @@ hipError_t launch_gemm(int dtype, const GemmProblem *probs, int nprob, hipStream
   if (nprob < 1 || nprob > GEMM_MAX_PROBLEMS) return hipErrorInvalidValue;
   GemmBatch b;
   for (int i = 0; i < GEMM_MAX_PROBLEMS; i++) b.p[i] = probs[i < nprob ? i : 0];
+  if (dtype == MIXLORA_F32) {
+    int t32 = 0, t64 = 0, all64 = 0;
+    for (int i = 0; i < nprob; i++) {
+      if (probs[i].M <= 0 || probs[i].N <= 0) return hipErrorInvalidValue;
+      const int a = ((probs[i].M + 31) / 32) * ((probs[i].N + 31) / 32);
+      const int c = ((probs[i].M + 63) / 64) * ((probs[i].N + 63) / 64);
+      t32 = a > t32 ? a : t32;
+      t64 = c > t64 ? c : t64;
+      all64 += c;
+    }
+    if (all64 >= 512)   // two tiles of 64 x 64 per CU
+      hipLaunchKernelGGL((gemm_f32_kernel<64, 4>), dim3(t64, 1, nprob), dim3(256), 0, st, b);
+    else
+      hipLaunchKernelGGL((gemm_f32_kernel<32, 8>), dim3(t32, 1, nprob), dim3(512), 0, st, b);
+    return hipGetLastError();
+  }
   const int M = probs[0].M, N = probs[0].N;
   bool uniform = true, any_big = false, same_m = true;
   for (int i = 0; i < nprob; i++) {
@@ -1075,11 +1121,6 @@ hipError_t launch_gemm(int dtype, const GemmProblem *probs, int nprob, hipStream
       if (e != hipSuccess) return e;
     }
     return hipSuccess;
-  }
-  if (dtype == MIXLORA_F32) {
-    const int tiles = ((M + 63) / 64) * ((N + 63) / 64);
-    hipLaunchKernelGGL(gemm_f32_kernel, dim3(tiles, 1, nprob), dim3(256), 0, st, b);
-    return hipGetLastError();
   }
   const bool f32out = probs[0].c_f32 != 0;
   if (N <= 128 || M <= 128) {

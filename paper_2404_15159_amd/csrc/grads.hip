@@ -13,23 +13,27 @@ namespace mixlora {
 constexpr int GO_COLS = 512;   // 256 threads x 2 adjacent columns
 constexpr int GO_STAGE = 64;   // rows staged per pass
 
-__device__ __forceinline__ float2 ld2(const float *p) { return *reinterpret_cast<const float2 *>(p); }
-__device__ __forceinline__ float2 ld2(const bf16_t *p) {
-  typedef bf16_t bf16x2_t __attribute__((ext_vector_type(2)));
-  const bf16x2_t v = *reinterpret_cast<const bf16x2_t *>(p);
-  return make_float2((float)v[0], (float)v[1]);
-}
+// fp32 storage: all sums of a pass in one launch (each alone is little more than a launch's latency).
+struct GoBatch {
+  GoJob job[GO_MAX_JOBS];
+  float *partial[GO_MAX_JOBS];
+  int nsplit[GO_MAX_JOBS], y0[GO_MAX_JOBS];   // y0: first blockIdx.y of the job
+  int njobs;
+};
 
-// partial[split][g][q][c], q < r.  RQ = rank chunk held in registers.
-template <typename E, int RQ>
-__global__ __launch_bounds__(256) void group_outer_kernel(
-    const int32_t *__restrict__ offs, const int32_t *__restrict__ pair_of_row, int k,
-    const float *__restrict__ small, int r, const E *__restrict__ wide, int C, int nsplit,
-    float *__restrict__ partial) {
+// partial[split][g][q][c], q < r.  RQ = rank chunk held in registers.  blockIdx.y = y0 of the job +
+// split * G + group.
+template <int RQ>
+__global__ __launch_bounds__(256) void group_outer_kernel(GoBatch batch) {
   __shared__ float sm[GO_STAGE][RQ];
   __shared__ int src_s[GO_STAGE];
-  const int g = blockIdx.y, sp = blockIdx.z, G = gridDim.y;
-  const int lo = offs[g], hi = offs[g + 1];
+  int ji = 0;
+  while (ji + 1 < batch.njobs && batch.y0[ji + 1] <= (int)blockIdx.y) ji++;
+  const GoJob &J = batch.job[ji];
+  const int G = J.G, r = J.r, C = J.C, nsplit = batch.nsplit[ji];
+  if ((int)blockIdx.x * GO_COLS >= C) return;
+  const int g = (blockIdx.y - batch.y0[ji]) % G, sp = (blockIdx.y - batch.y0[ji]) / G;
+  const int lo = J.offs[g], hi = J.offs[g + 1];
   const int len = (hi - lo + nsplit - 1) / nsplit;
   const int r_lo = lo + sp * len;
   const int r_hi = r_lo + len < hi ? r_lo + len : hi;
@@ -44,14 +48,15 @@ __global__ __launch_bounds__(256) void group_outer_kernel(
       __syncthreads();
       for (int i = threadIdx.x; i < GO_STAGE * RQ; i += 256) {
         const int rr = i / RQ, q = i % RQ;
-        sm[rr][q] = (rr < n && q0 + q < r) ? small[(int64_t)(rb + rr) * r + q0 + q] : 0.f;
+        sm[rr][q] = (rr < n && q0 + q < r) ? J.small[(int64_t)(rb + rr) * r + q0 + q] : 0.f;
       }
       if (threadIdx.x < GO_STAGE && threadIdx.x < n)
-        src_s[threadIdx.x] = pair_of_row ? pair_of_row[rb + threadIdx.x] / k : rb + threadIdx.x;
+        src_s[threadIdx.x] = J.pair_of_row ? J.pair_of_row[rb + threadIdx.x] / J.k : rb + threadIdx.x;
       __syncthreads();
       if (active) {
+#pragma unroll 4
         for (int rr = 0; rr < n; rr++) {
-          const float2 v = ld2(wide + (int64_t)src_s[rr] * C + c);
+          const float2 v = *reinterpret_cast<const float2 *>(J.wide + (int64_t)src_s[rr] * C + c);
 #pragma unroll
           for (int q = 0; q < RQ; q++) {
             const float sv = sm[rr][q];
@@ -65,11 +70,30 @@ __global__ __launch_bounds__(256) void group_outer_kernel(
 #pragma unroll
       for (int q = 0; q < RQ; q++) {
         if (q0 + q < r) {
-          float *o = partial + (((int64_t)sp * G + g) * r + q0 + q) * C + c;
+          float *o = batch.partial[ji] + (((int64_t)sp * G + g) * r + q0 + q) * C + c;
           *reinterpret_cast<float2 *>(o) = make_float2(acc[q][0], acc[q][1]);
         }
       }
     }
+  }
+}
+
+// out = scale * sum of the job's partials in split order, written as [g][q][c] or [g][c][q]
+__global__ __launch_bounds__(256) void group_outer_sum_kernel(GoBatch batch) {
+  const GoJob &J = batch.job[blockIdx.y];
+  const int64_t n = (int64_t)J.G * J.r * J.C;
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const float *__restrict__ partial = batch.partial[blockIdx.y] + i;
+  float acc = 0.f;
+#pragma unroll 4
+  for (int sp = 0; sp < batch.nsplit[blockIdx.y]; sp++) acc += partial[sp * n];
+  acc *= J.scale;
+  if (J.layout_qc) {
+    J.out[i] = acc;
+  } else {
+    const int c = (int)(i % J.C), q = (int)((i / J.C) % J.r), g = (int)(i / ((int64_t)J.C * J.r));
+    J.out[((int64_t)g * J.C + c) * J.r + q] = acc;
   }
 }
 
@@ -109,45 +133,48 @@ __global__ void group_outer_reduce_kernel(ReduceBatch batch, int G, int r, int C
   }
 }
 
-static int go_splits(int G, int C) {
+// Row slices of a job: enough workgroups for the chip, at least 16 rows of an average group each
+// (a slice of two rows costs more in partial sums than it saves).
+static int go_splits(int G, int C, int rows) {
   const int col_tiles = (C + GO_COLS - 1) / GO_COLS;
   int s = 1024 / (col_tiles * G);
-  if (s < 1) s = 1;
+  if (s > rows / (16 * G)) s = rows / (16 * G);
   if (s > 32) s = 32;
-  return s;
+  return s < 1 ? 1 : s;
 }
 
-size_t group_outer_partial_floats(int G, int r, int C) {
-  return (size_t)go_splits(G, C) * G * r * C;
+size_t group_outer_partial_floats(int G, int r, int C, int rows) {
+  return (size_t)go_splits(G, C, rows) * G * r * C;
 }
 
-hipError_t launch_group_outer(int dtype, const int32_t *offs, int G, int max_rows,
-                              const int32_t *pair_of_row, int k, const float *small, int r,
-                              const void *wide, int C, float scale, int layout_qc, float *out,
-                              float *partials, size_t partial_floats, hipStream_t st) {
-  (void)max_rows;
-  const int nsplit = go_splits(G, C);
-  if ((size_t)nsplit * G * r * C > partial_floats) return hipErrorInvalidValue;
-  const dim3 grid((C + GO_COLS - 1) / GO_COLS, G, nsplit), block(256);
-  const bool r16 = r > 8;
-#define MIXLORA_GO(E_, RQ_)                                                                   \
-  hipLaunchKernelGGL((group_outer_kernel<E_, RQ_>), grid, block, 0, st, offs, pair_of_row, k,   \
-                     small, r, (const E_ *)wide, C, nsplit, partials)
-  if (dtype == MIXLORA_BF16) {
-    if (r16) MIXLORA_GO(bf16_t, 16); else MIXLORA_GO(bf16_t, 8);
-  } else {
-    if (r16) MIXLORA_GO(float, 16); else MIXLORA_GO(float, 8);
+hipError_t launch_group_outer(const GoJob *jobs, int njobs, float *partials, size_t partial_floats,
+                              hipStream_t st) {
+  if (njobs < 1 || njobs > GO_MAX_JOBS) return hipErrorInvalidValue;
+  GoBatch b{};
+  b.njobs = njobs;
+  size_t used = 0;
+  int y = 0, x = 0, rmax = 0;
+  int64_t n = 0;
+  for (int i = 0; i < njobs; i++) {
+    const GoJob &J = jobs[i];
+    b.job[i] = J;
+    b.nsplit[i] = go_splits(J.G, J.C, J.rows);
+    b.partial[i] = partials + used;
+    used += (size_t)b.nsplit[i] * J.G * J.r * J.C;
+    b.y0[i] = y;
+    y += J.G * b.nsplit[i];
+    const int ct = (J.C + GO_COLS - 1) / GO_COLS;
+    x = ct > x ? ct : x;
+    rmax = J.r > rmax ? J.r : rmax;
+    const int64_t m = (int64_t)J.G * J.r * J.C;
+    n = m > n ? m : n;
   }
-#undef MIXLORA_GO
-  hipError_t e = hipGetLastError();
+  if (used > partial_floats) return hipErrorInvalidValue;
+  if (rmax > 8) hipLaunchKernelGGL(group_outer_kernel<16>, dim3(x, y), dim3(256), 0, st, b);
+  else hipLaunchKernelGGL(group_outer_kernel<8>, dim3(x, y), dim3(256), 0, st, b);
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const int64_t n = (int64_t)G * r * C;
-  ReduceBatch rb{};
-  rb.partial[0] = partials;
-  rb.out[0] = out;
-  rb.layout_qc[0] = layout_qc;
-  hipLaunchKernelGGL(group_outer_reduce_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0,
-                     st, rb, G, r, C, nsplit, scale);
+  hipLaunchKernelGGL(group_outer_sum_kernel, dim3((unsigned)((n + 255) / 256), njobs), dim3(256), 0, st, b);
   return hipGetLastError();
 }
 

@@ -55,14 +55,12 @@ LinLayout make_layout(const mixlora_linear_dims &D) {
   L.At = take(di * r * E);
   L.VB = take(T * r * 4);
   L.VB_T = take((size_t)L.ldT * r * 2);
-  const int big = (int)(di > dn ? di : dn);
-  size_t pf = group_outer_partial_floats(1, (int)r, big);
-  const size_t pm = group_outer_mfma_partial_floats(1, (int)r, big);
-  for (size_t v : {group_outer_partial_floats(1, (int)r, (int)di), group_outer_partial_floats(1, (int)r, (int)dn),
-                   group_outer_mfma_partial_floats(1, (int)r, (int)di),
-                   group_outer_mfma_partial_floats(1, (int)r, (int)dn), pm})
-    pf = v > pf ? v : pf;
+  size_t pf = group_outer_mfma_partial_floats(1, (int)r, (int)di);
+  const size_t pfn = group_outer_mfma_partial_floats(1, (int)r, (int)dn);
+  if (pfn > pf) pf = pfn;
   if (di == dn) pf *= 2;   // both sums in one launch
+  if (E == 4)
+    pf = group_outer_partial_floats(1, (int)r, (int)di, (int)T) + group_outer_partial_floats(1, (int)r, (int)dn, (int)T);
   L.partial_floats = pf;
   L.partials = take(pf * 4);
   L.padgA = take(padded ? r * di * 4 : 0);
@@ -318,10 +316,10 @@ int mixlora_lora_linear_backward(const mixlora_linear_dims *dims, const void *W,
                                       L.partial_floats, st));
     }
   } else {
-    HIP_TRY(launch_group_outer(dt, tok, 1, T, nullptr, 1, (const float *)(ws + L.VB), r, x, di, s, 1,
-                               dA, part, L.partial_floats, st));
-    HIP_TRY(launch_group_outer(dt, tok, 1, T, nullptr, 1, (const float *)(ws + L.P), r, dy, dn, s, 0,
-                               dB, part, L.partial_floats, st));
+    const GoJob go[2] = {
+        GoJob{tok, nullptr, (const float *)(ws + L.VB), (const float *)x, dA, 1, r, di, 1, T, 1, s},
+        GoJob{tok, nullptr, (const float *)(ws + L.P), (const float *)dy, dB, 1, r, dn, 1, T, 0, s}};
+    HIP_TRY(launch_group_outer(go, 2, part, L.partial_floats, st));
   }
   if (L.rp != D.r) {
     const RelayoutJob jobs[2] = {job_rank_resize(dA, dA_user, 1, L.rp, D.r, di, true),

@@ -37,6 +37,25 @@ def test_tile_edges_match_oracle(shape):
     pu.compare_all(res, bw["forward"], bw, cfg)
 
 
+# fp32 storage: 32 x 32 tiles and, from 512 tiles of 64 x 64 on, those; row slices of the gradient
+# sums on both sides of one, ranks on both sides of 8
+@pytest.mark.parametrize("shape", [(33, 40, 104, 3, 4), (200, 72, 264, 8, 8), (1200, 264, 1032, 4, 16)],
+                         ids=lambda s: "T%d_d%d_f%d_N%d_r%d" % s)
+def test_f32_tiles_match_oracle(shape):
+    T, d, f, N, r = shape
+    cfg = synth.scaled(synth.CONFIGS["tiny_f32"], name="tiles_f32", T=T, d=d, d_ff=f, N=N, r=r, alpha=2.0 * r)
+    print(f"case f32 T={T} d={d} f={f} N={N} r={r}", flush=True)
+    host = synth.make_inputs(cfg)
+    m = MixLoraFFN(cfg, host)
+    m.workspace.fill_(0xFF)
+    m.forward()
+    m.backward(d_aux=1.0)
+    res = m.results()
+    W = {n: host[n] for n in synth.WEIGHT_NAMES}
+    bw = orc.backward(host["x"], W, cfg.k, cfg.lora_scale, host["dy"], 1.0, cfg.aux_coeff, "top1")
+    pu.compare_all(res, bw["forward"], bw, cfg)
+
+
 def test_repeated_passes_are_bit_identical():
     """Slices are added in a fixed order."""
     cfg = synth.scaled(synth.CONFIGS["llama2_7b"], name="tiles_rerun", T=300, d=1024, d_ff=2744)
