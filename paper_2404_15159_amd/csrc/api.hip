@@ -376,21 +376,13 @@ static int forward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mod
   if (dora) {
     // factors c = m / n of the three projections (n: row norms of W + s B_e A_e)
     float *w2 = (float *)(ws + L.w2), *AA = (float *)(ws + L.AA);
-    HIP_TRY_AS(PROF_OTHER, 0, launch_row_sqnorm(w->W_gate, f, d, w2, st));
-    HIP_TRY_AS(PROF_OTHER, 0, launch_row_sqnorm(w->W_up, f, d, w2 + f, st));
-    HIP_TRY_AS(PROF_OTHER, 0, launch_row_sqnorm(w->W_down, d, f, w2 + 2 * (size_t)f, st));
-    HIP_TRY_AS(PROF_OTHER, 0, launch_gram(w->A_gate, N, r, d, AA, st));
-    const size_t gpf = gram_part_floats(N, r);
-    HIP_TRY_AS(PROF_OTHER, 0, launch_gram(w->A_up, N, r, d, AA + gpf, st));
-    HIP_TRY_AS(PROF_OTHER, 0, launch_gram(w->A_down, N, r, f, AA + 2 * gpf, st));
-    HIP_TRY_AS(PROF_OTHER, 0, launch_dora_scale(w->B_gate, (float *)(ws + L.WA_g), AA, w2, dora->m_gate, dora->shared, N, f, r,
-                              D.lora_scale, (float *)(ws + L.c_g), (float *)(ws + L.ninv_g), st));
-    HIP_TRY_AS(PROF_OTHER, 0, launch_dora_scale(w->B_up, (float *)(ws + L.WA_u), AA + gpf, w2 + f,
-                              dora->m_up, dora->shared, N, f, r, D.lora_scale, (float *)(ws + L.c_u),
-                              (float *)(ws + L.ninv_u), st));
-    HIP_TRY_AS(PROF_OTHER, 0, launch_dora_scale(w->B_down, (float *)(ws + L.WA_d), AA + 2 * gpf, w2 + 2 * (size_t)f,
-                              dora->m_down, dora->shared, N, d, r, D.lora_scale, (float *)(ws + L.c_d),
-                              (float *)(ws + L.ninv_d), st));
+    HIP_TRY_AS(PROF_OTHER, 0, launch_row_sqnorm(w->W_gate, w->W_up, w->W_down, f, d, w2, st));
+    HIP_TRY_AS(PROF_OTHER, 0, launch_gram(w->A_gate, w->A_up, w->A_down, N, r, f, d, AA, st));
+    const DoraScale proj[3] = {
+        {w->B_gate, (float *)(ws + L.WA_g), dora->m_gate, (float *)(ws + L.c_g), (float *)(ws + L.ninv_g)},
+        {w->B_up, (float *)(ws + L.WA_u), dora->m_up, (float *)(ws + L.c_u), (float *)(ws + L.ninv_u)},
+        {w->B_down, (float *)(ws + L.WA_d), dora->m_down, (float *)(ws + L.c_d), (float *)(ws + L.ninv_d)}};
+    HIP_TRY_AS(PROF_OTHER, 0, launch_dora_scale(proj, dora->shared, N, f, d, r, D.lora_scale, AA, w2, st));
     dargs.cg = (float *)(ws + L.c_g);
     dargs.cu = (float *)(ws + L.c_u);
   }

@@ -373,13 +373,20 @@ hipError_t launch_router_bwd(int dtype, const PairCtx &pc, const float *probs, c
                              int s_by_first_pair = 0);   // S has one row per grouped pair row
 
 // ---- weight-decomposed experts (csrc/dora.hip); bf16 storage only --------------------------------
-hipError_t launch_row_sqnorm(const void *W, int rows, int cols, float *out, hipStream_t st);
+hipError_t launch_row_sqnorm(const void *W_gate, const void *W_up, const void *W_down, int f, int d,
+                             float *out, hipStream_t st);   // out [2 f + d]
 size_t gram_part_floats(int N, int r);   // floats of one bank's Gram slice sums
-hipError_t launch_gram(const void *A_bank, int N, int r, int in, float *part, hipStream_t st);
-// c = m / n, ninv = 1 / n with n the row norms of W + s B_e A_e (from w2, WA = W A_cat^T, AA)
-hipError_t launch_dora_scale(const void *B_bank, const float *WA, const float *AA, const float *w2,
-                             const float *m, int shared, int N, int out, int r, float s, float *c,
-                             float *ninv, hipStream_t st);
+hipError_t launch_gram(const void *A_gate, const void *A_up, const void *A_down, int N, int r, int f,
+                       int d, float *part, hipStream_t st);   // part: 3 * gram_part_floats
+// c = m / n, ninv = 1 / n with n the row norms of W + s B_e A_e (from w2, WA = W A_cat^T, AA) for the
+// projections gate, up, down
+struct DoraScale {
+  const void *B_bank;
+  const float *WA, *m;
+  float *c, *ninv;
+};
+hipError_t launch_dora_scale(const DoraScale *proj, int shared, int N, int f, int d, int r, float s,
+                             const float *AA, const float *w2, hipStream_t st);
 hipError_t launch_scale_bank(void *bank, const float *c, int N, int r, int d, hipStream_t st);
 hipError_t launch_gather_rows_scaled(const PairCtx &pc, int width, const void *src, const float *c,
                                      void *dst, hipStream_t st);

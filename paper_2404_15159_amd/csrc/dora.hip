@@ -13,13 +13,21 @@
 namespace mixlora {
 
 // ---- w2[j] = sum_i W[j, i]^2, one wavefront per row, lanes in a fixed order ---------------------
-__global__ __launch_bounds__(256) void row_sqnorm_kernel(const bf16_t *__restrict__ W, int rows,
-                                                         int cols, float *__restrict__ out) {
+// The three frozen matrices in one launch (270 MB at the 7B shape, HBM-bound): w2 holds the rows of
+// W_gate, W_up and W_down one after the other.
+__global__ __launch_bounds__(256) void row_sqnorm_kernel(const bf16_t *__restrict__ Wg,
+                                                         const bf16_t *__restrict__ Wu,
+                                                         const bf16_t *__restrict__ Wd, int f, int d,
+                                                         float *__restrict__ out) {
   const int lane = threadIdx.x & 63;
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row >= rows) return;
-  const bf16_t *p = W + (int64_t)row * cols;
+  if (row >= 2 * f + d) return;
+  const bf16_t *p = row < f       ? Wg + (int64_t)row * d
+                    : row < 2 * f ? Wu + (int64_t)(row - f) * d
+                                  : Wd + (int64_t)(row - 2 * f) * f;
+  const int cols = row < 2 * f ? d : f;
   float acc = 0.f;
+#pragma unroll 4
   for (int c = lane * 8; c < cols; c += 64 * 8) {
     const bf16x8_t v = *reinterpret_cast<const bf16x8_t *>(p + c);
 #pragma unroll
@@ -30,104 +38,170 @@ __global__ __launch_bounds__(256) void row_sqnorm_kernel(const bf16_t *__restric
   if (lane == 0) out[row] = acc;
 }
 
-hipError_t launch_row_sqnorm(const void *W, int rows, int cols, float *out, hipStream_t st) {
-  hipLaunchKernelGGL(row_sqnorm_kernel, dim3((rows + 3) / 4), dim3(256), 0, st, (const bf16_t *)W,
-                     rows, cols, out);
+hipError_t launch_row_sqnorm(const void *W_gate, const void *W_up, const void *W_down, int f, int d,
+                             float *out, hipStream_t st) {
+  hipLaunchKernelGGL(row_sqnorm_kernel, dim3((2 * f + d + 3) / 4), dim3(256), 0, st,
+                     (const bf16_t *)W_gate, (const bf16_t *)W_up, (const bf16_t *)W_down, f, d, out);
   return hipGetLastError();
 }
 
-// ---- AA[e][q][q'] = sum_i A[e, q, i] A[e, q', i]  (A bank [N, r, in]) ----------------------------
-// The input dimension is cut into GRAM_SLICES slices (blockIdx.y); slice sums go to
-// part[slice][e][q][q'] and are added in slice order by the consumer.
-constexpr int GRAM_SLICES = 16;
+// ---- AA[b][e][q][q'] = sum_i A_b[e, q, i] A_b[e, q', i]  (banks A_gate, A_up, A_down) -----------
+// MFMA 16x16x32 with both operands straight from memory (the bank is its own transpose's K-major
+// form).  The input dimension is cut into GRAM_SLICES slices of eight waves each; slice sums go to
+// part[b][slice][e][q][q'] and are added in slice order by the consumer.  All banks in one launch:
+// bound by a chain of a few loads per wave (68 -> 8 us against one launch per bank with r^2 scalar
+// products from LDS, 7B shape, 8 experts of rank 16).
+constexpr int GRAM_SLICES = 4;
 
-__global__ __launch_bounds__(256) void gram_kernel(const bf16_t *__restrict__ A, int r, int in,
+template <int NQ>
+__global__ __launch_bounds__(512) void gram_kernel(const bf16_t *__restrict__ Ag,
+                                                   const bf16_t *__restrict__ Au,
+                                                   const bf16_t *__restrict__ Ad, int r, int f, int d,
                                                    int N, float *__restrict__ part) {
-  __shared__ float t[64][65];
-  const int e = blockIdx.x, sl = blockIdx.y;
-  const bf16_t *Ae = A + (int64_t)e * r * in;
-  const int per = ((in + GRAM_SLICES - 1) / GRAM_SLICES + 63) / 64 * 64;
-  const int lo = sl * per, hi = lo + per < in ? lo + per : in;
-  float acc[16];   // r <= 64: at most 4096 outputs over 256 threads
+  __shared__ float red[8][NQ][64][4];
+  const int e = blockIdx.x, sl = blockIdx.y, b = blockIdx.z;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int l15 = lane & 15, hi = lane >> 4;
+  const int in = b == 2 ? f : d;
+  const bf16_t *A = (b == 0 ? Ag : b == 1 ? Au : Ad) + (int64_t)e * r * in;
+  float *out = part + (((int64_t)b * GRAM_SLICES + sl) * N + e) * r * r;
+  const bf16_t *ar[NQ];
 #pragma unroll
-  for (int o = 0; o < 16; o++) acc[o] = 0.f;
-  for (int i0 = lo; i0 < hi; i0 += 64) {
-    for (int idx = threadIdx.x; idx < r * 64; idx += 256) {
-      const int q = idx / 64, i = idx % 64;
-      t[q][i] = i0 + i < hi ? (float)Ae[(int64_t)q * in + i0 + i] : 0.f;
-    }
-    __syncthreads();
+  for (int j = 0; j < NQ; j++) ar[j] = A + (int64_t)(j * 16 + l15 < r ? j * 16 + l15 : r - 1) * in;
+  f32x4_t acc[NQ][NQ];
 #pragma unroll
-    for (int o = 0; o < 16; o++) {
-      const int out = threadIdx.x + o * 256;
-      if (out < r * r) {
-        const int q = out / r, q2 = out % r;
-        float a = acc[o];
-        for (int i = 0; i < 64; i++) a = fmaf(t[q][i], t[q2][i], a);
-        acc[o] = a;
+  for (int i = 0; i < NQ; i++)
+#pragma unroll
+    for (int j = 0; j < NQ; j++) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  for (int k0 = (sl * 8 + wave) * 32; k0 < in; k0 += GRAM_SLICES * 8 * 32) {
+    const int k = k0 + hi * 8;
+    bf16x8_t fr[NQ];
+#pragma unroll
+    for (int j = 0; j < NQ; j++) {
+      fr[j] = *reinterpret_cast<const bf16x8_t *>(ar[j] + (k < in ? k : 0));
+      if (k >= in) {   // in % 8 == 0
+#pragma unroll
+        for (int m = 0; m < 8; m++) fr[j][m] = (bf16_t)0.f;
       }
     }
-    __syncthreads();
-  }
 #pragma unroll
-  for (int o = 0; o < 16; o++) {
-    const int out = threadIdx.x + o * 256;
-    if (out < r * r) part[((int64_t)sl * N + e) * r * r + out] = acc[o];
+    for (int i = 0; i < NQ; i++)
+#pragma unroll
+      for (int j = 0; j < NQ; j++)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fr[j], fr[i], acc[i][j], 0, 0, 0);
+  }
+  // acc[i][j][m] of lane (l15, hi): q = 16 i + l15, q' = 16 j + 4 hi + m
+#pragma unroll
+  for (int i = 0; i < NQ; i++) {
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < NQ; j++) *reinterpret_cast<f32x4_t *>(red[wave][j][lane]) = acc[i][j];
+    __syncthreads();
+    for (int x = threadIdx.x; x < NQ * 256; x += 512) {
+      const int j = x >> 8, ln = (x >> 2) & 63, m = x & 3;
+      const int q = i * 16 + (ln & 15), q2 = j * 16 + (ln >> 4) * 4 + m;
+      float v = red[0][j][ln][m];
+#pragma unroll
+      for (int w = 1; w < 8; w++) v += red[w][j][ln][m];
+      if (q < r && q2 < r) out[q * r + q2] = v;
+    }
   }
 }
 
 size_t gram_part_floats(int N, int r) { return (size_t)GRAM_SLICES * N * r * r; }
 
-hipError_t launch_gram(const void *A_bank, int N, int r, int in, float *part, hipStream_t st) {
-  hipLaunchKernelGGL(gram_kernel, dim3(N, GRAM_SLICES), dim3(256), 0, st, (const bf16_t *)A_bank, r,
-                     in, N, part);
+hipError_t launch_gram(const void *A_gate, const void *A_up, const void *A_down, int N, int r, int f,
+                       int d, float *part, hipStream_t st) {
+  const dim3 grid(N, GRAM_SLICES, 3), block(512);
+#define MIXLORA_GRAM(NQ_)                                                                       \
+  hipLaunchKernelGGL(gram_kernel<NQ_>, grid, block, 0, st, (const bf16_t *)A_gate,              \
+                     (const bf16_t *)A_up, (const bf16_t *)A_down, r, f, d, N, part)
+  if (r <= 16) MIXLORA_GRAM(1);
+  else if (r <= 32) MIXLORA_GRAM(2);
+  else MIXLORA_GRAM(4);
+#undef MIXLORA_GRAM
   return hipGetLastError();
 }
 
 // ---- c[e, j] = m[e, j] / n_e[j],  ninv[e, j] = 1 / n_e[j] ----------------------------------------
-// B bank [N, out, r] bf16; WA [out, N*r] float32; AA: the Gram kernel's slice sums
-// [GRAM_SLICES][N][r][r]; w2 [out]; c, ninv [N, out]; m [N, out] (m_stride = out) or one [out]
-// vector shared by the experts (m_stride = 0).
-__global__ __launch_bounds__(256) void dora_scale_kernel(const bf16_t *__restrict__ B,
-                                                         const float *__restrict__ WA,
-                                                         const float *__restrict__ AA,
-                                                         const float *__restrict__ w2,
-                                                         const float *__restrict__ m,
-                                                         int64_t m_stride, int N, int out,
-                                                         int r, float s, float *__restrict__ c,
-                                                         float *__restrict__ ninv) {
-  __shared__ float aa[64 * 64];
-  const int e = blockIdx.y;
+// B banks [N, out, r] bf16; WA [out, N*r] float32; AA: the Gram kernel's slice sums; w2 as above;
+// c, ninv [N, out]; m [N, out] or one [out] vector shared by the experts.  The three projections in
+// one launch (blockIdx.z); a thread owns one output feature and keeps its r bank entries in registers.
+struct DoraScaleJob {
+  const bf16_t *B;
+  const float *WA, *AA, *w2, *m;
+  int out;
+  float *c, *ninv;
+};
+struct DoraScaleBatch {
+  DoraScaleJob job[3];
+};
+
+template <int RMAX>
+__global__ __launch_bounds__(256) void dora_scale_kernel(DoraScaleBatch batch, int shared, int N, int r,
+                                                         float s) {
+  __shared__ float aa[RMAX * RMAX];
+  const DoraScaleJob &J = batch.job[blockIdx.z];
+  const int e = blockIdx.y, out = J.out;
+  if ((int)blockIdx.x * 256 >= out) return;
   for (int i = threadIdx.x; i < r * r; i += 256) {
     float a = 0.f;
-    for (int sl = 0; sl < GRAM_SLICES; sl++) a += AA[((int64_t)sl * N + e) * r * r + i];
+#pragma unroll
+    for (int sl = 0; sl < GRAM_SLICES; sl++) a += J.AA[((int64_t)sl * N + e) * r * r + i];
     aa[i] = a;
   }
   __syncthreads();
   const int j = blockIdx.x * 256 + threadIdx.x;
   if (j >= out) return;
-  const bf16_t *b = B + ((int64_t)e * out + j) * r;
-  const float *wa = WA + (int64_t)j * N * r + e * r;
+  const bf16_t *b = J.B + ((int64_t)e * out + j) * r;
+  const float *wa = J.WA + (int64_t)j * N * r + e * r;
+  float bv[RMAX];
   float cross = 0.f, quad = 0.f;
-  for (int q = 0; q < r; q++) {
-    const float bq = (float)b[q];
-    cross = fmaf(bq, wa[q], cross);
-    float row = 0.f;
-    for (int q2 = 0; q2 < r; q2++) row = fmaf(aa[q * r + q2], (float)b[q2], row);
-    quad = fmaf(bq, row, quad);
+#pragma unroll
+  for (int q0 = 0; q0 < RMAX; q0 += 8) {   // r % 8 == 0
+    if (q0 < r) {
+      Vec8<bf16_t> v;
+      Vec8<float> w;
+      v.load(b + q0);
+      w.load(wa + q0);
+#pragma unroll
+      for (int q = 0; q < 8; q++) {
+        bv[q0 + q] = v.get(q);
+        cross = fmaf(v.get(q), w.get(q), cross);
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < 8; q++) bv[q0 + q] = 0.f;
+    }
   }
-  const float n2 = w2[j] + 2.f * s * cross + s * s * quad;
+#pragma unroll
+  for (int q = 0; q < RMAX; q++) {
+    if (q < r) {
+      float row = 0.f;
+#pragma unroll
+      for (int q2 = 0; q2 < RMAX; q2++)
+        if (q2 < r) row = fmaf(aa[q * r + q2], bv[q2], row);
+      quad = fmaf(bv[q], row, quad);
+    }
+  }
+  const float n2 = J.w2[j] + 2.f * s * cross + s * s * quad;
   const float inv = n2 > 0.f ? 1.f / sqrtf(n2) : 0.f;
-  ninv[(int64_t)e * out + j] = inv;
-  c[(int64_t)e * out + j] = m[e * m_stride + j] * inv;
+  J.ninv[(int64_t)e * out + j] = inv;
+  J.c[(int64_t)e * out + j] = J.m[(shared ? 0 : (int64_t)e * out) + j] * inv;
 }
 
-hipError_t launch_dora_scale(const void *B_bank, const float *WA, const float *AA, const float *w2,
-                             const float *m, int shared, int N, int out, int r, float s, float *c,
-                             float *ninv, hipStream_t st) {
-  hipLaunchKernelGGL(dora_scale_kernel, dim3((out + 255) / 256, N), dim3(256), 0, st,
-                     (const bf16_t *)B_bank, WA, AA, w2, m, (int64_t)(shared ? 0 : out), N, out, r, s,
-                     c, ninv);
+hipError_t launch_dora_scale(const DoraScale *p, int shared, int N, int f, int d, int r, float s,
+                             const float *AA, const float *w2, hipStream_t st) {
+  DoraScaleBatch b;
+  const int out[3] = {f, f, d}, w2_at[3] = {0, f, 2 * f};
+  for (int i = 0; i < 3; i++)
+    b.job[i] = DoraScaleJob{(const bf16_t *)p[i].B_bank, p[i].WA, AA + i * gram_part_floats(N, r), w2 + w2_at[i],
+                            p[i].m, out[i], p[i].c, p[i].ninv};
+  const dim3 grid(((f > d ? f : d) + 255) / 256, N, 3), block(256);
+  if (r <= 8) hipLaunchKernelGGL(dora_scale_kernel<8>, grid, block, 0, st, b, shared, N, r, s);
+  else if (r <= 16) hipLaunchKernelGGL(dora_scale_kernel<16>, grid, block, 0, st, b, shared, N, r, s);
+  else if (r <= 32) hipLaunchKernelGGL(dora_scale_kernel<32>, grid, block, 0, st, b, shared, N, r, s);
+  else hipLaunchKernelGGL(dora_scale_kernel<64>, grid, block, 0, st, b, shared, N, r, s);
   return hipGetLastError();
 }
 
@@ -223,13 +297,31 @@ __global__ __launch_bounds__(256) void dm_down_part_kernel(PairCtx pc, int d,
   const int per = (hi - lo + DMD_SLICES - 1) / DMD_SLICES;
   const int r0 = lo + sl * per, r1 = r0 + per < hi ? r0 + per : hi;
   float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  for (int row = r0; row < r1; row++) {
-    const int pair = pc.pair_of_row[row];
-    const float w = pc.w[pair];
-    const bf16x8_t a = *reinterpret_cast<const bf16x8_t *>(dy + (int64_t)(pair / pc.k) * d + col);
-    const bf16x8_t b = *reinterpret_cast<const bf16x8_t *>(v + (int64_t)row * d + col);
+  // eight rows requested together (their additions keep the row order): one at a time, the chain of
+  // three dependent loads per row took 27 us for 34 MB, now 17
+  constexpr int RB = 8;
+  for (int rb = r0; rb < r1; rb += RB) {
+    int pair[RB];
+    float w[RB];
+    bf16x8_t a[RB], b[RB];
 #pragma unroll
-    for (int i = 0; i < 8; i++) acc[i] = fmaf(w * (float)a[i], (float)b[i], acc[i]);
+    for (int p = 0; p < RB; p++) pair[p] = pc.pair_of_row[rb + p < r1 ? rb + p : rb];
+#pragma unroll
+    for (int p = 0; p < RB; p++) {
+      w[p] = pc.w[pair[p]];
+      a[p] = *reinterpret_cast<const bf16x8_t *>(dy + (int64_t)(pair[p] / pc.k) * d + col);
+      b[p] = *reinterpret_cast<const bf16x8_t *>(v + (int64_t)(rb + p < r1 ? rb + p : rb) * d + col);
+    }
+    __builtin_amdgcn_sched_barrier(0);   // or the loads sink into the additions' conditions
+#pragma unroll
+    for (int p = 0; p < RB; p++) {
+      const bool valid = rb + p < r1;
+#pragma unroll
+      for (int i = 0; i < 8; i++) {
+        const float t = fmaf(w[p] * (float)a[p][i], (float)b[p][i], acc[i]);
+        acc[i] = valid ? t : acc[i];
+      }
+    }
   }
   float *o = part + ((int64_t)sl * pc.N + e) * d + col;
 #pragma unroll
@@ -287,6 +379,7 @@ __global__ __launch_bounds__(256) void dm_tiles_reduce_kernel(
   for (int e = e_lo; e < e_hi; e++) {
     const int nt = (offs[e + 1] - offs[e] + 31) / 32;
     float acc = 0.f;
+#pragma unroll 8
     for (int t = 0; t < nt; t++) acc += part[(int64_t)(tile0 + t) * f + c];
     tile0 += nt;
     tot += acc * ninv[(int64_t)e * f + c];
