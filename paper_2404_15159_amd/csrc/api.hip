@@ -34,6 +34,7 @@ struct Layout {
   size_t a_comb, Qw, Bd_cat, rank_part, splitk, gp_scratch, gemm_part;
   size_t gemm_floats;   // floats at gemm_part: partial tiles of GEMM launches cut along K
   size_t base_end;      // forward workspace without them
+  size_t gemm_part_bwd, gemm_floats_bwd;   // the same for the backward pass
   size_t fwd_end;
   // backward scratch
   size_t WdT, WgT, WuT, H, Bd_T, VB_all, dg_grp, du_grp, dgsum, dusum, dw_part, dw, Bg_T, Bu_T, AdT,
@@ -61,6 +62,12 @@ inline int pad_rank(int r) { return (r + 7) & ~7; }
 inline size_t bank_elems(int i, size_t N, size_t rp, size_t d, size_t f) {
   const size_t width[6] = {d, f, d, f, f, d};
   return N * rp * width[i];
+}
+
+// Whether every contraction of the forward pass is in whole 64-wide K tiles, which the narrow-tile
+// kernel for few rows needs.
+inline bool whole_k_tiles(const mixlora_dims &D) {
+  return D.d % 64 == 0 && D.d_ff % 64 == 0 && (D.N * pad_rank(D.r)) % 64 == 0;
 }
 
 // Buffers a schedule does not use get size 0 (per-token G, U in the unshared schedule, the
@@ -130,13 +137,21 @@ Layout make_layout(const mixlora_dims &D, int schedule = MIXLORA_SCHEDULE_LINEAR
     // enough to cut (the longest is that of the input-gradient product)
     const size_t slices = (2 * f + (size_t)L.Kx) / 64 / 4, rows = (pair_down ? kT : T) / 192 + 1;
     const size_t tiles = rows * (2 * (f / 256 + 1) + d / 256 + 4) * slices;
-    size_t bytes = E == 2 && T > SPLITK_MAX_ROWS && slices >= 2 ? GEMM_SCRATCH_FLOATS * 4 : 0;
+    const bool large = T > SPLITK_MAX_ROWS || !whole_k_tiles(D);
+    size_t bytes = E == 2 && large && slices >= 2 ? GEMM_SCRATCH_FLOATS * 4 : 0;
     if (tiles < 256) bytes = bytes / 256 * tiles;
     L.gemm_floats = bytes / 4;
     L.base_end = o;
     L.gemm_part = take(bytes);
+    L.fwd_end = o;
+    // few tokens: only the backward pass, whose products have no K-split buffer of their own
+    L.gemm_floats_bwd = L.gemm_floats;
+    L.gemm_part_bwd = L.gemm_part;
+    if (E == 2 && !large && slices >= 2) {
+      L.gemm_floats_bwd = GEMM_SCRATCH_FLOATS / 256 * (tiles < 256 ? tiles : 256);
+      L.gemm_part_bwd = take(L.gemm_floats_bwd * 4);
+    }
   }
-  L.fwd_end = o;
   L.nct = swiglu_col_tiles((int)f);
   L.WdT = take(f * d * E);
   L.WgT = take(f * d * E);
@@ -314,7 +329,8 @@ static int forward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mod
 
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   char *ws = reinterpret_cast<char *>(workspace);
-  const GemmScratch gs{gemm_part ? gemm_part : (float *)(ws + L.gemm_part), L.gemm_floats};
+  const GemmScratch gs{!L.gemm_floats ? nullptr : gemm_part ? gemm_part : (float *)(ws + L.gemm_part),
+                       L.gemm_floats};
   mixlora_dims D = Du;   // the pass runs on the rank-padded banks
   D.r = L.rp;
   mixlora_weights wpad;
@@ -518,7 +534,7 @@ static int forward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mod
     HIP_TRY_AS(PROF_COMBINE, (double)(k + 1) * T * f * Eb,
                launch_pair_combine(dt, pc, f, ws + L.a_grp, ws + L.a_comb, 1, st));
   // down projection (Algorithm 1 line 14): y = a_comb W_down^T + Qw (s B_down)^T
-  if (dt == MIXLORA_BF16 && (size_t)T <= SPLITK_MAX_ROWS) {
+  if (dt == MIXLORA_BF16 && (size_t)T <= SPLITK_MAX_ROWS && whole_k_tiles(D) && !gemm_rows_ok(dt, T, f + R)) {
     // Few rows: the d output columns alone give too few tiles to stream W_down at full rate, so
     // the K range is cut into S slices (whole 64-wide K tiles), one GEMM problem each with an
     // fp32 partial output, and the partial outputs are added in slice order.
@@ -638,7 +654,7 @@ static int backward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mo
 
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   char *ws = reinterpret_cast<char *>(workspace);
-  const GemmScratch gs{(float *)(ws + L.gemm_part), L.gemm_floats};
+  const GemmScratch gs{L.gemm_floats_bwd ? (float *)(ws + L.gemm_part_bwd) : nullptr, L.gemm_floats_bwd};
   mixlora_dims D = Du;   // rank-padded banks (the forward pass left them in the workspace) and
   D.r = L.rp;            // rank-padded gradients, cut back to r entries at the end
   mixlora_weights wpad;

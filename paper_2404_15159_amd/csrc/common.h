@@ -78,6 +78,8 @@ struct GemmScratch {
 };
 hipError_t launch_gemm(int dtype, const GemmProblem *probs, int nprob, hipStream_t st,
                        const GemmScratch &scratch = GemmScratch{nullptr, 0});
+// whether products of M rows over a contraction of K go to the row kernel (no need to cut K)
+bool gemm_rows_ok(int dtype, int M, int K);
 // whether problems of different M may share one launch_gemm call
 bool gemm_mixed_rows_ok(int dtype, const GemmProblem *probs, int nprob);
 

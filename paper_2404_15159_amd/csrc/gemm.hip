@@ -224,6 +224,13 @@ __device__ __forceinline__ void dma16(uint32_t voff, const void *sbase, uint32_t
                : "v"(voff), "s"(sbase), "s"(lds_addr)
                : "memory", "m0");
 }
+// the same, streaming: for data that this launch reads once
+__device__ __forceinline__ void dma16_nt(uint32_t voff, const void *sbase, uint32_t lds_addr) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt"
+               :
+               : "v"(voff), "s"(sbase), "s"(lds_addr)
+               : "memory", "m0");
+}
 template <int N> __device__ __forceinline__ void wait_vmcnt() {
   static_assert(N >= 0 && N < 64, "vmcnt range");
   asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
@@ -235,7 +242,8 @@ __device__ __forceinline__ const void *uniform_ptr(const void *p) {
   return reinterpret_cast<const void *>(((uint64_t)hi << 32) | lo);
 }
 
-template <int BM, int BN, int BK, int STAGES, int WGM, int WGN>
+// NT: the B operand (the weights, of which every column tile reads its own rows) is copied streaming.
+template <int BM, int BN, int BK, int STAGES, int WGM, int WGN, bool NT>
 __global__ __launch_bounds__(WGM *WGN * 64) void gemm_bf16_dl_kernel(GemmBatch args) {
   constexpr int NW = WGM * WGN;
   constexpr int ROWB = BK * 2;            // bytes per tile row in LDS
@@ -306,7 +314,10 @@ __global__ __launch_bounds__(WGM *WGN * 64) void gemm_bf16_dl_kernel(GemmBatch a
 #pragma unroll
     for (int j = 0; j < IA; j++) dma16(offA[j], ga, la + j * 1024);
 #pragma unroll
-    for (int j = 0; j < IB; j++) dma16(offB[j], gb, lb + j * 1024);
+    for (int j = 0; j < IB; j++) {
+      if constexpr (NT) dma16_nt(offB[j], gb, lb + j * 1024);
+      else dma16(offB[j], gb, lb + j * 1024);
+    }
   };
 
   int total_tiles = 0;
@@ -813,6 +824,108 @@ __global__ __launch_bounds__(256) void gemm_tail_reduce_kernel(GemmBatch args, G
   }
 }
 
+// ---- bf16, one to four rows (decode) ---------------------------------------------------------------
+// Matrix-vector products: bound by streaming the weights once.  A wavefront takes RN rows of B (output
+// columns), its lanes 16-byte pieces of the same 1 KiB run of each, UN runs in flight (RN x UN KiB per
+// wave); the rows of A wait in LDS.  No matrix instruction: a row tile would be padding but for one to
+// four rows, and products of few columns would still have to be cut along K into launches of their own.
+// Lane sums are fp32, added by a butterfly.
+constexpr int GEMV_MAX_ROWS = 4;
+constexpr int GEMV_WAVES = 8;
+
+template <int MR, int RN, int UN>
+__global__ __launch_bounds__(GEMV_WAVES * 64) void gemm_bf16_rows_kernel(GemmBatch args) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  bf16_t *xs = reinterpret_cast<bf16_t *>(smem);       // [MR][segments of K one after the other]
+  const GemmProblem &P = args.p[blockIdx.z];
+  const int N = P.N;
+  if ((int)blockIdx.x * GEMV_WAVES * RN >= N) return;   // problems of one launch may differ in N
+  int Ksum = 0;
+  for (int sgi = 0; sgi < P.nseg; sgi++) Ksum += P.seg[sgi].K;
+  {
+    int at = 0;
+    for (int sgi = 0; sgi < P.nseg; sgi++) {
+      const GemmSeg &S = P.seg[sgi];
+#pragma unroll
+      for (int m = 0; m < MR; m++) {
+        const bf16_t *a = reinterpret_cast<const bf16_t *>(S.A) + (int64_t)(m < P.M ? m : 0) * S.lda;
+        for (int c = threadIdx.x * 8; c < S.K; c += GEMV_WAVES * 64 * 8)
+          *reinterpret_cast<bf16x8_t *>(xs + m * Ksum + at + c) = *reinterpret_cast<const bf16x8_t *>(a + c);
+      }
+      at += S.K;
+    }
+  }
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int n0 = (blockIdx.x * GEMV_WAVES + wave) * RN;
+  float acc[RN][MR];
+#pragma unroll
+  for (int i = 0; i < RN; i++)
+#pragma unroll
+    for (int m = 0; m < MR; m++) acc[i][m] = 0.f;
+  __syncthreads();
+  if (n0 >= N) return;
+  int at = 0;
+  for (int sgi = 0; sgi < P.nseg; sgi++) {
+    const GemmSeg &S = P.seg[sgi];
+    const bf16_t *b[RN];
+#pragma unroll
+    for (int i = 0; i < RN; i++)
+      b[i] = reinterpret_cast<const bf16_t *>(S.B) + (int64_t)(n0 + i < N ? n0 + i : N - 1) * S.ldb;
+    auto add = [&](const bf16x8_t (&w)[RN], int k) {
+#pragma unroll
+      for (int m = 0; m < MR; m++) {
+        const bf16x8_t x = *reinterpret_cast<const bf16x8_t *>(xs + m * Ksum + at + k);
+#pragma unroll
+        for (int i = 0; i < RN; i++)
+#pragma unroll
+          for (int e = 0; e < 8; e++) acc[i][m] = fmaf((float)w[i][e], (float)x[e], acc[i][m]);
+      }
+    };
+    int k0 = lane * 8;
+    const int whole = S.K / (512 * UN);
+    bf16x8_t w[2][UN][RN];
+    auto load = [&](int buf, int k) {
+#pragma unroll
+      for (int u = 0; u < UN; u++)
+#pragma unroll
+        for (int i = 0; i < RN; i++)
+          w[buf][u][i] = __builtin_nontemporal_load(reinterpret_cast<const bf16x8_t *>(b[i] + k + u * 512));
+    };
+    if (whole > 0) load(0, k0);
+    for (int it = 0; it < whole; it += 2) {   // two register sets: the next runs are on their way
+#pragma unroll
+      for (int h = 0; h < 2; h++) {
+        if (it + h < whole) {
+          if (it + h + 1 < whole) load(h ^ 1, k0 + 512 * UN);
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int u = 0; u < UN; u++) add(w[h][u], k0 + u * 512);
+          k0 += 512 * UN;
+        }
+      }
+    }
+    for (; k0 < S.K; k0 += 512) {
+      bf16x8_t v[RN];
+#pragma unroll
+      for (int i = 0; i < RN; i++) v[i] = __builtin_nontemporal_load(reinterpret_cast<const bf16x8_t *>(b[i] + k0));
+      add(v, k0);
+    }
+    at += S.K;
+  }
+#pragma unroll
+  for (int i = 0; i < RN; i++)
+#pragma unroll
+    for (int m = 0; m < MR; m++) {
+      float v = acc[i][m];
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+      if (lane == 0 && n0 + i < N && m < P.M) {
+        if (P.c_f32) reinterpret_cast<float *>(P.C)[m * P.ldc + n0 + i] = v;
+        else reinterpret_cast<bf16_t *>(P.C)[m * P.ldc + n0 + i] = (bf16_t)v;
+      }
+    }
+}
+
 // ---- fp32 storage ---------------------------------------------------------------------------
 // MFMA 16x16x4 fp32 (each product and sum rounded to fp32) on a TB x TB tile; the waves of a
 // workgroup take every NWV-th 16-wide run of K (of all segments in a row) and their sums are added
@@ -927,10 +1040,10 @@ static hipError_t launch_bf16(const GemmBatch &b, int nprob, hipStream_t st) {
   return hipGetLastError();
 }
 
-template <int BM, int BN, int BK, int STAGES, int WGM, int WGN>
+template <int BM, int BN, int BK, int STAGES, int WGM, int WGN, bool NT>
 static hipError_t launch_bf16_dl(const GemmBatch &b, int nprob, hipStream_t st) {
   constexpr size_t smem = (size_t)STAGES * (BM + BN) * BK * sizeof(bf16_t);
-  auto kern = gemm_bf16_dl_kernel<BM, BN, BK, STAGES, WGM, WGN>;
+  auto kern = gemm_bf16_dl_kernel<BM, BN, BK, STAGES, WGM, WGN, NT>;
   static bool attr_set = false;
   if (!attr_set) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
@@ -950,6 +1063,15 @@ static hipError_t launch_bf16_dl(const GemmBatch &b, int nprob, hipStream_t st) 
   if (slot >= 0) prof_mark_end(slot, st, batch_flops(b, nprob));
   return hipGetLastError();
 }
+
+// bytes of a launch's B operands
+static double b_bytes(const GemmBatch &b, int nprob) {
+  double by = 0.0;
+  for (int i = 0; i < nprob; i++)
+    for (int sgi = 0; sgi < b.p[i].nseg; sgi++) by += 2.0 * b.p[i].N * b.p[i].seg[sgi].K;
+  return by;
+}
+constexpr double STREAM_BYTES = 64.0 * 1024 * 1024;
 
 // The direct-to-LDS kernels need 32-bit operand offsets, and (the narrow-tile one) whole K tiles.
 static bool dl_eligible(const GemmBatch &b, int nprob, int BK) {
@@ -1056,6 +1178,39 @@ static hipError_t launch_large(const GemmBatch &b, int nprob, const GemmScratch 
               : launch_pp<256>(b, nprob, ntail, S, scratch.part, st);
 }
 
+// One to four rows: as many rows of B per wave as leave the chip two waves per SIMD or more.
+static hipError_t launch_rows(const GemmBatch &b, int nprob, hipStream_t st) {
+  int n = 0, total = 0, kmax = 0;
+  for (int i = 0; i < nprob; i++) {
+    n = b.p[i].N > n ? b.p[i].N : n;
+    total += b.p[i].N;
+    int kt = 0;
+    for (int sgi = 0; sgi < b.p[i].nseg; sgi++) kt += b.p[i].seg[sgi].K;
+    kmax = kt > kmax ? kt : kmax;
+  }
+  const int M = b.p[0].M, mr = M == 1 ? 1 : M == 2 ? 2 : 4, rn = total > 8192 ? 2 : 1;
+  const size_t smem = (size_t)mr * kmax * sizeof(bf16_t);
+  const dim3 grid((n + GEMV_WAVES * rn - 1) / (GEMV_WAVES * rn), 1, nprob), block(GEMV_WAVES * 64);
+  const int slot = prof_on() ? prof_mark_begin(PROF_GEMM, st) : -1;
+#define MIXLORA_ROWS(MR_)                                                                          \
+  do {                                                                                             \
+    if (rn == 2) hipLaunchKernelGGL((gemm_bf16_rows_kernel<MR_, 2, 4>), grid, block, smem, st, b);  \
+    else hipLaunchKernelGGL((gemm_bf16_rows_kernel<MR_, 1, 4>), grid, block, smem, st, b);          \
+  } while (0)
+  if (mr == 1) MIXLORA_ROWS(1);
+  else if (mr == 2) MIXLORA_ROWS(2);
+  else MIXLORA_ROWS(4);
+#undef MIXLORA_ROWS
+  if (slot >= 0) prof_mark_end(slot, st, batch_flops(b, nprob));
+  return hipGetLastError();
+}
+
+// Whether one to four rows of this contraction length go to the row kernel: its copy of A takes 64 KiB of
+// LDS at most.
+bool gemm_rows_ok(int dtype, int M, int K) {
+  return dtype == MIXLORA_BF16 && M >= 1 && M <= 2 && (size_t)M * K * sizeof(bf16_t) <= 65536;
+}
+
 bool gemm_mixed_rows_ok(int dtype, const GemmProblem *probs, int nprob) {
   if (dtype != MIXLORA_BF16 || nprob < 1 || nprob > GEMM_MAX_PROBLEMS) return false;
   GemmBatch b;
@@ -1104,16 +1259,43 @@ hipError_t launch_gemm(int dtype, const GemmProblem *probs, int nprob, hipStream
     return launch_large(b, nprob, scratch, st);
   }
   if (M <= 0) return hipSuccess;
+  if (dtype == MIXLORA_BF16 && M <= GEMV_MAX_ROWS) {
+    int64_t kmax = 0;
+    for (int i = 0; i < nprob; i++) {
+      int64_t kt = 0;
+      for (int sgi = 0; sgi < probs[i].nseg; sgi++) kt += probs[i].seg[sgi].K;
+      kmax = kt > kmax ? kt : kmax;
+    }
+    int64_t cols = 0;
+    for (int i = 0; i < nprob; i++) cols += probs[i].N;
+    if (kmax < (1 << 20) && (gemm_rows_ok(dtype, M, (int)kmax) || (cols <= 8192 && kmax * 8 <= 65536)))
+      return launch_rows(b, nprob, st);
+  }
   // Large tiles.  Problems of one launch may differ in N and output type (narrow ones ride in the
   // slack of the last, partially filled round of workgroups).
   if (dtype == MIXLORA_BF16 && M > 128 && any_big && dl_eligible(b, nprob, 8))
     return launch_large(b, nprob, scratch, st);
+  // Few rows, and too few 64-column tiles to stream the weights (or ragged K, which the narrow tiles do
+  // not take): the large tiles cut along K.  28 x 1024 x 4096 and 100 x 5120 x 5120 with their
+  // rank-r term 33 -> 30 and 41 -> 38 us; 30 tokens of a 1296 x 4272 block 181 -> 57.
+  if (dtype == MIXLORA_BF16 && M <= 128 && any_big && scratch.part && dl_eligible(b, nprob, 8)) {
+    int narrow = 0;
+    for (int i = 0; i < nprob; i++) narrow += (probs[i].N + 63) / 64;
+    if (narrow < 128 || !dl_eligible(b, nprob, 64)) return launch_large(b, nprob, scratch, st);
+  }
   if (dtype == MIXLORA_BF16 && M <= 128 && any_big && dl_eligible(b, nprob, 64)) {
     // few rows (decode-shaped calls): the launch is bound by streaming the weights once, so the
     // tiles are narrow (64 output columns: enough workgroups to cover the chip) and the ring is
     // deep (4 K tiles in flight per workgroup, 2 workgroups per CU)
-    if (M <= 64) return launch_bf16_dl<64, 64, 64, 4, 1, 2>(b, nprob, st);
-    return launch_bf16_dl<128, 64, 64, 4, 2, 2>(b, nprob, st);
+    // Weights of 64 MiB or more are streamed past the caches: the last level (256 MiB) would not hold
+    // them until the next pass anyway, and reading them costs less without the attempt (64 tokens of
+    // the 7B block 98.5 -> 93.4 us, 16 tokens 86.5 -> 80.4).  Smaller ones may still be there
+    // (52 MB: 40.6 us cached, 44.4 streamed).
+    if (b_bytes(b, nprob) >= STREAM_BYTES)
+      return M <= 64 ? launch_bf16_dl<64, 64, 64, 4, 1, 2, true>(b, nprob, st)
+                     : launch_bf16_dl<128, 64, 64, 4, 2, 2, true>(b, nprob, st);
+    return M <= 64 ? launch_bf16_dl<64, 64, 64, 4, 1, 2, false>(b, nprob, st)
+                   : launch_bf16_dl<128, 64, 64, 4, 2, 2, false>(b, nprob, st);
   }
   if (!uniform || nprob > 2) {   // the generic kernels take uniform batches of at most two
     for (int i = 0; i < nprob; i++) {

@@ -1,6 +1,6 @@
 // Plain LoRA linear (Eq. 1 with the scale alpha / r), the form the method puts on the attention
 // projections (Section 3.2):  y = x W^T + s (x A^T) B^T  with W frozen.  Built from the same
-// pieces as the feed-forward block.  bf16 with more than 128 rows: the rank-r projection s x A^T
+// pieces as the feed-forward block.  bf16 with more than four rows: the rank-r projection s x A^T
 // is made first (rank_project_kernel) and enters the frozen product as two extra K segments, its
 // bf16 value and the bf16 rounding residue of it.  Otherwise the frozen product and the projection
 // share one GEMM launch and the rank-r update is added in place in fp32.  The gradients of A and B
@@ -24,7 +24,7 @@ struct LinLayout {
   size_t W_T, Bt, At, VB, VB_T, partials, bwd_end;
   size_t partial_floats, gemm_floats;
   int ldT;
-  bool extend;                    // the rank-r term rides in the frozen product
+  bool ext_fwd, ext_bwd;          // the rank-r term rides in the frozen product of that direction
 };
 
 LinLayout make_layout(const mixlora_linear_dims &D) {
@@ -38,15 +38,20 @@ LinLayout make_layout(const mixlora_linear_dims &D) {
   L.padA = take(padded ? r * di * E : 0);
   L.padB = take(padded ? dn * r * E : 0);
   L.P = take(T * r * 4);
-  L.extend = E == 2 && T > 128;
+  // Up to four rows are matrix-vector products; up to 128 rows into many columns stream the weights
+  // through narrow tiles that take whole K tiles only (128 rows into 14336 columns 44 us that way, 56
+  // with the extension).
+  auto extends = [&](size_t cols) { return E == 2 && (T > 128 || (T > 4 && cols < 8192)); };
+  L.ext_fwd = extends(dn);
+  L.ext_bwd = extends(di);
   L.ldT = (int)((T + 15) / 16 * 16 + 16);
   L.P_T = take((size_t)L.ldT * r * 2);
   L.tok_offs = take(2 * 4);
-  L.ext = take(L.extend ? T * 2 * r * 2 : 0);
+  L.ext = take(L.ext_fwd || L.ext_bwd ? T * 2 * r * 2 : 0);
   {   // partial tiles of products cut along K: at most one tile per CU
     const size_t slices = (di > dn ? di : dn) / 64 / 4;
     const size_t tiles = (T / 192 + 1) * ((di > dn ? di : dn) / 256 + 1) * slices;
-    L.gemm_floats = L.extend && slices >= 2 ? GEMM_SCRATCH_FLOATS / 256 * (tiles < 256 ? tiles : 256) : 0;
+    L.gemm_floats = (L.ext_fwd || L.ext_bwd) && slices >= 2 ? GEMM_SCRATCH_FLOATS / 256 * (tiles < 256 ? tiles : 256) : 0;
     L.gemm_part = take(L.gemm_floats * 4);
   }
   L.fwd_end = o;
@@ -171,7 +176,7 @@ __global__ __launch_bounds__(512) void rank_project_kernel(const bf16_t *__restr
   }
 }
 
-// C = X Wmain^T + s (X Wq^T) Wr^T for bf16 and more than 128 rows: the projection, then one product
+// C = X Wmain^T + s (X Wq^T) Wr^T for bf16 and more than four rows: the projection, then one product
 // over the K segments [X | hi | lo] x [Wmain | Wr | Wr].  P and PT keep the projection (unscaled).
 // Against the product beside an unextended projection, its slices' sum and an in-place update of C:
 // 4096 x 4096 x 4096, rank 16, 157 -> 108 us, and one rounding of C less.
@@ -193,7 +198,7 @@ int extended_product(const LinLayout &L, char *ws, int T, int Nmain, int r, int 
   p.seg[1] = GemmSeg{ext, Wr, 2 * r, r, r};
   p.seg[2] = GemmSeg{ext + r, Wr, 2 * r, r, r};
   p.nseg = 3;
-  HIP_TRY(launch_gemm(MIXLORA_BF16, &p, 1, st, GemmScratch{(float *)(ws + L.gemm_part), L.gemm_floats}));
+  HIP_TRY(launch_gemm(MIXLORA_BF16, &p, 1, st, GemmScratch{L.gemm_floats ? (float *)(ws + L.gemm_part) : nullptr, L.gemm_floats}));
   return MIXLORA_OK;
 }
 
@@ -238,7 +243,7 @@ int mixlora_lora_linear_forward(const mixlora_linear_dims *dims, const void *W, 
     B = ws + L.padB;
     D.r = L.rp;
   }
-  if (L.extend)
+  if (L.ext_fwd)
     return extended_product(L, ws, D.T, D.d_out, D.r, D.d_in, D.lora_scale, x, W, y, A, B,
                             (float *)(ws + L.P), ws + L.P_T, st);
   // y0 = x W^T and P = x A^T in one launch (both read x), then y = y0 + s P B^T in place
@@ -284,7 +289,7 @@ int mixlora_lora_linear_backward(const mixlora_linear_dims *dims, const void *W,
                                  job_bank_T(A, 1, r, di, ws + L.At)};    // [r, d_in]  -> [d_in, r]
     HIP_TRY(launch_relayout(dt, jobs, 2, st));
   }
-  if (L.extend) {
+  if (L.ext_bwd) {
     const int erc = extended_product(L, ws, T, di, r, dn, s, dy, W_T, dx, ws + L.Bt, ws + L.At,
                                      (float *)(ws + L.VB), ws + L.VB_T, st);
     if (erc) return erc;
@@ -296,11 +301,11 @@ int mixlora_lora_linear_backward(const mixlora_linear_dims *dims, const void *W,
                                            (float *)(ws + L.VB), st);
     if (grc) return grc;
     HIP_TRY(launch_lowrank_add(dt, dx, (const float *)(ws + L.VB), ws + L.At, T, di, r, s, st));
-    if (dt == MIXLORA_BF16) {
+    if (dt == MIXLORA_BF16)
       HIP_TRY(launch_f32_to_bf16T((const float *)(ws + L.VB), T, r, ws + L.VB_T, L.ldT, st));
-      HIP_TRY(launch_f32_to_bf16T((const float *)(ws + L.P), T, r, ws + L.P_T, L.ldT, st));
-    }
   }
+  if (dt == MIXLORA_BF16 && !L.ext_fwd)   // else the forward's projection kernel has written it
+    HIP_TRY(launch_f32_to_bf16T((const float *)(ws + L.P), T, r, ws + L.P_T, L.ldT, st));
   // dA = s VB^T x  [r, d_in];  dB = s dy^T P  [d_out, r]: outer-product sums over all tokens
   const int32_t *tok = (const int32_t *)(ws + L.tok_offs);
   float *part = (float *)(ws + L.partials);

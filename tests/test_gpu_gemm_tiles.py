@@ -56,6 +56,23 @@ def test_f32_tiles_match_oracle(shape):
     pu.compare_all(res, bw["forward"], bw, cfg)
 
 
+# few rows: matrix-vector products (one and two rows; K around whole 512-element runs), narrow tiles with
+# the weights streamed or cached, and large tiles where a contraction is not in whole 64-wide K tiles
+@pytest.mark.parametrize("shape", [(1, 512, 1400, 5), (1, 4104, 1024, 8), (2, 1032, 2744, 8), (2, 4096, 9216, 8),
+                                   (3, 264, 712, 8), (5, 4096, 9216, 4), (30, 264, 712, 8), (100, 1032, 2744, 3)],
+                         ids=lambda s: "T%d_d%d_f%d_N%d" % s)
+def test_few_rows_match_oracle(shape):
+    T, d, f, N = shape
+    cfg = synth.scaled(synth.CONFIGS["llama2_7b_decode"], name="rows", T=T, d=d, d_ff=f, N=N)
+    print(f"case T={T} d={d} f={f} N={N}", flush=True)
+    host = synth.make_inputs(cfg)
+    m = MixLoraFFN(cfg, host, with_backward=False)
+    m.workspace.fill_(0xFF)
+    m.forward()
+    W = {n: host[n] for n in synth.WEIGHT_NAMES}
+    pu.compare_all(m.results(), orc.forward(host["x"], W, cfg.k, cfg.lora_scale, cfg.aux_coeff, "top1"), None, cfg)
+
+
 def test_repeated_passes_are_bit_identical():
     """Slices are added in a fixed order."""
     cfg = synth.scaled(synth.CONFIGS["llama2_7b"], name="tiles_rerun", T=300, d=1024, d_ff=2744)

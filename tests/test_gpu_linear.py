@@ -26,6 +26,10 @@ CASES = [
     ("bf16_129_rows", 129, 264, 264, 40, "bf16", True),
     ("bf16_square_split", 200, 1024, 1024, 8, "bf16", True),
     ("bf16_r12_square", 331, 1032, 1032, 12, "bf16", False),
+    ("bf16_2_rows", 2, 1032, 520, 16, "bf16", True),
+    ("bf16_4_rows", 4, 520, 1032, 8, "bf16", True),
+    ("bf16_5_rows", 5, 520, 1032, 8, "bf16", True),
+    ("bf16_60_rows_wide", 60, 264, 8200, 16, "bf16", True),
 ]
 
 
