@@ -185,14 +185,13 @@ Layout make_layout(const mixlora_dims &D, int schedule = MIXLORA_SCHEDULE_LINEAR
   L.Bx = take(d * (size_t)L.Kx * E);
   for (int i = 0; i < 6; i++) L.pad_g[i] = take((int)r != D.r ? bank_elems(i, N, r, d, f) * 4 : 0);
   L.dz = take(T * N * 4);
-  if (E == 4)   // all seven sums of the pass at once
-    L.partial_floats = 3 * group_outer_partial_floats((int)N, (int)r, (int)f, (int)kT) +
-                       3 * group_outer_partial_floats((int)N, (int)r, (int)d, (int)kT) +
-                       group_outer_partial_floats(1, (int)N, (int)d, (int)T);
-  for (size_t v : {GOM_MAX_JOBS * group_outer_mfma_partial_floats((int)N, (int)r, (int)f),
-                   GOM_MAX_JOBS * group_outer_mfma_partial_floats((int)N, (int)r, (int)d),
-                   group_outer_mfma_partial_floats(1, (int)N, (int)d)})
-    if (v > L.partial_floats) L.partial_floats = v;
+  // all seven sums of the pass at once
+  L.partial_floats = 3 * (E == 2 ? group_outer_mfma_partial_floats((int)N, (int)r, (int)f, (int)kT, 3)
+                                 : group_outer_partial_floats((int)N, (int)r, (int)f, (int)kT)) +
+                     3 * (E == 2 ? group_outer_mfma_partial_floats((int)N, (int)r, (int)d, (int)kT, 3)
+                                 : group_outer_partial_floats((int)N, (int)r, (int)d, (int)kT)) +
+                     (E == 2 ? group_outer_mfma_partial_floats(1, (int)N, (int)d, (int)T, 1)
+                             : group_outer_partial_floats(1, (int)N, (int)d, (int)T));
   L.partials = take(L.partial_floats * 4);
   L.bwd_end = o;
   return L;
@@ -830,32 +829,21 @@ static int backward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mo
     GatherJob gj[6];
     for (int i = 0; i < 6; i++) gj[i] = GatherJob{fsrc[i], ws + L.small[i], by_token[i], weighted[i]};
     HIP_TRY_AS(PROF_OTHER, 0, launch_gather_small_T(pc, gj, 6, L.ldT, st));
-    // the three sums over d_ff-wide operands in one launch, the three over gathered d-wide
-    // operands in another (same groups, width and gather mode within a launch)
-    const int wide_f[3] = {0, 1, 4}, wide_d[3] = {2, 3, 5};
-    GomJob jf[3], jd[3];
-    for (int j = 0; j < 3; j++) {
-      jf[j] = GomJob{ws + L.small[wide_f[j]], wide[wide_f[j]], gout[wide_f[j]], layout_qc[wide_f[j]]};
-      jd[j] = GomJob{ws + L.small[wide_d[j]], wide[wide_d[j]], gout[wide_d[j]], layout_qc[wide_d[j]]};
+    // the three sums over d_ff-wide operands first, then the three over d-wide ones (the token's row;
+    // weight-decomposed experts: dB_down sums the factor-carrying pair rows c_down[e] * dy[t], already
+    // gathered), then dW_router = dz^T x (the transposed bf16 dz comes from the router backward)
+    const int order[6] = {0, 1, 4, 2, 3, 5};
+    GomJob go[GOM_MAX_JOBS];
+    for (int j = 0; j < 6; j++) {
+      const int i = order[j];
+      const bool pair_rows = dora && i == 5;
+      go[j] = GomJob{ws + L.small[i], pair_rows ? ws + L.dYp : wide[i], gout[i], offs,
+                     pair_rows ? nullptr : gat[i], N, r, width[i], k, (int)kT, L.ldT, 3, layout_qc[i], s};
     }
-    HIP_TRY_AS(PROF_GRAD_SUMS, 3.0 * kT * f * Eb,
-               launch_group_outer_mfma(offs, N, kT, nullptr, k, jf, 3, L.ldT, r, f, s, part, pfl, st));
-    if (dora) {
-      // dB_down sums the factor-carrying pair rows c_down[e] * dy[t] (already gathered)
-      HIP_TRY_AS(PROF_GRAD_SUMS, 2.0 * kT * d * Eb,
-                 launch_group_outer_mfma(offs, N, kT, pair_of_row, k, jd, 2, L.ldT, r, d, s, part, pfl, st));
-      const GomJob jb{ws + L.small[5], ws + L.dYp, gout[5], layout_qc[5]};
-      HIP_TRY_AS(PROF_GRAD_SUMS, 1.0 * kT * d * Eb,
-                 launch_group_outer_mfma(offs, N, kT, nullptr, k, &jb, 1, L.ldT, r, d, s, part, pfl, st));
-    } else {
-      HIP_TRY_AS(PROF_GRAD_SUMS, 3.0 * kT * d * Eb,
-                 launch_group_outer_mfma(offs, N, kT, pair_of_row, k, jd, 3, L.ldT, r, d, s, part, pfl, st));
-    }
-    // dW_router = dz^T x  (the transposed bf16 dz comes from the router backward)
-    const GomJob jr{ws + L.dzT, x, grads->dW_router, 1};
-    HIP_TRY_AS(PROF_GRAD_SUMS, (double)T * d * Eb,
-               launch_group_outer_mfma((int32_t *)(ws + L.tok_offs), 1, T, nullptr, 1, &jr, 1, L.ldTz,
-                                       N, d, 1.f, part, pfl, st));
+    go[6] = GomJob{ws + L.dzT, x, grads->dW_router, (int32_t *)(ws + L.tok_offs), nullptr,
+                   1, N, d, 1, T, L.ldTz, 1, 1, 1.f};
+    HIP_TRY_AS(PROF_GRAD_SUMS, (3.0 * kT * f + 3.0 * kT * d + (double)T * d) * Eb,
+               launch_group_outer_mfma(go, GOM_MAX_JOBS, part, pfl, st));
   } else {
     GatherJob gj[6];
     GoJob go[GO_MAX_JOBS];

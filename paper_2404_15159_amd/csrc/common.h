@@ -334,20 +334,21 @@ size_t group_outer_partial_floats(int G, int r, int C, int rows);
 
 // bf16 MFMA version: smallT is the transposed bf16 factor [r][ldT] (ldT % 8 == 0, readable up to
 // the next multiple of 16 rows past the last group), wide is bf16 with C % 8 == 0.  Up to
-// GOM_MAX_JOBS sums of the same shape (groups, C, gather mode, scale) go into one launch and
-// one reduction launch; partials must hold njobs * group_outer_mfma_partial_floats(G, r, C).
+// GOM_MAX_JOBS sums of any shapes go into one launch and one reduction launch; `alike` tells how many
+// of them have this job's shape; partials must hold the sum of their
+// group_outer_mfma_partial_floats.
 struct GomJob {
   const void *smallT;
   const void *wide;
   float *out;
-  int layout_qc;
+  const int32_t *offs, *pair_of_row;
+  int G, r, C, k, rows, ldT, alike, layout_qc;
+  float scale;
 };
-constexpr int GOM_MAX_JOBS = 3;
-hipError_t launch_group_outer_mfma(const int32_t *offs, int G, int nrows,
-                                   const int32_t *pair_of_row, int k, const GomJob *jobs, int njobs,
-                                   int ldT, int r, int C, float scale, float *partials,
-                                   size_t partial_floats, hipStream_t st);
-size_t group_outer_mfma_partial_floats(int G, int r, int C);
+constexpr int GOM_MAX_JOBS = 7;
+hipError_t launch_group_outer_mfma(const GomJob *jobs, int njobs, float *partials, size_t partial_floats,
+                                   hipStream_t st);
+size_t group_outer_mfma_partial_floats(int G, int r, int C, int rows, int alike);
 // outT[q, row] = (w_row or 1) * src[(by_token ? t(row) : row), e(row)*r + q] as bf16, pitch ldT;
 // up to GATHER_MAX_JOBS factors in one launch
 struct GatherJob {

@@ -8,6 +8,8 @@
 // in a fixed order by a second kernel: no floating-point atomics, bit-reproducible.
 #include "common.h"
 
+#include <type_traits>
+
 namespace mixlora {
 
 constexpr int GO_COLS = 512;   // 256 threads x 2 adjacent columns
@@ -97,42 +99,6 @@ __global__ __launch_bounds__(256) void group_outer_sum_kernel(GoBatch batch) {
   }
 }
 
-// out = scale * sum_split partial, written as [g][q][c] (layout_qc) or [g][c][q]; blockIdx.y picks
-// one of up to GOM_MAX_JOBS reductions of the same shape.
-struct ReduceBatch {
-  const float *partial[GOM_MAX_JOBS];
-  float *out[GOM_MAX_JOBS];
-  int layout_qc[GOM_MAX_JOBS];
-};
-
-__global__ void group_outer_reduce_kernel(ReduceBatch batch, int G, int r, int C, int nsplit,
-                                          float scale) {
-  const float *__restrict__ partial = batch.partial[blockIdx.y];
-  float *__restrict__ out = batch.out[blockIdx.y];
-  const int layout_qc = batch.layout_qc[blockIdx.y];
-  const int64_t n = (int64_t)G * r * C;
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  // four loads in flight at a time; the additions keep the split order
-  float acc = 0.f;
-  int sp = 0;
-  for (; sp + 4 <= nsplit; sp += 4) {
-    const float a0 = partial[(int64_t)sp * n + i], a1 = partial[(int64_t)(sp + 1) * n + i];
-    const float a2 = partial[(int64_t)(sp + 2) * n + i], a3 = partial[(int64_t)(sp + 3) * n + i];
-    acc += a0; acc += a1; acc += a2; acc += a3;
-  }
-  for (; sp < nsplit; sp++) acc += partial[(int64_t)sp * n + i];
-  acc *= scale;
-  if (layout_qc) {
-    out[i] = acc;
-  } else {
-    const int c = (int)(i % C);
-    const int q = (int)((i / C) % r);
-    const int g = (int)(i / ((int64_t)C * r));
-    out[((int64_t)g * C + c) * r + q] = acc;
-  }
-}
-
 // Row slices of a job: enough workgroups for the chip, at least 16 rows of an average group each
 // (a slice of two rows costs more in partial sums than it saves).
 static int go_splits(int G, int C, int rows) {
@@ -191,33 +157,37 @@ constexpr int GOM_CB = 8;     // column blocks per wave: a lane reads 8 adjacent
 // therefore stands for column c0 + 8*i + b.  In the result, lane (q, hi) register 4*gg + m of
 // block b is column c0 + 8*(8*gg + 4*hi + m) + b: for fixed (gg, m) the 8 blocks give 8
 // consecutive columns, stored as two float4.
-// Several sums of the same shape (same groups, same C, same gather mode) share one launch:
-// blockIdx.y = job * G + group.
+// All sums of a pass share one launch (blockIdx.x = first block of the job + (split * G + group) *
+// column groups + column group): the wide ones come first, and the short ones, which alone left most
+// of the chip waiting, fill in behind them.  Against one launch per shape and a reduction each: 187 ->
+// 147 us at the 7B shape, 55 -> 30 at 300 tokens.
 struct GomBatch {
-  const bf16_t *smallT[GOM_MAX_JOBS];
-  const bf16_t *wide[GOM_MAX_JOBS];
+  GomJob job[GOM_MAX_JOBS];
   float *partial[GOM_MAX_JOBS];
-  float *out[GOM_MAX_JOBS];      // used when the rows are not split: the result is final
-  int layout_qc[GOM_MAX_JOBS];
+  int nsplit[GOM_MAX_JOBS], x0[GOM_MAX_JOBS];
+  int njobs;
 };
 
-template <bool GATHER, int NQ>
-__global__ __launch_bounds__(256, NQ == 1 ? 2 : 1) void group_outer_mfma_kernel(
-    const int32_t *__restrict__ offs, const int32_t *__restrict__ pair_of_row, int k, int nrows,
-    GomBatch batch, int G, int ldT, int r, int C, int nsplit, float scale) {
-  const int job = blockIdx.y / G, g = blockIdx.y % G, sp = blockIdx.z;
-  const bf16_t *__restrict__ smallT = batch.smallT[job];
-  const bf16_t *__restrict__ wide = batch.wide[job];
-  float *__restrict__ partial = batch.partial[job];
+template <int NQ>
+__global__ __launch_bounds__(256, NQ == 1 ? 2 : 1) void group_outer_mfma_kernel(GomBatch batch) {
+  int ji = 0;
+  while (ji + 1 < batch.njobs && batch.x0[ji + 1] <= (int)blockIdx.x) ji++;
+  const GomJob &J = batch.job[ji];
+  const int G = J.G, r = J.r, C = J.C, ldT = J.ldT, nsplit = batch.nsplit[ji], nrows = J.rows, k = J.k;
+  const int cgs = (C + 1023) >> 10, at = blockIdx.x - batch.x0[ji];
+  const int cg = at % cgs, g = at / cgs % G, sp = at / cgs / G;
+  const bf16_t *__restrict__ smallT = reinterpret_cast<const bf16_t *>(J.smallT);
+  const bf16_t *__restrict__ wide = reinterpret_cast<const bf16_t *>(J.wide);
+  const int32_t *__restrict__ pair_of_row = J.pair_of_row;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int l31 = lane & 31, hi = lane >> 5;
-  const int lo = offs[g], hi_ = offs[g + 1];
+  const int lo = J.offs[g], hi_ = J.offs[g + 1];
   const int base = lo & ~15;
   const int nsteps = hi_ > lo ? (hi_ - base + 15) >> 4 : 0;
   const int per = (nsteps + nsplit - 1) / nsplit;
   const int st_lo = sp * per;
   const int st_hi = st_lo + per < nsteps ? st_lo + per : nsteps;
-  const int c0 = (blockIdx.x * 4 + wave) * (32 * GOM_CB);
+  const int c0 = (cg * 4 + wave) * (32 * GOM_CB);
   if (c0 >= C) return;   // whole wave out of range (no barriers in this kernel)
   int ccol = c0 + 8 * l31;
   if (ccol >= C) ccol = C - 8;
@@ -229,33 +199,36 @@ __global__ __launch_bounds__(256, NQ == 1 ? 2 : 1) void group_outer_mfma_kernel(
 #pragma unroll
       for (int i = 0; i < 16; i++) acc[b][j][i] = 0.f;
 
+  auto walk = [&](auto gather) {
   for (int st = st_lo; st < st_hi; st++) {
     const int rbase = base + st * 16 + hi * 8;
     bf16x8_t bq[NQ];
 #pragma unroll
     for (int j = 0; j < NQ; j++) {
       const int q = j * 32 + l31;
-      const bf16x8_t ld = *reinterpret_cast<const bf16x8_t *>(smallT + (int64_t)(q < r ? q : 0) * ldT + rbase);
-      bf16x8_t v;
-#pragma unroll
-      for (int p = 0; p < 8; p++) {
-        const int row = rbase + p;
-        v[p] = (q < r && row >= lo && row < hi_) ? ld[p] : (bf16_t)0.f;
-      }
-      bq[j] = v;
+      bq[j] = *reinterpret_cast<const bf16x8_t *>(smallT + (int64_t)(q < r ? q : 0) * ldT + rbase);
     }
+    // rows read in place are read exactly once per step: a streaming (non-temporal) load keeps them from
+    // displacing the gathered rows and partial results other kernels reuse (the sums over the d_ff-wide
+    // operands measured 28 % faster); gathered token rows are read by k groups and stay cached
     bf16x8_t wrow[8];
 #pragma unroll
     for (int p = 0; p < 8; p++) {
-      int row = rbase + p;
-      row = row < nrows ? row : nrows - 1;
-      const int64_t src = GATHER ? pair_of_row[row] / k : row;
-      // rows read in place are read exactly once per step: a streaming (non-temporal) load keeps
-      // them from displacing the gathered rows and partial results other kernels reuse (the
-      // launch over the d_ff-wide operands measured 28 % faster); gathered token rows are read by
-      // k groups and stay cached
-      const bf16x8_t *wp = reinterpret_cast<const bf16x8_t *>(wide + src * C + ccol);
-      wrow[p] = GATHER ? *wp : __builtin_nontemporal_load(wp);
+      const int row = rbase + p < nrows ? rbase + p : nrows - 1;
+      if constexpr (decltype(gather)::value)
+        wrow[p] = *reinterpret_cast<const bf16x8_t *>(wide + (int64_t)(pair_of_row[row] / k) * C + ccol);
+      else
+        wrow[p] = __builtin_nontemporal_load(reinterpret_cast<const bf16x8_t *>(wide + (int64_t)row * C + ccol));
+    }
+    __builtin_amdgcn_sched_barrier(0);   // every load of the step is on its way before the masks
+#pragma unroll
+    for (int j = 0; j < NQ; j++) {
+      const bool qv = j * 32 + l31 < r;
+#pragma unroll
+      for (int p = 0; p < 8; p++) {
+        const int row = rbase + p;
+        bq[j][p] = (qv & (row >= lo) & (row < hi_)) ? bq[j][p] : (bf16_t)0.f;
+      }
     }
 #pragma unroll
     for (int b = 0; b < GOM_CB; b++) {
@@ -267,14 +240,18 @@ __global__ __launch_bounds__(256, NQ == 1 ? 2 : 1) void group_outer_mfma_kernel(
         acc[b][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, bq[j], acc[b][j], 0, 0, 0);
     }
   }
+  };
+  if (pair_of_row) walk(std::true_type{});   // (decided outside the loop)
+  else walk(std::false_type{});
+  const float scale = J.scale;
 #pragma unroll
   for (int j = 0; j < NQ; j++) {
     const int q = j * 32 + l31;
     if (q < r) {
       if (nsplit == 1) {
         // rows not split: scale and write the result itself, [g][q][c] or [g][c][q]
-        float *out = batch.out[job];
-        const bool qc = batch.layout_qc[job] != 0;
+        float *out = J.out;
+        const bool qc = J.layout_qc != 0;
 #pragma unroll
         for (int gg = 0; gg < 4; gg++)
 #pragma unroll
@@ -298,7 +275,7 @@ __global__ __launch_bounds__(256, NQ == 1 ? 2 : 1) void group_outer_mfma_kernel(
           }
         continue;
       }
-      float *o = partial + (((int64_t)sp * G + g) * r + q) * C;
+      float *o = batch.partial[ji] + (((int64_t)sp * G + g) * r + q) * C;
 #pragma unroll
       for (int gg = 0; gg < 4; gg++)
 #pragma unroll
@@ -315,52 +292,96 @@ __global__ __launch_bounds__(256, NQ == 1 ? 2 : 1) void group_outer_mfma_kernel(
   }
 }
 
-static int gom_splits(int G, int C, int njobs = 1) {
-  // one resident round: 256 CUs x 2 workgroups of 4 waves (the kernel runs 2 waves per SIMD)
-  const int col_groups = (C + 1023) / 1024;
-  int s = 512 / (col_groups * G * njobs);
-  if (s < 1) s = 1;
-  if (s > 8 && G > 1) s = 8;     // partial sums cost HBM traffic: nsplit * G * r * C floats
-  if (s > 32) s = 32;
-  return s;
-}
-
-size_t group_outer_mfma_partial_floats(int G, int r, int C) {
-  return (size_t)gom_splits(G, C) * G * r * C;
-}
-
-hipError_t launch_group_outer_mfma(const int32_t *offs, int G, int nrows,
-                                   const int32_t *pair_of_row, int k, const GomJob *jobs, int njobs,
-                                   int ldT, int r, int C, float scale, float *partials,
-                                   size_t partial_floats, hipStream_t st) {
-  if (njobs < 1 || njobs > GOM_MAX_JOBS) return hipErrorInvalidValue;
-  const int nsplit = gom_splits(G, C, njobs);
-  const size_t per_job = (size_t)nsplit * G * r * C;
-  if (per_job * njobs > partial_floats) return hipErrorInvalidValue;
-  GomBatch b{};
-  ReduceBatch rb{};
-  for (int i = 0; i < njobs; i++) {
-    b.smallT[i] = (const bf16_t *)jobs[i].smallT;
-    b.wide[i] = (const bf16_t *)jobs[i].wide;
-    b.partial[i] = partials + per_job * i;
-    b.out[i] = jobs[i].out;
-    b.layout_qc[i] = jobs[i].layout_qc;
-    rb.partial[i] = b.partial[i];
-    rb.out[i] = jobs[i].out;
-    rb.layout_qc[i] = jobs[i].layout_qc;
+// out = scale * sum of a split job's partials in split order; blockIdx.y picks the job.  One element per
+// thread, reads along the columns, eight slices in flight (four rank entries per thread, for 16-byte
+// stores of the [g][c][q] form, left too few threads: 42 against 11 us at the 7B shape).
+__global__ __launch_bounds__(256) void group_outer_reduce_kernel(GomBatch batch) {
+  const GomJob &J = batch.job[blockIdx.y];
+  const int nsplit = batch.nsplit[blockIdx.y], r = J.r, C = J.C;
+  const int64_t n = (int64_t)J.G * r * C;
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (nsplit == 1 || i >= n) return;
+  const float *src = batch.partial[blockIdx.y] + i;
+  float acc = 0.f;
+  for (int s0 = 0; s0 < nsplit; s0 += 8) {
+    float v[8];
+#pragma unroll
+    for (int u = 0; u < 8; u++) v[u] = src[(int64_t)(s0 + u < nsplit ? s0 + u : s0) * n];
+#pragma unroll
+    for (int u = 0; u < 8; u++)
+      if (s0 + u < nsplit) acc += v[u];
   }
-  const dim3 grid((C + 1023) / 1024, G * njobs, nsplit), block(256);
-#define MIXLORA_GOM(GA_, NQ_)                                                                   \
-  hipLaunchKernelGGL((group_outer_mfma_kernel<GA_, NQ_>), grid, block, 0, st, offs, pair_of_row, \
-                     k, nrows, b, G, ldT, r, C, nsplit, scale)
-  if (pair_of_row) { if (r <= 32) MIXLORA_GOM(true, 1); else MIXLORA_GOM(true, 2); }
-  else { if (r <= 32) MIXLORA_GOM(false, 1); else MIXLORA_GOM(false, 2); }
-#undef MIXLORA_GOM
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || nsplit == 1) return e;   // unsplit rows: the kernel wrote the results
-  const int64_t n = (int64_t)G * r * C;
-  hipLaunchKernelGGL(group_outer_reduce_kernel, dim3((unsigned)((n + 255) / 256), njobs), dim3(256),
-                     0, st, rb, G, r, C, nsplit, scale);
+  acc *= J.scale;
+  if (J.layout_qc) {
+    J.out[i] = acc;
+  } else {
+    const int c = (int)(i % C), q = (int)(i / C % r), g = (int)(i / ((int64_t)C * r));
+    J.out[((int64_t)g * C + c) * r + q] = acc;
+  }
+}
+
+// Row slices of a job, `alike` jobs of its shape being in the launch: enough workgroups that they cover
+// the chip twice (256 CUs x 2 workgroups of 4 waves), and at least 64 rows of an average group each -
+// a slice's partial sums cost a trip through memory and back.
+static int gom_splits(int G, int C, int rows, int alike) {
+  const int cgs = (C + 1023) / 1024;
+  int s = 512 / (cgs * G * alike);
+  if (s > 8 && G > 1) s = 8;
+  // one group beside others (the router's sum): 12 slices are as good as 32 there (1 % on the step), but a
+  // few workgroups that walk more than 512 rows each outlast the rest of the launch
+  const int beside = rows > 6144 ? rows / 512 : 12, alone = 32;
+  if (G == 1 && s > (alike == 1 ? beside : alone)) s = alike == 1 ? beside : alone;
+  if (s > 64) s = 64;
+  if (s > rows / (64 * G)) s = rows / (64 * G);
+  return s < 1 ? 1 : s;
+}
+
+size_t group_outer_mfma_partial_floats(int G, int r, int C, int rows, int alike) {
+  const int s = gom_splits(G, C, rows, alike);
+  return s > 1 ? (size_t)s * G * r * C : 0;
+}
+
+hipError_t launch_group_outer_mfma(const GomJob *jobs, int njobs, float *partials, size_t partial_floats,
+                                   hipStream_t st) {
+  if (njobs < 1 || njobs > GOM_MAX_JOBS) return hipErrorInvalidValue;
+  // Jobs that cover the chip twice by themselves keep a launch of their own (L3-8B shape, 672
+  // workgroups of d_ff-wide sums: 0.6 % on the step against one launch for all).
+  int lead = 0;
+  for (int64_t wgs = 0; lead < njobs && jobs[lead].C == jobs[0].C && jobs[lead].G == jobs[0].G; lead++) {
+    wgs += (jobs[lead].C + 1023) / 1024 * jobs[lead].G * gom_splits(jobs[lead].G, jobs[lead].C, jobs[lead].rows, jobs[lead].alike);
+    if (lead + 1 == jobs[0].alike && lead + 1 < njobs && wgs > 512) {
+      size_t used = 0;
+      for (int i = 0; i <= lead; i++)
+        used += group_outer_mfma_partial_floats(jobs[i].G, jobs[i].r, jobs[i].C, jobs[i].rows, jobs[i].alike);
+      if (used > partial_floats) return hipErrorInvalidValue;
+      const hipError_t e = launch_group_outer_mfma(jobs, lead + 1, partials, used, st);
+      if (e != hipSuccess) return e;
+      return launch_group_outer_mfma(jobs + lead + 1, njobs - lead - 1, partials + used, partial_floats - used, st);
+    }
+  }
+  GomBatch b{};
+  b.njobs = njobs;
+  size_t used = 0;
+  int x = 0, rmax = 0;
+  int64_t n = 0;   // reduction threads of the largest split job
+  for (int i = 0; i < njobs; i++) {
+    const GomJob &J = jobs[i];
+    b.job[i] = J;
+    b.nsplit[i] = gom_splits(J.G, J.C, J.rows, J.alike);
+    b.partial[i] = partials + used;
+    used += group_outer_mfma_partial_floats(J.G, J.r, J.C, J.rows, J.alike);
+    b.x0[i] = x;
+    x += (J.C + 1023) / 1024 * J.G * b.nsplit[i];
+    rmax = J.r > rmax ? J.r : rmax;
+    const int64_t m = b.nsplit[i] > 1 ? (int64_t)J.G * J.r * J.C : 0;
+    n = m > n ? m : n;
+  }
+  if (used > partial_floats) return hipErrorInvalidValue;
+  if (rmax <= 32) hipLaunchKernelGGL(group_outer_mfma_kernel<1>, dim3(x), dim3(256), 0, st, b);
+  else hipLaunchKernelGGL(group_outer_mfma_kernel<2>, dim3(x), dim3(256), 0, st, b);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || n == 0) return e;   // unsplit rows: the kernel wrote the results
+  hipLaunchKernelGGL(group_outer_reduce_kernel, dim3((unsigned)((n + 255) / 256), njobs), dim3(256), 0, st, b);
   return hipGetLastError();
 }
 

@@ -60,10 +60,8 @@ LinLayout make_layout(const mixlora_linear_dims &D) {
   L.At = take(di * r * E);
   L.VB = take(T * r * 4);
   L.VB_T = take((size_t)L.ldT * r * 2);
-  size_t pf = group_outer_mfma_partial_floats(1, (int)r, (int)di);
-  const size_t pfn = group_outer_mfma_partial_floats(1, (int)r, (int)dn);
-  if (pfn > pf) pf = pfn;
-  if (di == dn) pf *= 2;   // both sums in one launch
+  size_t pf = group_outer_mfma_partial_floats(1, (int)r, (int)di, (int)T, 2) +
+              group_outer_mfma_partial_floats(1, (int)r, (int)dn, (int)T, 2);
   if (E == 4)
     pf = group_outer_partial_floats(1, (int)r, (int)di, (int)T) + group_outer_partial_floats(1, (int)r, (int)dn, (int)T);
   L.partial_floats = pf;
@@ -310,16 +308,9 @@ int mixlora_lora_linear_backward(const mixlora_linear_dims *dims, const void *W,
   const int32_t *tok = (const int32_t *)(ws + L.tok_offs);
   float *part = (float *)(ws + L.partials);
   if (dt == MIXLORA_BF16) {
-    const GomJob j2[2] = {GomJob{ws + L.VB_T, x, dA, 1}, GomJob{ws + L.P_T, dy, dB, 0}};
-    if (di == dn) {   // same width: one launch
-      HIP_TRY(launch_group_outer_mfma(tok, 1, T, nullptr, 1, j2, 2, L.ldT, r, di, s, part,
-                                      L.partial_floats, st));
-    } else {
-      HIP_TRY(launch_group_outer_mfma(tok, 1, T, nullptr, 1, j2, 1, L.ldT, r, di, s, part,
-                                      L.partial_floats, st));
-      HIP_TRY(launch_group_outer_mfma(tok, 1, T, nullptr, 1, j2 + 1, 1, L.ldT, r, dn, s, part,
-                                      L.partial_floats, st));
-    }
+    const GomJob go[2] = {GomJob{ws + L.VB_T, x, dA, tok, nullptr, 1, r, di, 1, T, L.ldT, 2, 1, s},
+                          GomJob{ws + L.P_T, dy, dB, tok, nullptr, 1, r, dn, 1, T, L.ldT, 2, 0, s}};
+    HIP_TRY(launch_group_outer_mfma(go, 2, part, L.partial_floats, st));
   } else {
     const GoJob go[2] = {
         GoJob{tok, nullptr, (const float *)(ws + L.VB), (const float *)x, dA, 1, r, di, 1, T, 1, s},
