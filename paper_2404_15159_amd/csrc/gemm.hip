@@ -826,10 +826,12 @@ __global__ __launch_bounds__(256) void gemm_tail_reduce_kernel(GemmBatch args, G
 
 // ---- bf16, one to four rows (decode) ---------------------------------------------------------------
 // Matrix-vector products: bound by streaming the weights once.  A wavefront takes RN rows of B (output
-// columns), its lanes 16-byte pieces of the same 1 KiB run of each, UN runs in flight (RN x UN KiB per
-// wave); the rows of A wait in LDS.  No matrix instruction: a row tile would be padding but for one to
-// four rows, and products of few columns would still have to be cut along K into launches of their own.
-// Lane sums are fp32, added by a butterfly.
+// columns), its lanes 16-byte pieces of the same 1 KiB run of each, UN runs requested while the UN
+// before them are used (two register sets; streaming loads: without the hint 76 against 70.5 us per
+// token of the 7B block).  The rows of A wait in LDS.  No matrix instruction: a row tile would be
+// padding but for one to four rows, and products of few columns would have to be cut along K into
+// launches of their own.  Lane sums are fp32, added by a butterfly.
+// One token of the 7B block: gate/up 39 -> 31 us (5.8 TB/s), down 21 + 4 -> 18 us.
 constexpr int GEMV_MAX_ROWS = 4;
 constexpr int GEMV_WAVES = 8;
 
@@ -1178,7 +1180,9 @@ static hipError_t launch_large(const GemmBatch &b, int nprob, const GemmScratch 
               : launch_pp<256>(b, nprob, ntail, S, scratch.part, st);
 }
 
-// One to four rows: as many rows of B per wave as leave the chip two waves per SIMD or more.
+// Two rows of B per wave, one where the columns are so few that two would leave SIMDs empty.  One token of
+// the 7B block: four rows per wave 73.7 us, two 71.6, and with one for the down projection's 4096 columns
+// 70.5 against 71.4; one row through a 4096 x 4096 linear layer 13.8 -> 12.7.
 static hipError_t launch_rows(const GemmBatch &b, int nprob, hipStream_t st) {
   int n = 0, total = 0, kmax = 0;
   for (int i = 0; i < nprob; i++) {
@@ -1205,8 +1209,11 @@ static hipError_t launch_rows(const GemmBatch &b, int nprob, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Whether one to four rows of this contraction length go to the row kernel: its copy of A takes 64 KiB of
-// LDS at most.
+// Rows and contraction length for which the row kernel is the better one whatever the columns: one and
+// two rows (from three on, reading A out of LDS costs more than the matrix tiles' padding: three rows of
+// the 7B block 89 us against 85, four of the 13B block 122 against 108), their copy of A at most 64 KiB of
+// LDS.  launch_gemm also takes three and four rows into at most 8192 columns, which are too few column
+// tiles (forward of a linear layer of rank 16, 4 rows, 4096 -> 1024: 28 -> 13 us).
 bool gemm_rows_ok(int dtype, int M, int K) {
   return dtype == MIXLORA_BF16 && M >= 1 && M <= 2 && (size_t)M * K * sizeof(bf16_t) <= 65536;
 }
