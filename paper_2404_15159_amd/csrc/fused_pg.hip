@@ -544,12 +544,12 @@ static size_t pg_bwd_lds(int NQ) {
   return tiles > red ? tiles : red;
 }
 
-// At least 12 tokens per pair of experts: with fewer, most of a 32-token tile is padding and the
-// expert-grouped stages are ahead (training step, us, these / those: 1000 tokens and 16 experts
-// 1015 / 905, 700 tokens of two 8-expert adapters 680 / 639, 300 tokens and 8 experts 416 / 410; but
-// 1500 tokens and 16 experts, forward, 432 / 444, 517 tokens and 8 experts, forward, 206 / 212).
+// No lower limit on the tokens per pair of experts, although with few of them a 32-token tile is mostly
+// padding (training step, us, these stages / the expert-grouped ones: 1000 tokens and 16 experts
+// 1015 / 905, 300 tokens and 8 experts 416 / 410): these add a token's two activations in fp32 and
+// round the sum once, those add what was rounded to bf16 before (3.3e-3 of the output).
 bool fused_pg_ok(const PairCtx &pc, int f) {
-  return pc.T >= 6 * pc.N * (pc.N - 1) && pc.k == 2 && pc.N <= PG_MAX_EXPERTS && pc.r <= 16 && pc.T > 128 && pc.T <= PG_MAX_TOKENS &&
+  return pc.k == 2 && pc.N <= PG_MAX_EXPERTS && pc.r <= 16 && pc.T > 128 && pc.T <= PG_MAX_TOKENS &&
          f >= 64 && (int64_t)2 * pc.T * f < ((int64_t)1 << 31);
 }
 

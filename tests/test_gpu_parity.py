@@ -132,6 +132,28 @@ def test_small_cases(name, base, over):
     pu.compare_all(res, fw, bw, cfg)
 
 
+@pytest.mark.parametrize("T,N,r,M", [(129, 8, 16, 1), (300, 8, 16, 1), (1000, 16, 8, 1), (700, 4, 16, 4)],
+                         ids=lambda v: str(v))
+def test_token_outputs_do_not_depend_on_the_batch(T, N, r, M):
+    """The first T tokens of a 2048-token call give the same outputs in a call of their own, however few
+    tokens that leaves per pair of experts: a token's two expert activations are added in fp32 and rounded
+    once.  Rounding them to bf16 first adds two errors of up to 2^-9 (3e-3 seen); 32-bit sums in another
+    order move a rounding in one element of 2^14 or so."""
+    over = dict(d=256, d_ff=776, N=N, k=2, r=r, alpha=2.0 * r, M=M)
+    long_cfg = synth.scaled(BASE_BF16, name="batch_long", T=2048, **over)
+    host = synth.make_inputs(long_cfg)
+    tm = (np.arange(2048) * 7 % M).astype(np.int32) if M > 1 else None
+    ys = []
+    for cfg in (long_cfg, synth.scaled(BASE_BF16, name="batch_short", T=T, **over)):
+        h = dict(host, x=host["x"][:cfg.T], dy=host["dy"][:cfg.T])
+        m = MixLoraFFN(cfg, h, token_model=None if tm is None else tm[:cfg.T])
+        m.forward()
+        ys.append(m.results())
+    assert np.array_equal(ys[0]["topk_idx"][:T], ys[1]["topk_idx"])
+    _, e = pu.rel_errors(ys[1]["y"], ys[0]["y"][:T])
+    assert e < 5e-4, e
+
+
 def test_million_tokens():
     """A very long batch of narrow rows (two million pairs): row indices times row widths pass
     2^31 elements only in 64-bit arithmetic, the grouping runs as thousands of chunks, and the
