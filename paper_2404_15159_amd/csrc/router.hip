@@ -22,6 +22,10 @@ __device__ __forceinline__ float wave_max(float v) {
 // logits go to the lower expert index; slots in descending order) and renormalisation of the kept
 // probabilities.  probs gets all Ntot columns (0 outside the adapter); idx_out is the index
 // inside the adapter, idx_ws the index among all Ntot experts.
+// The kept experts are k different ones of the adapter's own whatever the logits are (everything after
+// this addresses memory with them): a kept lane is closed rather than lowered, because its logit may
+// be -inf like every other one's, and NaN ranks with -inf, because the maximum passes over it.  The
+// weights of a token with NaN or +inf among its logits are NaN.
 __device__ __forceinline__ void route_token(float z, int lane, int t, int lo, int N, int Ntot,
                                             int k, float *__restrict__ probs,
                                             int32_t *__restrict__ idx_out,
@@ -34,19 +38,20 @@ __device__ __forceinline__ void route_token(float z, int lane, int t, int lo, in
   const float ez = own ? expf(z - zmax) : 0.f;
   const float p = ez / wave_sum(ez);
   if (lane < Ntot) probs[(int64_t)t * Ntot + lane] = p;
-  // k rounds of arg-max with ties to the lowest lane
-  float zc = z;
+  // k rounds of arg-max with ties to the lowest lane (k <= N: an open lane is left in each)
+  const float zc = z == z ? z : -INFINITY;
+  bool open = own;
   float psel = 0.f;     // lane j keeps the probability of slot j
   int esel = 0;
   float ksum = 0.f;
   for (int j = 0; j < k; j++) {
-    const float m = wave_max(zc);
-    const unsigned long long b = __ballot(zc == m && own);
+    const float m = wave_max(open ? zc : -INFINITY);
+    const unsigned long long b = __ballot(open && zc == m);
     const int e = __ffsll((long long)b) - 1;
     const float pe = __shfl(p, e, 64);
     ksum += pe;
     if (lane == j) { psel = pe; esel = e; }
-    if (lane == e) zc = -INFINITY;
+    if (lane == e) open = false;
   }
   if (lane < k) {
     const float w = psel / ksum;

@@ -154,6 +154,38 @@ def test_token_outputs_do_not_depend_on_the_batch(T, N, r, M):
     assert e < 5e-4, e
 
 
+@pytest.mark.parametrize("base,T", [(BASE_BF16, 2), (BASE_BF16, 40), (BASE_BF16, 300), (BASE_F32, 200)],
+                         ids=["bf16_2", "bf16_40", "bf16_300", "f32_200"])
+def test_tokens_with_non_finite_logits_stay_to_themselves(base, T):
+    """A token whose logits are NaN, infinite or all -inf is still routed to k different experts of the
+    block (its own outputs are NaN); every other token's outputs are those of a clean batch."""
+    cfg = synth.scaled(base, name="nonfinite", T=T, d=256, d_ff=776, N=8, k=2, r=8, alpha=16.0)
+    host = synth.make_inputs(cfg)
+    host["W_router"][:, 0] = 0.015625       # one feature that reaches every logit with the same sign
+    bad = {0: (slice(None), np.nan), T // 3: (0, np.inf), T // 2: (0, -np.inf), T - 1: (3, np.inf)}
+    if T == 2:
+        bad = {0: (0, -np.inf)}
+    clean, dirty = host["x"].copy(), host["x"].copy()
+    for t, (col, v) in bad.items():
+        clean[t] = 0.0
+        dirty[t, col] = v
+    rest = np.setdiff1d(np.arange(T), list(bad))
+    out = []
+    for x in (clean, dirty):
+        m = MixLoraFFN(cfg, dict(host, x=x))
+        m.workspace.fill_(0)
+        print(f"case {cfg.dtype} T={T} finite={bool(np.isfinite(x).all())}", flush=True)
+        m.forward()
+        idx = m.topk_idx.cpu().numpy()
+        assert ((idx >= 0) & (idx < cfg.N)).all() and (idx[:, 0] != idx[:, 1]).all()
+        assert int(m.counts.sum()) == cfg.k * T
+        m.backward(d_aux=0.0)
+        out.append(m.results())
+    assert np.isnan(out[1]["topk_w"][list(bad)]).all()
+    for n in ("topk_idx", "topk_w", "y", "dx"):
+        assert np.array_equal(out[0][n][rest], out[1][n][rest]), n
+
+
 def test_million_tokens():
     """A very long batch of narrow rows (two million pairs): row indices times row widths pass
     2^31 elements only in 64-bit arithmetic, the grouping runs as thousands of chunks, and the
