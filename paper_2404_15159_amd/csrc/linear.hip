@@ -1,11 +1,13 @@
 // Plain LoRA linear (Eq. 1 with the scale alpha / r), the form the method puts on the attention
 // projections (Section 3.2):  y = x W^T + s (x A^T) B^T  with W frozen.  Built from the same
-// pieces as the feed-forward block.  bf16 with more than four rows: the rank-r projection s x A^T
-// is made first (rank_project_kernel) and enters the frozen product as two extra K segments, its
-// bf16 value and the bf16 rounding residue of it.  Otherwise the frozen product and the projection
-// share one GEMM launch and the rank-r update is added in place in fp32.  The gradients of A and B
-// are outer-product sums over all tokens as one group.
+// pieces as the feed-forward block.  bf16 with more than 128 rows, or more than four into fewer than
+// 8192 columns: the rank-r projection s x A^T is made first (rank_project_kernel) and enters the
+// frozen product as an extra K segment, in three bf16 pieces that hold all of its 24 bits.  Otherwise
+// the frozen product and the projection share one GEMM launch and the rank-r update is added in place
+// in fp32.  The gradients of A and B are outer-product sums over all tokens as one group.
 #include "common.h"
+
+#include <cmath>
 
 using namespace mixlora;
 
@@ -20,7 +22,7 @@ inline int pad_rank(int r) { return (r + 7) & ~7; }
 struct LinLayout {
   int rp;                         // rank entries the pass runs on: r rounded up to a multiple of 8
   size_t padA, padB, padgA, padgB;   // zero-padded copies of A, B (kept for the backward) and of dA, dB
-  size_t P, P_T, tok_offs, ext, gemm_part, fwd_end;
+  size_t P, P_T, tok_offs, ext, ext_B, gemm_part, fwd_end;
   size_t W_T, Bt, At, VB, VB_T, partials, bwd_end;
   size_t partial_floats, gemm_floats;
   int ldT;
@@ -47,7 +49,11 @@ LinLayout make_layout(const mixlora_linear_dims &D) {
   L.ldT = (int)((T + 15) / 16 * 16 + 16);
   L.P_T = take((size_t)L.ldT * r * 2);
   L.tok_offs = take(2 * 4);
-  L.ext = take(L.ext_fwd || L.ext_bwd ? T * 2 * r * 2 : 0);
+  L.ext = take(L.ext_fwd || L.ext_bwd ? T * 3 * r * 2 : 0);
+  {
+    const size_t cf = L.ext_fwd ? dn : 0, cb = L.ext_bwd ? di : 0;
+    L.ext_B = take((cf > cb ? cf : cb) * 3 * r * 2);
+  }
   {   // partial tiles of products cut along K: at most one tile per CU
     const size_t slices = (di > dn ? di : dn) / 64 / 4;
     const size_t tiles = (T / 192 + 1) * ((di > dn ? di : dn) / 256 + 1) * slices;
@@ -100,20 +106,42 @@ GemmProblem problem(int M, int N, void *C, int64_t ldc, int c_f32, const void *A
 }
 
 // P[t, q] = sum_c X[t, c] * Wq[q, c]  (r <= 64 columns), in three forms: fp32, transposed bf16 (the
-// row factor of the gradient sums) and s * P split into a bf16 value and its bf16 residue,
-// ext[t] = [hi(r) | lo(r)]: hi + lo carries s * P to 2^-17, far below the rounding of the product
-// that it is added to.  Bound by reading X once (33 MB at 4096 x 4096: 9 us); a workgroup owns 16
-// rows, its eight waves every eighth 128-column run of them, so that 256 workgroups have 2 waves
-// per SIMD with 4 KB each in flight; fragments come straight from memory (whole 128-byte lines over
-// four MFMA steps), Wq from the caches.  The waves' sums are added in a fixed order.
+// row factor of the gradient sums) and m * P (s = m 2^e, 1/2 <= |m| < 1) cut into three bf16 pieces by
+// truncation, ext[t] = [hi(r) | mid(r) | lo(r)]: their sum is m * P to its last bit, and no piece
+// overflows.  Trailing workgroups lay out the other factor of that term, Bx[c] = [B | B' | B'] 2^e with
+// B' = B but zeros for infinities: hi alone meets those, or two pieces of opposite signs would make
+// NaN of them.
+// Bound by reading X once (33 MB at 4096 x 4096: 9 us); a workgroup owns 16 rows, its eight waves every
+// eighth 128-column run of them, so that 256 workgroups have 2 waves per SIMD with 4 KB each in flight;
+// fragments come straight from memory (whole 128-byte lines over four MFMA steps), Wq from the caches.
+// The waves' sums are added in a fixed order.
 template <int NQ>
 __global__ __launch_bounds__(512) void rank_project_kernel(const bf16_t *__restrict__ X,
                                                            const bf16_t *__restrict__ Wq, int T, int K,
-                                                           int r, float s, float *__restrict__ P,
+                                                           int r, float m, float *__restrict__ P,
                                                            bf16_t *__restrict__ PT, int ldT,
                                                            bf16_t *__restrict__ ext,
-                                                           int32_t *__restrict__ tok_offs) {
+                                                           int32_t *__restrict__ tok_offs,
+                                                           const bf16_t *__restrict__ Bm, int cols,
+                                                           float b_scale, bf16_t *__restrict__ Bx) {
   __shared__ float red[8][NQ][64][4];
+  const int row_blocks = (T + 15) >> 4;
+  if ((int)blockIdx.x >= row_blocks) {   // workgroup-uniform; eight entries of a row of B per thread
+    const int per = r >> 3, i = (blockIdx.x - row_blocks) * 512 + threadIdx.x;
+    if (i >= cols * per) return;
+    const int c = i / per, q0 = i % per * 8;
+    bf16x8_t v = *reinterpret_cast<const bf16x8_t *>(Bm + (int64_t)c * r + q0), fin;
+#pragma unroll
+    for (int e = 0; e < 8; e++) {
+      v[e] = (bf16_t)((float)v[e] * b_scale);
+      fin[e] = __builtin_isinf((float)v[e]) ? (bf16_t)0.f : v[e];
+    }
+    bf16_t *o = Bx + (int64_t)c * 3 * r + q0;
+    *reinterpret_cast<bf16x8_t *>(o) = v;
+    *reinterpret_cast<bf16x8_t *>(o + r) = fin;
+    *reinterpret_cast<bf16x8_t *>(o + 2 * r) = fin;
+    return;
+  }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int l15 = lane & 15, hi = lane >> 4;
   const int t0 = blockIdx.x * 16;
@@ -143,11 +171,11 @@ __global__ __launch_bounds__(512) void rank_project_kernel(const bf16_t *__restr
     for (int ks = 0; ks < 4; ks++) {
       if (k0 + ks * 32 + hi * 8 >= K) {   // past the end: zeros on both sides
 #pragma unroll
-        for (int m = 0; m < 8; m++) fx[ks][m] = (bf16_t)0.f;
+        for (int u = 0; u < 8; u++) fx[ks][u] = (bf16_t)0.f;
 #pragma unroll
         for (int j = 0; j < NQ; j++)
 #pragma unroll
-          for (int m = 0; m < 8; m++) fw[j][ks][m] = (bf16_t)0.f;
+          for (int u = 0; u < 8; u++) fw[j][ks][u] = (bf16_t)0.f;
       }
 #pragma unroll
       for (int j = 0; j < NQ; j++)
@@ -157,45 +185,53 @@ __global__ __launch_bounds__(512) void rank_project_kernel(const bf16_t *__restr
 #pragma unroll
   for (int j = 0; j < NQ; j++) *reinterpret_cast<f32x4_t *>(red[wave][j][lane]) = acc[j];
   __syncthreads();
-  // acc[j][m] of lane (l15, hi): row l15, q = 16 j + 4 hi + m
+  // acc[j][u] of lane (l15, hi): row l15, q = 16 j + 4 hi + u
   for (int i = threadIdx.x; i < NQ * 256; i += 512) {
     const int j = i >> 8, q = j * 16 + (i & 15), t = t0 + ((i >> 4) & 15);
     if (q >= r || t >= T) continue;
-    const int ln = ((i >> 2) & 3) * 16 + ((i >> 4) & 15), m = i & 3;
-    float v = red[0][j][ln][m];
+    const int ln = ((i >> 2) & 3) * 16 + ((i >> 4) & 15), u = i & 3;
+    float v = red[0][j][ln][u];
 #pragma unroll
-    for (int w = 1; w < 8; w++) v += red[w][j][ln][m];
+    for (int w = 1; w < 8; w++) v += red[w][j][ln][u];
     P[(int64_t)t * r + q] = v;
     PT[(int64_t)q * ldT + t] = (bf16_t)v;
-    const float sv = s * v;
-    const bf16_t h = (bf16_t)sv;
-    ext[(int64_t)t * 2 * r + q] = h;
-    ext[(int64_t)t * 2 * r + r + q] = (bf16_t)(__builtin_isinf((float)h) ? 0.f : sv - (float)h);
+    const float mp = m * v;
+    const bool finite = (__float_as_uint(mp) & 0x7f800000u) != 0x7f800000u;
+    const float h = finite ? __uint_as_float(__float_as_uint(mp) & 0xffff0000u) : mp;
+    const float rest = finite ? mp - h : 0.f;
+    const float mid = __uint_as_float(__float_as_uint(rest) & 0xffff0000u);
+    bf16_t *o = ext + (int64_t)t * 3 * r + q;
+    o[0] = (bf16_t)h;
+    o[r] = (bf16_t)mid;
+    o[2 * r] = (bf16_t)(rest - mid);
   }
 }
 
-// C = X Wmain^T + s (X Wq^T) Wr^T for bf16 and more than four rows: the projection, then one product
-// over the K segments [X | hi | lo] x [Wmain | Wr | Wr].  P and PT keep the projection (unscaled).
+// C = X Wmain^T + s (X Wq^T) Wr^T where the rank-r term rides in the product: the projection, then one
+// product over the K segments [X | hi mid lo] x [Wmain | Bx].  P and PT keep the projection (unscaled).
 // Against the product beside an unextended projection, its slices' sum and an in-place update of C:
 // 4096 x 4096 x 4096, rank 16, 157 -> 108 us, and one rounding of C less.
 int extended_product(const LinLayout &L, char *ws, int T, int Nmain, int r, int K, float s, const void *X,
                      const void *Wmain, void *C, const void *Wq, const void *Wr, float *P, void *PT,
                      hipStream_t st) {
-  const dim3 grid((T + 15) / 16), block(512);
+  int e = 0;   // s = m 2^e
+  if (std::isfinite(s)) std::frexp(s, &e);
+  e = e < -100 ? -100 : e > 100 ? 100 : e;
+  const float m = std::ldexp(s, -e);
+  const dim3 grid((T + 15) / 16 + (Nmain * (r / 8) + 511) / 512), block(512);
 #define MIXLORA_RANKP(NQ_)                                                                          \
   hipLaunchKernelGGL(rank_project_kernel<NQ_>, grid, block, 0, st, (const bf16_t *)X,               \
-                     (const bf16_t *)Wq, T, K, r, s, P, (bf16_t *)PT, L.ldT, (bf16_t *)(ws + L.ext), \
-                     (int32_t *)(ws + L.tok_offs))
+                     (const bf16_t *)Wq, T, K, r, m, P, (bf16_t *)PT, L.ldT, (bf16_t *)(ws + L.ext), \
+                     (int32_t *)(ws + L.tok_offs), (const bf16_t *)Wr, Nmain, std::ldexp(1.f, e),   \
+                     (bf16_t *)(ws + L.ext_B))
   if (r <= 16) MIXLORA_RANKP(1);
   else if (r <= 32) MIXLORA_RANKP(2);
   else MIXLORA_RANKP(4);
 #undef MIXLORA_RANKP
   HIP_TRY(hipGetLastError());
   GemmProblem p = problem(T, Nmain, C, Nmain, 0, X, K, Wmain, K, K);
-  const bf16_t *ext = (const bf16_t *)(ws + L.ext);
-  p.seg[1] = GemmSeg{ext, Wr, 2 * r, r, r};
-  p.seg[2] = GemmSeg{ext + r, Wr, 2 * r, r, r};
-  p.nseg = 3;
+  p.seg[1] = GemmSeg{ws + L.ext, ws + L.ext_B, 3 * r, 3 * r, 3 * r};
+  p.nseg = 2;
   HIP_TRY(launch_gemm(MIXLORA_BF16, &p, 1, st, GemmScratch{L.gemm_floats ? (float *)(ws + L.gemm_part) : nullptr, L.gemm_floats}));
   return MIXLORA_OK;
 }

@@ -54,6 +54,60 @@ def test_lora_linear_small(name, T, d_in, d_out, r, dtype, pre):
     assert pu.rel_errors(base, y)[0] > 5 * tol
 
 
+@pytest.mark.parametrize("T,r", [(5, 16), (100, 8), (131, 64), (300, 12)])
+def test_rank_term_keeps_24_bits(T, r):
+    """W cancels the rank-r term but for an identity, in whole numbers: x A^T reaches 2^22, every product
+    and partial sum is below 2^24, so the result is exact unless the term is held in fewer bits.  Forward
+    with large A and B of +-1, backward (s (dy B) A) the other way round."""
+    rng = np.random.default_rng(T)
+    n, cols = 512, 264
+    big = lambda shape: rng.integers(-127, 128, size=shape).astype(np.float32)
+    x, dy = np.abs(big((T, n))), np.abs(big((T, n)))      # (absolute values: sums of one sign)
+    pick = np.zeros((cols, r), np.float32)                # row c picks rank entry c % r, with a sign
+    pick[np.arange(cols), np.arange(cols) % r] = np.where(np.arange(cols) // r % 2, 1.0, -1.0)
+    bank = np.abs(big((r, n)))
+    keep = np.zeros((cols, n), np.float32)
+    keep[np.arange(cols), np.arange(cols) * 5 % n] = 1.0
+    host = dict(x=x, W=keep - pick @ bank, A=bank, B=pick, dy=big((T, cols)))
+    print(f"case forward T={T} r={r}", flush=True)
+    m = LoraLinear(T, n, cols, r, 1.0, "bf16", host)
+    m.forward()
+    assert np.array_equal(m.results()["y"], x @ keep.T)
+    host = dict(x=big((T, cols)), W=(keep - pick @ bank).T.copy(), A=pick.T.copy(), B=bank.T.copy(), dy=dy)
+    print(f"case backward T={T} r={r}", flush=True)
+    m = LoraLinear(T, cols, n, r, 1.0, "bf16", host)
+    m.forward(); m.backward()
+    assert np.array_equal(m.results()["dx"], dy @ keep.T)
+
+
+@pytest.mark.parametrize("T", [5, 131, 300])
+def test_rank_term_with_infinite_and_huge_weights(T):
+    """An infinite element of B (forward) or A (backward) gives the infinities that 64-bit arithmetic
+    gives; a projection that only overflows once it is scaled does not."""
+    r, s = 16, 3.0
+    host = synth.make_linear_inputs(T, 256, 264, r, "bf16", seed=77)
+    with np.errstate(invalid="ignore", over="ignore"):
+        for n, at in (("B", (3, 1)), ("A", (2, 5))):
+            h = dict(host, **{n: host[n].copy()})
+            h[n][at] = -np.inf
+            m = LoraLinear(T, 256, 264, r, s, "bf16", h)
+            m.forward(); m.backward()
+            h64 = {k: v.astype(np.float64) for k, v in h.items()}
+            ref = dict(y=h64["x"] @ h64["W"].T + s * (h64["x"] @ h64["A"].T) @ h64["B"].T,
+                       dx=h64["dy"] @ h64["W"] + s * (h64["dy"] @ h64["B"]) @ h64["A"])
+            res = m.results()
+            for out in ("y", "dx"):
+                assert np.array_equal(np.isnan(res[out]), np.isnan(ref[out])), (n, out)
+                assert np.array_equal(np.isinf(res[out]) * np.sign(res[out]),
+                                      np.isinf(ref[out]) * np.sign(ref[out])), (n, out)
+        h = {n: host[n].copy() for n in host}
+        h["x"][:, 5], h["A"][2, 5], h["B"][:, 2] = 1.0, synth.round_to_bf16(np.float32([3e38]))[0], 0.01
+        h["B"] = synth.round_to_bf16(h["B"])
+        m = LoraLinear(T, 256, 264, r, s, "bf16", h)
+        m.forward()
+        pu.assert_close("y", m.results()["y"], orc.lora_linear_forward(h["x"], h["W"], h["A"], h["B"], s), 2e-2)
+
+
 def test_lora_linear_full_size_attention_projection():
     """A q/k/v/o-sized projection of the LLaMA-2-7B shape (4096 -> 4096, rank 16, 4096 tokens),
     as bench.py --workload llama2_7b_attn_proj times it: sampled outputs and the full A/B
