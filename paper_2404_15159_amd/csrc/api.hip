@@ -33,6 +33,7 @@ struct Layout {
   // forward scratch
   size_t a_comb, Qw, Bd_cat, rank_part, splitk, gp_scratch, gemm_part;
   size_t gemm_floats;   // floats at gemm_part: partial tiles of GEMM launches cut along K
+  size_t joint_floats;  // those that the default schedule would have
   size_t base_end;      // forward workspace without them
   size_t gemm_part_bwd, gemm_floats_bwd;   // the same for the backward pass
   size_t fwd_end;
@@ -135,14 +136,15 @@ Layout make_layout(const mixlora_dims &D, int schedule = MIXLORA_SCHEDULE_LINEAR
   L.Kx = up64((int)(2 * R) + (int)N);   // whole K tiles of the GEMM's DMA path
   {   // scratch of both passes' GEMM launches: at most one partial tile per CU, none where no K range is long
     // enough to cut (the longest is that of the input-gradient product)
-    const size_t slices = (2 * f + (size_t)L.Kx) / 64 / 4, rows = (pair_down ? kT : T) / 192 + 1;
-    const size_t tiles = rows * (2 * (f / 256 + 1) + d / 256 + 4) * slices;
+    const size_t slices = (2 * f + (size_t)L.Kx) / 64 / 4;
+    const size_t row_tiles = (2 * (f / 256 + 1) + d / 256 + 4) * slices;
+    const size_t tiles = ((pair_down ? kT : T) / 192 + 1) * row_tiles, tiles_T = (T / 192 + 1) * row_tiles;
     const bool large = T > SPLITK_MAX_ROWS || !whole_k_tiles(D);
-    size_t bytes = E == 2 && large && slices >= 2 ? GEMM_SCRATCH_FLOATS * 4 : 0;
-    if (tiles < 256) bytes = bytes / 256 * tiles;
-    L.gemm_floats = bytes / 4;
+    const size_t per_tile = E == 2 && large && slices >= 2 ? GEMM_SCRATCH_FLOATS / 256 : 0;
+    L.gemm_floats = per_tile * (tiles < 256 ? tiles : 256);
+    L.joint_floats = per_tile * (tiles_T < 256 ? tiles_T : 256);
     L.base_end = o;
-    L.gemm_part = take(bytes);
+    L.gemm_part = take(L.gemm_floats * 4);
     L.fwd_end = o;
     // few tokens: only the backward pass, whose products have no K-split buffer of their own
     L.gemm_floats_bwd = L.gemm_floats;
@@ -366,8 +368,16 @@ static int forward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mod
     add_seg(p[5], w->W_gate, d, w->A_gate, d, d);
     add_seg(p[6], w->W_up, d, w->A_up, d, d);
     add_seg(p[7], w->W_down, f, w->A_down, f, f);
-    if (vanilla) {   // unshared schedule: the frozen gate/up products follow the routing, per pair;
-      HIP_TRY(launch_gemm(dt, p + 4, 1, st, gs));   // only the router logits are needed up front
+    // Cuts along K as in the default schedule, whatever scratch the others' per-pair products have.
+    // The narrow problems go first: where the launch's last round is cut, frozen tiles are cut before
+    // the router's (all are in a launch of at most 128 tiles).
+    const GemmScratch js{gs.part, L.joint_floats};
+    const GemmProblem joint[5] = {p[2], p[3], p[4], p[0], p[1]};
+    if (vanilla) {
+      // unshared schedule: the frozen gate/up products follow the routing, per pair; only the router
+      // logits are needed up front, summed as in the other schedules' launch (the same routing bit for
+      // bit)
+      HIP_TRY(launch_gemm(dt, joint, 5, st, js, 2));
     } else if (dora) {
       // the W_down product has the longest K range: its tiles go first so that they do not
       // trail the launch
@@ -380,11 +390,7 @@ static int forward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mod
         HIP_TRY(launch_gemm(dt, p + 7, 1, st, gs));
       }
     } else {
-      // the narrow problems go first: where the launch's last round is cut along K, it is frozen
-      // tiles that are cut, not the router's (whose logits then are summed in one order at every
-      // schedule)
-      const GemmProblem q[5] = {p[2], p[3], p[4], p[0], p[1]};
-      HIP_TRY(dt == MIXLORA_BF16 ? launch_gemm(dt, q, 5, st, gs) : launch_gemm(dt, p, 4, st));
+      HIP_TRY(dt == MIXLORA_BF16 ? launch_gemm(dt, joint, 5, st, js) : launch_gemm(dt, p, 4, st));
     }
   }
   DoraArgs dargs{};

@@ -76,8 +76,10 @@ struct GemmScratch {
   float *part;
   size_t floats;
 };
+// only >= 0: that problem alone is computed, with the kernel and the cuts it has in the launch of all, so
+// that its sums are taken in the same order.
 hipError_t launch_gemm(int dtype, const GemmProblem *probs, int nprob, hipStream_t st,
-                       const GemmScratch &scratch = GemmScratch{nullptr, 0});
+                       const GemmScratch &scratch = GemmScratch{nullptr, 0}, int only = -1);
 // whether products of M rows over a contraction of K go to the row kernel (no need to cut K)
 bool gemm_rows_ok(int dtype, int M, int K);
 // whether problems of different M may share one launch_gemm call

@@ -1161,8 +1161,10 @@ static hipError_t launch_pp(const GemmBatch &b, int nprob, int ntail, int S, flo
   return hipGetLastError();
 }
 
-// Large-tile launch of any number of problems (row counts may differ).
-static hipError_t launch_large(const GemmBatch &b, int nprob, const GemmScratch &scratch, hipStream_t st) {
+// Large-tile launch of any number of problems (row counts may differ); only >= 0: of that one alone, its
+// tiles being cut as in the launch of all.
+static hipError_t launch_large(const GemmBatch &b, int nprob, const GemmScratch &scratch, hipStream_t st,
+                               int only = -1) {
   // 192 rows per tile where that needs no more tiles than 256 (129-192, 257-384, 513-576 rows)
   bool m192 = true;
   int ktiles = 1 << 30;
@@ -1176,6 +1178,16 @@ static hipError_t launch_large(const GemmBatch &b, int nprob, const GemmScratch 
   int tiles = 0, ntail, S;
   for (int i = 0; i < nprob; i++) tiles += pp_tiles(b.p[i], BM);
   plan_tail(tiles, ktiles, BM, scratch.part ? scratch.floats : 0, ntail, S);
+  if (only >= 0) {
+    int behind = 0;   // tiles of the problems that follow: the trailing ones are cut first
+    for (int i = only + 1; i < nprob; i++) behind += pp_tiles(b.p[i], BM);
+    const int own = pp_tiles(b.p[only], BM);
+    ntail = ntail <= behind ? 0 : ntail - behind < own ? ntail - behind : own;
+    GemmBatch one;
+    for (int i = 0; i < GEMM_MAX_PROBLEMS; i++) one.p[i] = b.p[only];
+    return m192 ? launch_pp<192>(one, 1, ntail, S, scratch.part, st)
+                : launch_pp<256>(one, 1, ntail, S, scratch.part, st);
+  }
   return m192 ? launch_pp<192>(b, nprob, ntail, S, scratch.part, st)
               : launch_pp<256>(b, nprob, ntail, S, scratch.part, st);
 }
@@ -1231,10 +1243,15 @@ bool gemm_mixed_rows_ok(int dtype, const GemmProblem *probs, int nprob) {
 }
 
 hipError_t launch_gemm(int dtype, const GemmProblem *probs, int nprob, hipStream_t st,
-                       const GemmScratch &scratch) {
-  if (nprob < 1 || nprob > GEMM_MAX_PROBLEMS) return hipErrorInvalidValue;
+                       const GemmScratch &scratch, int only) {
+  if (nprob < 1 || nprob > GEMM_MAX_PROBLEMS || only >= nprob) return hipErrorInvalidValue;
   GemmBatch b;
   for (int i = 0; i < GEMM_MAX_PROBLEMS; i++) b.p[i] = probs[i < nprob ? i : 0];
+  // what is launched; the route is chosen from all problems
+  GemmBatch l = b;
+  if (only >= 0)
+    for (int i = 0; i < GEMM_MAX_PROBLEMS; i++) l.p[i] = probs[only];
+  const int nl = only >= 0 ? 1 : nprob;
   if (dtype == MIXLORA_F32) {
     int t32 = 0, t64 = 0, all64 = 0;
     for (int i = 0; i < nprob; i++) {
@@ -1246,9 +1263,9 @@ hipError_t launch_gemm(int dtype, const GemmProblem *probs, int nprob, hipStream
       all64 += c;
     }
     if (all64 >= 512)   // two tiles of 64 x 64 per CU
-      hipLaunchKernelGGL((gemm_f32_kernel<64, 4>), dim3(t64, 1, nprob), dim3(256), 0, st, b);
+      hipLaunchKernelGGL((gemm_f32_kernel<64, 4>), dim3(t64, 1, nl), dim3(256), 0, st, l);
     else
-      hipLaunchKernelGGL((gemm_f32_kernel<32, 8>), dim3(t32, 1, nprob), dim3(512), 0, st, b);
+      hipLaunchKernelGGL((gemm_f32_kernel<32, 8>), dim3(t32, 1, nl), dim3(512), 0, st, l);
     return hipGetLastError();
   }
   const int M = probs[0].M, N = probs[0].N;
@@ -1263,7 +1280,7 @@ hipError_t launch_gemm(int dtype, const GemmProblem *probs, int nprob, hipStream
     // problems of different row counts (per-token and per-pair operands) can share a launch of
     // the large-tile kernel only: every tile takes M from its own problem
     if (!gemm_mixed_rows_ok(dtype, probs, nprob)) return hipErrorInvalidValue;
-    return launch_large(b, nprob, scratch, st);
+    return launch_large(b, nprob, scratch, st, only);
   }
   if (M <= 0) return hipSuccess;
   if (dtype == MIXLORA_BF16 && M <= GEMV_MAX_ROWS) {
@@ -1276,19 +1293,19 @@ hipError_t launch_gemm(int dtype, const GemmProblem *probs, int nprob, hipStream
     int64_t cols = 0;
     for (int i = 0; i < nprob; i++) cols += probs[i].N;
     if (kmax < (1 << 20) && (gemm_rows_ok(dtype, M, (int)kmax) || (cols <= 8192 && kmax * 8 <= 65536)))
-      return launch_rows(b, nprob, st);
+      return launch_rows(l, nl, st);
   }
   // Large tiles.  Problems of one launch may differ in N and output type (narrow ones ride in the
   // slack of the last, partially filled round of workgroups).
   if (dtype == MIXLORA_BF16 && M > 128 && any_big && dl_eligible(b, nprob, 8))
-    return launch_large(b, nprob, scratch, st);
+    return launch_large(b, nprob, scratch, st, only);
   // Few rows, and too few 64-column tiles to stream the weights (or ragged K, which the narrow tiles do
   // not take): the large tiles cut along K.  28 x 1024 x 4096 and 100 x 5120 x 5120 with their
   // rank-r term 33 -> 30 and 41 -> 38 us; 30 tokens of a 1296 x 4272 block 181 -> 57.
   if (dtype == MIXLORA_BF16 && M <= 128 && any_big && scratch.part && dl_eligible(b, nprob, 8)) {
     int narrow = 0;
     for (int i = 0; i < nprob; i++) narrow += (probs[i].N + 63) / 64;
-    if (narrow < 128 || !dl_eligible(b, nprob, 64)) return launch_large(b, nprob, scratch, st);
+    if (narrow < 128 || !dl_eligible(b, nprob, 64)) return launch_large(b, nprob, scratch, st, only);
   }
   if (dtype == MIXLORA_BF16 && M <= 128 && any_big && dl_eligible(b, nprob, 64)) {
     // few rows (decode-shaped calls): the launch is bound by streaming the weights once, so the
@@ -1299,13 +1316,14 @@ hipError_t launch_gemm(int dtype, const GemmProblem *probs, int nprob, hipStream
     // the 7B block 98.5 -> 93.4 us, 16 tokens 86.5 -> 80.4).  Smaller ones may still be there
     // (52 MB: 40.6 us cached, 44.4 streamed).
     if (b_bytes(b, nprob) >= STREAM_BYTES)
-      return M <= 64 ? launch_bf16_dl<64, 64, 64, 4, 1, 2, true>(b, nprob, st)
-                     : launch_bf16_dl<128, 64, 64, 4, 2, 2, true>(b, nprob, st);
-    return M <= 64 ? launch_bf16_dl<64, 64, 64, 4, 1, 2, false>(b, nprob, st)
-                   : launch_bf16_dl<128, 64, 64, 4, 2, 2, false>(b, nprob, st);
+      return M <= 64 ? launch_bf16_dl<64, 64, 64, 4, 1, 2, true>(l, nl, st)
+                     : launch_bf16_dl<128, 64, 64, 4, 2, 2, true>(l, nl, st);
+    return M <= 64 ? launch_bf16_dl<64, 64, 64, 4, 1, 2, false>(l, nl, st)
+                   : launch_bf16_dl<128, 64, 64, 4, 2, 2, false>(l, nl, st);
   }
   if (!uniform || nprob > 2) {   // the generic kernels take uniform batches of at most two
     for (int i = 0; i < nprob; i++) {
+      if (only >= 0 && i != only) continue;
       const hipError_t e = launch_gemm(dtype, probs + i, 1, st, scratch);
       if (e != hipSuccess) return e;
     }
@@ -1313,11 +1331,11 @@ hipError_t launch_gemm(int dtype, const GemmProblem *probs, int nprob, hipStream
   }
   const bool f32out = probs[0].c_f32 != 0;
   if (N <= 128 || M <= 128) {
-    return f32out ? launch_bf16<128, 128, 64, 2, 2, float>(b, nprob, st)
-                  : launch_bf16<128, 128, 64, 2, 2, bf16_t>(b, nprob, st);
+    return f32out ? launch_bf16<128, 128, 64, 2, 2, float>(l, nl, st)
+                  : launch_bf16<128, 128, 64, 2, 2, bf16_t>(l, nl, st);
   }
-  return f32out ? launch_bf16<256, 256, 64, 2, 4, float>(b, nprob, st)
-                : launch_bf16<256, 256, 64, 2, 4, bf16_t>(b, nprob, st);
+  return f32out ? launch_bf16<256, 256, 64, 2, 4, float>(l, nl, st)
+                : launch_bf16<256, 256, 64, 2, 4, bf16_t>(l, nl, st);
 }
 
 }  // namespace mixlora

@@ -75,6 +75,23 @@ def test_schedules_agree_on_routing_and_need_more_workspace():
     assert ws["linear"] < ws["shared"] < ws["vanilla"]
 
 
+# launches whose tiles are all cut along K (the router's among them), a few rows on either side of the
+# matrix-vector products' limit, ragged contractions of few and of many rows, no cut
+@pytest.mark.parametrize("T,d,f,N", [(150, 1024, 2752, 8), (300, 1032, 2744, 5), (1, 512, 704, 8), (2, 264, 712, 8),
+                                     (4, 512, 1408, 8), (4, 264, 2744, 8), (30, 264, 712, 8), (100, 1032, 2744, 3),
+                                     (120, 512, 1408, 8), (1500, 512, 1408, 16)])
+def test_schedules_sum_the_logits_alike(T, d, f, N):
+    cfg, host = _inputs("logits", dict(T=T, d=d, d_ff=f, N=N, k=2, r=16))
+    out = []
+    for schedule in (B.SCHEDULE_LINEAR_DOWN, B.SCHEDULE_SHARED, B.SCHEDULE_VANILLA):
+        m = MixLoraFFN(cfg, host, schedule=schedule, with_backward=False)
+        m.forward()
+        out.append(m.results())
+    for o in out[1:]:
+        for n in ("topk_idx", "topk_w", "counts"):
+            assert np.array_equal(o[n], out[0][n]), n
+
+
 def test_schedule_argument_errors():
     cfg, host = _inputs("errors", dict(T=64, d=64, d_ff=128, N=4, k=2, r=8, alpha=16.0))
     m = MixLoraFFN(cfg, host)
