@@ -65,6 +65,11 @@ inline size_t bank_elems(int i, size_t N, size_t rp, size_t d, size_t f) {
   return N * rp * width[i];
 }
 
+// The bf16 gradient sum of the router takes its experts 32 at a time, in two sums where there are more:
+// one sum of 33 to 64 rows would put the whole launch of sums, the LoRA ones of rank 8 with it, on the
+// kernel with two row blocks (twice the MFMAs and accumulators, half the workgroups per CU).
+inline int router_part(int N, int i) { return i == 0 ? (N < 32 ? N : 32) : (N > 32 ? N - 32 : 0); }
+
 // Whether every contraction of the forward pass is in whole 64-wide K tiles, which the narrow-tile
 // kernel for few rows needs.
 inline bool whole_k_tiles(const mixlora_dims &D) {
@@ -192,7 +197,8 @@ Layout make_layout(const mixlora_dims &D, int schedule = MIXLORA_SCHEDULE_LINEAR
                                  : group_outer_partial_floats((int)N, (int)r, (int)f, (int)kT)) +
                      3 * (E == 2 ? group_outer_mfma_partial_floats((int)N, (int)r, (int)d, (int)kT, 3)
                                  : group_outer_partial_floats((int)N, (int)r, (int)d, (int)kT)) +
-                     (E == 2 ? group_outer_mfma_partial_floats(1, (int)N, (int)d, (int)T, 1)
+                     (E == 2 ? group_outer_mfma_partial_floats(1, router_part((int)N, 0), (int)d, (int)T, 1) +
+                                   group_outer_mfma_partial_floats(1, router_part((int)N, 1), (int)d, (int)T, 1)
                              : group_outer_partial_floats(1, (int)N, (int)d, (int)T));
   L.partials = take(L.partial_floats * 4);
   L.bwd_end = o;
@@ -846,10 +852,12 @@ static int backward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mo
       go[j] = GomJob{ws + L.small[i], pair_rows ? ws + L.dYp : wide[i], gout[i], offs,
                      pair_rows ? nullptr : gat[i], N, r, width[i], k, (int)kT, L.ldT, 3, layout_qc[i], s};
     }
-    go[6] = GomJob{ws + L.dzT, x, grads->dW_router, (int32_t *)(ws + L.tok_offs), nullptr,
-                   1, N, d, 1, T, L.ldTz, 1, 1, 1.f};
+    int njobs = 6;
+    for (int i = 0; i < 2 && router_part(N, i) > 0; i++)
+      go[njobs++] = GomJob{(char *)(ws + L.dzT) + (size_t)i * 32 * L.ldTz * 2, x, grads->dW_router + (size_t)i * 32 * d,
+                           (int32_t *)(ws + L.tok_offs), nullptr, 1, router_part(N, i), d, 1, T, L.ldTz, 1, 1, 1.f};
     HIP_TRY_AS(PROF_GRAD_SUMS, (3.0 * kT * f + 3.0 * kT * d + (double)T * d) * Eb,
-               launch_group_outer_mfma(go, GOM_MAX_JOBS, part, pfl, st));
+               launch_group_outer_mfma(go, njobs, part, pfl, st));
   } else {
     GatherJob gj[6];
     GoJob go[GO_MAX_JOBS];

@@ -347,7 +347,7 @@ struct GomJob {
   int G, r, C, k, rows, ldT, alike, layout_qc;
   float scale;
 };
-constexpr int GOM_MAX_JOBS = 7;
+constexpr int GOM_MAX_JOBS = 8;
 hipError_t launch_group_outer_mfma(const GomJob *jobs, int njobs, float *partials, size_t partial_floats,
                                    hipStream_t st);
 size_t group_outer_mfma_partial_floats(int G, int r, int C, int rows, int alike);

@@ -186,6 +186,15 @@ def test_tokens_with_non_finite_logits_stay_to_themselves(base, T):
         assert np.array_equal(out[0][n][rest], out[1][n][rest]), n
 
 
+# more than 32 experts: the router's gradient in two sums, of 32 experts and of the rest
+@pytest.mark.parametrize("T,N", [(70, 33), (2100, 33), (1300, 64)])
+def test_many_experts_match_oracle(T, N):
+    cfg = synth.scaled(BASE_BF16, name="many_experts", T=T, d=520, d_ff=264, N=N, k=2, r=8, alpha=16.0)
+    host = synth.make_inputs(cfg)
+    res, fw, bw, _ = run_case(cfg, host, d_aux=1.5)
+    pu.compare_all(res, fw, bw, cfg)
+
+
 def test_million_tokens():
     """A very long batch of narrow rows (two million pairs): row indices times row widths pass
     2^31 elements only in 64-bit arithmetic, the grouping runs as thousands of chunks, and the
