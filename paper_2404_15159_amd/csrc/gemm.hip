@@ -1224,8 +1224,10 @@ static hipError_t launch_rows(const GemmBatch &b, int nprob, hipStream_t st) {
 // Rows and contraction length for which the row kernel is the better one whatever the columns: one and
 // two rows (from three on, reading A out of LDS costs more than the matrix tiles' padding: three rows of
 // the 7B block 89 us against 85, four of the 13B block 122 against 108), their copy of A at most 64 KiB of
-// LDS.  launch_gemm also takes three and four rows into at most 8192 columns, which are too few column
-// tiles (forward of a linear layer of rank 16, 4 rows, 4096 -> 1024: 28 -> 13 us).
+// LDS.  launch_gemm also takes three and four rows of one or two problems into at most 8192 columns, which
+// are too few column tiles (forward of a linear layer of rank 16, 4 rows, 4096 -> 1024: 28 -> 13 us); the
+// block's forward launches, of five problems or of one per K slice, are not (3 tokens of 1024 x 2752:
+// 38.4 us per pass on the tiles, 43.4 here).
 bool gemm_rows_ok(int dtype, int M, int K) {
   return dtype == MIXLORA_BF16 && M >= 1 && M <= 2 && (size_t)M * K * sizeof(bf16_t) <= 65536;
 }
@@ -1292,7 +1294,7 @@ hipError_t launch_gemm(int dtype, const GemmProblem *probs, int nprob, hipStream
     }
     int64_t cols = 0;
     for (int i = 0; i < nprob; i++) cols += probs[i].N;
-    if (kmax < (1 << 20) && (gemm_rows_ok(dtype, M, (int)kmax) || (cols <= 8192 && kmax * 8 <= 65536)))
+    if (kmax < (1 << 20) && (gemm_rows_ok(dtype, M, (int)kmax) || (nprob <= 2 && cols <= 8192 && kmax * 8 <= 65536)))
       return launch_rows(l, nl, st);
   }
   // Large tiles.  Problems of one launch may differ in N and output type (narrow ones ride in the
