@@ -280,8 +280,10 @@ MIXLORA_API int mixlora_transpose(const void *in, void *out, int32_t rows, int32
 
 /* Measurement hook for benchmarks.  These three and mixlora_mfma_probe are measurement aids, not
  * part of the block's contract: they are the only entry points that synchronise or create HIP
- * objects.  Between begin and end, every launch of the library is bracketed by HIP events on its
- * stream (at most max_launches of them; later launches go untimed).  end waits for those events
+ * objects.  Between begin and end, the launches of the block's bf16 passes, and of the LoRA linear
+ * the products and projections, are bracketed by HIP events on their stream (at most max_launches
+ * of them; later ones go untimed).  A product cut along K counts together with the launch that
+ * adds its slices, as one.  end waits for those events
  * and returns, in HOST memory, the summed time in milliseconds, the number of launches and the
  * floating-point operations (2*M*N*K over their K segments) of the bf16 MFMA GEMM launches that
  * carry the frozen projections.  After end, mixlora_profile_kind returns the same three figures

@@ -1150,14 +1150,11 @@ static hipError_t launch_pp(const GemmBatch &b, int nprob, int ntail, int S, flo
     before += n;
   }
   plan.tail_start = at;
+  // (a cut launch and the one that adds its slices count as one)
   const int slot = prof_on() ? prof_mark_begin(PROF_GEMM, st) : -1;
   hipLaunchKernelGGL(kern, dim3(at + ntail * S), dim3(512), smem, st, b, plan);
+  if (ntail > 0) hipLaunchKernelGGL(gemm_tail_reduce_kernel<BM>, dim3(ntail, BM / 4), dim3(256), 0, st, b, plan);
   if (slot >= 0) prof_mark_end(slot, st, batch_flops(b, nprob));
-  if (ntail > 0) {
-    const int s2 = prof_on() ? prof_mark_begin(PROF_OTHER, st) : -1;
-    hipLaunchKernelGGL(gemm_tail_reduce_kernel<BM>, dim3(ntail, BM / 4), dim3(256), 0, st, b, plan);
-    if (s2 >= 0) prof_mark_end(s2, st, 0.0);
-  }
   return hipGetLastError();
 }
 

@@ -219,6 +219,7 @@ int extended_product(const LinLayout &L, char *ws, int T, int Nmain, int r, int 
   e = e < -100 ? -100 : e > 100 ? 100 : e;
   const float m = std::ldexp(s, -e);
   const dim3 grid((T + 15) / 16 + (Nmain * (r / 8) + 511) / 512), block(512);
+  const int slot = prof_on() ? prof_mark_begin(PROF_OTHER, st) : -1;
 #define MIXLORA_RANKP(NQ_)                                                                          \
   hipLaunchKernelGGL(rank_project_kernel<NQ_>, grid, block, 0, st, (const bf16_t *)X,               \
                      (const bf16_t *)Wq, T, K, r, m, P, (bf16_t *)PT, L.ldT, (bf16_t *)(ws + L.ext), \
@@ -228,6 +229,7 @@ int extended_product(const LinLayout &L, char *ws, int T, int Nmain, int r, int 
   else if (r <= 32) MIXLORA_RANKP(2);
   else MIXLORA_RANKP(4);
 #undef MIXLORA_RANKP
+  if (slot >= 0) prof_mark_end(slot, st, 0.0);
   HIP_TRY(hipGetLastError());
   GemmProblem p = problem(T, Nmain, C, Nmain, 0, X, K, Wmain, K, K);
   p.seg[1] = GemmSeg{ws + L.ext, ws + L.ext_B, 3 * r, 3 * r, 3 * r};

@@ -13,7 +13,7 @@ import torch
 from oracle import mixlora_oracle as orc
 from paper_2404_15159_amd import binding as B
 from paper_2404_15159_amd import synth
-from paper_2404_15159_amd.runner import MixLoraFFN
+from paper_2404_15159_amd.runner import LoraLinear, MixLoraFFN
 
 import parity_utils as pu
 
@@ -316,6 +316,21 @@ def test_graph_capture_and_replay(variant):
         got = m.results()
         for n in ref:
             assert np.array_equal(np.asarray(ref[n]), np.asarray(got[n])), (rep, n)
+
+
+def test_profile_counts_cut_products_whole():
+    """150 tokens: both frozen launches of the forward are cut along K, and adding the slices belongs to
+    them, not to the small launches.  A LoRA linear's projection is counted among those."""
+    cfg = synth.scaled(BASE_BF16, name="profile", T=150, d=1024, d_ff=2752, N=8, k=2, r=16)
+    m = MixLoraFFN(cfg, synth.make_inputs(cfg), with_backward=False)
+    lin = LoraLinear(300, 256, 264, 16, 2.0, "bf16", synth.make_linear_inputs(300, 256, 264, 16, "bf16", seed=5))
+    for run, want in ((m.forward, (2, 0)), (lin.forward, (1, 1))):
+        run()
+        torch.cuda.synchronize()
+        B.mixlora_profile_begin(64)
+        run()
+        B.mixlora_profile_end()
+        assert tuple(B.mixlora_profile_kind(kind)[1] for kind in (0, 6)) == want
 
 
 def test_mfma_probe_is_plausible():
