@@ -18,7 +18,10 @@ pytestmark = pytest.mark.gpu
 # T, d, d_ff, N: one row tile of 192 / of 256, two of 192 / of 256, three of 192, four of 256
 SHAPES = [(129, 512, 1400, 8), (192, 1024, 2744, 8), (193, 1032, 2048, 5), (256, 1024, 1416, 8),
           (257, 1024, 2744, 5), (384, 520, 2056, 8), (385, 1024, 2816, 8), (513, 776, 1544, 3),
-          (577, 1024, 1032, 8)]
+          (577, 1024, 1032, 8),
+          # whole tiles and a cut tail in one launch of several problems: 11 of the fifth problem's tiles
+          # behind 256 whole ones (forward), and all 8 of the second's with 8 of the first's (backward)
+          (517, 1024, 11008, 8), (2000, 1024, 8448, 8)]
 
 
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "T%d_d%d_f%d_N%d" % s)
