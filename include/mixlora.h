@@ -125,7 +125,9 @@ MIXLORA_API int mixlora_ffn_forward(const mixlora_dims *dims, const mixlora_weig
  * activations, partial results of the split down projection, ...) lives instead in a device
  * array inside the library, one copy per GPU, held until the process ends:
  * MIXLORA_STATIC_SCRATCH_BYTES, and 64 MiB for the partial tiles of matrix products cut along
- * their contraction (calls of more than 128 tokens).  The call allocates nothing and frees
+ * their contraction (calls of more than 128 tokens, and shorter ones where d, d_ff or N times the
+ * padded rank is not a multiple of 64).  The array is reserved when the library is loaded on a GPU,
+ * whether this call is used or not.  The call allocates nothing and frees
  * nothing; inputs and outputs are the caller's as before, results are bit-identical to
  * mixlora_ffn_forward.  Forward only: the array is not a handle for mixlora_ffn_backward.
  *   - dims whose forward workspace, the partial tiles apart, exceeds MIXLORA_STATIC_SCRATCH_BYTES
