@@ -2,10 +2,13 @@
 //
 // bf16 storage: the frozen projections of more than 128 rows run on gemm_bf16_pp_kernel (256-wide
 // tiles, two groups of four waves taking turns at the matrix pipe and at memory, trailing tiles
-// cut along K); few rows (decode) on gemm_bf16_dl_kernel's narrow tiles; what neither takes on
-// the register-staged gemm_bf16_kernel.  XCD-aware + grouped tile order everywhere, so that the
-// tiles resident on one XCD share operand rows in that XCD's L2.
-// fp32 storage: plain FMA tiles (the fp32 configuration is a small parity case).
+// cut along K); few rows (decode) on gemm_bf16_dl_kernel's narrow tiles, or cut along K on the large
+// ones where a contraction is ragged or the columns are few; one and two rows, and up to four into few
+// columns, on the matrix-vector kernel gemm_bf16_rows_kernel; what none of them takes on the
+// register-staged gemm_bf16_kernel.  XCD-aware + grouped tile order everywhere, so that the tiles
+// resident on one XCD share operand rows in that XCD's L2.
+// fp32 storage: MFMA 16x16x4 tiles with K spread over the waves (gemm_f32_kernel; the fp32
+// configuration is a small parity case).
 //
 // Every frozen projection of the block (shared gate/up: Algorithm 1 lines 7-8; down: line 14)
 // and their transposes in the backward go through here; LoRA terms enter either as extra
@@ -1201,19 +1204,16 @@ static hipError_t launch_rows(const GemmBatch &b, int nprob, hipStream_t st) {
     for (int sgi = 0; sgi < b.p[i].nseg; sgi++) kt += b.p[i].seg[sgi].K;
     kmax = kt > kmax ? kt : kmax;
   }
-  const int M = b.p[0].M, mr = M == 1 ? 1 : M == 2 ? 2 : 4, rn = total > 8192 ? 2 : 1;
+  // (three and four rows come with at most 8192 columns: one row of B per wave)
+  const int M = b.p[0].M, mr = M == 1 ? 1 : M == 2 ? 2 : 4, rn = mr < 4 && total > 8192 ? 2 : 1;
   const size_t smem = (size_t)mr * kmax * sizeof(bf16_t);
   const dim3 grid((n + GEMV_WAVES * rn - 1) / (GEMV_WAVES * rn), 1, nprob), block(GEMV_WAVES * 64);
   const int slot = prof_on() ? prof_mark_begin(PROF_GEMM, st) : -1;
-#define MIXLORA_ROWS(MR_)                                                                          \
-  do {                                                                                             \
-    if (rn == 2) hipLaunchKernelGGL((gemm_bf16_rows_kernel<MR_, 2, 4>), grid, block, smem, st, b);  \
-    else hipLaunchKernelGGL((gemm_bf16_rows_kernel<MR_, 1, 4>), grid, block, smem, st, b);          \
-  } while (0)
-  if (mr == 1) MIXLORA_ROWS(1);
-  else if (mr == 2) MIXLORA_ROWS(2);
-  else MIXLORA_ROWS(4);
-#undef MIXLORA_ROWS
+  if (mr == 4) hipLaunchKernelGGL((gemm_bf16_rows_kernel<4, 1, 4>), grid, block, smem, st, b);
+  else if (mr == 2 && rn == 2) hipLaunchKernelGGL((gemm_bf16_rows_kernel<2, 2, 4>), grid, block, smem, st, b);
+  else if (mr == 2) hipLaunchKernelGGL((gemm_bf16_rows_kernel<2, 1, 4>), grid, block, smem, st, b);
+  else if (rn == 2) hipLaunchKernelGGL((gemm_bf16_rows_kernel<1, 2, 4>), grid, block, smem, st, b);
+  else hipLaunchKernelGGL((gemm_bf16_rows_kernel<1, 1, 4>), grid, block, smem, st, b);
   if (slot >= 0) prof_mark_end(slot, st, batch_flops(b, nprob));
   return hipGetLastError();
 }
