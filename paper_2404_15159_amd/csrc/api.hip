@@ -747,7 +747,7 @@ static int backward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mo
   int nct = L.nct;
   // tokens grouped by expert pair (tables left by the forward pass): the per-token sums of dg and
   // du come out of the same launch
-  const bool use_pg = dt == MIXLORA_BF16 && !pair_down && !dora && fused_pg_ok(pc, f);
+  const bool use_pg = dt == MIXLORA_BF16 && !pair_down && !dora && fused_pg_bwd_ok(pc, f, Nl);
   if (use_pg) {
     nct = fused_pg_splits(f, T, N);
     HIP_TRY_AS(PROF_FUSED_BWD, 9.0 * T * f * Eb,

@@ -544,13 +544,22 @@ static size_t pg_bwd_lds(int NQ) {
   return tiles > red ? tiles : red;
 }
 
-// No lower limit on the tokens per pair of experts, although with few of them a 32-token tile is mostly
-// padding (training step, us, these stages / the expert-grouped ones: 1000 tokens and 16 experts
-// 1015 / 905, 300 tokens and 8 experts 416 / 410): these add a token's two activations in fp32 and
-// round the sum once, those add what was rounded to bf16 before (3.3e-3 of the output).
+// The forward has no lower limit on the tokens per pair of experts: the expert-grouped stage would add a
+// token's two activations after rounding each to bf16, here they are added in fp32 and rounded once
+// (3.3e-3 of the output).
 bool fused_pg_ok(const PairCtx &pc, int f) {
   return pc.k == 2 && pc.N <= PG_MAX_EXPERTS && pc.r <= 16 && pc.T > 128 && pc.T <= PG_MAX_TOKENS &&
          f >= 64 && (int64_t)2 * pc.T * f < ((int64_t)1 << 31);
+}
+
+// The backward takes at least 12 tokens per pair of experts that can occur (pairs of one adapter's own).
+// With fewer, most of a 32-token tile is padding, and the expert-grouped stage and its combine are ahead;
+// both form a token's sums from the same bf16 gradients.  Training step at the 7B shape, us, here / there:
+// 16 experts 300 tokens 538 / 438, 1000 818 / 760, 1400 1029 / 1006; 8 experts 200 356 / 342, 330 390 / 386;
+// two adapters of 8 experts 500 539 / 507, 1400 1028 / 1055; four of 4 200 399 / 395, 500 509 / 513, 1400
+// 1032 / 1060.
+bool fused_pg_bwd_ok(const PairCtx &pc, int f, int Nl) {
+  return fused_pg_ok(pc, f) && pc.T >= 6 * pc.N * (Nl - 1);
 }
 
 int fused_pg_max_tiles(int T, int N) { return (T + FT_ROWS - 1) / FT_ROWS + N * N; }

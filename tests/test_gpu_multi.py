@@ -117,6 +117,16 @@ def test_multi_one_adapter_matches_single_entry_point():
         assert np.array_equal(v.cpu().numpy(), ra[n]), n
 
 
+# both sides of 12 tokens per pair of experts that can occur (two adapters of 10 pairs each), where the
+# backward changes from the expert-grouped to the pair-grouped stage
+@pytest.mark.parametrize("T", [239, 240])
+def test_backward_stage_edge(T):
+    cfg = synth.scaled(BASE_BF16, name="multi_edge", T=T, d=264, d_ff=648, N=5, k=2, r=16, M=2, seq_len=30)
+    host = synth.make_inputs(cfg)
+    res, fw, bw, tm = run_multi(cfg, host, "round_robin")
+    compare_multi(res, fw, bw, cfg, tm)
+
+
 def test_multi_full_size_two_adapters():
     """Two adapters at the LLaMA-2-7B shape, in the configuration bench.py --workload
     llama2_7b_multi2 times: y / dx on sampled tokens and the gradients of the experts through

@@ -97,7 +97,8 @@ SMALL_CASES = [
     ("bf16_scale_0p7", BASE_BF16, dict(T=257, d=136, d_ff=264, N=5, k=3, r=40, alpha=28.0)),
     ("f32_scale_1p3", BASE_F32, dict(T=333, d=72, d_ff=200, N=6, k=2, r=8, alpha=10.4)),
     # edges of the stage that runs on token tiles of one expert pair (top-2, bf16, r <= 16,
-    # N <= 16, 128 < T <= 65536, d_ff >= 64): fewest tokens, a single pair group with many tiles,
+    # N <= 16, 128 < T <= 65536, d_ff >= 64; the backward's also wants 12 tokens per pair of experts,
+    # which the first of these has not): fewest tokens, a single pair group with many tiles,
     # sixteen experts (120 groups, most tiles ragged) with a ragged last column block, the
     # narrowest d_ff, the largest token count and the first one past it (expert-grouped path)
     ("bf16_pg_129_tokens", BASE_BF16, dict(T=129, d=128, d_ff=264, N=8, k=2, r=16)),
@@ -184,6 +185,16 @@ def test_tokens_with_non_finite_logits_stay_to_themselves(base, T):
     assert np.isnan(out[1]["topk_w"][list(bad)]).all()
     for n in ("topk_idx", "topk_w", "y", "dx"):
         assert np.array_equal(out[0][n][rest], out[1][n][rest]), n
+
+
+# the backward's per-pair stage on both sides of 12 tokens per pair of experts (28 pairs), and on its fewest
+# tokens (four experts have 6 pairs)
+@pytest.mark.parametrize("T,N", [(335, 8), (336, 8), (129, 4)])
+def test_backward_stage_edge_matches_oracle(T, N):
+    cfg = synth.scaled(BASE_BF16, name="bwd_edge", T=T, d=264, d_ff=648, N=N, k=2, r=16)
+    host = synth.make_inputs(cfg)
+    res, fw, bw, _ = run_case(cfg, host, d_aux=1.5)
+    pu.compare_all(res, fw, bw, cfg)
 
 
 # more than 32 experts: the router's gradient in two sums, of 32 experts and of the rest
