@@ -1025,6 +1025,17 @@ static double batch_flops(const GemmBatch &b, int nprob) {
   return fl;
 }
 
+// launches that carry a frozen projection (more than 128 output columns) count as GEMM launches for the
+// measurement hook; a launch of narrow rank-r or router problems does not
+static int batch_kind(const GemmBatch &b, int nprob) {
+  for (int i = 0; i < nprob; i++)
+    if (b.p[i].N > 128) return PROF_GEMM;
+  return PROF_OTHER;
+}
+static void mark_end(int slot, const GemmBatch &b, int nprob, hipStream_t st) {
+  if (slot >= 0) prof_mark_end(slot, st, batch_kind(b, nprob) == PROF_GEMM ? batch_flops(b, nprob) : 0.0);
+}
+
 template <int BM, int BN, int BK, int WGM, int WGN, typename OutT>
 static hipError_t launch_bf16(const GemmBatch &b, int nprob, hipStream_t st) {
   constexpr size_t smem = (size_t)2 * (BM + BN) * (BK + 8) * sizeof(bf16_t);
@@ -1037,11 +1048,9 @@ static hipError_t launch_bf16(const GemmBatch &b, int nprob, hipStream_t st) {
     attr_set = true;
   }
   const int tiles = ((b.p[0].M + BM - 1) / BM) * ((b.p[0].N + BN - 1) / BN);
-  // launches that carry a frozen projection (more than 128 output columns) count as GEMM
-  // launches for the measurement hook; a launch of narrow rank-r or router problems does not
-  const int slot = prof_on() ? prof_mark_begin(b.p[0].N > 128 ? PROF_GEMM : PROF_OTHER, st) : -1;
+  const int slot = prof_on() ? prof_mark_begin(batch_kind(b, nprob), st) : -1;
   hipLaunchKernelGGL(kern, dim3(tiles, 1, nprob), dim3(WGM * WGN * 64), smem, st, b);
-  if (slot >= 0) prof_mark_end(slot, st, b.p[0].N > 128 ? batch_flops(b, nprob) : 0.0);
+  mark_end(slot, b, nprob, st);
   return hipGetLastError();
 }
 
@@ -1061,11 +1070,9 @@ static hipError_t launch_bf16_dl(const GemmBatch &b, int nprob, hipStream_t st) 
     const int t = ((b.p[i].M + BM - 1) / BM) * ((b.p[i].N + BN - 1) / BN);
     tiles = t > tiles ? t : tiles;
   }
-  // every launch of this kernel family is a frozen-projection launch (large tiles at training
-  // shapes, the narrow weight-streaming tiles at decode shapes): all count as GEMM launches
-  const int slot = prof_on() ? prof_mark_begin(PROF_GEMM, st) : -1;
+  const int slot = prof_on() ? prof_mark_begin(batch_kind(b, nprob), st) : -1;
   hipLaunchKernelGGL(kern, dim3(tiles, 1, nprob), dim3(WGM * WGN * 64), smem, st, b);
-  if (slot >= 0) prof_mark_end(slot, st, batch_flops(b, nprob));
+  mark_end(slot, b, nprob, st);
   return hipGetLastError();
 }
 
@@ -1154,10 +1161,10 @@ static hipError_t launch_pp(const GemmBatch &b, int nprob, int ntail, int S, flo
   }
   plan.tail_start = at;
   // (a cut launch and the one that adds its slices count as one)
-  const int slot = prof_on() ? prof_mark_begin(PROF_GEMM, st) : -1;
+  const int slot = prof_on() ? prof_mark_begin(batch_kind(b, nprob), st) : -1;
   hipLaunchKernelGGL(kern, dim3(at + ntail * S), dim3(512), smem, st, b, plan);
   if (ntail > 0) hipLaunchKernelGGL(gemm_tail_reduce_kernel<BM>, dim3(ntail, BM / 4), dim3(256), 0, st, b, plan);
-  if (slot >= 0) prof_mark_end(slot, st, batch_flops(b, nprob));
+  mark_end(slot, b, nprob, st);
   return hipGetLastError();
 }
 
@@ -1208,13 +1215,13 @@ static hipError_t launch_rows(const GemmBatch &b, int nprob, hipStream_t st) {
   const int M = b.p[0].M, mr = M == 1 ? 1 : M == 2 ? 2 : 4, rn = mr < 4 && total > 8192 ? 2 : 1;
   const size_t smem = (size_t)mr * kmax * sizeof(bf16_t);
   const dim3 grid((n + GEMV_WAVES * rn - 1) / (GEMV_WAVES * rn), 1, nprob), block(GEMV_WAVES * 64);
-  const int slot = prof_on() ? prof_mark_begin(PROF_GEMM, st) : -1;
+  const int slot = prof_on() ? prof_mark_begin(batch_kind(b, nprob), st) : -1;
   if (mr == 4) hipLaunchKernelGGL((gemm_bf16_rows_kernel<4, 1, 4>), grid, block, smem, st, b);
   else if (mr == 2 && rn == 2) hipLaunchKernelGGL((gemm_bf16_rows_kernel<2, 2, 4>), grid, block, smem, st, b);
   else if (mr == 2) hipLaunchKernelGGL((gemm_bf16_rows_kernel<2, 1, 4>), grid, block, smem, st, b);
   else if (rn == 2) hipLaunchKernelGGL((gemm_bf16_rows_kernel<1, 2, 4>), grid, block, smem, st, b);
   else hipLaunchKernelGGL((gemm_bf16_rows_kernel<1, 1, 4>), grid, block, smem, st, b);
-  if (slot >= 0) prof_mark_end(slot, st, batch_flops(b, nprob));
+  mark_end(slot, b, nprob, st);
   return hipGetLastError();
 }
 

@@ -331,11 +331,13 @@ def test_graph_capture_and_replay(variant):
 
 def test_profile_counts_cut_products_whole():
     """150 tokens: both frozen launches of the forward are cut along K, and adding the slices belongs to
-    them, not to the small launches.  A LoRA linear's projection is counted among those."""
+    them, not to the small launches.  A LoRA linear's projection is counted among those, and so are the
+    unshared schedule's gathering of rows and its router product, which is launched alone."""
     cfg = synth.scaled(BASE_BF16, name="profile", T=150, d=1024, d_ff=2752, N=8, k=2, r=16)
     m = MixLoraFFN(cfg, synth.make_inputs(cfg), with_backward=False)
+    van = MixLoraFFN(cfg, synth.make_inputs(cfg), schedule=B.SCHEDULE_VANILLA, with_backward=False)
     lin = LoraLinear(300, 256, 264, 16, 2.0, "bf16", synth.make_linear_inputs(300, 256, 264, 16, "bf16", seed=5))
-    for run, want in ((m.forward, (2, 0)), (lin.forward, (1, 1))):
+    for run, want in ((m.forward, (2, 0)), (van.forward, (2, 2)), (lin.forward, (1, 1))):
         run()
         torch.cuda.synchronize()
         B.mixlora_profile_begin(64)
