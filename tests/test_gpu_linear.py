@@ -20,8 +20,9 @@ CASES = [
     ("bf16_multi_tile", 1000, 512, 1288, 8, "bf16", True),
     ("bf16_few_rows", 17, 512, 704, 16, "bf16", True),
     ("bf16_one_row", 1, 64, 128, 8, "bf16", True),
-    # both sides of the row count from which the rank-r term rides in the frozen product; square
-    # (one launch for both gradient sums), column blocks of 16 that are not full, cut K ranges
+    # both sides of the row counts from which the rank-r term rides in the frozen product (5 into fewer
+    # than 8192 columns, 129 into any); square (one launch for both gradient sums), column blocks of 16
+    # that are not full, cut K ranges
     ("bf16_128_rows", 128, 264, 264, 40, "bf16", True),
     ("bf16_129_rows", 129, 264, 264, 40, "bf16", True),
     ("bf16_square_split", 200, 1024, 1024, 8, "bf16", True),
@@ -30,6 +31,9 @@ CASES = [
     ("bf16_4_rows", 4, 520, 1032, 8, "bf16", True),
     ("bf16_5_rows", 5, 520, 1032, 8, "bf16", True),
     ("bf16_60_rows_wide", 60, 264, 8200, 16, "bf16", True),
+    ("bf16_128_rows_wide", 128, 264, 8200, 8, "bf16", True),
+    ("bf16_129_rows_wide", 129, 264, 8200, 8, "bf16", True),
+    ("bf16_40_rows_8184", 40, 264, 8184, 16, "bf16", True),
 ]
 
 
