@@ -419,7 +419,7 @@ def main():
         alg_bytes_per_launch = units_per_step * cfg.d * cfg.d_ff * 2.0 / max(launches_per_step, 1e-9)
         achieved = alg_bytes_per_launch / avg_launch_s if launches_per_step else 0.0
         roofline = {"bound": "hbm",
-                    "kernel": "gemm_bf16_dl_kernel<64 or 128 rows,64,64,4 stages> (weight streaming)",
+                    "kernel": "gemm_bf16_few_kernel (weight streaming)",
                     "achieved": achieved / 1e9, "peak": HBM_PEAK / 1e9, "unit": "GB/s",
                     "frac": achieved / HBM_PEAK, "launches_per_step": launches_per_step,
                     "avg_launch_ms": avg_launch_s * 1e3, "traffic": traffic,

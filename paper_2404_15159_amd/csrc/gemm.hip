@@ -2,7 +2,7 @@
 //
 // bf16 storage: the frozen projections of more than 128 rows run on gemm_bf16_pp_kernel (256-wide
 // tiles, two groups of four waves taking turns at the matrix pipe and at memory, trailing tiles
-// cut along K); few rows (decode) on gemm_bf16_dl_kernel's narrow tiles, or cut along K on the large
+// cut along K); few rows (decode) on gemm_bf16_few_kernel's narrow tiles, or cut along K on the large
 // ones where a contraction is ragged or the columns are few; one and two rows, and up to four into few
 // columns, on the matrix-vector kernel gemm_bf16_rows_kernel; what none of them takes on the
 // register-staged gemm_bf16_kernel.  XCD-aware + grouped tile order everywhere, so that the tiles
@@ -210,17 +210,15 @@ __global__ __launch_bounds__(WGM *WGN * 64) void gemm_bf16_kernel(GemmBatch args
     }
 }
 
-// ---- bf16, direct-to-LDS variant ---------------------------------------------------------------
-// Same tiling and MFMA fragments as above, but the operand tiles go from global memory straight
-// into LDS (global_load_lds_dwordx4: lane i's 16 bytes land at M0 + 16*i, no VGPR round trip)
-// through a ring of STAGES tiles, so that STAGES-1 K tiles are in flight while one is consumed:
-// HBM latency under load is longer than one K tile's worth of MFMA work.  LDS rows are unpadded
-// (the DMA writes 1 KiB contiguous per wave instruction); bank conflicts of the 128-bit
-// fragment reads are avoided by an XOR swizzle of the 16-byte chunk index with the row's
-// 256-byte bank-row number, applied on the global-address side of the copy.
+// ---- bf16, direct to LDS ------------------------------------------------------------------------
+// Operand tiles go from global memory straight into LDS (global_load_lds_dwordx4: lane i's 16 bytes
+// land at M0 + 16*i, no VGPR round trip) through a ring, so that several K tiles are in flight while
+// one is consumed.  LDS rows are unpadded (the DMA writes 1 KiB contiguous per wave instruction); bank
+// conflicts of the 128-bit fragment reads are avoided by an XOR swizzle of the 16-byte chunk index with
+// the row's 256-byte bank-row number, applied on the global-address side of the copy.
 // The loads and their s_waitcnt are inline asm: the compiler's own bookkeeping would wait for
 // all outstanding LDS DMA before every LDS read and collapse the ring to depth one.
-// Requires every K_s % BK == 0 and operands below 4 GiB (32-bit lane offsets).
+// Requires operands below 4 GiB (32-bit lane offsets).
 __device__ __forceinline__ void dma16(uint32_t voff, const void *sbase, uint32_t lds_addr) {
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                :
@@ -245,97 +243,93 @@ __device__ __forceinline__ const void *uniform_ptr(const void *p) {
   return reinterpret_cast<const void *>(((uint64_t)hi << 32) | lo);
 }
 
-// NT: the B operand (the weights, of which every column tile reads its own rows) is copied streaming.
-template <int BM, int BN, int BK, int STAGES, int WGM, int WGN, bool NT>
-__global__ __launch_bounds__(WGM *WGN * 64) void gemm_bf16_dl_kernel(GemmBatch args) {
-  constexpr int NW = WGM * WGN;
-  constexpr int ROWB = BK * 2;            // bytes per tile row in LDS
-  constexpr int CPR = BK / 8;             // 16-byte chunks per row
-  constexpr int RPI = 64 / CPR;           // rows covered by one wave-wide DMA instruction
-  constexpr int RPB = 256 / ROWB;         // rows per 256-byte bank row
-  constexpr int IA = BM / RPI / NW, IB = BN / RPI / NW;   // DMA instructions per wave per tile
-  constexpr int IPW = IA + IB;
-  constexpr int STAGE_BYTES = (BM + BN) * ROWB;
-  constexpr int TM = BM / WGM, TN = BN / WGN, MI = TM / 32, NI = TN / 32, KS = BK / 16;
-  static_assert(BM % (RPI * NW) == 0 && BN % (RPI * NW) == 0, "tile/waves mismatch");
-  static_assert((STAGES - 2) * IPW < 64 && STAGES >= 2, "ring depth");
+// ---- bf16, few rows: one row tile, narrow column tiles -------------------------------------------
+// Up to 128 rows (decode): bound by streaming the weights once.  One tile holds all rows (BM = 32, 64 or
+// 128) and BN weight rows, four waves two by two, MFMA 16x16x32, a ring of four 64-wide K tiles.  What
+// sets the rate is how many times the activations go through the L2s beside the weights (once per
+// column tile: with 64-column tiles as much as the weights themselves) and how many CUs stream: the
+// tiles are as wide as still leaves one for nearly every CU (few_width below).  64 tokens of the
+// 7B block, gate and up projections: 349 tiles of 64 columns 44.6 us, 177 of 128 37.4, 233 of 96 36.0
+// (5.0 TB/s); a token's own matrix-vector kernel, which has no second operand to fetch, 31.7.  Without
+// effect there: rings of 4 to 9 tiles, K tiles of 128.
+// Requires whole K tiles.
+template <int MAX, int PER> __device__ __forceinline__ void wait_tiles(int n) {   // all but min(n, MAX) groups
+  if constexpr (MAX == 0) {
+    wait_vmcnt<0>();
+  } else {
+    if (n >= MAX) wait_vmcnt<MAX * PER>();
+    else wait_tiles<MAX - 1, PER>(n);
+  }
+}
+struct FewPlan {
+  int nprob, streaming;              // streaming: the weights (B, read once by this launch) bypass the caches
+  int start[GEMM_MAX_PROBLEMS];      // first block of every problem
+};
+
+template <int BM, int BN, int STAGES>
+__global__ __launch_bounds__(256) void gemm_bf16_few_kernel(GemmBatch args, FewPlan plan) {
+  constexpr int BK = 64, ROWB = BK * 2;
+  constexpr int IA = BM / 32, IB = BN / 32, IPW = IA + IB;   // 1 KiB pieces (8 rows) per wave and K tile
+  constexpr int STAGE = (BM + BN) * ROWB;
+  constexpr int TM = BM / 2, TN = BN / 2, MI = TM / 16, NI = TN / 16;
+  static_assert(BM % 32 == 0 && BN % 32 == 0 && STAGES >= 2 && (STAGES - 2) * IPW < 64, "tile shape");
 
   extern __shared__ __align__(16) unsigned char smem[];
   const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) unsigned char *)smem;
+  int pi = 0;
+  while (pi + 1 < plan.nprob && plan.start[pi + 1] <= (int)blockIdx.x) pi++;
+  const GemmProblem &P = args.p[pi];
+  const int M = P.M, N = P.N, col0 = ((int)blockIdx.x - plan.start[pi]) * BN;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
 
-  const GemmProblem &P = args.p[blockIdx.z];
-  const int M = P.M, N = P.N;
-  const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
-  if ((int)blockIdx.x >= tiles_m * tiles_n) return;   // problems of one launch may differ in N
-  int tm, tn;
-  tile_of_block(blockIdx.x, tiles_m, tiles_n, tm, tn);
-  const int row0 = tm * BM, col0 = tn * BN;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave / WGN, wn = wave % WGN;
-
-  f32x16_t acc[MI][NI];
+  f32x4_t acc[MI][NI];
 #pragma unroll
   for (int i = 0; i < MI; i++)
 #pragma unroll
-    for (int j = 0; j < NI; j++)
-#pragma unroll
-      for (int e = 0; e < 16; e++) acc[i][j][e] = 0.f;
+    for (int j = 0; j < NI; j++) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-  // --- producer side: per-lane byte offsets of this wave's DMA instructions -----------------
-  const int lrow = lane / CPR, lpos = lane % CPR;
+  const int lrow = lane >> 3, lpos = lane & 7;
   uint32_t offA[IA], offB[IB];
   const unsigned char *baseA = nullptr, *baseB = nullptr;
-  int Kcur = 0;
-  auto setup = [&](int sgi) {
-    const GemmSeg &S = P.seg[sgi];
+  int seg = 0, k0 = 0, Kcur = 0, issued = 0, total = 0;
+  for (int sgi = 0; sgi < P.nseg; sgi++) total += P.seg[sgi].K / BK;
+  auto setup = [&]() {
+    const GemmSeg &S = P.seg[seg];
 #pragma unroll
     for (int j = 0; j < IA; j++) {
-      const int rt = (wave * IA + j) * RPI + lrow;        // row within the tile
-      const int kc = lpos ^ ((rt / RPB) % CPR);
-      int r = row0 + rt;
-      r = r < M ? r : M - 1;
-      offA[j] = (uint32_t)r * (uint32_t)S.lda * 2u + kc * 16;
+      const int q = (wave + 4 * j) * 8 + lrow, rr = q < M ? q : M - 1;
+      offA[j] = (uint32_t)rr * (uint32_t)S.lda * 2u + (lpos ^ ((q >> 1) & 7)) * 16;
     }
 #pragma unroll
     for (int j = 0; j < IB; j++) {
-      const int rt = (wave * IB + j) * RPI + lrow;
-      const int kc = lpos ^ ((rt / RPB) % CPR);
-      int c = col0 + rt;
-      c = c < N ? c : N - 1;
-      offB[j] = (uint32_t)c * (uint32_t)S.ldb * 2u + kc * 16;
+      const int q = (wave + 4 * j) * 8 + lrow, c = col0 + q < N ? col0 + q : N - 1;
+      offB[j] = (uint32_t)c * (uint32_t)S.ldb * 2u + (lpos ^ ((q >> 1) & 7)) * 16;
     }
     baseA = reinterpret_cast<const unsigned char *>(S.A);
     baseB = reinterpret_cast<const unsigned char *>(S.B);
     Kcur = S.K;
   };
-  auto issue = [&](int k0, int stage) {
-    const void *ga = uniform_ptr(baseA + (size_t)k0 * 2);
-    const void *gb = uniform_ptr(baseB + (size_t)k0 * 2);
-    const uint32_t la = lds0 + stage * STAGE_BYTES + wave * IA * 1024;
-    const uint32_t lb = lds0 + stage * STAGE_BYTES + BM * ROWB + wave * IB * 1024;
-#pragma unroll
-    for (int j = 0; j < IA; j++) dma16(offA[j], ga, la + j * 1024);
-#pragma unroll
-    for (int j = 0; j < IB; j++) {
-      if constexpr (NT) dma16_nt(offB[j], gb, lb + j * 1024);
-      else dma16(offB[j], gb, lb + j * 1024);
-    }
-  };
-
-  int total_tiles = 0;
-  for (int sgi = 0; sgi < P.nseg; sgi++) total_tiles += P.seg[sgi].K / BK;
-
-  int seg = 0, k0 = 0, issued = 0;
-  setup(0);
-  auto issue_next = [&]() {   // issue tile number `issued` (if any) into its ring slot
-    if (issued < total_tiles) {
+  setup();
+  auto issue_next = [&]() {   // copies of tile number `issued` (if there is one) into its ring slot
+    if (issued < total) {
       if (k0 >= Kcur) {
         seg++;
-        setup(seg);
+        setup();
         k0 = 0;
       }
-      issue(k0, issued % STAGES);
+      const void *ga = uniform_ptr(baseA + (size_t)k0 * 2), *gb = uniform_ptr(baseB + (size_t)k0 * 2);
+      const uint32_t la = lds0 + (issued % STAGES) * STAGE + wave * 1024, lb = la + BM * ROWB;
+#pragma unroll
+      for (int j = 0; j < IA; j++) dma16(offA[j], ga, la + j * 4096);
+      if (plan.streaming) {
+#pragma unroll
+        for (int j = 0; j < IB; j++) dma16_nt(offB[j], gb, lb + j * 4096);
+      } else {
+#pragma unroll
+        for (int j = 0; j < IB; j++) dma16(offB[j], gb, lb + j * 4096);
+      }
       k0 += BK;
     }
     issued++;
@@ -343,123 +337,55 @@ __global__ __launch_bounds__(WGM *WGN * 64) void gemm_bf16_dl_kernel(GemmBatch a
 #pragma unroll
   for (int s0 = 0; s0 < STAGES - 1; s0++) issue_next();
 
-  // --- consumer side: swizzled fragment addresses -------------------------------------------
-  const int l31 = lane & 31, hi = lane >> 5;
-  const int swz = (l31 / RPB) % CPR;
-  int koff[KS];
-#pragma unroll
-  for (int ks = 0; ks < KS; ks++) koff[ks] = ((ks * 2 + hi) ^ swz) * 16;
-  const unsigned char *a_rd = smem + (wm * TM + l31) * ROWB;
-  const unsigned char *b_rd = smem + BM * ROWB + (wn * TN + l31) * ROWB;
-
-  auto wait_tile = [&](int it) {
-    // tiles it+1 .. min(it+STAGES-2, last) may stay in flight; tile `it` must have landed
-    const int newer = total_tiles - 1 - it;
-    if (newer >= STAGES - 2) wait_vmcnt<(STAGES - 2) * IPW>();
-    else if (STAGES > 3 && newer == 1) wait_vmcnt<IPW>();
-    else if (STAGES > 4 && newer == 2) wait_vmcnt<2 * IPW>();
-    else wait_vmcnt<0>();
-  };
-  for (int it = 0; it < total_tiles; it++) {
-    wait_tile(it);
+  const int l15 = lane & 15, hi = lane >> 4;
+  const int koff[2] = {(hi ^ (l15 >> 1)) * 16, ((4 + hi) ^ (l15 >> 1)) * 16};   // swizzled chunks
+  const unsigned char *a_rd = smem + (wm * TM + l15) * ROWB;
+  const unsigned char *b_rd = smem + BM * ROWB + (wn * TN + l15) * ROWB;
+  for (int it = 0; it < total; it++) {
+    wait_tiles<STAGES - 2, IPW>(total - 1 - it);   // tile `it` has landed, up to STAGES - 2 newer ones fly on
     __syncthreads();
     issue_next();   // refills the slot that tile it-1 occupied: every wave is past reading it
-    const int st = it % STAGES;
-    const unsigned char *a = a_rd + st * STAGE_BYTES;
-    const unsigned char *b = b_rd + st * STAGE_BYTES;
+    const int st = (it % STAGES) * STAGE;
 #pragma unroll
-    for (int ks = 0; ks < KS; ks++) {
-      bf16x8_t af[MI], bfr[NI];
+    for (int ks = 0; ks < 2; ks++) {
+      bf16x8_t fa[MI], fb[NI];
 #pragma unroll
       for (int i = 0; i < MI; i++)
-        af[i] = *reinterpret_cast<const bf16x8_t *>(a + i * 32 * ROWB + koff[ks]);
+        fa[i] = *reinterpret_cast<const bf16x8_t *>(a_rd + st + i * 16 * ROWB + koff[ks]);
 #pragma unroll
       for (int j = 0; j < NI; j++)
-        bfr[j] = *reinterpret_cast<const bf16x8_t *>(b + j * 32 * ROWB + koff[ks]);
+        fb[j] = *reinterpret_cast<const bf16x8_t *>(b_rd + st + j * 16 * ROWB + koff[ks]);
 #pragma unroll
       for (int i = 0; i < MI; i++)
 #pragma unroll
         for (int j = 0; j < NI; j++)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[j], af[i], acc[i][j], 0, 0, 0);
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j], fa[i], acc[i][j], 0, 0, 0);
     }
   }
-
-  const int cbase = col0 + wn * TN + hi * 4;
-  const int rbase = row0 + wm * TM + l31;
-  auto store_all = [&](auto *C) {
+  // a lane holds 4 consecutive columns of a row
+  auto store = [&](auto *C) {
     typedef typename std::remove_pointer<decltype(C)>::type OutT;
+    const bool whole = (P.ldc & 3) == 0 && (reinterpret_cast<uintptr_t>(C) & 15) == 0;
 #pragma unroll
     for (int i = 0; i < MI; i++) {
-      const int r = rbase + i * 32;
-      if (r < M) {
+      const int r = wm * TM + i * 16 + l15;
+      if (r >= M) continue;
 #pragma unroll
-        for (int j = 0; j < NI; j++)
+      for (int j = 0; j < NI; j++) {
+        const int c = col0 + wn * TN + j * 16 + hi * 4;
+        OutT *o = C + (int64_t)r * P.ldc + c;
+        if (whole && c + 4 <= N) {
+          store_c4<OutT>(o, acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
+        } else {
 #pragma unroll
-          for (int g = 0; g < 4; g++) {
-            const int c = cbase + j * 32 + g * 8;
-            OutT *o = C + (int64_t)r * P.ldc + c;
-            if (c + 3 < N && (P.ldc & 3) == 0) {
-              store_c4<OutT>(o, acc[i][j][g * 4], acc[i][j][g * 4 + 1], acc[i][j][g * 4 + 2],
-                             acc[i][j][g * 4 + 3]);
-            } else {
-#pragma unroll
-              for (int m = 0; m < 4; m++)
-                if (c + m < N) store_c<OutT>(o + m, acc[i][j][g * 4 + m]);
-            }
-          }
-      }
-    }
-  };
-  // Outputs whose rows are whole 16-byte pieces: the accumulators go through a per-wave LDS tile
-  // (32 rows x TN columns, padded pitch; the ring is free by now) so that every global store is
-  // 16 bytes per lane and a whole row segment of the wave tile per group of lanes, instead of
-  // short pieces of 32 different rows.  LDS operations of one wave execute in order, so the
-  // tile needs no workgroup barrier after the first one.
-  auto store_rows = [&](auto *C) {
-    typedef typename std::remove_pointer<decltype(C)>::type OutT;
-    constexpr int PER = 16 / (int)sizeof(OutT);     // elements per 16-byte piece
-    constexpr int EP = TN + PER;                    // tile pitch in elements
-    constexpr int CPW = TN / PER, RPW = 64 / CPW;   // pieces per row, rows per instruction
-    static_assert(NW * 32 * EP * (int)sizeof(OutT) <= STAGES * STAGE_BYTES, "epilogue tiles fit in the ring");
-    static_assert(CPW <= 64 && 32 % RPW == 0, "lane mapping of the row-major stores");
-    typedef OutT out4_t __attribute__((ext_vector_type(4)));
-    typedef OutT outp_t __attribute__((ext_vector_type(PER)));
-    __syncthreads();   // every wave has finished reading the last ring slot
-    OutT *tile = reinterpret_cast<OutT *>(smem) + wave * 32 * EP;
-    const int rr = lane / CPW, cc = lane % CPW;
-    const int c = col0 + wn * TN + cc * PER;
-#pragma unroll
-    for (int i = 0; i < MI; i++) {
-#pragma unroll
-      for (int j = 0; j < NI; j++)
-#pragma unroll
-        for (int g = 0; g < 4; g++) {
-          out4_t v;
-#pragma unroll
-          for (int m = 0; m < 4; m++) v[m] = (OutT)acc[i][j][g * 4 + m];
-          *reinterpret_cast<out4_t *>(tile + l31 * EP + j * 32 + g * 8 + hi * 4) = v;
+          for (int m = 0; m < 4; m++)
+            if (c + m < N) store_c<OutT>(o + m, acc[i][j][m]);
         }
-      __builtin_amdgcn_wave_barrier();
-#pragma unroll
-      for (int p = 0; p < 32 / RPW; p++) {
-        const int rl = p * RPW + rr;
-        const int r = row0 + wm * TM + i * 32 + rl;
-        const outp_t v = *reinterpret_cast<const outp_t *>(tile + rl * EP + cc * PER);
-        // streaming (non-temporal) stores: an output tile is never read again by this launch,
-        // so it should not displace the operand tiles that other workgroups re-read from L2
-        if (r < M && c < N) __builtin_nontemporal_store(v, reinterpret_cast<outp_t *>(C + (int64_t)r * P.ldc + c));
       }
-      __builtin_amdgcn_wave_barrier();
     }
   };
-  const int per = P.c_f32 ? 4 : 8;
-  if ((N % per) == 0 && (P.ldc % per) == 0 && (reinterpret_cast<uintptr_t>(P.C) & 15) == 0) {
-    if (P.c_f32) store_rows(reinterpret_cast<float *>(P.C));
-    else store_rows(reinterpret_cast<bf16_t *>(P.C));
-    return;
-  }
-  if (P.c_f32) store_all(reinterpret_cast<float *>(P.C));
-  else store_all(reinterpret_cast<bf16_t *>(P.C));
+  if (P.c_f32) store(reinterpret_cast<float *>(P.C));
+  else store(reinterpret_cast<bf16_t *>(P.C));
 }
 
 // ---- bf16, large tiles: two wave groups in turns -------------------------------------------------
@@ -1054,28 +980,6 @@ static hipError_t launch_bf16(const GemmBatch &b, int nprob, hipStream_t st) {
   return hipGetLastError();
 }
 
-template <int BM, int BN, int BK, int STAGES, int WGM, int WGN, bool NT>
-static hipError_t launch_bf16_dl(const GemmBatch &b, int nprob, hipStream_t st) {
-  constexpr size_t smem = (size_t)STAGES * (BM + BN) * BK * sizeof(bf16_t);
-  auto kern = gemm_bf16_dl_kernel<BM, BN, BK, STAGES, WGM, WGN, NT>;
-  static bool attr_set = false;
-  if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
-  int tiles = 0;
-  for (int i = 0; i < nprob; i++) {
-    const int t = ((b.p[i].M + BM - 1) / BM) * ((b.p[i].N + BN - 1) / BN);
-    tiles = t > tiles ? t : tiles;
-  }
-  const int slot = prof_on() ? prof_mark_begin(batch_kind(b, nprob), st) : -1;
-  hipLaunchKernelGGL(kern, dim3(tiles, 1, nprob), dim3(WGM * WGN * 64), smem, st, b);
-  mark_end(slot, b, nprob, st);
-  return hipGetLastError();
-}
-
 // bytes of a launch's B operands
 static double b_bytes(const GemmBatch &b, int nprob) {
   double by = 0.0;
@@ -1084,6 +988,59 @@ static double b_bytes(const GemmBatch &b, int nprob) {
   return by;
 }
 constexpr double STREAM_BYTES = 64.0 * 1024 * 1024;
+
+template <int BM, int BN, int STAGES>
+static hipError_t launch_few(const GemmBatch &b, int nprob, bool streaming, hipStream_t st) {
+  constexpr size_t smem = (size_t)STAGES * (BM + BN) * 128;
+  auto kern = gemm_bf16_few_kernel<BM, BN, STAGES>;
+  static bool attr_set = false;
+  if (!attr_set) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    if (e != hipSuccess) return e;
+    attr_set = true;
+  }
+  FewPlan plan{};
+  plan.nprob = nprob;
+  plan.streaming = streaming;
+  int at = 0;
+  for (int i = 0; i < nprob; i++) {
+    plan.start[i] = at;
+    at += (b.p[i].N + BN - 1) / BN;
+  }
+  const int slot = prof_on() ? prof_mark_begin(batch_kind(b, nprob), st) : -1;
+  hipLaunchKernelGGL(kern, dim3(at), dim3(256), smem, st, b, plan);
+  mark_end(slot, b, nprob, st);
+  return hipGetLastError();
+}
+
+template <int BM>
+static hipError_t launch_few_w(const GemmBatch &b, int nprob, int width, bool streaming, hipStream_t st) {
+  switch (width) {
+    case 32: return launch_few<BM, 32, 4>(b, nprob, streaming, st);
+    case 64: return launch_few<BM, 64, 4>(b, nprob, streaming, st);
+    case 96: return launch_few<BM, 96, 4>(b, nprob, streaming, st);
+    default: return launch_few<BM, 128, 4>(b, nprob, streaming, st);
+  }
+}
+
+// Column width of the tiles of a few-rows launch: the one with the least columns per CU, the widest of
+// equals.  Whole forwards, against 64 always: 64 tokens of the 7B block 92.9 -> 84.0 us, 128 of the 13B
+// block 157.9 -> 137.0, 128 of a 1024 x 2752 one 41.5 -> 38.6 (32 columns; 41.0 with 64 at least).
+static int few_width(const GemmBatch &b, int nprob) {
+  int best = 64, cost = 1 << 30;
+  const int widths[4] = {128, 96, 64, 32};
+  for (int w : widths) {
+    int tiles = 0;
+    for (int i = 0; i < nprob; i++) tiles += (b.p[i].N + w - 1) / w;
+    const int c = (tiles + 255) / 256 * w;
+    if (c < cost) {
+      cost = c;
+      best = w;
+    }
+  }
+  return best;
+}
 
 // The direct-to-LDS kernels need 32-bit operand offsets, and (the narrow-tile one) whole K tiles.
 static bool dl_eligible(const GemmBatch &b, int nprob, int BK) {
@@ -1315,17 +1272,15 @@ hipError_t launch_gemm(int dtype, const GemmProblem *probs, int nprob, hipStream
   }
   if (dtype == MIXLORA_BF16 && M <= 128 && any_big && dl_eligible(b, nprob, 64)) {
     // few rows (decode-shaped calls): the launch is bound by streaming the weights once, so the
-    // tiles are narrow (64 output columns: enough workgroups to cover the chip) and the ring is
-    // deep (4 K tiles in flight per workgroup, 2 workgroups per CU)
+    // tiles are narrow enough to cover the chip
     // Weights of 64 MiB or more are streamed past the caches: the last level (256 MiB) would not hold
     // them until the next pass anyway, and reading them costs less without the attempt (64 tokens of
-    // the 7B block 98.5 -> 93.4 us, 16 tokens 86.5 -> 80.4).  Smaller ones may still be there
-    // (52 MB: 40.6 us cached, 44.4 streamed).
-    if (b_bytes(b, nprob) >= STREAM_BYTES)
-      return M <= 64 ? launch_bf16_dl<64, 64, 64, 4, 1, 2, true>(l, nl, st)
-                     : launch_bf16_dl<128, 64, 64, 4, 2, 2, true>(l, nl, st);
-    return M <= 64 ? launch_bf16_dl<64, 64, 64, 4, 1, 2, false>(l, nl, st)
-                   : launch_bf16_dl<128, 64, 64, 4, 2, 2, false>(l, nl, st);
+    // the 7B block 91.1 -> 84.0 us, 12 tokens 81.9 -> 75.0).  Smaller ones may still be there
+    // (52 MB, with an earlier kernel: 40.6 us cached, 44.4 streamed).
+    const bool nt = b_bytes(b, nprob) >= STREAM_BYTES;
+    const int w = few_width(b, nprob);
+    if (M <= 32) return launch_few_w<32>(l, nl, w, nt, st);
+    return M <= 64 ? launch_few_w<64>(l, nl, w, nt, st) : launch_few_w<128>(l, nl, w, nt, st);
   }
   if (!uniform || nprob > 2) {   // the generic kernels take uniform batches of at most two
     for (int i = 0; i < nprob; i++) {

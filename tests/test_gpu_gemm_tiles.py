@@ -76,6 +76,23 @@ def test_few_rows_match_oracle(shape):
     pu.compare_all(m.results(), orc.forward(host["x"], W, cfg.k, cfg.lora_scale, cfg.aux_coeff, "top1"), None, cfg)
 
 
+# few-rows tiles: row counts on both sides of 32 and 64, and column counts that take 32-, 64-, 96- and
+# 128-column tiles in the gate/up launch, whole and cut at the last one
+@pytest.mark.parametrize("shape", [(3, 256, 1408, 8), (32, 256, 5504, 8), (33, 256, 11008, 8), (64, 256, 13824, 8),
+                                   (65, 256, 1408, 8), (100, 256, 11008, 8), (128, 256, 13888, 8)],
+                         ids=lambda s: "T%d_d%d_f%d_N%d" % s)
+def test_few_rows_tile_widths_match_oracle(shape):
+    T, d, f, N = shape
+    cfg = synth.scaled(synth.CONFIGS["llama2_7b_decode"], name="widths", T=T, d=d, d_ff=f, N=N)
+    print(f"case T={T} d={d} f={f} N={N}", flush=True)
+    host = synth.make_inputs(cfg)
+    m = MixLoraFFN(cfg, host, with_backward=False)
+    m.workspace.fill_(0xFF)
+    m.forward()
+    W = {n: host[n] for n in synth.WEIGHT_NAMES}
+    pu.compare_all(m.results(), orc.forward(host["x"], W, cfg.k, cfg.lora_scale, cfg.aux_coeff, "top1"), None, cfg)
+
+
 def test_repeated_passes_are_bit_identical():
     """Slices are added in a fixed order."""
     cfg = synth.scaled(synth.CONFIGS["llama2_7b"], name="tiles_rerun", T=300, d=1024, d_ff=2744)
