@@ -32,6 +32,7 @@ struct Layout {
   size_t G, U, Pg_all, Pu_all, a_grp, Q_all;
   // forward scratch
   size_t a_comb, Qw, Bd_cat, rank_part, splitk, gp_scratch, gemm_part;
+  bool few;   // the few-token stage of csrc/fused_few.hip runs (its partial sums are rank_part)
   size_t gemm_floats;   // floats at gemm_part: partial tiles of GEMM launches cut along K
   size_t joint_floats;  // those that the default schedule would have
   size_t base_end;      // forward workspace without them
@@ -76,11 +77,35 @@ inline bool whole_k_tiles(const mixlora_dims &D) {
   return D.d % 64 == 0 && D.d_ff % 64 == 0 && (D.N * pad_rank(D.r)) % 64 == 0;
 }
 
+// K slices of the down projection of few tokens (whole 64-wide K tiles), one problem each: the d output
+// columns alone give too few tiles to stream W_down at full rate.
+struct DownSlices {
+  int n, chunk;
+};
+inline DownSlices down_slices(int d, int f) {
+  const int tiles_n = (d + 63) / 64, ktiles = (f + 63) / 64;
+  int S = 256 / tiles_n;
+  S = S < 1 ? 1 : (S > GEMM_MAX_PROBLEMS ? GEMM_MAX_PROBLEMS : S);
+  S = S > ktiles ? ktiles : S;
+  const int chunk = ((ktiles + S - 1) / S) * 64;
+  return DownSlices{(f + chunk - 1) / chunk, chunk};
+}
+
+// Whether a forward pass can take the few-token stage: what its tables hold, and a down projection that
+// takes the rank-r term afterwards (K slices) or in its own launch (one and two tokens).
+inline bool few_shapes(const mixlora_dims &D, int schedule, bool dora) {
+  const int r = pad_rank(D.r);
+  if (D.dtype != MIXLORA_BF16 || schedule != MIXLORA_SCHEDULE_LINEAR_DOWN || dora) return false;
+  if (!few_pairs_ok(D.T, D.N, D.k, r)) return false;
+  if (gemm_rows_ok(D.dtype, D.T, D.d_ff + D.N * r)) return gemm_rows_rank_ok(D.dtype, D.T, D.d_ff);
+  return D.d % 64 == 0 && gemm_few_rank_ok(D.dtype, D.T, D.d, D.d_ff);
+}
+
 // Buffers a schedule does not use get size 0 (per-token G, U in the unshared schedule, the
 // combined activations where the down projection runs per pair, ...).
-Layout make_layout(const mixlora_dims &D, int schedule = MIXLORA_SCHEDULE_LINEAR_DOWN,
-                   bool dora = false) {
+Layout make_layout_as(const mixlora_dims &D, int schedule, bool dora, bool few) {
   Layout L{};
+  L.few = few;
   const bool pair_down = schedule != MIXLORA_SCHEDULE_LINEAR_DOWN;
   const bool vanilla = schedule == MIXLORA_SCHEDULE_VANILLA;
   const size_t T = D.T, d = D.d, f = D.d_ff, N = D.N, k = D.k, r = pad_rank(D.r);
@@ -133,10 +158,12 @@ Layout make_layout(const mixlora_dims &D, int schedule = MIXLORA_SCHEDULE_LINEAR
   L.Bd_cat = take(d * R * E);
   {   // per-split rank-r partial sums (two banks), for the grouped and the token-major stages
     const size_t sp_g = (size_t)fused_splits((int)f, (int)kT), sp_t = (size_t)fused_pg_splits((int)f, (int)T, (int)(N <= PG_MAX_EXPERTS ? N : 1));
-    L.rank_part = take(2 * (sp_g > sp_t ? sp_g : sp_t) * kT * r * 4);
+    const size_t grouped = 2 * (sp_g > sp_t ? sp_g : sp_t) * kT * r * 4;
+    const size_t cols = few ? up(few_part_floats((int)f, (int)kT, (int)r) * 4) + T * FEW_RANK_SUMS * 4 : 0;
+    L.rank_part = take(cols > grouped ? cols : grouped);
   }
   // few tokens (decode-shaped calls): partial outputs of the K-split down projection
-  L.splitk = take(T <= SPLITK_MAX_ROWS ? (size_t)GEMM_MAX_PROBLEMS * T * d * 4 : 0);
+  L.splitk = take(T <= SPLITK_MAX_ROWS ? (size_t)(few ? down_slices((int)d, (int)f).n : GEMM_MAX_PROBLEMS) * T * d * 4 : 0);
   L.gp_scratch = take(kT > GROUP_SINGLE_WG_PAIRS ? group_pairs_scratch_bytes((int)T, (int)k) : 0);
   L.Kx = up64((int)(2 * R) + (int)N);   // whole K tiles of the GEMM's DMA path
   {   // scratch of both passes' GEMM launches: at most one partial tile per CU, none where no K range is long
@@ -202,6 +229,20 @@ Layout make_layout(const mixlora_dims &D, int schedule = MIXLORA_SCHEDULE_LINEAR
                              : group_outer_partial_floats(1, (int)N, (int)d, (int)T));
   L.partials = take(L.partial_floats * 4);
   L.bwd_end = o;
+  return L;
+}
+
+// The few-token stage keeps a partial sum per column block, the grouped stages one per split: where only
+// the latter's workspace fits the library's own array, they run (the layout and with it the path depend on the
+// dims alone, whichever entry point is called).
+Layout make_layout(const mixlora_dims &D, int schedule = MIXLORA_SCHEDULE_LINEAR_DOWN,
+                   bool dora = false) {
+  const bool few = few_shapes(D, schedule, dora);
+  const Layout L = make_layout_as(D, schedule, dora, few);
+  if (few && L.base_end > (size_t)MIXLORA_STATIC_SCRATCH_BYTES) {
+    const Layout G = make_layout_as(D, schedule, dora, false);
+    if (G.base_end <= (size_t)MIXLORA_STATIC_SCRATCH_BYTES) return G;
+  }
   return L;
 }
 
@@ -413,6 +454,48 @@ static int forward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mod
     dargs.cg = (float *)(ws + L.c_g);
     dargs.cu = (float *)(ws + L.c_u);
   }
+  if (L.few) {
+    // few tokens: routing, grouping, Eq. 8-9, the per-pair stage and the weighted combination in one
+    // launch; the rank-r term of the down projection joins where its K slices are added
+    FewStage fs{};
+    fs.Z = (const float *)(ws + L.Z);
+    fs.token_model = token_model;
+    fs.T = T, fs.N = N, fs.Nl = Nl, fs.k = k, fs.r = r, fs.f = f;
+    fs.s = D.lora_scale, fs.coeff = D.aux_coeff, fs.mode = D.aux_mode;
+    fs.G = (const bf16_t *)(ws + L.G), fs.U = (const bf16_t *)(ws + L.U);
+    fs.B_gate = (const bf16_t *)w->B_gate, fs.B_up = (const bf16_t *)w->B_up, fs.A_down = (const bf16_t *)w->A_down;
+    fs.Pg_all = (const float *)(ws + L.Pg_all), fs.Pu_all = (const float *)(ws + L.Pu_all);
+    fs.a_comb = (bf16_t *)(ws + L.a_comb);
+    fs.a_grp = workspace_bytes >= L.bwd_end ? (bf16_t *)(ws + L.a_grp) : nullptr;
+    fs.Q_part = (float *)(ws + L.rank_part);
+    fs.probs = probs, fs.w_out = topk_w, fs.w_ws = wts, fs.loss = aux_loss;
+    fs.F = (float *)(ws + L.F), fs.P = (float *)(ws + L.P);
+    fs.idx_out = topk_idx, fs.idx_ws = idx, fs.counts = (int32_t *)(ws + L.counts), fs.counts_out = expert_counts;
+    fs.first_counts = (int32_t *)(ws + L.first_counts), fs.offs = offs, fs.row_of_pair = row_of_pair;
+    fs.pair_of_row = pair_of_row, fs.tok_offs = (int32_t *)(ws + L.tok_offs);
+    fs.model_tokens = (int32_t *)(ws + L.model_tokens);
+    HIP_TRY_AS(PROF_FUSED_FWD, 3.0 * T * f * Eb, launch_few_stage(fs, st));
+    const FewRank rk{(const float *)(ws + L.rank_part), wts, idx, row_of_pair, (const bf16_t *)w->B_down,
+                     (float *)(ws + L.Q_all), (float *)(ws + L.rank_part + up(few_part_floats(f, kT, r) * 4)),
+                     T, N, k, r, few_column_blocks(f), D.lora_scale};
+    if (gemm_rows_ok(dt, T, f + R)) {
+      GemmProblem p = problem(T, d, y, d, 0);
+      add_seg(p, ws + L.a_comb, f, w->W_down, f, f);
+      HIP_TRY(launch_gemm_rows_rank(p, rk, st));
+      return MIXLORA_OK;
+    }
+    const DownSlices sl = down_slices(d, f);
+    GemmProblem p[GEMM_MAX_PROBLEMS];
+    float *part = (float *)(ws + L.splitk);
+    for (int i = 0; i < sl.n; i++) {
+      const int k0 = i * sl.chunk, klen = f - k0 < sl.chunk ? f - k0 : sl.chunk;
+      p[i] = problem(T, d, part + (size_t)i * T * d, d, 1);
+      add_seg(p[i], ws + L.a_comb + (size_t)k0 * 2, f, (const char *)w->W_down + (size_t)k0 * 2, f, klen);
+    }
+    HIP_TRY(launch_gemm_few_rank(p, sl.n, rk, st));
+    HIP_TRY_AS(PROF_OTHER, 0, launch_few_finish(rk, part, sl.n, d, y, st));
+    return MIXLORA_OK;
+  }
   // Eq. 7 + Norm (Algorithm 1 lines 4-5)
   // s * B_down packed for the K-extension of the down GEMM; in bf16 also zeros for the
   // block-sparse operand Qw, whose non-zero blocks the fused stage fills in.  In bf16 these
@@ -546,14 +629,9 @@ static int forward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mod
                launch_pair_combine(dt, pc, f, ws + L.a_grp, ws + L.a_comb, 1, st));
   // down projection (Algorithm 1 line 14): y = a_comb W_down^T + Qw (s B_down)^T
   if (dt == MIXLORA_BF16 && (size_t)T <= SPLITK_MAX_ROWS && whole_k_tiles(D) && !gemm_rows_ok(dt, T, f + R)) {
-    // Few rows: the d output columns alone give too few tiles to stream W_down at full rate, so
-    // the K range is cut into S slices (whole 64-wide K tiles), one GEMM problem each with an
-    // fp32 partial output, and the partial outputs are added in slice order.
-    const int tiles_n = (d + 63) / 64, ktiles = (f + 63) / 64;
-    int S = 256 / tiles_n;
-    S = S < 1 ? 1 : (S > GEMM_MAX_PROBLEMS ? GEMM_MAX_PROBLEMS : S);
-    S = S > ktiles ? ktiles : S;
-    const int chunk = ((ktiles + S - 1) / S) * 64;
+    // Few rows: the K range is cut into slices, one GEMM problem each with an fp32 partial output, and
+    // the partial outputs are added in slice order.
+    const int chunk = down_slices(d, f).chunk;
     GemmProblem p[GEMM_MAX_PROBLEMS];
     float *part = (float *)(ws + L.splitk);
     const size_t E = 2;

@@ -80,6 +80,13 @@ struct GemmScratch {
 // that its sums are taken in the same order.
 hipError_t launch_gemm(int dtype, const GemmProblem *probs, int nprob, hipStream_t st,
                        const GemmScratch &scratch = GemmScratch{nullptr, 0}, int only = -1);
+// the row kernel with the rank-r term of the down projection added, for one or two tokens
+struct FewRank;
+// the few-rows kernel over K slices of the down projection, and the rank term's sums in further workgroups
+bool gemm_few_rank_ok(int dtype, int M, int N, int K);
+hipError_t launch_gemm_few_rank(const GemmProblem *probs, int nprob, const FewRank &rank, hipStream_t st);
+bool gemm_rows_rank_ok(int dtype, int M, int K);
+hipError_t launch_gemm_rows_rank(const GemmProblem &p, const FewRank &rank, hipStream_t st);
 // whether products of M rows over a contraction of K go to the row kernel (no need to cut K)
 bool gemm_rows_ok(int dtype, int M, int K);
 // whether problems of different M may share one launch_gemm call
@@ -105,6 +112,70 @@ int prof_mark_begin(int kind, hipStream_t st);            // returns a slot (or 
 void prof_mark_end(int slot, hipStream_t st, double work);
 int prof_end();
 int prof_kind(int kind, double *ms_total, int *launches, double *work_total);
+
+// ---- few tokens (csrc/fused_few.hip; the rank term also in csrc/gemm.hip's row kernel) -----------
+constexpr int FEW_MAX_TOKENS = 128, FEW_MAX_PAIRS = 256, FEW_MAX_EXPERTS = 32, FEW_MAX_K = 4;
+bool few_pairs_ok(int T, int N, int k, int r);
+int few_column_blocks(int f);
+size_t few_part_floats(int f, int kT, int r);   // floats of Q_part
+// Routing from the logits Z, grouping, Eq. 8-9, the per-pair stage, A_down projections (Q_part
+// [column block][grouped row][r]) and the weighted combination; bf16 storage.
+struct FewStage {
+  const float *Z;
+  const int32_t *token_model;
+  int T, N, Nl, k, r, f;
+  float s, coeff;
+  int mode;
+  const bf16_t *G, *U, *B_gate, *B_up, *A_down;
+  const float *Pg_all, *Pu_all;
+  bf16_t *a_comb, *a_grp;   // a_grp may be NULL
+  float *Q_part;
+  float *probs, *w_out, *w_ws, *loss, *F, *P;
+  int32_t *idx_out, *idx_ws, *counts, *counts_out, *first_counts, *offs, *row_of_pair, *pair_of_row, *tok_offs,
+      *model_tokens;
+};
+hipError_t launch_few_stage(const FewStage &a, hipStream_t st);
+// The rank-r term of the down projection from the stage's partial sums; writes Q_all like the other stages.
+struct FewRank {
+  const float *Q_part, *w;
+  const int32_t *idx, *row_of_pair;
+  const bf16_t *B_down;
+  float *Q_all, *sums;   // sums [T][FEW_RANK_SUMS]: s w_j Q_j, few rows' down product only
+  int T, N, k, r, nblk;
+  float s;
+};
+constexpr int FEW_RANK_SUMS = 64;
+hipError_t launch_few_finish(const FewRank &a, const float *part, int S, int d, void *y, hipStream_t st);
+// sq[j r + q] = s w_j Q[row of slot j of token t][q] for all threads of the workgroup (k r <= 64); red and sq are in LDS
+__device__ __forceinline__ void few_rank_sums(const FewRank &a, int t, bool keep, int nthreads, float *red, float *sq) {
+  const int V = a.k * a.r, G = nthreads / V, tid = threadIdx.x;
+  const int v = tid % V, g = tid / V, j = v / a.r, q = v % a.r;
+  const int row = a.row_of_pair[t * a.k + j];
+  if (g < G) {
+    const float *src = a.Q_part + (int64_t)row * a.r + q;
+    const int64_t step = (int64_t)a.T * a.k * a.r;
+    float s = 0.f;
+    constexpr int INFLIGHT = 8;
+    for (int b = g; b < a.nblk; b += INFLIGHT * G) {
+      float x[INFLIGHT];
+#pragma unroll
+      for (int u = 0; u < INFLIGHT; u++) x[u] = src[(b + u * G < a.nblk ? b + u * G : b) * step];
+#pragma unroll
+      for (int u = 0; u < INFLIGHT; u++)
+        if (b + u * G < a.nblk) s += x[u];
+    }
+    red[tid] = s;
+  }
+  __syncthreads();
+  if (tid < V) {
+    float s = 0.f;
+    for (int gg = 0; gg < G; gg++) s += red[gg * V + tid];
+    const int e = a.idx[t * a.k + j];
+    if (keep) a.Q_all[(int64_t)row * a.N * a.r + e * a.r + q] = s;
+    sq[tid] = a.s * a.w[t * a.k + j] * s;
+  }
+  __syncthreads();
+}
 
 // ---- routing -----------------------------------------------------------------------------
 // N experts in all; with several adapters (token_model != NULL) token t is routed among the Nl

@@ -262,12 +262,12 @@ template <int MAX, int PER> __device__ __forceinline__ void wait_tiles(int n) { 
   }
 }
 struct FewPlan {
-  int nprob, streaming;              // streaming: the weights (B, read once by this launch) bypass the caches
+  int nprob, tiles, streaming;       // streaming: the weights (B, read once by this launch) bypass the caches
   int start[GEMM_MAX_PROBLEMS];      // first block of every problem
 };
 
 template <int BM, int BN, int STAGES>
-__global__ __launch_bounds__(256) void gemm_bf16_few_kernel(GemmBatch args, FewPlan plan) {
+__global__ __launch_bounds__(256) void gemm_bf16_few_kernel(GemmBatch args, FewPlan plan, FewRank rk) {
   constexpr int BK = 64, ROWB = BK * 2;
   constexpr int IA = BM / 32, IB = BN / 32, IPW = IA + IB;   // 1 KiB pieces (8 rows) per wave and K tile
   constexpr int STAGE = (BM + BN) * ROWB;
@@ -276,6 +276,13 @@ __global__ __launch_bounds__(256) void gemm_bf16_few_kernel(GemmBatch args, FewP
 
   extern __shared__ __align__(16) unsigned char smem[];
   const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) unsigned char *)smem;
+  if ((int)blockIdx.x >= plan.tiles) {   // behind the tiles: the rank term's sums, a token each
+    float *sq = reinterpret_cast<float *>(smem), *red = sq + FEW_RANK_SUMS;
+    const int t = blockIdx.x - plan.tiles;
+    few_rank_sums(rk, t, true, 256, red, sq);
+    if ((int)threadIdx.x < rk.k * rk.r) rk.sums[t * FEW_RANK_SUMS + threadIdx.x] = sq[threadIdx.x];
+    return;
+  }
   int pi = 0;
   while (pi + 1 < plan.nprob && plan.start[pi + 1] <= (int)blockIdx.x) pi++;
   const GemmProblem &P = args.p[pi];
@@ -764,8 +771,8 @@ __global__ __launch_bounds__(256) void gemm_tail_reduce_kernel(GemmBatch args, G
 constexpr int GEMV_MAX_ROWS = 4;
 constexpr int GEMV_WAVES = 8;
 
-template <int MR, int RN, int UN>
-__global__ __launch_bounds__(GEMV_WAVES * 64) void gemm_bf16_rows_kernel(GemmBatch args) {
+template <int MR, int RN, int UN, bool RANK>
+__global__ __launch_bounds__(GEMV_WAVES * 64) void gemm_bf16_rows_kernel(GemmBatch args, FewRank rk) {
   extern __shared__ __align__(16) unsigned char smem[];
   bf16_t *xs = reinterpret_cast<bf16_t *>(smem);       // [MR][segments of K one after the other]
   const GemmProblem &P = args.p[blockIdx.z];
@@ -788,6 +795,21 @@ __global__ __launch_bounds__(GEMV_WAVES * 64) void gemm_bf16_rows_kernel(GemmBat
   }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int n0 = (blockIdx.x * GEMV_WAVES + wave) * RN;
+  // the rank term: lane j r + q holds B_down[e_j][n][q]; its factor s w_j Q_j[q] is summed into LDS meanwhile
+  float bd[RN][MR];
+  float *sq = reinterpret_cast<float *>(xs + (size_t)MR * Ksum);
+  if constexpr (RANK) {
+    const int v = lane < rk.k * rk.r ? lane : 0;
+#pragma unroll
+    for (int m = 0; m < MR; m++) {
+      const int e = rk.idx[(m < P.M ? m : 0) * rk.k + v / rk.r];
+#pragma unroll
+      for (int i = 0; i < RN; i++)
+        bd[i][m] = (float)rk.B_down[((int64_t)e * N + (n0 + i < N ? n0 + i : N - 1)) * rk.r + v % rk.r];
+    }
+    for (int m = 0; m < P.M; m++)
+      few_rank_sums(rk, m, blockIdx.x == 0, GEMV_WAVES * 64, sq + MR * 64, sq + m * 64);
+  }
   float acc[RN][MR];
 #pragma unroll
   for (int i = 0; i < RN; i++)
@@ -842,6 +864,14 @@ __global__ __launch_bounds__(GEMV_WAVES * 64) void gemm_bf16_rows_kernel(GemmBat
       add(v, k0);
     }
     at += S.K;
+  }
+  if constexpr (RANK) {
+    if (lane < rk.k * rk.r) {
+#pragma unroll
+      for (int i = 0; i < RN; i++)
+#pragma unroll
+        for (int m = 0; m < MR; m++) acc[i][m] = fmaf(sq[(m < P.M ? m : 0) * 64 + lane], bd[i][m], acc[i][m]);
+    }
   }
 #pragma unroll
   for (int i = 0; i < RN; i++)
@@ -990,7 +1020,7 @@ static double b_bytes(const GemmBatch &b, int nprob) {
 constexpr double STREAM_BYTES = 64.0 * 1024 * 1024;
 
 template <int BM, int BN, int STAGES>
-static hipError_t launch_few(const GemmBatch &b, int nprob, bool streaming, hipStream_t st) {
+static hipError_t launch_few(const GemmBatch &b, int nprob, bool streaming, const FewRank &rk, hipStream_t st) {
   constexpr size_t smem = (size_t)STAGES * (BM + BN) * 128;
   auto kern = gemm_bf16_few_kernel<BM, BN, STAGES>;
   static bool attr_set = false;
@@ -1009,19 +1039,28 @@ static hipError_t launch_few(const GemmBatch &b, int nprob, bool streaming, hipS
     at += (b.p[i].N + BN - 1) / BN;
   }
   const int slot = prof_on() ? prof_mark_begin(batch_kind(b, nprob), st) : -1;
-  hipLaunchKernelGGL(kern, dim3(at), dim3(256), smem, st, b, plan);
+  plan.tiles = at;
+  hipLaunchKernelGGL(kern, dim3(at + rk.T), dim3(256), smem, st, b, plan, rk);
   mark_end(slot, b, nprob, st);
   return hipGetLastError();
 }
 
 template <int BM>
-static hipError_t launch_few_w(const GemmBatch &b, int nprob, int width, bool streaming, hipStream_t st) {
+static hipError_t launch_few_w(const GemmBatch &b, int nprob, int width, bool streaming, const FewRank &rk,
+                               hipStream_t st) {
   switch (width) {
-    case 32: return launch_few<BM, 32, 4>(b, nprob, streaming, st);
-    case 64: return launch_few<BM, 64, 4>(b, nprob, streaming, st);
-    case 96: return launch_few<BM, 96, 4>(b, nprob, streaming, st);
-    default: return launch_few<BM, 128, 4>(b, nprob, streaming, st);
+    case 32: return launch_few<BM, 32, 4>(b, nprob, streaming, rk, st);
+    case 64: return launch_few<BM, 64, 4>(b, nprob, streaming, rk, st);
+    case 96: return launch_few<BM, 96, 4>(b, nprob, streaming, rk, st);
+    default: return launch_few<BM, 128, 4>(b, nprob, streaming, rk, st);
   }
+}
+static hipError_t launch_few_m(const GemmBatch &b, int nprob, int width, bool streaming, const FewRank &rk,
+                               hipStream_t st) {
+  const int M = b.p[0].M;
+  if (M <= 32) return launch_few_w<32>(b, nprob, width, streaming, rk, st);
+  return M <= 64 ? launch_few_w<64>(b, nprob, width, streaming, rk, st)
+                 : launch_few_w<128>(b, nprob, width, streaming, rk, st);
 }
 
 // Column width of the tiles of a few-rows launch: the one with the least columns per CU, the widest of
@@ -1173,11 +1212,12 @@ static hipError_t launch_rows(const GemmBatch &b, int nprob, hipStream_t st) {
   const size_t smem = (size_t)mr * kmax * sizeof(bf16_t);
   const dim3 grid((n + GEMV_WAVES * rn - 1) / (GEMV_WAVES * rn), 1, nprob), block(GEMV_WAVES * 64);
   const int slot = prof_on() ? prof_mark_begin(batch_kind(b, nprob), st) : -1;
-  if (mr == 4) hipLaunchKernelGGL((gemm_bf16_rows_kernel<4, 1, 4>), grid, block, smem, st, b);
-  else if (mr == 2 && rn == 2) hipLaunchKernelGGL((gemm_bf16_rows_kernel<2, 2, 4>), grid, block, smem, st, b);
-  else if (mr == 2) hipLaunchKernelGGL((gemm_bf16_rows_kernel<2, 1, 4>), grid, block, smem, st, b);
-  else if (rn == 2) hipLaunchKernelGGL((gemm_bf16_rows_kernel<1, 2, 4>), grid, block, smem, st, b);
-  else hipLaunchKernelGGL((gemm_bf16_rows_kernel<1, 1, 4>), grid, block, smem, st, b);
+  const FewRank rk{};
+  if (mr == 4) hipLaunchKernelGGL((gemm_bf16_rows_kernel<4, 1, 4, false>), grid, block, smem, st, b, rk);
+  else if (mr == 2 && rn == 2) hipLaunchKernelGGL((gemm_bf16_rows_kernel<2, 2, 4, false>), grid, block, smem, st, b, rk);
+  else if (mr == 2) hipLaunchKernelGGL((gemm_bf16_rows_kernel<2, 1, 4, false>), grid, block, smem, st, b, rk);
+  else if (rn == 2) hipLaunchKernelGGL((gemm_bf16_rows_kernel<1, 2, 4, false>), grid, block, smem, st, b, rk);
+  else hipLaunchKernelGGL((gemm_bf16_rows_kernel<1, 1, 4, false>), grid, block, smem, st, b, rk);
   mark_end(slot, b, nprob, st);
   return hipGetLastError();
 }
@@ -1191,6 +1231,43 @@ static hipError_t launch_rows(const GemmBatch &b, int nprob, hipStream_t st) {
 // 38.4 us per pass on the tiles, 43.4 here).
 bool gemm_rows_ok(int dtype, int M, int K) {
   return dtype == MIXLORA_BF16 && M >= 1 && M <= 2 && (size_t)M * K * sizeof(bf16_t) <= 65536;
+}
+
+bool gemm_few_rank_ok(int dtype, int M, int N, int K) {
+  return dtype == MIXLORA_BF16 && M >= 1 && M <= 128 && K % 64 == 0 && (uint64_t)N * K * 2 < (1ull << 32);
+}
+hipError_t launch_gemm_few_rank(const GemmProblem *probs, int nprob, const FewRank &rk, hipStream_t st) {
+  if (nprob < 1 || nprob > GEMM_MAX_PROBLEMS || rk.k * rk.r > FEW_RANK_SUMS) return hipErrorInvalidValue;
+  GemmBatch b;
+  for (int i = 0; i < GEMM_MAX_PROBLEMS; i++) b.p[i] = probs[i < nprob ? i : 0];
+  if (b.p[0].M < 1 || b.p[0].M > 128 || !dl_eligible(b, nprob, 64)) return hipErrorInvalidValue;
+  return launch_few_m(b, nprob, few_width(b, nprob), b_bytes(b, nprob) >= STREAM_BYTES, rk, st);
+}
+
+// The row kernel with the rank-r term of the down projection (one problem, one K segment).  Every workgroup adds
+// up the partial sums of the term's left factor (22 KB per token at the 7B shape) while its weights start:
+// 18.6 -> 19.9 us against the term as a K segment, which needs a launch of 4.5 us in front of it.
+static size_t rows_rank_smem(int mr, int K) {
+  return (size_t)mr * K * sizeof(bf16_t) + ((size_t)mr * 64 + GEMV_WAVES * 64) * sizeof(float);
+}
+bool gemm_rows_rank_ok(int dtype, int M, int K) {
+  return dtype == MIXLORA_BF16 && M >= 1 && M <= 2 && rows_rank_smem(M, K) <= 65536;
+}
+hipError_t launch_gemm_rows_rank(const GemmProblem &p, const FewRank &rk, hipStream_t st) {
+  const int K = p.seg[0].K;
+  if (p.nseg != 1 || !gemm_rows_rank_ok(MIXLORA_BF16, p.M, K) || rk.k * rk.r > 64) return hipErrorInvalidValue;
+  GemmBatch b;
+  for (int i = 0; i < GEMM_MAX_PROBLEMS; i++) b.p[i] = p;
+  const int mr = p.M, rn = p.N > 8192 ? 2 : 1;
+  const dim3 grid((p.N + GEMV_WAVES * rn - 1) / (GEMV_WAVES * rn)), block(GEMV_WAVES * 64);
+  const size_t smem = rows_rank_smem(mr, K);
+  const int slot = prof_on() ? prof_mark_begin(batch_kind(b, 1), st) : -1;
+  if (mr == 2 && rn == 2) hipLaunchKernelGGL((gemm_bf16_rows_kernel<2, 2, 4, true>), grid, block, smem, st, b, rk);
+  else if (mr == 2) hipLaunchKernelGGL((gemm_bf16_rows_kernel<2, 1, 4, true>), grid, block, smem, st, b, rk);
+  else if (rn == 2) hipLaunchKernelGGL((gemm_bf16_rows_kernel<1, 2, 4, true>), grid, block, smem, st, b, rk);
+  else hipLaunchKernelGGL((gemm_bf16_rows_kernel<1, 1, 4, true>), grid, block, smem, st, b, rk);
+  mark_end(slot, b, 1, st);
+  return hipGetLastError();
 }
 
 bool gemm_mixed_rows_ok(int dtype, const GemmProblem *probs, int nprob) {
@@ -1277,10 +1354,7 @@ hipError_t launch_gemm(int dtype, const GemmProblem *probs, int nprob, hipStream
     // them until the next pass anyway, and reading them costs less without the attempt (64 tokens of
     // the 7B block 91.1 -> 84.0 us, 12 tokens 81.9 -> 75.0).  Smaller ones may still be there
     // (52 MB, with an earlier kernel: 40.6 us cached, 44.4 streamed).
-    const bool nt = b_bytes(b, nprob) >= STREAM_BYTES;
-    const int w = few_width(b, nprob);
-    if (M <= 32) return launch_few_w<32>(l, nl, w, nt, st);
-    return M <= 64 ? launch_few_w<64>(l, nl, w, nt, st) : launch_few_w<128>(l, nl, w, nt, st);
+    return launch_few_m(l, nl, few_width(b, nprob), b_bytes(b, nprob) >= STREAM_BYTES, FewRank{}, st);
   }
   if (!uniform || nprob > 2) {   // the generic kernels take uniform batches of at most two
     for (int i = 0; i < nprob; i++) {
