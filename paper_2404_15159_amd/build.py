@@ -27,8 +27,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libmixlora.so")
 SOURCES = ("gemm.hip", "router.hip", "elementwise.hip", "grads.hip", "fused.hip", "fused_pg.hip", "fused_few.hip",
-           "probe.hip",
-           "linear.hip", "optim.hip", "dora.hip", "prof.hip", "api.hip")
+           "tail.hip",
+           "probe.hip", "linear.hip", "optim.hip", "dora.hip", "prof.hip", "api.hip")
 
 FLAGS = [
     "-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC",

@@ -204,8 +204,8 @@ Layout make_layout_as(const mixlora_dims &D, int schedule, bool dora, bool few) 
   L.Bg_T = take(R * f * E);
   L.Bu_T = take(R * f * E);
   L.AdT = take(R * f * E);
-  L.TG_all = take(kT * R * 4);
-  L.TU_all = take(kT * R * 4);
+  L.TG_all = take(E == 4 ? kT * R * 4 : 0);
+  L.TU_all = take(E == 4 ? kT * R * 4 : 0);
   L.ldT = (int)((kT + 15) / 16 * 16 + 16);   // transposed bf16 factors, padded for whole MFMA steps
   L.ldTz = (int)((T + 15) / 16 * 16 + 16);
   for (int i = 0; i < 6; i++) L.small[i] = take(kT * r * 4 > (size_t)L.ldT * r * 2 ? kT * r * 4 : (size_t)L.ldT * r * 2);
@@ -615,8 +615,6 @@ static int forward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mod
     GemmProblem p = problem(kT, R, ws + L.Q_all, R, 1);
     add_seg(p, ws + L.a_grp, f, w->A_down, f, f);
     HIP_TRY(launch_gemm(dt, &p, 1, st, gs));
-    // the block-sparse low-rank operand
-    HIP_TRY_AS(PROF_OTHER, 0, launch_scatter_blocks(dt, pc, (float *)(ws + L.Q_all), 0, 1, R, 1, 1, ws + L.Qw, R, 0, st));
   }
   // weighted combine of the pair activations (Algorithm 1 line 15, moved in front of the linear
   // frozen down projection)
@@ -624,9 +622,18 @@ static int forward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mod
     HIP_TRY_AS(PROF_COMBINE, (double)(k + 1) * T * f * Eb,
                launch_pair_combine_reduce(pc, f, ws + L.a_grp, ws + L.a_comb, (float *)(ws + L.rank_part),
                                           fused_splits(f, kT), (float *)(ws + L.Q_all), ws + L.Qw, R, st));
-  else
+  else if (dt == MIXLORA_BF16)
     HIP_TRY_AS(PROF_COMBINE, (double)(k + 1) * T * f * Eb,
                launch_pair_combine(dt, pc, f, ws + L.a_grp, ws + L.a_comb, 1, st));
+  else {   // and, in the same launch, the block-sparse low-rank operand
+    TailArgs ta{};
+    ta.pc = pc;
+    ta.scatter_src[0] = (float *)(ws + L.Q_all), ta.scatter_dst = ws + L.Qw;
+    ta.nscatter = 1, ta.ld_scatter = R, ta.scatter_weighted = 1;
+    ta.comb_in[0] = ws + L.a_grp, ta.comb_out[0] = ws + L.a_comb;
+    ta.ncombine = 1, ta.width = f, ta.comb_weighted = 1;
+    HIP_TRY_AS(PROF_COMBINE, (double)(k + 1) * T * f * Eb, launch_tail(dt, ta, st));
+  }
   // down projection (Algorithm 1 line 14): y = a_comb W_down^T + Qw (s B_down)^T
   if (dt == MIXLORA_BF16 && (size_t)T <= SPLITK_MAX_ROWS && whole_k_tiles(D) && !gemm_rows_ok(dt, T, f + R)) {
     // Few rows: the K range is cut into slices, one GEMM problem each with an fp32 partial output, and
@@ -835,8 +842,7 @@ static int backward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mo
                                     (float *)(ws + L.VB_all), w->B_gate, w->B_up, ws + L.AdT,
                                     ws + L.Bg_T, ws + L.Bu_T, ws + L.dg_grp, ws + L.du_grp,
                                     ws + L.dgsum, ws + L.dusum, (float *)(ws + L.dw_part),
-                                    (float *)(ws + L.rank_part), (float *)(ws + L.TG_all),
-                                    (float *)(ws + L.TU_all), Sop, Kx, st));
+                                    (float *)(ws + L.rank_part), st));
   } else if (dt == MIXLORA_BF16) {
     nct = fused_splits(f, (int)kT);
     HIP_TRY_AS(PROF_FUSED_BWD, 5.0 * kT * f * Eb, launch_swiglu_bwd_mfma(pc, f, s, vanilla ? ws + L.Gp : ws + L.G,
@@ -845,9 +851,7 @@ static int backward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mo
                                    (float *)(ws + L.Pu_all), (float *)(ws + L.VB_all), w->B_gate,
                                    w->B_up, ws + L.AdT, ws + L.Bg_T, ws + L.Bu_T, ws + L.dg_grp,
                                    ws + L.du_grp, (float *)(ws + L.dw_part),
-                                   (float *)(ws + L.rank_part), (float *)(ws + L.TG_all),
-                                   (float *)(ws + L.TU_all), Sop, Kx, st, rows_mode,
-                                   dora ? &dargs : nullptr));
+                                   (float *)(ws + L.rank_part), st, rows_mode, dora ? &dargs : nullptr));
   } else {
     HIP_TRY_AS(PROF_FUSED_BWD, 5.0 * kT * f * Eb, launch_swiglu_bwd(pc, f, s, ws + L.G, ws + L.U, (float *)(ws + L.Pg_all),
                               (float *)(ws + L.Pu_all), w->B_gate, w->B_up, ws + L.H,
@@ -857,10 +861,6 @@ static int backward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mo
     add_seg(p[0], ws + L.dg_grp, f, ws + L.Bg_T, f, f);
     add_seg(p[1], ws + L.du_grp, f, ws + L.Bu_T, f, f);
     HIP_TRY(launch_gemm(dt, p, 2, st, gs));
-  }
-  if (!vanilla && !use_pg) {   // shared gate/up: their input gradient needs the per-token sums only
-    HIP_TRY_AS(PROF_COMBINE, 2.0 * (k + 1) * T * f * Eb, launch_pair_combine2(dt, pc, f, ws + L.dg_grp, ws + L.dgsum, ws + L.du_grp,
-                                 ws + L.dusum, 0, st));
   }
   // per-row rank-r factors of the LoRA gradients, then the grouped outer-product sums:
   //   dB_gate[e] = s sum dg (x) Pg ; dA_gate[e] = s sum TG (x) x ; same for up ;
@@ -876,20 +876,42 @@ static int backward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mo
   const int width[6] = {f, f, d, d, f, d}, layout_qc[6] = {0, 0, 1, 1, 1, 0};
   float *gout[6] = {grads->dB_gate, grads->dB_up, grads->dA_gate, grads->dA_up,
                     grads->dA_down, grads->dB_down};
-  // router: dw -> dz (also written into the K-extension operand S)
-  HIP_TRY_AS(PROF_ROUTING, (double)T * N * 8, launch_router_bwd(dt, pc, probs, (float *)(ws + L.dw_part), nct,
-                            (float *)(ws + L.VB_all), (float *)(ws + L.Q_all), (float *)(ws + L.F),
-                            s, d_aux, D.aux_coeff, (float *)(ws + L.dw), (float *)(ws + L.dz),
-                            Sop, Kx, 2 * R, Kx - 2 * R, Nl, token_model,
-                            (const int32_t *)(ws + L.model_tokens),
-                            dt == MIXLORA_BF16 ? ws + L.dzT : nullptr, L.ldTz, st, vanilla ? 1 : 0));
+  // One launch: router gradient dw -> dz (also written into the K-extension operand S), the rank-r terms of
+  // S, the row factors and, where the fused stage has not made them, the per-token sums of dg and du (shared
+  // gate/up: their input gradient needs no more)
+  TailArgs ta{};
+  ta.pc = pc;
+  ta.probs = probs, ta.dw_part = (float *)(ws + L.dw_part), ta.n_col_tiles = nct;
+  ta.VB_all = (float *)(ws + L.VB_all), ta.Q_all = (float *)(ws + L.Q_all), ta.F = (float *)(ws + L.F);
+  ta.s = s, ta.aux_coeff = D.aux_coeff, ta.d_aux = d_aux;
+  ta.dw_ws = (float *)(ws + L.dw), ta.dz = (float *)(ws + L.dz);
+  ta.S = Sop, ta.ld_s = Kx, ta.col0 = 2 * R, ta.ncols = Kx - 2 * R, ta.s_by_first_pair = vanilla ? 1 : 0;
+  ta.Nl = Nl, ta.token_model = token_model, ta.model_tokens = (const int32_t *)(ws + L.model_tokens);
+  ta.dzT = dt == MIXLORA_BF16 ? (bf16_t *)(ws + L.dzT) : nullptr, ta.ldTz = L.ldTz;
+  for (int i = 0; i < 6; i++) {
+    if (dt == MIXLORA_BF16 && (i == 2 || i == 3)) {   // still partial products of the fused stage
+      ta.redT[i - 2] = (bf16_t *)(ws + L.small[i]);
+      continue;
+    }
+    ta.gather[ta.ngather++] = GatherJob{fsrc[i], ws + L.small[i], by_token[i], weighted[i]};
+  }
+  if (dt == MIXLORA_BF16) {
+    ta.part = (float *)(ws + L.rank_part), ta.nsplit = nct, ta.bank_stride = (int64_t)nct * kT * r, ta.ldT = L.ldT;
+  } else {
+    ta.scatter_src[0] = (float *)(ws + L.TG_all), ta.scatter_src[1] = (float *)(ws + L.TU_all);
+    ta.nscatter = 2, ta.scatter_dst = ws + L.S, ta.ld_scatter = Kx;
+  }
+  const bool combine = !vanilla && !use_pg;
+  if (combine) {
+    ta.comb_in[0] = ws + L.dg_grp, ta.comb_out[0] = ws + L.dgsum;
+    ta.comb_in[1] = ws + L.du_grp, ta.comb_out[1] = ws + L.dusum;
+    ta.ncombine = 2, ta.width = f;
+  }
+  HIP_TRY_AS(combine ? PROF_COMBINE : PROF_ROUTING, combine ? 2.0 * (k + 1) * T * f * Eb : (double)T * N * 8,
+             launch_tail(dt, ta, st));
   // The input gradient goes before the gradient sums: those stream what the fused stage wrote, and
   // measured 15 us faster behind this long GEMM launch than right behind that stage.
   // dx = dgsum W_gate + dusum W_up + [TG | TU | dz] [s A_gate ; s A_up ; W_router]
-  if (dt != MIXLORA_BF16)   // in bf16 the fused stage has already written these blocks
-    HIP_TRY_AS(PROF_OTHER, 0, launch_scatter_blocks(dt, pc, (float *)(ws + L.TG_all),
-                                  (int64_t)((float *)(ws + L.TU_all) - (float *)(ws + L.TG_all)), 2, R,
-                                  1, 0, ws + L.S, Kx, 0, st));
   if (dora) {
     // magnitude gradients: dm = (1 / n) * sum over the expert's rows of (output gradient *
     // unscaled projection output); gate / up sums come from the fused stage per row tile
@@ -916,9 +938,6 @@ static int backward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mo
     HIP_TRY(launch_gemm(dt, &p, 1, st, gs));
   }
   if (dt == MIXLORA_BF16) {
-    GatherJob gj[6];
-    for (int i = 0; i < 6; i++) gj[i] = GatherJob{fsrc[i], ws + L.small[i], by_token[i], weighted[i]};
-    HIP_TRY_AS(PROF_OTHER, 0, launch_gather_small_T(pc, gj, 6, L.ldT, st));
     // the three sums over d_ff-wide operands first, then the three over d-wide ones (the token's row;
     // weight-decomposed experts: dB_down sums the factor-carrying pair rows c_down[e] * dy[t], already
     // gathered), then dW_router = dz^T x (the transposed bf16 dz comes from the router backward)
@@ -937,16 +956,12 @@ static int backward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mo
     HIP_TRY_AS(PROF_GRAD_SUMS, (3.0 * kT * f + 3.0 * kT * d + (double)T * d) * Eb,
                launch_group_outer_mfma(go, njobs, part, pfl, st));
   } else {
-    GatherJob gj[6];
     GoJob go[GO_MAX_JOBS];
-    for (int i = 0; i < 6; i++) {
-      gj[i] = GatherJob{fsrc[i], ws + L.small[i], by_token[i], weighted[i]};
+    for (int i = 0; i < 6; i++)
       go[i] = GoJob{offs, gat[i], (float *)(ws + L.small[i]), (const float *)wide[i], gout[i],
                     N, r, width[i], k, (int)kT, layout_qc[i], s};
-    }
     go[6] = GoJob{(int32_t *)(ws + L.tok_offs), nullptr, (float *)(ws + L.dz), (const float *)x,
                   grads->dW_router, 1, N, d, 1, T, 1, 1.f};
-    HIP_TRY_AS(PROF_OTHER, 0, launch_gather_small(pc, gj, 6, st));
     HIP_TRY_AS(PROF_GRAD_SUMS, (3.0 * kT * f + 3.0 * kT * d + (double)T * d) * Eb,
                launch_group_outer(go, GO_MAX_JOBS, part, pfl, st));
   }

@@ -271,14 +271,14 @@ hipError_t launch_swiglu_fwd_mfma(const PairCtx &pc, int f, float s, const void 
 constexpr int ROWS_GU = 1, ROWS_H = 2, ROWS_SPARSE = 4;
 
 // bf16 MFMA backward of the same stage: dg_grp, du_grp, dw_part[row][split]
-// (split count = fused_splits(f, kT)), TG_all / TU_all at [row, e(row)*r + q].  AdT = A_down re-laid
-// [N, f, r]; BgT / BuT = B banks re-laid [N, r, f]; rank_part is scratch of 2 * fused_splits(f, kT) * kT * r floats.
+// (split count = fused_splits(f, kT)), and per split the rank-r partial products of dg with B_gate and of du
+// with B_up, [2][split][kT][r] at rank_part.  AdT = A_down re-laid [N, f, r]; BgT / BuT = B banks re-laid
+// [N, r, f].
 hipError_t launch_swiglu_bwd_mfma(const PairCtx &pc, int f, float s, const void *G, const void *U,
                                   const void *H, const float *Pg_all, const float *Pu_all,
                                   const float *VB_all, const void *B_gate, const void *B_up,
                                   const void *AdT, const void *BgT, const void *BuT, void *dg_grp,
-                                  void *du_grp, float *dw_part, float *rank_part, float *TG_all,
-                                  float *TU_all, void *S, int lds_, hipStream_t st,
+                                  void *du_grp, float *dw_part, float *rank_part, hipStream_t st,
                                   int rows_mode = 0, const DoraArgs *dora = nullptr);
 // Pair-grouped token tiles (csrc/fused_pg.hip) for top-2 routing, N <= PG_MAX_EXPERTS, 128 < T <=
 // PG_MAX_TOKENS, r <= 16: tokens are grouped by their unordered expert pair, a workgroup handles
@@ -303,21 +303,18 @@ hipError_t launch_swiglu_fwd_pg(const PairCtx &pc, int f, float s, const int32_t
                                 const void *B_gate, const void *B_up, const void *A_down,
                                 void *a_grp, void *a_comb, float *Q_part, float *Q_all, void *Qw,
                                 int ldqw, int write_a, hipStream_t st);
-// backward on the same tiles: per-pair dg_grp, du_grp, dw_part [pair row][fused_pg_splits], TG / TU
-// (reduced into TG_all, TU_all and the block-sparse operand S) and the per-token sums dgsum, dusum
+// backward on the same tiles: per-pair dg_grp, du_grp, dw_part [pair row][fused_pg_splits], the rank-r partial
+// products as above and the per-token sums dgsum, dusum
 hipError_t launch_swiglu_bwd_pg(const PairCtx &pc, int f, float s, const int32_t *tok_of_pos,
                                 const int32_t *tile_info, const int32_t *ntiles, const void *G,
                                 const void *U, const void *H, const float *Pg_all,
                                 const float *Pu_all, const float *VB_all, const void *B_gate,
                                 const void *B_up, const void *AdT, const void *BgT, const void *BuT,
                                 void *dg_grp, void *du_grp, void *dgsum, void *dusum, float *dw_part,
-                                float *rank_part, float *TG_all, float *TU_all, void *S, int ld_s,
-                                hipStream_t st);
-// dense[row, e(row)*r + q] = sum over splits of part[split][row][q] (fixed order) for one bank
-// (dense1 == NULL) or two banks bank_stride floats apart; the value (times the routing weight if
-// weighted) also goes as bf16 into the block-sparse operand sparse[t(row) or row, bank*N*r + e*r + q]
-hipError_t launch_reduce_rank_parts(const PairCtx &pc, const float *part0, int64_t bank_stride,
-                                    int nsplit, float *dense0, float *dense1, void *sparse,
+                                float *rank_part, hipStream_t st);
+// dense[row, e(row)*r + q] = sum over splits of part[split][row][q] (fixed order); the value (times the
+// routing weight if weighted) also goes as bf16 into the block-sparse operand sparse[t(row) or row, e*r + q]
+hipError_t launch_reduce_rank_parts(const PairCtx &pc, const float *part, int nsplit, float *dense, void *sparse,
                                     int ld_sparse, int weighted, int by_row, hipStream_t st);
 int fused_row_tiles(int kT, int N);   // grid.x of the fused stages
 int fused_splits(int f, int kT);   // at most FUSED_MAX_SPLITS
@@ -331,19 +328,9 @@ hipError_t launch_pair_combine_reduce(const PairCtx &pc, int width, const void *
                                       int ld_sparse, hipStream_t st);
 hipError_t launch_pair_combine(int dtype, const PairCtx &pc, int width, const void *in_grp,
                                void *out, int weighted, hipStream_t st);
-// two combines of the same shape in one launch (in_grp1 == NULL: only the first)
-hipError_t launch_pair_combine2(int dtype, const PairCtx &pc, int width, const void *in_grp0,
-                                void *out0, const void *in_grp1, void *out1, int weighted,
-                                hipStream_t st);
 // dst[row, :] = src[token of grouped row, :]   (width a multiple of 8)
 hipError_t launch_gather_rows(int dtype, const PairCtx &pc, int width, const void *src, void *dst,
                               hipStream_t st);
-// dst[t, col0 + e_j*r + q] = scale_j * src[row_j, (src_dense ? e_j*r : 0) + q] for the kept
-// experts, 0 elsewhere; dst is in the storage dtype with leading dimension ldd.  nsrc sources
-// (src + b*src_stride, b < nsrc) fill consecutive N*r-column blocks in one launch.
-hipError_t launch_scatter_blocks(int dtype, const PairCtx &pc, const float *src, int64_t src_stride,
-                                 int nsrc, int lds_, int src_dense, int weighted, void *dst,
-                                 int ldd, int col0, hipStream_t st);
 // io[t, c] += s * sum_q P[t, q] * Wt[c, q]   (io [T,C] storage dtype, P [T,r] f32, Wt [C,r])
 hipError_t launch_lowrank_add(int dtype, void *io, const float *P, const void *Wt, int T, int C,
                               int r, float s, hipStream_t st);
@@ -423,31 +410,56 @@ constexpr int GOM_MAX_JOBS = 8;
 hipError_t launch_group_outer_mfma(const GomJob *jobs, int njobs, float *partials, size_t partial_floats,
                                    hipStream_t st);
 size_t group_outer_mfma_partial_floats(int G, int r, int C, int rows, int alike);
-// outT[q, row] = (w_row or 1) * src[(by_token ? t(row) : row), e(row)*r + q] as bf16, pitch ldT;
-// up to GATHER_MAX_JOBS factors in one launch
+// a per-row rank-r factor: (w_row or 1) * src[(by_token ? t(row) : row), e(row)*r + q], as bf16 at
+// outT[q, row] (pitch ldT) or in fp32 storage at outT[row, q]
 struct GatherJob {
   const float *src;
   void *outT;
   int by_token, weighted;
 };
 constexpr int GATHER_MAX_JOBS = 6;
-// the same untransposed in float32:  out[row, q]
-hipError_t launch_gather_small(const PairCtx &pc, const GatherJob *jobs, int njobs, hipStream_t st);
-hipError_t launch_gather_small_T(const PairCtx &pc, const GatherJob *jobs, int njobs, int ldT,
-                                 hipStream_t st);
 hipError_t launch_f32_to_bf16T(const float *src, int rows, int r, void *outT, int ldT,
                                hipStream_t st);
 
 struct AuxUpstream {   // upstream gradient of every adapter's auxiliary loss
   float v[64];
 };
-hipError_t launch_router_bwd(int dtype, const PairCtx &pc, const float *probs, const float *dw_part,
-                             int n_col_tiles, const float *VB_all, const float *Q_all,
-                             const float *F, float s, const AuxUpstream &d_aux, float aux_coeff,
-                             float *dw_ws, float *dz, void *S, int lds_, int col0, int ncols,
-                             int Nl, const int32_t *token_model, const int32_t *model_tokens,
-                             void *dzT, int ldTz, hipStream_t st,    // dzT: bf16 [N][ldTz] copy or NULL
-                             int s_by_first_pair = 0);   // S has one row per grouped pair row
+// ---- row-wise steps behind a fused stage, one launch (csrc/tail.hip) ----------------------------------
+// Parts that are not wanted are left zero.
+struct TailArgs {
+  PairCtx pc;
+  // router gradient (probs != NULL): dw -> dz, also into columns col0 .. of the K-extension operand S
+  const float *probs, *dw_part, *VB_all, *Q_all, *F;
+  int n_col_tiles;
+  float s, aux_coeff;
+  AuxUpstream d_aux;
+  float *dw_ws, *dz;
+  void *S;
+  int ld_s, col0, ncols, Nl;
+  const int32_t *token_model, *model_tokens;
+  bf16_t *dzT;             // bf16 [N][ldTz] copy or NULL
+  int ldTz, s_by_first_pair;   // S has one row per grouped pair row
+  // bf16 storage (part != NULL): two banks of rank-r partial products -> S and their transposed factors
+  const float *part;
+  int64_t bank_stride;
+  int nsplit, ldT;
+  bf16_t *redT[2];
+  // row factors
+  GatherJob gather[GATHER_MAX_JOBS];
+  int ngather;
+  // fp32 storage: block-sparse operand from dense rank-r rows, up to two banks side by side
+  const float *scatter_src[2];
+  void *scatter_dst;
+  int nscatter, ld_scatter, scatter_weighted;
+  // sums over a token's pair rows
+  const void *comb_in[2];
+  void *comb_out[2];
+  int ncombine, width, comb_weighted;
+};
+struct TailBlocks {   // workgroups of each part (of one bank, job, token)
+  int router, reduce, gather, scatter, combine;
+};
+hipError_t launch_tail(int dtype, const TailArgs &a, hipStream_t st);
 
 // ---- weight-decomposed experts (csrc/dora.hip); bf16 storage only --------------------------------
 hipError_t launch_row_sqnorm(const void *W_gate, const void *W_up, const void *W_down, int f, int d,

@@ -6,6 +6,7 @@
 // projections, then SiLU * up).
 #include "common.h"
 #include "relayout_body.h"
+#include "row_bodies.h"
 
 namespace mixlora {
 
@@ -244,53 +245,12 @@ hipError_t launch_swiglu_bwd(const PairCtx &pc, int f, float s, const void *G, c
   return hipGetLastError();
 }
 
-// ---- out[t, :] = sum_j (w[t,j] or 1) * in_grp[row_of_pair[t,j], :] ------------------------------
-// Gather form of the weighted combine (Eq. 6; Algorithm 1 line 15): each output row is written
-// once, by one thread per 8 columns, slots added in ascending order (deterministic).
-template <typename E>
-__device__ __forceinline__ void pair_combine_body(const PairCtx &pc, int width,
-                                                  const E *__restrict__ in_grp,
-                                                  E *__restrict__ out, int weighted, int t, int by) {
-  // a thread owns two 8-column chunks, 2048 columns apart: 2k independent loads in flight
-  const int c0 = (by * 512 + threadIdx.x) * 8;
-  const int c1 = c0 + 2048;
-  if (c0 >= width) return;
-  const bool two = c1 < width;
-  float acc0[8] = {0, 0, 0, 0, 0, 0, 0, 0}, acc1[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  for (int j = 0; j < pc.k; j++) {
-    const int p = t * pc.k + j;
-    const float w = weighted ? pc.w[p] : 1.f;
-    const E *src = in_grp + (int64_t)pc.row_of_pair[p] * width;
-    Vec8<E> v0, v1;
-    v0.load(src + c0);
-    if (two) v1.load(src + c1);
-#pragma unroll
-    for (int i = 0; i < 8; i++) acc0[i] = fmaf(w, v0.get(i), acc0[i]);
-    if (two) {
-#pragma unroll
-      for (int i = 0; i < 8; i++) acc1[i] = fmaf(w, v1.get(i), acc1[i]);
-    }
-  }
-  Vec8<E> o;
-#pragma unroll
-  for (int i = 0; i < 8; i++) o.set(i, acc0[i]);
-  o.store(out + (int64_t)t * width + c0);
-  if (two) {
-#pragma unroll
-    for (int i = 0; i < 8; i++) o.set(i, acc1[i]);
-    o.store(out + (int64_t)t * width + c1);
-  }
-}
-
+// (csrc/row_bodies.h)
 template <typename E>
 __global__ __launch_bounds__(256) void pair_combine_kernel(PairCtx pc, int width,
-                                                           const E *__restrict__ in_grp0,
-                                                           E *__restrict__ out0,
-                                                           const E *__restrict__ in_grp1,
-                                                           E *__restrict__ out1, int weighted) {
-  // blockIdx.z picks one of two combines of the same shape that share the launch
-  pair_combine_body<E>(pc, width, blockIdx.z ? in_grp1 : in_grp0, blockIdx.z ? out1 : out0, weighted,
-                       blockIdx.x, blockIdx.y);
+                                                           const E *__restrict__ in_grp,
+                                                           E *__restrict__ out, int weighted) {
+  pair_combine_body<E>(pc, width, in_grp, out, weighted, blockIdx.x, blockIdx.y);
 }
 
 // Few tokens: the weighted combine and, as one more slice of workgroups (blockIdx.y == ny), the sum
@@ -336,24 +296,16 @@ hipError_t launch_pair_combine_reduce(const PairCtx &pc, int width, const void *
   return hipGetLastError();
 }
 
-hipError_t launch_pair_combine2(int dtype, const PairCtx &pc, int width, const void *in_grp0,
-                                void *out0, const void *in_grp1, void *out1, int weighted,
-                                hipStream_t st) {
-  const dim3 grid(pc.T, (width / 8 + 511) / 512, in_grp1 ? 2 : 1), block(256);
-  if (dtype == MIXLORA_BF16)
-    hipLaunchKernelGGL(pair_combine_kernel<bf16_t>, grid, block, 0, st, pc, width,
-                       (const bf16_t *)in_grp0, (bf16_t *)out0, (const bf16_t *)in_grp1,
-                       (bf16_t *)out1, weighted);
-  else
-    hipLaunchKernelGGL(pair_combine_kernel<float>, grid, block, 0, st, pc, width,
-                       (const float *)in_grp0, (float *)out0, (const float *)in_grp1,
-                       (float *)out1, weighted);
-  return hipGetLastError();
-}
-
 hipError_t launch_pair_combine(int dtype, const PairCtx &pc, int width, const void *in_grp,
                                void *out, int weighted, hipStream_t st) {
-  return launch_pair_combine2(dtype, pc, width, in_grp, out, nullptr, nullptr, weighted, st);
+  const dim3 grid(pc.T, pair_combine_slices(width)), block(256);
+  if (dtype == MIXLORA_BF16)
+    hipLaunchKernelGGL(pair_combine_kernel<bf16_t>, grid, block, 0, st, pc, width, (const bf16_t *)in_grp,
+                       (bf16_t *)out, weighted);
+  else
+    hipLaunchKernelGGL(pair_combine_kernel<float>, grid, block, 0, st, pc, width, (const float *)in_grp,
+                       (float *)out, weighted);
+  return hipGetLastError();
 }
 
 // ---- dst[row, :] = src[token of grouped row, :] : the routed tokens' rows in expert-grouped order
@@ -380,71 +332,6 @@ hipError_t launch_gather_rows(int dtype, const PairCtx &pc, int width, const voi
   else
     hipLaunchKernelGGL(gather_rows_kernel<float>, grid, block, 0, st, pc, width, (const float *)src,
                        (float *)dst);
-  return hipGetLastError();
-}
-
-// dst[t, col0 + e*r + q] = (w[t,j] or 1) * src[row_j, (src_dense ? e*r : 0) + q] when expert e is
-// slot j of token t, else 0.  Builds the block-sparse low-rank operand of a K-extension.
-// blockIdx.y = b handles a further source src + b*src_stride into columns col0 + b*N*r.
-template <typename E>
-__global__ void scatter_blocks_kernel(PairCtx pc, const float *__restrict__ src0,
-                                      int64_t src_stride, int lds_, int src_dense, int weighted,
-                                      E *__restrict__ dst, int ldd, int col00) {
-  const int R = pc.N * pc.r;
-  const float *__restrict__ src = src0 + blockIdx.y * src_stride;
-  const int col0 = col00 + blockIdx.y * R;
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (int64_t)pc.T * R) return;
-  const int t = (int)(i / R), er = (int)(i % R);
-  const int e = er / pc.r, q = er % pc.r;
-  float v = 0.f;
-  for (int j = 0; j < pc.k; j++) {
-    const int p = t * pc.k + j;
-    if (pc.idx[p] == e) {
-      const float w = weighted ? pc.w[p] : 1.f;
-      v = w * src[(int64_t)pc.row_of_pair[p] * lds_ + (src_dense ? e * pc.r : 0) + q];
-    }
-  }
-  dst[(int64_t)t * ldd + col0 + er] = from_f32<E>(v);
-}
-
-hipError_t launch_scatter_blocks(int dtype, const PairCtx &pc, const float *src, int64_t src_stride,
-                                 int nsrc, int lds_, int src_dense, int weighted, void *dst,
-                                 int ldd, int col0, hipStream_t st) {
-  const int64_t n = (int64_t)pc.T * pc.N * pc.r;
-  const dim3 grid((unsigned)((n + 255) / 256), nsrc), block(256);
-  if (dtype == MIXLORA_BF16)
-    hipLaunchKernelGGL(scatter_blocks_kernel<bf16_t>, grid, block, 0, st, pc, src, src_stride, lds_,
-                       src_dense, weighted, (bf16_t *)dst, ldd, col0);
-  else
-    hipLaunchKernelGGL(scatter_blocks_kernel<float>, grid, block, 0, st, pc, src, src_stride, lds_,
-                       src_dense, weighted, (float *)dst, ldd, col0);
-  return hipGetLastError();
-}
-
-// out[row, q] = (w_row or 1) * src[(by_token ? t(row) : row), e(row)*r + q]; one job per blockIdx.y
-struct GatherSmallBatch {
-  GatherJob job[GATHER_MAX_JOBS];
-};
-__global__ void gather_small_kernel(PairCtx pc, GatherSmallBatch batch) {
-  const GatherJob &J = batch.job[blockIdx.y];
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int nP = pc.T * pc.k;
-  if (i >= (int64_t)nP * pc.r) return;
-  const int row = (int)(i / pc.r), q = (int)(i % pc.r);
-  const int p = pc.pair_of_row[row];
-  const int e = pc.idx[p];
-  const int64_t srow = J.by_token ? p / pc.k : row;
-  const float w = J.weighted ? pc.w[p] : 1.f;
-  reinterpret_cast<float *>(J.outT)[i] = w * J.src[srow * (pc.N * pc.r) + e * pc.r + q];
-}
-
-hipError_t launch_gather_small(const PairCtx &pc, const GatherJob *jobs, int njobs, hipStream_t st) {
-  if (njobs < 1 || njobs > GATHER_MAX_JOBS) return hipErrorInvalidValue;
-  GatherSmallBatch b;
-  for (int i = 0; i < GATHER_MAX_JOBS; i++) b.job[i] = jobs[i < njobs ? i : 0];
-  const int64_t n = (int64_t)pc.T * pc.k * pc.r;
-  hipLaunchKernelGGL(gather_small_kernel, dim3((unsigned)((n + 255) / 256), njobs), dim3(256), 0, st, pc, b);
   return hipGetLastError();
 }
 

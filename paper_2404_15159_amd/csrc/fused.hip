@@ -465,49 +465,39 @@ __global__ __launch_bounds__(FT_WAVES * 64, (KSR == 1 && !DORA) ? 2 : 1) void sw
         (dwred[0][threadIdx.x] + dwred[1][threadIdx.x]) + (dwred[2][threadIdx.x] + dwred[3][threadIdx.x]);
 }
 
-// dense[row, e(row)*r + q] = sum over splits of part[split][row][q]   (fixed order); blockIdx.y
-// picks the bank (partials bank_stride floats apart, outputs dense0 / dense1).  The same value
-// (times the routing weight if weighted) also goes, as bf16, into the block-sparse per-token
-// operand of a K-extension:  sparse[t(row), col0 + bank*N*r + e*r + q]; the rest of that
-// operand was zero-filled beforehand.  With by_row the operand has one row per grouped pair row
-// (sparse[row, ...]) instead of one per token.
-__global__ void reduce_rank_parts_kernel(PairCtx pc, const float *__restrict__ part0,
-                                         int64_t bank_stride, int nsplit,
-                                         float *__restrict__ dense0, float *__restrict__ dense1,
-                                         bf16_t *__restrict__ sparse, int ld_sparse, int col0,
-                                         int weighted, int by_row) {
+// dense[row, e(row)*r + q] = sum over the column splits, in split order, of part[split][row][q].  The same
+// value (times the routing weight if weighted) also goes, as bf16, into the block-sparse per-token operand of
+// a K-extension, sparse[t(row), e*r + q], the rest of which was zero-filled beforehand; with by_row that
+// operand has one row per grouped pair row.
+__global__ void reduce_rank_parts_kernel(PairCtx pc, const float *__restrict__ part, int nsplit,
+                                         float *__restrict__ dense, bf16_t *__restrict__ sparse,
+                                         int ld_sparse, int weighted, int by_row) {
   const int nP = pc.T * pc.k, r = pc.r;
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= (int64_t)nP * r) return;
-  const float *part = part0 + blockIdx.y * bank_stride;
-  float *dense = blockIdx.y ? dense1 : dense0;
   const int row = (int)(i / r), q = (int)(i % r);
   float acc = 0.f;
   int sp = 0;
-  for (; sp + 4 <= nsplit; sp += 4) {   // four loads in flight; additions in split order
-    const float a0 = part[(int64_t)sp * nP * r + i], a1 = part[(int64_t)(sp + 1) * nP * r + i];
-    const float a2 = part[(int64_t)(sp + 2) * nP * r + i], a3 = part[(int64_t)(sp + 3) * nP * r + i];
-    acc += a0; acc += a1; acc += a2; acc += a3;
+  for (; sp + 8 <= nsplit; sp += 8) {   // eight loads in flight; additions in split order
+    float v[8];
+#pragma unroll
+    for (int u = 0; u < 8; u++) v[u] = part[(int64_t)(sp + u) * nP * r + i];
+#pragma unroll
+    for (int u = 0; u < 8; u++) acc += v[u];
   }
   for (; sp < nsplit; sp++) acc += part[(int64_t)sp * nP * r + i];
   const int pair = pc.pair_of_row[row];
   const int e = pc.idx[pair];
-  const int R = pc.N * r;
-  dense[(int64_t)row * R + e * r + q] = acc;
+  dense[(int64_t)row * pc.N * r + e * r + q] = acc;
   const float wv = weighted ? pc.w[pair] : 1.f;
-  sparse[(int64_t)(by_row ? row : pair / pc.k) * ld_sparse + col0 + blockIdx.y * R + e * r + q] =
-      (bf16_t)(wv * acc);
+  sparse[(int64_t)(by_row ? row : pair / pc.k) * ld_sparse + e * r + q] = (bf16_t)(wv * acc);
 }
 
-// one bank (dense1 == NULL) or two banks bank_stride floats apart, as described above
-hipError_t launch_reduce_rank_parts(const PairCtx &pc, const float *part0, int64_t bank_stride,
-                                    int nsplit, float *dense0, float *dense1, void *sparse,
+hipError_t launch_reduce_rank_parts(const PairCtx &pc, const float *part, int nsplit, float *dense, void *sparse,
                                     int ld_sparse, int weighted, int by_row, hipStream_t st) {
   const int64_t n = (int64_t)pc.T * pc.k * pc.r;
-  const dim3 grid((unsigned)((n + 255) / 256), dense1 ? 2 : 1);
-  hipLaunchKernelGGL(reduce_rank_parts_kernel, grid, dim3(256), 0, st, pc, part0, bank_stride, nsplit,
-                     dense0, dense1 ? dense1 : dense0, (bf16_t *)sparse, ld_sparse, 0, weighted,
-                     by_row);
+  hipLaunchKernelGGL(reduce_rank_parts_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, pc, part, nsplit,
+                     dense, (bf16_t *)sparse, ld_sparse, weighted, by_row);
   return hipGetLastError();
 }
 
@@ -547,19 +537,15 @@ hipError_t launch_swiglu_fwd_mfma(const PairCtx &pc, int f, float s, const void 
 #undef MIXLORA_FWD
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !reduce_parts) return e;
-  const int64_t n = (int64_t)nP * pc.r;
-  hipLaunchKernelGGL(reduce_rank_parts_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
-                     pc, Q_part, (int64_t)0, nsplit, Q_all, Q_all, (bf16_t *)Qw, ldqw, 0,
-                     (rows_mode & ROWS_SPARSE) ? 0 : 1, (rows_mode & ROWS_SPARSE) ? 1 : 0);
-  return hipGetLastError();
+  return launch_reduce_rank_parts(pc, Q_part, nsplit, Q_all, Qw, ldqw, (rows_mode & ROWS_SPARSE) ? 0 : 1,
+                                  (rows_mode & ROWS_SPARSE) ? 1 : 0, st);
 }
 
 hipError_t launch_swiglu_bwd_mfma(const PairCtx &pc, int f, float s, const void *G, const void *U,
                                   const void *H, const float *Pg_all, const float *Pu_all,
                                   const float *VB_all, const void *B_gate, const void *B_up,
                                   const void *AdT, const void *BgT, const void *BuT, void *dg_grp,
-                                  void *du_grp, float *dw_part, float *rank_part, float *TG_all,
-                                  float *TU_all, void *S, int lds_, hipStream_t st, int rows_mode,
+                                  void *du_grp, float *dw_part, float *rank_part, hipStream_t st, int rows_mode,
                                   const DoraArgs *dora) {
   const int nP = pc.T * pc.k, nsplit = fused_splits(f, nP);
   float *TG_part = rank_part, *TU_part = rank_part + (size_t)nsplit * nP * pc.r;
@@ -581,13 +567,6 @@ hipError_t launch_swiglu_bwd_mfma(const PairCtx &pc, int f, float s, const void 
     else MIXLORA_BWD(4, 2, false);
   }
 #undef MIXLORA_BWD
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const int64_t n = (int64_t)nP * pc.r;
-  const dim3 rgrid((unsigned)((n + 255) / 256), 2);
-  hipLaunchKernelGGL(reduce_rank_parts_kernel, rgrid, dim3(256), 0, st, pc, TG_part,
-                     (int64_t)(TU_part - TG_part), nsplit, TG_all, TU_all, (bf16_t *)S, lds_, 0, 0,
-                     (rows_mode & ROWS_SPARSE) ? 1 : 0);
   return hipGetLastError();
 }
 

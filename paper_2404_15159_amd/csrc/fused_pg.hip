@@ -606,7 +606,7 @@ hipError_t launch_swiglu_fwd_pg(const PairCtx &pc, int f, float s, const int32_t
 #undef MIXLORA_PGF
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  return launch_reduce_rank_parts(pc, Q_part, 0, nsplit, Q_all, nullptr, Qw, ldqw, 1, 0, st);
+  return launch_reduce_rank_parts(pc, Q_part, nsplit, Q_all, Qw, ldqw, 1, 0, st);
 }
 
 hipError_t launch_swiglu_bwd_pg(const PairCtx &pc, int f, float s, const int32_t *tok_of_pos,
@@ -615,8 +615,7 @@ hipError_t launch_swiglu_bwd_pg(const PairCtx &pc, int f, float s, const int32_t
                                 const float *Pu_all, const float *VB_all, const void *B_gate,
                                 const void *B_up, const void *AdT, const void *BgT, const void *BuT,
                                 void *dg_grp, void *du_grp, void *dgsum, void *dusum, float *dw_part,
-                                float *rank_part, float *TG_all, float *TU_all, void *S, int ld_s,
-                                hipStream_t st) {
+                                float *rank_part, hipStream_t st) {
   if (!fused_pg_ok(pc, f)) return hipErrorInvalidValue;
   const int nP = pc.T * 2, nsplit = fused_pg_splits(f, pc.T, pc.N);
   float *TG_part = rank_part, *TU_part = rank_part + (size_t)nsplit * nP * pc.r;
@@ -635,10 +634,7 @@ hipError_t launch_swiglu_bwd_pg(const PairCtx &pc, int f, float s, const int32_t
                      (const bf16_t *)B_gate, (const bf16_t *)B_up, (const bf16_t *)AdT,
                      (const bf16_t *)BgT, (const bf16_t *)BuT, (bf16_t *)dg_grp, (bf16_t *)du_grp,
                      (bf16_t *)dgsum, (bf16_t *)dusum, dw_part, TG_part, TU_part, nsplit);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  return launch_reduce_rank_parts(pc, TG_part, (int64_t)(TU_part - TG_part), nsplit, TG_all, TU_all, S,
-                                  ld_s, 0, 0, st);
+  return hipGetLastError();
 }
 
 }  // namespace mixlora

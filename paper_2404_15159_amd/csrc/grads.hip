@@ -385,37 +385,6 @@ hipError_t launch_group_outer_mfma(const GomJob *jobs, int njobs, float *partial
   return hipGetLastError();
 }
 
-// Transposed bf16 row factors for the MFMA gradient sums, several factors per launch:
-//   outT[q, row] = (w_row or 1) * src[(by_token ? t(row) : row), e(row)*r + q]
-struct GatherBatch {
-  GatherJob job[GATHER_MAX_JOBS];
-};
-
-__global__ void gather_small_T_kernel(PairCtx pc, GatherBatch batch, int ldT) {
-  const GatherJob &J = batch.job[blockIdx.y];
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int nP = pc.T * pc.k;
-  if (i >= (int64_t)nP * pc.r) return;
-  const int q = (int)(i / nP), row = (int)(i % nP);
-  const int p = pc.pair_of_row[row];
-  const int e = pc.idx[p];
-  const int64_t srow = J.by_token ? p / pc.k : row;
-  const float w = J.weighted ? pc.w[p] : 1.f;
-  reinterpret_cast<bf16_t *>(J.outT)[(int64_t)q * ldT + row] =
-      (bf16_t)(w * J.src[srow * (pc.N * pc.r) + e * pc.r + q]);
-}
-
-hipError_t launch_gather_small_T(const PairCtx &pc, const GatherJob *jobs, int njobs, int ldT,
-                                 hipStream_t st) {
-  if (njobs < 1 || njobs > GATHER_MAX_JOBS) return hipErrorInvalidValue;
-  GatherBatch b;
-  for (int i = 0; i < GATHER_MAX_JOBS; i++) b.job[i] = jobs[i < njobs ? i : 0];
-  const int64_t n = (int64_t)pc.T * pc.k * pc.r;
-  hipLaunchKernelGGL(gather_small_T_kernel, dim3((unsigned)((n + 255) / 256), njobs), dim3(256), 0,
-                     st, pc, b, ldT);
-  return hipGetLastError();
-}
-
 // outT[q][row] (bf16) = src[row][q] (fp32, [rows, r])
 __global__ void f32_to_bf16T_kernel(const float *__restrict__ src, int rows, int r,
                                     bf16_t *__restrict__ outT, int ldT) {
@@ -430,112 +399,6 @@ hipError_t launch_f32_to_bf16T(const float *src, int rows, int r, void *outT, in
   const int64_t n = (int64_t)rows * r;
   hipLaunchKernelGGL(f32_to_bf16T_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, src,
                      rows, r, (bf16_t *)outT, ldT);
-  return hipGetLastError();
-}
-
-// ---- router backward -------------------------------------------------------------------------
-// One wavefront per token.  dw_j = <dy_t, o_pair> is assembled from the column-tile partials of
-// <H[t], a_row> plus the low-rank part  s <B_down[e]^T dy_t, A_down[e] a_row>  (lanes split the
-// terms, a butterfly adds them).  Then, with w_j = p_j / sum_kept p (Norm of Algorithm 1):
-// dp_j = (dw_j - sum_i w_i dw_i) / sum_kept p on the kept experts, plus the auxiliary term
-// d_aux * a * N * F_e / T  on every expert (Eq. 8-9; F is piecewise constant; evaluated as its
-// deviation from 1/N, see below), and
-// dz = p * (dp - <p, dp>) through the softmax of Eq. 7 (lane e holds expert e).  With several
-// adapters p is zero outside the token's adapter, so dz is too; T and the upstream gradient of
-// the auxiliary loss are those of the token's adapter.
-__device__ __forceinline__ float rb_wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-
-template <typename E>
-__global__ __launch_bounds__(256) void router_bwd_kernel(
-    PairCtx pc, const float *__restrict__ probs, const float *__restrict__ dw_part,
-    int n_col_tiles, const float *__restrict__ VB_all, const float *__restrict__ Q_all,
-    const float *__restrict__ F, float s, AuxUpstream d_aux, float aux_coeff,
-    float *__restrict__ dw_ws, float *__restrict__ dz, E *__restrict__ S, int lds_, int col0,
-    int ncols, int Nl, const int32_t *__restrict__ token_model,
-    const int32_t *__restrict__ model_tokens, bf16_t *__restrict__ dzT, int ldTz,
-    int s_by_first_pair) {
-  const int lane = threadIdx.x & 63;
-  const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (t >= pc.T) return;   // whole wave leaves together
-  const int N = pc.N, k = pc.k, r = pc.r, R = N * r;
-  float my_dw = 0.f, my_w = 0.f, my_p = 0.f;   // lane j < k: slot j of the token
-  int my_e = -1;
-  for (int j = 0; j < k; j++) {
-    const int p = t * k + j;
-    const int row = pc.row_of_pair[p];
-    const int e = pc.idx[p];
-    float part = 0.f;
-    for (int ct = lane; ct < n_col_tiles; ct += 64) part += dw_part[(int64_t)row * n_col_tiles + ct];
-    float lr = 0.f;
-    for (int q = lane; q < r; q += 64)
-      lr = fmaf(VB_all[(int64_t)t * R + e * r + q], Q_all[(int64_t)row * R + e * r + q], lr);
-    const float dwj = rb_wave_sum(part + s * lr);
-    if (lane == j) {
-      my_dw = dwj;
-      my_e = e;
-      my_w = pc.w[p];
-      my_p = probs[(int64_t)t * N + e];
-      dw_ws[p] = dwj;
-    }
-  }
-  const float wdw = rb_wave_sum(my_w * my_dw);
-  const float ssum = rb_wave_sum(my_p);
-  // auxiliary term of the token's adapter: statistics over that adapter's own tokens
-  const int m = __builtin_amdgcn_readfirstlane(token_model ? token_model[t] : 0);   // wave-uniform
-  const float auxg = d_aux.v[m] * aux_coeff * (float)Nl / (float)model_tokens[m];
-  // The softmax Jacobian ignores a constant added to dp, so F_e - 1/Nl stands in for F_e: with
-  // nearly balanced loads (what the loss drives towards) p * (F_e - <p, F>) would otherwise be a
-  // difference of nearly equal numbers.  F_e * (k * tokens) is an integer in both modes of Eq. 9
-  // (k times the first-slot count, or the kept count), recovered exactly by rounding, so the
-  // deviation (num_e * Nl - k * tokens) / (k * tokens * Nl) has an exact numerator.
-  float dp = 0.f;
-  if (lane < N) {
-    const float kt = (float)k * (float)model_tokens[m];
-    const int64_t num = (int64_t)rintf(F[lane] * kt);
-    const int64_t dev = num * Nl - (int64_t)k * model_tokens[m];
-    dp = auxg * ((float)dev / (kt * (float)Nl));
-  }
-  for (int j = 0; j < k; j++) {
-    const int ej = __shfl(my_e, j, 64);
-    const float dwj = __shfl(my_dw, j, 64);
-    if (ej == lane) dp += (dwj - wdw) / ssum;
-  }
-  const float pe = lane < N ? probs[(int64_t)t * N + lane] : 0.f;
-  const float dot = rb_wave_sum(pe * dp);
-  const float v = pe * (dp - dot);   // 0 on lanes >= N
-  if (lane < N) {
-    dz[(int64_t)t * N + lane] = v;
-    // transposed bf16 copy: the row factor of the dW_router outer-product sum
-    if (dzT) dzT[(int64_t)lane * ldTz + t] = (bf16_t)v;
-  }
-  // row of the K-extension operand: the token's, or (operand with one row per grouped pair row)
-  // the row of the token's first slot, whose other rows keep zeros in these columns
-  const int64_t srow = s_by_first_pair ? pc.row_of_pair[t * pc.k] : t;
-  for (int e = lane; e < ncols; e += 64)
-    S[srow * lds_ + col0 + e] = from_f32<E>(e < N ? v : 0.f);
-}
-
-hipError_t launch_router_bwd(int dtype, const PairCtx &pc, const float *probs, const float *dw_part,
-                             int n_col_tiles, const float *VB_all, const float *Q_all,
-                             const float *F, float s, const AuxUpstream &d_aux, float aux_coeff,
-                             float *dw_ws, float *dz, void *S, int lds_, int col0, int ncols,
-                             int Nl, const int32_t *token_model, const int32_t *model_tokens,
-                             void *dzT, int ldTz, hipStream_t st, int s_by_first_pair) {
-  const dim3 grid((pc.T + 3) / 4), block(256);
-  if (dtype == MIXLORA_BF16)
-    hipLaunchKernelGGL(router_bwd_kernel<bf16_t>, grid, block, 0, st, pc, probs, dw_part,
-                       n_col_tiles, VB_all, Q_all, F, s, d_aux, aux_coeff, dw_ws, dz, (bf16_t *)S,
-                       lds_, col0, ncols, Nl, token_model, model_tokens, (bf16_t *)dzT, ldTz,
-                       s_by_first_pair);
-  else
-    hipLaunchKernelGGL(router_bwd_kernel<float>, grid, block, 0, st, pc, probs, dw_part,
-                       n_col_tiles, VB_all, Q_all, F, s, d_aux, aux_coeff, dw_ws, dz, (float *)S,
-                       lds_, col0, ncols, Nl, token_model, model_tokens, (bf16_t *)dzT, ldTz,
-                       s_by_first_pair);
   return hipGetLastError();
 }
 

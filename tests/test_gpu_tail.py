@@ -1,0 +1,29 @@
+"""GPU parity of the row-wise steps that share one launch behind the fused backward stage: ranks whose rows
+do not fill a 256-thread block evenly, pair counts that end inside one, with and without the sums over a
+token's pairs (top-2 on pair-grouped tiles makes them itself).  Against the oracle, usual tolerances."""
+import pytest
+
+from oracle import mixlora_oracle as orc
+from paper_2404_15159_amd import synth
+from paper_2404_15159_amd.runner import MixLoraFFN
+
+import parity_utils as pu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("base,T,N,k,r", [("llama2_7b", 37, 5, 3, 24), ("llama2_7b", 150, 8, 2, 40),
+                                          ("llama2_7b", 131, 8, 1, 56), ("llama2_7b", 401, 8, 2, 8),
+                                          ("llama2_7b", 203, 7, 4, 64), ("tiny_f32", 77, 5, 3, 24),
+                                          ("tiny_f32", 131, 4, 2, 40)])
+def test_backward_rows_match_oracle(base, T, N, k, r):
+    cfg = synth.scaled(synth.CONFIGS[base], name="tail", T=T, d=128, d_ff=344, N=N, k=k, r=r, alpha=2.0 * r)
+    print(f"case {base} T={T} N={N} k={k} r={r}", flush=True)
+    host = synth.make_inputs(cfg)
+    m = MixLoraFFN(cfg, host)
+    m.workspace.fill_(0xFF)          # NaN patterns: nothing may be read before it is written
+    m.forward()
+    m.backward(d_aux=1.0)
+    W = {n: host[n] for n in synth.WEIGHT_NAMES}
+    bw = orc.backward(host["x"], W, cfg.k, cfg.lora_scale, host["dy"], 1.0, cfg.aux_coeff, "top1")
+    pu.compare_all(m.results(), bw["forward"], bw, cfg)
