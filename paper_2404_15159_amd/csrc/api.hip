@@ -398,8 +398,8 @@ static int forward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mod
 
   // Shared frozen projections, once for all tokens (Algorithm 1 lines 7-8), and in the same
   // launch the LoRA A projections of every expert (rank-r, N*r output columns per bank).  None
-  // of them depends on the routing; in bf16 the router logits (Eq. 7) ride along as a fifth,
-  // N-column problem, so x is not read a second time.
+  // of them depends on the routing; the router logits (Eq. 7) ride along as a fifth, N-column problem, so
+  // x is not read a second time.
   {
     GemmProblem p[8] = {problem(T, f, ws + L.G, f, 0), problem(T, f, ws + L.U, f, 0),
                         problem(T, R, ws + L.Pg_all, R, 1), problem(T, R, ws + L.Pu_all, R, 1),
@@ -437,7 +437,7 @@ static int forward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mod
         HIP_TRY(launch_gemm(dt, p + 7, 1, st, gs));
       }
     } else {
-      HIP_TRY(dt == MIXLORA_BF16 ? launch_gemm(dt, joint, 5, st, js) : launch_gemm(dt, p, 4, st));
+      HIP_TRY(dt == MIXLORA_BF16 ? launch_gemm(dt, joint, 5, st, js) : launch_gemm(dt, p, 5, st));
     }
   }
   DoraArgs dargs{};
@@ -471,7 +471,7 @@ static int forward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mod
     fs.probs = probs, fs.w_out = topk_w, fs.w_ws = wts, fs.loss = aux_loss;
     fs.F = (float *)(ws + L.F), fs.P = (float *)(ws + L.P);
     fs.idx_out = topk_idx, fs.idx_ws = idx, fs.counts = (int32_t *)(ws + L.counts), fs.counts_out = expert_counts;
-    fs.first_counts = (int32_t *)(ws + L.first_counts), fs.offs = offs, fs.row_of_pair = row_of_pair;
+    fs.offs = offs, fs.row_of_pair = row_of_pair;
     fs.pair_of_row = pair_of_row, fs.tok_offs = (int32_t *)(ws + L.tok_offs);
     fs.model_tokens = (int32_t *)(ws + L.model_tokens);
     HIP_TRY_AS(PROF_FUSED_FWD, 3.0 * T * f * Eb, launch_few_stage(fs, st));
@@ -498,44 +498,52 @@ static int forward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mod
   }
   // Eq. 7 + Norm (Algorithm 1 lines 4-5)
   // s * B_down packed for the K-extension of the down GEMM; in bf16 also zeros for the
-  // block-sparse operand Qw, whose non-zero blocks the fused stage fills in.  In bf16 these
-  // re-layouts ride in the routing launch.
+  // block-sparse operand Qw, whose non-zero blocks the fused stage fills in.
   const RelayoutJob fwd_jobs[2] = {job_bank_cat(w->B_down, N, d, r, D.lora_scale, ws + L.Bd_cat, R, 0),
                                    pair_down ? job_zero_fill(ws + L.Qp, (size_t)kT * R * 2)
                                              : job_zero_fill(ws + L.Qw, (size_t)T * R * 2)};
-  if (dt == MIXLORA_BF16)
-    HIP_TRY_AS(PROF_ROUTING, (double)T * N * 8,
-               launch_route_logits_relayout((const float *)(ws + L.Z), N, T, N, k, probs, topk_idx,
-                                            topk_w, idx, wts, Nl, token_model, fwd_jobs, 2, st));
-  else
-    HIP_TRY_AS(PROF_ROUTING, (double)T * d * Eb, launch_router(dt, x, w->W_router, T, d, N, k, probs, topk_idx, topk_w, idx, wts, Nl,
-                          token_model, st));
   PairCtx pc{offs, pair_of_row, row_of_pair, wts, idx, T, N, k, r};
   // the per-pair stages on tokens grouped by expert pair (csrc/fused_pg.hip), when they apply
   const bool use_pg = dt == MIXLORA_BF16 && !pair_down && !dora && fused_pg_ok(pc, f);
   int32_t *pg_tok = (int32_t *)(ws + L.pg_tok), *pg_tiles = (int32_t *)(ws + L.pg_tiles),
           *pg_ntiles = (int32_t *)(ws + L.pg_ntiles);
-  // grouping of the pairs by expert and Eq. 8-9, one launch
-  if ((size_t)kT > GROUP_SINGLE_WG_PAIRS) {
-    HIP_TRY_AS(PROF_ROUTING, (double)kT * 16, launch_group_pairs_aux_multi(idx, T, N, k, (int32_t *)(ws + L.counts), expert_counts,
-                                         (int32_t *)(ws + L.first_counts), offs, row_of_pair,
-                                         pair_of_row, (int32_t *)(ws + L.tok_offs), probs,
-                                         D.aux_coeff, D.aux_mode, aux_loss, (float *)(ws + L.F),
-                                         (float *)(ws + L.P), Nl, token_model,
-                                         (int32_t *)(ws + L.model_tokens), ws + L.gp_scratch, st));
-    if (use_pg)
-      HIP_TRY_AS(PROF_ROUTING, (double)T * 12, launch_group_token_pairs(pc, pg_tok, pg_tiles, pg_ntiles, st));
+  const int njobs = dt == MIXLORA_BF16 ? 2 : 1;
+  if (route_group_ok(T, N, k)) {   // routing, grouping, Eq. 8-9 and the re-layouts, one launch or two
+    RouteGroup rg{};
+    rg.Z = (const float *)(ws + L.Z), rg.token_model = token_model;
+    rg.T = T, rg.N = N, rg.Nl = Nl, rg.k = k, rg.mode = D.aux_mode, rg.coeff = D.aux_coeff;
+    rg.probs = probs, rg.w_out = topk_w, rg.w_ws = wts, rg.loss = aux_loss;
+    rg.F = (float *)(ws + L.F), rg.P = (float *)(ws + L.P);
+    rg.idx_out = topk_idx, rg.idx_ws = idx, rg.counts = (int32_t *)(ws + L.counts), rg.counts_out = expert_counts;
+    rg.offs = offs, rg.row_of_pair = row_of_pair;
+    rg.pair_of_row = pair_of_row, rg.tok_offs = (int32_t *)(ws + L.tok_offs);
+    rg.model_tokens = (int32_t *)(ws + L.model_tokens);
+    if (use_pg) rg.pg_tok = pg_tok, rg.pg_tiles = pg_tiles, rg.pg_ntiles = pg_ntiles;
+    HIP_TRY_AS(PROF_ROUTING, (double)T * N * 8 + (double)kT * 16 + (use_pg ? (double)T * 12 : 0.0),
+               launch_route_group(dt, rg, fwd_jobs, njobs, st));
   } else {
-    // (Eq. 8-9 and the tokens' grouping by expert pair run as further workgroups of the launch)
-    HIP_TRY_AS(PROF_ROUTING, (double)kT * 16 + (use_pg ? (double)T * 12 : 0.0),
-               launch_group_pairs_aux(idx, T, N, k, (int32_t *)(ws + L.counts), expert_counts,
-                                      (int32_t *)(ws + L.first_counts), offs, row_of_pair, pair_of_row,
-                                      (int32_t *)(ws + L.tok_offs), probs, D.aux_coeff, D.aux_mode,
-                                      aux_loss, (float *)(ws + L.F), (float *)(ws + L.P), Nl,
-                                      token_model, (int32_t *)(ws + L.model_tokens),
-                                      use_pg ? pg_tok : nullptr, pg_tiles, pg_ntiles, st));
+    HIP_TRY_AS(PROF_ROUTING, (double)T * N * 8,
+               launch_route_logits_relayout(dt, (const float *)(ws + L.Z), N, T, N, k, probs, topk_idx, topk_w, idx, wts,
+                                            Nl, token_model, fwd_jobs, njobs, st));
+    // grouping of the pairs by expert and Eq. 8-9, one launch
+    if ((size_t)kT > GROUP_SINGLE_WG_PAIRS) {
+      HIP_TRY_AS(PROF_ROUTING, (double)kT * 16, launch_group_pairs_aux_multi(idx, T, N, k, (int32_t *)(ws + L.counts), expert_counts,
+                                           (int32_t *)(ws + L.first_counts), offs, row_of_pair,
+                                           pair_of_row, (int32_t *)(ws + L.tok_offs), probs,
+                                           D.aux_coeff, D.aux_mode, aux_loss, (float *)(ws + L.F),
+                                           (float *)(ws + L.P), Nl, token_model,
+                                           (int32_t *)(ws + L.model_tokens), ws + L.gp_scratch, st));
+      if (use_pg)
+        HIP_TRY_AS(PROF_ROUTING, (double)T * 12, launch_group_token_pairs(pc, pg_tok, pg_tiles, pg_ntiles, st));
+    } else {
+      HIP_TRY_AS(PROF_ROUTING, (double)kT * 16,
+                 launch_group_pairs_aux(idx, T, N, k, (int32_t *)(ws + L.counts), expert_counts,
+                                        (int32_t *)(ws + L.first_counts), offs, row_of_pair, pair_of_row,
+                                        (int32_t *)(ws + L.tok_offs), probs, D.aux_coeff, D.aux_mode,
+                                        aux_loss, (float *)(ws + L.F), (float *)(ws + L.P), Nl,
+                                        token_model, (int32_t *)(ws + L.model_tokens), st));
+    }
   }
-  if (dt != MIXLORA_BF16) HIP_TRY_AS(PROF_OTHER, 0, launch_relayout(dt, fwd_jobs, 1, st));
   if (pair_down) {
     // The paper's schedules (Figure 3): every expert runs its own frozen products on its slice of
     // tokens.  (a) unshared: gate and up on the gathered token rows, k rows per token;

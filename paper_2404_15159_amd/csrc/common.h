@@ -114,7 +114,7 @@ int prof_end();
 int prof_kind(int kind, double *ms_total, int *launches, double *work_total);
 
 // ---- few tokens (csrc/fused_few.hip; the rank term also in csrc/gemm.hip's row kernel) -----------
-constexpr int FEW_MAX_TOKENS = 128, FEW_MAX_PAIRS = 256, FEW_MAX_EXPERTS = 32, FEW_MAX_K = 4;
+constexpr int FEW_MAX_TOKENS = 128, FEW_MAX_PAIRS = 256, FEW_MAX_EXPERTS = 32;
 bool few_pairs_ok(int T, int N, int k, int r);
 int few_column_blocks(int f);
 size_t few_part_floats(int f, int kT, int r);   // floats of Q_part
@@ -131,8 +131,7 @@ struct FewStage {
   bf16_t *a_comb, *a_grp;   // a_grp may be NULL
   float *Q_part;
   float *probs, *w_out, *w_ws, *loss, *F, *P;
-  int32_t *idx_out, *idx_ws, *counts, *counts_out, *first_counts, *offs, *row_of_pair, *pair_of_row, *tok_offs,
-      *model_tokens;
+  int32_t *idx_out, *idx_ws, *counts, *counts_out, *offs, *row_of_pair, *pair_of_row, *tok_offs, *model_tokens;
 };
 hipError_t launch_few_stage(const FewStage &a, hipStream_t st);
 // The rank-r term of the down projection from the stage's partial sums; writes Q_all like the other stages.
@@ -181,32 +180,34 @@ __device__ __forceinline__ void few_rank_sums(const FewRank &a, int t, bool keep
 // N experts in all; with several adapters (token_model != NULL) token t is routed among the Nl
 // experts [token_model[t] * Nl, ... + Nl) of its adapter: probs is 0 elsewhere, idx_out is the
 // index inside the adapter, idx_ws the index among all N.
-hipError_t launch_router(int dtype, const void *x, const void *W_router, int T, int d, int N,
-                         int k, float *probs, int32_t *idx_out, float *w_out, int32_t *idx_ws,
-                         float *w_ws, int Nl, const int32_t *token_model, hipStream_t st);
-// Same routing from logits Z[t, n] (row pitch ldz) that a GEMM launch produced.
+// Routing from logits Z[t, n] (row pitch ldz) that a GEMM launch produced, plus weight re-layout jobs.
 struct RelayoutJob;
-// routing from logits plus weight re-layout jobs (bf16 storage) in one launch
-hipError_t launch_route_logits_relayout(const float *Z, int ldz, int T, int N, int k, float *probs,
+hipError_t launch_route_logits_relayout(int dtype, const float *Z, int ldz, int T, int N, int k, float *probs,
                                         int32_t *idx_out, float *w_out, int32_t *idx_ws,
                                         float *w_ws, int Nl, const int32_t *token_model,
                                         const RelayoutJob *jobs, int njobs, hipStream_t st);
-hipError_t launch_route_logits(const float *Z, int ldz, int T, int N, int k, float *probs,
-                               int32_t *idx_out, float *w_out, int32_t *idx_ws, float *w_ws,
-                               int Nl, const int32_t *token_model, hipStream_t st);
-// Stable grouping of the k*T pairs by expert: counts[N], first_counts[N] (slot-0 histogram),
-// offs[N+1], row_of_pair[kT], pair_of_row[kT].  counts_out may be NULL.
-hipError_t launch_group_pairs(const int32_t *idx, int T, int N, int k, int32_t *counts,
-                              int32_t *counts_out, int32_t *first_counts, int32_t *offs,
-                              int32_t *row_of_pair, int32_t *pair_of_row, hipStream_t st);
-// launch_group_pairs and launch_aux_loss (without dprobs) in one launch; tok_offs gets {0, T}
+// Routing from logits Z [T, N], grouping as in launch_group_pairs_aux below (and of the tokens by expert pair with
+// pg_tok != NULL) and weight re-layout jobs, in one launch up to ROUTE_INLINE_TOKENS tokens, in two above.
+constexpr int ROUTE_MAX_K = 4, ROUTE_GROUP_MAX_PAIRS = 8192, ROUTE_GROUP_MAX_EXPERTS = 16, ROUTE_INLINE_TOKENS = 1024;
+struct RouteGroup {
+  const float *Z;
+  const int32_t *token_model;
+  int T, N, Nl, k, mode;
+  float coeff;
+  float *probs, *w_out, *w_ws, *loss, *F, *P;
+  int32_t *idx_out, *idx_ws, *counts, *counts_out, *offs, *row_of_pair, *pair_of_row, *tok_offs,
+      *model_tokens, *pg_tok, *pg_tiles, *pg_ntiles;
+};
+bool route_group_ok(int T, int N, int k);
+hipError_t launch_route_group(int dtype, const RouteGroup &a, const RelayoutJob *jobs, int njobs, hipStream_t st);
+// Stable grouping of the k*T pairs by expert: counts[N], first_counts[N] (slot-0 histogram), offs[N+1],
+// row_of_pair[kT], pair_of_row[kT], and launch_aux_loss (without dprobs); tok_offs gets {0, T}.
 hipError_t launch_group_pairs_aux(const int32_t *idx, int T, int N, int k, int32_t *counts,
                                   int32_t *counts_out, int32_t *first_counts, int32_t *offs,
                                   int32_t *row_of_pair, int32_t *pair_of_row, int32_t *tok_offs,
                                   const float *probs, float coeff, int mode, float *loss, float *F,
-                                  float *P, int Nl, const int32_t *token_model,
-                                  int32_t *model_tokens, int32_t *pg_tok, int32_t *pg_tiles,
-                                  int32_t *pg_ntiles, hipStream_t st);
+                                  float *P, int Nl, const int32_t *token_model, int32_t *model_tokens,
+                                  hipStream_t st);
 // The same over many workgroups, for long token batches (identical row maps; the probability
 // sums of Eq. 9 are added in a different, equally fixed order).  scratch:
 // group_pairs_scratch_bytes(T, k) bytes.

@@ -15,6 +15,7 @@
 // rank-r partial products (one per column block) in the closing launch costs 4 us more than in workgroups
 // of the down product's launch, where it is hidden.
 #include "fused_common.h"
+#include "route_lane.h"
 
 namespace mixlora {
 
@@ -23,64 +24,10 @@ constexpr int FEW_WAVES = 8;
 }  // namespace
 
 bool few_pairs_ok(int T, int N, int k, int r) {
-  return T <= FEW_MAX_TOKENS && T * k <= FEW_MAX_PAIRS && N <= FEW_MAX_EXPERTS && k <= FEW_MAX_K && r <= 16;
+  return T <= FEW_MAX_TOKENS && T * k <= FEW_MAX_PAIRS && N <= FEW_MAX_EXPERTS && k <= ROUTE_MAX_K && r <= 16;
 }
 int few_column_blocks(int f) { return (f + FT_SB - 1) / FT_SB; }
 size_t few_part_floats(int f, int kT, int r) { return (size_t)few_column_blocks(f) * kT * r; }
-
-// Softmax, top-k and renormalisation of one token by one lane, with the operations and their order of
-// route_token (csrc/router.hip), of which this is the serial form: sums over experts as a butterfly
-// would take them, ties to the lower index, kept experts closed, NaN ranked with -inf.
-template <int NMAX>
-__device__ __forceinline__ void route_lane(float (&z)[NMAX], int lo, int Nl, int k, float (&p)[NMAX],
-                                           int (&es)[FEW_MAX_K], float (&ws)[FEW_MAX_K]) {
-  float sum[NMAX];
-  float zmax = -INFINITY;
-#pragma unroll
-  for (int n = 0; n < NMAX; n++) {
-    if (n < lo || n >= lo + Nl) z[n] = -INFINITY;
-    zmax = fmaxf(zmax, z[n]);
-  }
-#pragma unroll
-  for (int n = 0; n < NMAX; n++) p[n] = sum[n] = n >= lo && n < lo + Nl ? expf(z[n] - zmax) : 0.f;
-#pragma unroll
-  for (int o = NMAX / 2; o > 0; o >>= 1)
-#pragma unroll
-    for (int n = 0; n < o; n++) sum[n] += sum[n + o];
-  unsigned open = 0;
-#pragma unroll
-  for (int n = 0; n < NMAX; n++) {
-    p[n] /= sum[0];
-    if (!(z[n] == z[n])) z[n] = -INFINITY;
-    if (n >= lo && n < lo + Nl) open |= 1u << n;
-  }
-  float ksum = 0.f;
-#pragma unroll
-  for (int j = 0; j < FEW_MAX_K; j++) {
-    es[j] = 0;
-    ws[j] = 0.f;
-    if (j < k) {
-      float m = -INFINITY;
-#pragma unroll
-      for (int n = 0; n < NMAX; n++)
-        if ((open >> n) & 1) m = fmaxf(m, z[n]);
-      int e = -1;
-      float pe = 0.f;
-#pragma unroll
-      for (int n = NMAX - 1; n >= 0; n--)
-        if (((open >> n) & 1) && z[n] == m) {
-          e = n;
-          pe = p[n];
-        }
-      open &= ~(1u << e);
-      ksum += pe;
-      es[j] = e;
-      ws[j] = pe;
-    }
-  }
-#pragma unroll
-  for (int j = 0; j < FEW_MAX_K; j++) ws[j] /= ksum;
-}
 
 template <int NMAX>
 __global__ __launch_bounds__(FEW_WAVES * 64) void few_stage_kernel(FewStage a, int nblk) {
@@ -95,14 +42,15 @@ __global__ __launch_bounds__(FEW_WAVES * 64) void few_stage_kernel(FewStage a, i
 
   // ---- routing: thread t, token t
   if (tid < T) {
-    float z[NMAX], p[NMAX], ws[FEW_MAX_K];
-    int es[FEW_MAX_K];
+    float z[NMAX], p[NMAX], ws[ROUTE_MAX_K];
+    int es[ROUTE_MAX_K];
 #pragma unroll
     for (int n = 0; n < NMAX; n++) z[n] = a.Z[(int64_t)tid * N + (n < N ? n : 0)];
     const int lo = a.token_model ? a.token_model[tid] * a.Nl : 0;
-    route_lane<NMAX>(z, lo, a.Nl, k, p, es, ws);
+    if (meta) route_lane<NMAX, true>(z, lo, a.Nl, k, p, es, ws);
+    else route_lane<NMAX, false>(z, lo, a.Nl, k, p, es, ws);
 #pragma unroll
-    for (int j = 0; j < FEW_MAX_K; j++)
+    for (int j = 0; j < ROUTE_MAX_K; j++)
       if (j < k) {
         eid[tid * k + j] = es[j];
         wgt[tid * k + j] = ws[j];
@@ -167,7 +115,6 @@ __global__ __launch_bounds__(FEW_WAVES * 64) void few_stage_kernel(FewStage a, i
       }
       if (lane == 0) {
         a.counts[ex] = a.counts_out[ex] = n;
-        a.first_counts[ex] = fc;
         a.offs[ex] = row0;
         if (ex % a.Nl == 0) a.model_tokens[ex / a.Nl] = Tm;
         const bool top1 = a.mode == MIXLORA_AUX_TOP1;
@@ -346,9 +293,9 @@ __global__ __launch_bounds__(256) void few_finish_kernel(FewRank a, const float 
   const bool in = c < d;   // d is even
   const int cr = in ? c : 0;
   const int r = a.r;
-  bf16x8_t b[FEW_MAX_K][2][2];   // [slot][column][half of the rank]
+  bf16x8_t b[ROUTE_MAX_K][2][2];   // [slot][column][half of the rank]
 #pragma unroll
-  for (int j = 0; j < FEW_MAX_K; j++)
+  for (int j = 0; j < ROUTE_MAX_K; j++)
     if (j < a.k) {
       const bf16_t *src = a.B_down + ((int64_t)a.idx[t * a.k + j] * d + cr) * r;
 #pragma unroll
@@ -365,7 +312,7 @@ __global__ __launch_bounds__(256) void few_finish_kernel(FewRank a, const float 
   }
   const float *sq = a.sums + t * FEW_RANK_SUMS;
 #pragma unroll
-  for (int j = 0; j < FEW_MAX_K; j++)
+  for (int j = 0; j < ROUTE_MAX_K; j++)
     if (j < a.k)
 #pragma unroll
       for (int h = 0; h < 2; h++)

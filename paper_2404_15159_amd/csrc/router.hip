@@ -3,6 +3,7 @@
 // and prefix counts, and the auxiliary load-balance loss (Eq. 8-9).
 #include "common.h"
 #include "relayout_body.h"
+#include "route_lane.h"
 
 namespace mixlora {
 
@@ -63,97 +64,10 @@ __device__ __forceinline__ void route_token(float z, int lane, int t, int lo, in
   }
 }
 
-// One wavefront per token.  Lane l accumulates, for every expert, the products of the 8-wide
-// chunks l, l+64, ... of the row; a butterfly then gives every lane the full logit.
-template <typename E, int NMAX>
-__global__ __launch_bounds__(256) void router_kernel(const E *__restrict__ x,
-                                                     const E *__restrict__ Wr, int T, int d,
-                                                     int N, int k, float *__restrict__ probs,
-                                                     int32_t *__restrict__ idx_out,
-                                                     float *__restrict__ w_out,
-                                                     int32_t *__restrict__ idx_ws,
-                                                     float *__restrict__ w_ws, int Nl,
-                                                     const int32_t *__restrict__ token_model) {
-  __shared__ float zbuf[4][64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int t = blockIdx.x * 4 + wave;
-  if (t >= T) return;   // whole wave leaves together; no block-wide barrier below
-  float acc[NMAX];
-#pragma unroll
-  for (int e = 0; e < NMAX; e++) acc[e] = 0.f;
-  const E *xr = x + (int64_t)t * d;
-  for (int c = lane * 8; c < d; c += 64 * 8) {
-    Vec8<E> xv;
-    xv.load(xr + c);
-#pragma unroll
-    for (int e = 0; e < NMAX; e++) {
-      if (e < N) {
-        Vec8<E> wv;
-        wv.load(Wr + (int64_t)e * d + c);
-#pragma unroll
-        for (int i = 0; i < 8; i++) acc[e] = fmaf(xv.get(i), wv.get(i), acc[e]);
-      }
-    }
-  }
-#pragma unroll
-  for (int e = 0; e < NMAX; e++) {
-    const float s = wave_sum(acc[e]);
-    if (lane == e) zbuf[wave][e] = s;
-  }
-  __builtin_amdgcn_wave_barrier();
-  const float z = lane < N ? zbuf[wave][lane] : -INFINITY;
-  const int lo = token_model ? token_model[t] * Nl : 0;
-  route_token(z, lane, t, lo, Nl, N, k, probs, idx_out, w_out, idx_ws, w_ws);
-}
-
-// Routing from logits that a GEMM launch has already produced: Z[t, n], row pitch ldz.
-__global__ __launch_bounds__(256) void route_logits_kernel(const float *__restrict__ Z, int ldz,
-                                                           int T, int N, int k,
-                                                           float *__restrict__ probs,
-                                                           int32_t *__restrict__ idx_out,
-                                                           float *__restrict__ w_out,
-                                                           int32_t *__restrict__ idx_ws,
-                                                           float *__restrict__ w_ws, int Nl,
-                                                           const int32_t *__restrict__ token_model) {
-  const int lane = threadIdx.x & 63;
-  const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (t >= T) return;
-  const float z = lane < N ? Z[(int64_t)t * ldz + lane] : -INFINITY;
-  const int lo = token_model ? token_model[t] * Nl : 0;
-  route_token(z, lane, t, lo, Nl, N, k, probs, idx_out, w_out, idx_ws, w_ws);
-}
-
+// Routing from logits that a GEMM launch has produced, Z[t, n] with row pitch ldz, a wave per token, and up to
+// RELAYOUT_MAX_JOBS weight re-layout jobs in the trailing workgroups of the launch: the re-layouts of a
+// forward pass depend on the weights only, and each of the two launches alone is dominated by its own latency.
 template <typename E>
-static hipError_t launch_router_t(const void *x, const void *Wr, int T, int d, int N, int k,
-                                  float *probs, int32_t *idx_out, float *w_out, int32_t *idx_ws,
-                                  float *w_ws, int Nl, const int32_t *token_model,
-                                  hipStream_t st) {
-  const dim3 grid((T + 3) / 4), block(256);
-  const E *xe = reinterpret_cast<const E *>(x), *we = reinterpret_cast<const E *>(Wr);
-#define MIXLORA_ROUTER(NM)                                                                    \
-  hipLaunchKernelGGL((router_kernel<E, NM>), grid, block, 0, st, xe, we, T, d, N, k, probs,   \
-                     idx_out, w_out, idx_ws, w_ws, Nl, token_model)
-  if (N <= 8) MIXLORA_ROUTER(8);
-  else if (N <= 16) MIXLORA_ROUTER(16);
-  else if (N <= 32) MIXLORA_ROUTER(32);
-  else MIXLORA_ROUTER(64);
-#undef MIXLORA_ROUTER
-  return hipGetLastError();
-}
-
-hipError_t launch_router(int dtype, const void *x, const void *W_router, int T, int d, int N,
-                         int k, float *probs, int32_t *idx_out, float *w_out, int32_t *idx_ws,
-                         float *w_ws, int Nl, const int32_t *token_model, hipStream_t st) {
-  return dtype == MIXLORA_BF16
-             ? launch_router_t<bf16_t>(x, W_router, T, d, N, k, probs, idx_out, w_out, idx_ws, w_ws,
-                                       Nl, token_model, st)
-             : launch_router_t<float>(x, W_router, T, d, N, k, probs, idx_out, w_out, idx_ws, w_ws,
-                                      Nl, token_model, st);
-}
-
-// The same routing with up to RELAYOUT_MAX_JOBS weight re-layout jobs (bf16) in the trailing
-// workgroups of the launch: the re-layouts of a forward pass depend on the weights only, and each
-// of the two launches alone is dominated by its own latency.
 __global__ __launch_bounds__(256) void route_logits_relayout_kernel(
     const float *__restrict__ Z, int ldz, int T, int N, int k, float *__restrict__ probs,
     int32_t *__restrict__ idx_out, float *__restrict__ w_out, int32_t *__restrict__ idx_ws,
@@ -161,7 +75,7 @@ __global__ __launch_bounds__(256) void route_logits_relayout_kernel(
     RelayoutBatch batch, int rblocks) {
   if ((int)blockIdx.x >= route_blocks) {   // workgroup-uniform
     const int b = blockIdx.x - route_blocks;
-    relayout_body<bf16_t>(batch.job[b / rblocks], b % rblocks, rblocks);
+    relayout_body<E>(batch.job[b / rblocks], b % rblocks, rblocks);
     return;
   }
   const int lane = threadIdx.x & 63;
@@ -172,7 +86,7 @@ __global__ __launch_bounds__(256) void route_logits_relayout_kernel(
   route_token(z, lane, t, lo, Nl, N, k, probs, idx_out, w_out, idx_ws, w_ws);
 }
 
-hipError_t launch_route_logits_relayout(const float *Z, int ldz, int T, int N, int k, float *probs,
+hipError_t launch_route_logits_relayout(int dtype, const float *Z, int ldz, int T, int N, int k, float *probs,
                                         int32_t *idx_out, float *w_out, int32_t *idx_ws,
                                         float *w_ws, int Nl, const int32_t *token_model,
                                         const RelayoutJob *jobs, int njobs, hipStream_t st) {
@@ -182,17 +96,13 @@ hipError_t launch_route_logits_relayout(const float *Z, int ldz, int T, int N, i
   const int64_t rblocks = relayout_blocks(jobs, njobs);
   if (rblocks == 0) return hipErrorInvalidValue;
   const int route_blocks = (T + 3) / 4;
-  hipLaunchKernelGGL(route_logits_relayout_kernel, dim3((unsigned)(route_blocks + njobs * rblocks)),
-                     dim3(256), 0, st, Z, ldz, T, N, k, probs, idx_out, w_out, idx_ws, w_ws, Nl,
-                     token_model, route_blocks, b, (int)rblocks);
-  return hipGetLastError();
-}
-
-hipError_t launch_route_logits(const float *Z, int ldz, int T, int N, int k, float *probs,
-                               int32_t *idx_out, float *w_out, int32_t *idx_ws, float *w_ws,
-                               int Nl, const int32_t *token_model, hipStream_t st) {
-  hipLaunchKernelGGL(route_logits_kernel, dim3((T + 3) / 4), dim3(256), 0, st, Z, ldz, T, N, k,
-                     probs, idx_out, w_out, idx_ws, w_ws, Nl, token_model);
+  const dim3 grid((unsigned)(route_blocks + njobs * rblocks)), block(256);
+  if (dtype == MIXLORA_BF16)
+    hipLaunchKernelGGL(route_logits_relayout_kernel<bf16_t>, grid, block, 0, st, Z, ldz, T, N, k, probs, idx_out, w_out,
+                       idx_ws, w_ws, Nl, token_model, route_blocks, b, (int)rblocks);
+  else
+    hipLaunchKernelGGL(route_logits_relayout_kernel<float>, grid, block, 0, st, Z, ldz, T, N, k, probs, idx_out, w_out,
+                       idx_ws, w_ws, Nl, token_model, route_blocks, b, (int)rblocks);
   return hipGetLastError();
 }
 
@@ -292,22 +202,6 @@ __device__ __forceinline__ void group_pairs_block(
     const int p = p0 + lane;
     place_step(p < hi ? idx[p] : -1, p);
   }
-}
-
-__global__ __launch_bounds__(GP_WAVES * 64) void group_pairs_kernel(
-    const int32_t *__restrict__ idx, int nP, int N, int k, int32_t *__restrict__ counts,
-    int32_t *__restrict__ counts_out, int32_t *__restrict__ first_counts,
-    int32_t *__restrict__ offs, int32_t *__restrict__ row_of_pair,
-    int32_t *__restrict__ pair_of_row) {
-  group_pairs_block(idx, nP, N, k, counts, counts_out, first_counts, offs, row_of_pair, pair_of_row);
-}
-
-hipError_t launch_group_pairs(const int32_t *idx, int T, int N, int k, int32_t *counts,
-                              int32_t *counts_out, int32_t *first_counts, int32_t *offs,
-                              int32_t *row_of_pair, int32_t *pair_of_row, hipStream_t st) {
-  hipLaunchKernelGGL(group_pairs_kernel, dim3(1), dim3(GP_WAVES * 64), 0, st, idx, T * k, N, k,
-                     counts, counts_out, first_counts, offs, row_of_pair, pair_of_row);
-  return hipGetLastError();
 }
 
 // ---- auxiliary loss (Eq. 8-9) -------------------------------------------------------------
@@ -477,10 +371,9 @@ hipError_t launch_group_token_pairs(const PairCtx &pc, int32_t *tok_of_pos, int3
   return hipGetLastError();
 }
 
-// Grouping and auxiliary loss of one forward pass in one launch of a few workgroups, each bound
-// by its own latency and independent of the others: the grouping of the pairs by expert (which
-// also writes the two-entry offsets {0, T} that let the grouped outer-product kernel treat all
-// tokens as one group), Eq. 8-9, and with pg_tok != NULL the grouping of the tokens by expert pair.
+// Grouping and auxiliary loss of one forward pass, for experts and slots that route_group_kernel does not take:
+// the grouping of the pairs by expert (which also writes the two-entry offsets {0, T} that let the grouped
+// outer-product kernel treat all tokens as one group) and Eq. 8-9, a workgroup each.
 __global__ __launch_bounds__(GP_WAVES * 64) void group_pairs_aux_kernel(
     const int32_t *__restrict__ idx, int T, int N, int k, int32_t *__restrict__ counts,
     int32_t *__restrict__ counts_out, int32_t *__restrict__ first_counts,
@@ -488,18 +381,14 @@ __global__ __launch_bounds__(GP_WAVES * 64) void group_pairs_aux_kernel(
     int32_t *__restrict__ pair_of_row, int32_t *__restrict__ tok_offs,
     const float *__restrict__ probs, float coeff, int mode, float *__restrict__ loss,
     float *__restrict__ F_out, float *__restrict__ P_out, int Nl,
-    const int32_t *__restrict__ token_model, int32_t *__restrict__ model_tokens,
-    int32_t *__restrict__ pg_tok, int32_t *__restrict__ pg_tiles, int32_t *__restrict__ pg_ntiles) {
+    const int32_t *__restrict__ token_model, int32_t *__restrict__ model_tokens) {
   static_assert(GP_WAVES * 64 == 1024, "the auxiliary-loss block code assumes 1024 threads");
-  static_assert(PG_GWAVES == GP_WAVES, "both block routines run with the same workgroup size");
   // independent pieces of work, one workgroup each (all workgroup-uniform branches)
   if (blockIdx.x == 0) {
     group_pairs_block(idx, T * k, N, k, counts, counts_out, first_counts, offs, row_of_pair, pair_of_row);
     if (threadIdx.x == 0) { tok_offs[0] = 0; tok_offs[1] = T; }
-  } else if (blockIdx.x == 1) {
+  } else {
     aux_loss_block(probs, idx, T, N, k, coeff, mode, loss, F_out, P_out, Nl, token_model, model_tokens);
-  } else if (pg_tok) {
-    group_token_pairs_block(idx, T, N, pg_tok, pg_tiles, pg_ntiles);
   }
 }
 
@@ -508,12 +397,394 @@ hipError_t launch_group_pairs_aux(const int32_t *idx, int T, int N, int k, int32
                                   int32_t *row_of_pair, int32_t *pair_of_row, int32_t *tok_offs,
                                   const float *probs, float coeff, int mode, float *loss, float *F,
                                   float *P, int Nl, const int32_t *token_model,
-                                  int32_t *model_tokens, int32_t *pg_tok, int32_t *pg_tiles,
-                                  int32_t *pg_ntiles, hipStream_t st) {
-  hipLaunchKernelGGL(group_pairs_aux_kernel, dim3(pg_tok ? 3 : 2), dim3(GP_WAVES * 64), 0, st, idx,
+                                  int32_t *model_tokens, hipStream_t st) {
+  hipLaunchKernelGGL(group_pairs_aux_kernel, dim3(2), dim3(GP_WAVES * 64), 0, st, idx,
                      T, N, k, counts, counts_out, first_counts, offs, row_of_pair, pair_of_row,
-                     tok_offs, probs, coeff, mode, loss, F, P, Nl, token_model, model_tokens,
-                     pg_tok, pg_tiles, pg_ntiles);
+                     tok_offs, probs, coeff, mode, loss, F, P, Nl, token_model, model_tokens);
+  return hipGetLastError();
+}
+
+// ---- grouping and auxiliary loss, and the routing with them -------------------------------------------
+// Up to 8192 pairs of at most 16 experts, a workgroup for each independent piece: the pairs' grouping by
+// expert, Eq. 8-9, the tokens' grouping by expert pair.  Bound by latency: wave w owns a contiguous range of
+// tokens, 64 at a time, the next ones on their way, and counts all experts at once in bytes of two words ; a
+// token has an expert at most once, so ascending tokens are ascending pairs.
+// ROUTE: every workgroup routes all tokens itself (a lane per token, csrc/route_lane.h), which up to
+// ROUTE_INLINE_TOKENS of at most 8 experts is cheaper than a launch of its own (forwards of a 512 x 1536 block: 300
+// tokens 52.4 -> 50.3 us, 1000 63.8 -> 62.9; 16 experts 73.9 -> 76.0); at 4096 tokens it is not (35 us against
+// 6), a CU being slower at it than the chip.  The forward's weight re-layouts ride behind the launch that routes.
+// The grouping launch at 4096 tokens and 8 experts, loops of ballots before: 16-19 -> 10 us.
+constexpr int RG_WAVES = 16;
+
+bool route_group_ok(int T, int N, int k) {
+  return T * k <= ROUTE_GROUP_MAX_PAIRS && N <= ROUTE_GROUP_MAX_EXPERTS && k <= ROUTE_MAX_K;
+}
+
+// each(token, valid, first expert of its adapter, probabilities, kept experts, weights) over a range of tokens, by
+// a whole wave; probabilities with ROUTE and PROBS only, weights with ROUTE only
+template <int NMAX, bool ROUTE, bool PROBS, typename F>
+__device__ __forceinline__ void token_range(const RouteGroup &a, int lo, int hi, F each) {
+  const int lane = threadIdx.x & 63;
+  float z[2][NMAX], w[ROUTE_MAX_K];
+  int e[2][ROUTE_MAX_K];
+  auto load = [&](int t0, float (&v)[NMAX], int (&es)[ROUTE_MAX_K]) {
+    const int t = t0 + lane < a.T ? t0 + lane : a.T - 1;
+    if constexpr (ROUTE) {
+      if (a.N == NMAX) {
+#pragma unroll
+        for (int n = 0; n < NMAX; n += 4) {
+          const float4 q = *reinterpret_cast<const float4 *>(a.Z + (int64_t)t * NMAX + n);
+          v[n] = q.x, v[n + 1] = q.y, v[n + 2] = q.z, v[n + 3] = q.w;
+        }
+      } else {
+#pragma unroll
+        for (int n = 0; n < NMAX; n++) v[n] = a.Z[(int64_t)t * a.N + (n < a.N ? n : 0)];
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < ROUTE_MAX_K; j++) es[j] = a.idx_ws[(int64_t)t * a.k + (j < a.k ? j : 0)];
+    }
+  };
+  if (lo < hi) load(lo, z[0], e[0]);
+  for (int t0 = lo; t0 < hi; t0 += 64) {
+    if (t0 + 64 < hi) load(t0 + 64, z[1], e[1]);
+    const int t = t0 + lane;
+    const bool valid = t < hi;
+    const int first = a.token_model ? a.token_model[valid ? t : lo] * a.Nl : 0;
+    if constexpr (ROUTE) {
+      float p[NMAX];
+      route_lane<NMAX, PROBS>(z[0], first, a.Nl, a.k, p, e[0], w);
+      each(t, valid, first, p, e[0], w);
+    } else {
+      each(t, valid, first, z[0], e[0], w);
+    }
+#pragma unroll
+    for (int n = 0; n < NMAX; n++) z[0][n] = z[1][n];
+#pragma unroll
+    for (int j = 0; j < ROUTE_MAX_K; j++) e[0][j] = e[1][j];
+  }
+}
+
+// A counter for each of up to 16 experts in bytes of two words: a lane adds its choices (at most eight tokens'
+// in a range), a scan or a sum adds the lanes, all experts at once.
+__device__ __forceinline__ unsigned long long lanes_sum(unsigned long long v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
+__device__ __forceinline__ unsigned long long lanes_scan(unsigned long long v) {   // inclusive
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const unsigned long long u = __shfl_up(v, o, 64);
+    if (lane >= o) v += u;
+  }
+  return v;
+}
+template <int NMAX> struct Counters {
+  unsigned long long v0 = 0, v1 = 0;
+  __device__ __forceinline__ void add(int n) {
+    const unsigned long long b = 1ull << ((n & 7) * 8);
+    if constexpr (NMAX > 8) v1 += n & 8 ? b : 0;
+    v0 += NMAX > 8 && (n & 8) ? 0 : b;
+  }
+  __device__ __forceinline__ int get(int n) const { return (int)(((NMAX > 8 && (n & 8) ? v1 : v0) >> ((n & 7) * 8)) & 255); }
+  __device__ __forceinline__ void scan() {
+    v0 = lanes_scan(v0);
+    if constexpr (NMAX > 8) v1 = lanes_scan(v1);
+  }
+  // the wave's total of expert n (16 bits: up to 512), for lane n
+  __device__ __forceinline__ int total(int n) const {
+    constexpr unsigned long long EVEN = 0x00ff00ff00ff00ffull;
+    unsigned long long x = lanes_sum(v0 & EVEN);
+    const unsigned long long y = lanes_sum((v0 >> 8) & EVEN);
+    if (n & 1) x = y;
+    if constexpr (NMAX > 8) {
+      const unsigned long long z = lanes_sum(v1 & EVEN), w = lanes_sum((v1 >> 8) & EVEN);
+      if (n & 8) x = n & 1 ? w : z;
+    }
+    return (int)((x >> ((n & 6) * 8)) & 0xffff);
+  }
+};
+
+template <typename E, int NMAX, bool ROUTE>
+__global__ __launch_bounds__(RG_WAVES * 64) void route_group_kernel(RouteGroup a, RelayoutBatch batch, int rblocks) {
+  __shared__ uint16_t tok[ROUTE_GROUP_MAX_PAIRS];            // kept experts, 4 bits a slot; or the pair's group
+  __shared__ int cnt[RG_WAVES][PG_GROUPS];
+  __shared__ int wtot[2][RG_WAVES];
+  if constexpr (ROUTE) {
+    if (blockIdx.x >= 3) {
+      const int b = blockIdx.x - 3;
+      relayout_body<E>(batch.job[b / rblocks], b % rblocks, rblocks);
+      return;
+    }
+  }
+  const int T = a.T, N = a.N, k = a.k, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int per = (((T + RG_WAVES - 1) / RG_WAVES) + 63) & ~63;   // at most 512: eight tokens a lane
+  const int lo = wave * per < T ? wave * per : T, hi = lo + per < T ? lo + per : T;
+  const unsigned long long lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+
+  if (blockIdx.x == 0) {   // ---- pairs by expert
+    Counters<NMAX> c;   // this wave's tokens with an expert
+    token_range<NMAX, ROUTE, false>(a, lo, hi, [&](int t, bool valid, int first, const float (&)[NMAX],
+                                                   const int (&es)[ROUTE_MAX_K], const float (&w)[ROUTE_MAX_K]) {
+      unsigned packed = 0;
+      if (!valid) return;
+#pragma unroll
+      for (int j = 0; j < ROUTE_MAX_K; j++)
+        if (j < k) {
+          c.add(es[j]);
+          packed |= (unsigned)es[j] << (4 * j);
+          if (ROUTE) {
+            const int64_t o = (int64_t)t * k + j;
+            a.idx_out[o] = es[j] - first;
+            a.w_out[o] = w[j];
+            a.idx_ws[o] = es[j];
+            a.w_ws[o] = w[j];
+          }
+        }
+      tok[t] = (uint16_t)packed;
+    });
+    const int own = c.total(lane & 15);
+    if (lane < N) cnt[wave][lane] = own;
+    __syncthreads();
+    if (wave == 0) {   // lane n: totals of expert n, first row, first row of every wave
+      int tot = 0, cw[RG_WAVES];
+#pragma unroll
+      for (int w = 0; w < RG_WAVES; w++) {
+        cw[w] = lane < N ? cnt[w][lane] : 0;
+        tot += cw[w];
+      }
+      int incl = tot;
+#pragma unroll
+      for (int o = 1; o < ROUTE_GROUP_MAX_EXPERTS; o <<= 1) {
+        const int v = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += v;
+      }
+      if (lane < N) {
+        a.counts[lane] = a.counts_out[lane] = tot;
+        a.offs[lane] = incl - tot;
+        if (lane == N - 1) a.offs[N] = incl;
+      }
+      int run = incl - tot;
+#pragma unroll
+      for (int w = 0; w < RG_WAVES; w++) {
+        if (lane < N) cnt[w][lane] = run;
+        run += cw[w];
+      }
+    }
+    if (tid == 0) {
+      a.tok_offs[0] = 0;
+      a.tok_offs[1] = T;
+    }
+    __syncthreads();
+    for (int t0 = lo; t0 < hi; t0 += 64) {
+      const int t = t0 + lane;
+      const bool valid = t < hi;
+      const unsigned packed = valid ? tok[t] : 0;
+      Counters<NMAX> s;   // tokens of this step up to this one, by expert
+#pragma unroll
+      for (int j = 0; j < ROUTE_MAX_K; j++)
+        if (j < k && valid) s.add((packed >> (4 * j)) & 15);
+      s.scan();
+#pragma unroll
+      for (int j = 0; j < ROUTE_MAX_K; j++)
+        if (j < k && valid) {
+          const int e = (packed >> (4 * j)) & 15, row = cnt[wave][e] + s.get(e) - 1;
+          a.row_of_pair[t * k + j] = row;
+          a.pair_of_row[row] = t * k + j;
+        }
+      s.v0 = __shfl(s.v0, 63, 64);
+      if constexpr (NMAX > 8) s.v1 = __shfl(s.v1, 63, 64);
+      if (lane < N) cnt[wave][lane] += s.get(lane);   // (LDS operations of a wave execute in order)
+    }
+  } else if (blockIdx.x == 1) {   // ---- probabilities and Eq. 8-9
+    float ps[NMAX];
+    Counters<NMAX> c;   // choices that F counts
+    const int M = N / a.Nl, slots = a.mode == MIXLORA_AUX_TOP1 ? 1 : k;
+    int *tm = &cnt[0][0], *ci = tm + 64;                                      // tokens by adapter; [waves][16]
+    float *fsum = reinterpret_cast<float *>(ci + RG_WAVES * 16);              // [waves][NMAX]
+#pragma unroll
+    for (int n = 0; n < NMAX; n++) ps[n] = 0.f;
+    if (tid < 64) tm[tid] = tid == 0 && !a.token_model ? T : 0;
+    __syncthreads();
+    if constexpr (!ROUTE) {
+      // the probabilities as one long run, a thread always at the same expert
+      const int G = RG_WAVES * 64 / N, en = tid % N, g = tid / N;
+      float *part = reinterpret_cast<float *>(tok), v = 0.f;
+      if (g < G) {
+#pragma unroll 8
+        for (int t = g; t < T; t += G) v += a.probs[(int64_t)t * N + en];
+      }
+      part[tid] = v;
+#pragma unroll 4
+      for (int t = tid; t < T; t += RG_WAVES * 64) {
+        for (int j = 0; j < slots; j++) c.add(a.idx_ws[(int64_t)t * k + j]);
+        if (a.token_model) atomicAdd(&tm[a.token_model[t]], 1);   // integer counts: order does not matter
+      }
+      __syncthreads();
+      if (wave < NMAX / 4) {   // wave w: experts 4 w .. 4 w + 3, 16 lanes each
+        const int n = wave * 4 + (lane >> 4);
+        float x = 0.f;
+        if (n < N)
+          for (int gg = lane & 15; gg < G; gg += 16) x += part[gg * N + n];
+#pragma unroll
+        for (int o = 8; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+        if ((lane & 15) == 0) fsum[n] = x;
+      }
+    } else token_range<NMAX, true, true>(a, lo, hi, [&](int t, bool valid, int first, const float (&p)[NMAX],
+                                                  const int (&es)[ROUTE_MAX_K], const float (&)[ROUTE_MAX_K]) {
+      if (!valid) return;
+#pragma unroll
+      for (int j = 0; j < ROUTE_MAX_K; j++)
+        if (j < slots) c.add(es[j]);
+      if (N == NMAX) {
+#pragma unroll
+        for (int n = 0; n < NMAX; n += 4)
+          *reinterpret_cast<float4 *>(a.probs + (int64_t)t * NMAX + n) = make_float4(p[n], p[n + 1], p[n + 2], p[n + 3]);
+      } else {
+#pragma unroll
+        for (int n = 0; n < NMAX; n++)
+          if (n < N) a.probs[(int64_t)t * N + n] = p[n];
+      }
+#pragma unroll
+      for (int n = 0; n < NMAX; n++) ps[n] += p[n];   // 0 past N
+      if (a.token_model) atomicAdd(&tm[first / a.Nl], 1);   // integer counts: order does not matter
+    });
+    const int own = c.total(lane & 15);
+    if (lane < 16) ci[wave * 16 + lane] = own;
+    if constexpr (ROUTE) {
+#pragma unroll
+      for (int n = 0; n < NMAX; n++) {
+        const float v = wave_sum(ps[n]);
+        if (lane == n) fsum[wave * NMAX + n] = v;
+      }
+    }
+    __syncthreads();
+    if (wave == 0) {
+      int ct = 0;
+      float st = 0.f;
+      for (int w = 0; w < RG_WAVES; w++) {
+        ct += lane < N ? ci[w * 16 + lane] : 0;
+        if (ROUTE || w == 0) st += lane < N ? fsum[w * NMAX + lane] : 0.f;
+      }
+      const int Tm = tm[lane < N ? lane / a.Nl : 0];
+      const float denom = a.mode == MIXLORA_AUX_TOP1 ? (float)Tm : (float)Tm * (float)k;
+      const float P = Tm > 0 ? st / (float)Tm : 0.f, F = Tm > 0 ? (float)ct / denom : 0.f;
+      if (lane < N) {
+        a.P[lane] = P;
+        a.F[lane] = F;
+      }
+      const float fp = F * P;
+      float acc = 0.f;   // lane m: the adapter's experts in ascending order
+      for (int n = 0; n < a.Nl; n++) acc += __shfl(fp, (lane < M ? lane : 0) * a.Nl + n, 64);
+      if (lane < M) {
+        a.loss[lane] = a.coeff * (float)a.Nl * acc;
+        a.model_tokens[lane] = tm[lane];
+      }
+    }
+  } else if (a.pg_tok) {   // ---- tokens by unordered expert pair (k = 2), as group_token_pairs_block
+    const int G = N * N;
+    for (int i = tid; i < RG_WAVES * PG_GROUPS; i += RG_WAVES * 64) (&cnt[0][0])[i] = 0;
+    __syncthreads();
+    token_range<NMAX, ROUTE, false>(a, lo, hi, [&](int t, bool valid, int, const float (&)[NMAX],
+                                                   const int (&es)[ROUTE_MAX_K], const float (&)[ROUTE_MAX_K]) {
+      const int gid = es[0] < es[1] ? es[0] * N + es[1] : es[1] * N + es[0];
+      if (valid) {
+        tok[t] = (uint16_t)gid;
+        atomicAdd(&cnt[wave][gid], 1);   // integer counts: order does not matter
+      }
+    });
+    __syncthreads();
+    int tot = 0, nt = 0, it = 0, in = 0;   // group tid: tokens and tiles, and their inclusive sums
+    if (tid < PG_GROUPS) {
+      if (tid < G)
+        for (int w = 0; w < RG_WAVES; w++) tot += cnt[w][tid];
+      nt = (tot + PG_TILE_ROWS - 1) / PG_TILE_ROWS;
+      it = tot;
+      in = nt;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int v = __shfl_up(it, o, 64), u = __shfl_up(in, o, 64);
+        if (lane >= o) {
+          it += v;
+          in += u;
+        }
+      }
+      if (lane == 63) {
+        wtot[0][wave] = it;
+        wtot[1][wave] = in;
+      }
+    }
+    __syncthreads();
+    if (tid < G) {
+      for (int w = 0; w < wave; w++) {
+        it += wtot[0][w];
+        in += wtot[1][w];
+      }
+      const int off = it - tot, tb = in - nt;
+      int run = off;
+      for (int w = 0; w < RG_WAVES; w++) {
+        const int c = cnt[w][tid];
+        cnt[w][tid] = run;
+        run += c;
+      }
+      for (int i = 0; i < nt; i++) {
+        int32_t *ti = a.pg_tiles + (int64_t)(tb + i) * 4;
+        ti[0] = tid;
+        ti[1] = off + i * PG_TILE_ROWS;
+        ti[2] = tot - i * PG_TILE_ROWS < PG_TILE_ROWS ? tot - i * PG_TILE_ROWS : PG_TILE_ROWS;
+        ti[3] = 0;
+      }
+      if (tid == G - 1) a.pg_ntiles[0] = in;
+    }
+    __syncthreads();
+    for (int t0 = lo; t0 < hi; t0 += 64) {
+      const int t = t0 + lane;
+      const bool valid = t < hi;
+      const int gid = valid ? tok[t] : 0;
+      unsigned long long m = __ballot(valid);   // lanes of the same group: one ballot per bit of its id
+#pragma unroll
+      for (int b = 0; b < 8; b++) {
+        const unsigned long long has = __ballot(valid && ((gid >> b) & 1));
+        m &= ((gid >> b) & 1) ? has : ~has;
+      }
+      if (valid) {
+        // every lane of the group reads the group's next free position (one LDS instruction for
+        // the whole wavefront), then the group's first lane moves it on
+        const int start = cnt[wave][gid];
+        const int pos = start + __popcll(m & lt);
+        if ((m & lt) == 0) cnt[wave][gid] = start + __popcll(m);
+        a.pg_tok[pos] = t;
+      }
+    }
+  }
+}
+
+hipError_t launch_route_group(int dtype, const RouteGroup &a, const RelayoutJob *jobs, int njobs, hipStream_t st) {
+  if (!route_group_ok(a.T, a.N, a.k) || (a.pg_tok && a.k != 2) || njobs < 1 || njobs > RELAYOUT_MAX_JOBS)
+    return hipErrorInvalidValue;
+  RelayoutBatch b;
+  for (int i = 0; i < RELAYOUT_MAX_JOBS; i++) b.job[i] = jobs[i < njobs ? i : 0];
+  int64_t rblocks = relayout_blocks(jobs, njobs);
+  if (rblocks == 0) return hipErrorInvalidValue;
+  const dim3 block(RG_WAVES * 64);
+  const bool small = a.N <= 8;
+  if (a.T > ROUTE_INLINE_TOKENS || !small) {
+    const hipError_t e = launch_route_logits_relayout(dtype, a.Z, a.N, a.T, a.N, a.k, a.probs, a.idx_out, a.w_out, a.idx_ws,
+                                                      a.w_ws, a.Nl, a.token_model, jobs, njobs, st);
+    if (e != hipSuccess) return e;
+    if (small) hipLaunchKernelGGL((route_group_kernel<bf16_t, 8, false>), dim3(3), block, 0, st, a, b, 0);
+    else hipLaunchKernelGGL((route_group_kernel<bf16_t, 16, false>), dim3(3), block, 0, st, a, b, 0);
+    return hipGetLastError();
+  }
+  // counted for 256 threads and (but for zero fills) single elements; bf16 moves 8 at a time
+  rblocks = dtype == MIXLORA_BF16 ? (rblocks + 31) / 32 : (rblocks + 3) / 4;
+  const dim3 grid((unsigned)(3 + njobs * rblocks));
+  if (dtype == MIXLORA_BF16)
+    hipLaunchKernelGGL((route_group_kernel<bf16_t, 8, true>), grid, block, 0, st, a, b, (int)rblocks);
+  else
+    hipLaunchKernelGGL((route_group_kernel<float, 8, true>), grid, block, 0, st, a, b, (int)rblocks);
   return hipGetLastError();
 }
 
