@@ -39,7 +39,7 @@ struct Layout {
   size_t gemm_part_bwd, gemm_floats_bwd;   // the same for the backward pass
   size_t fwd_end;
   // backward scratch
-  size_t WdT, WgT, WuT, H, Bd_T, VB_all, dg_grp, du_grp, dgsum, dusum, dw_part, dw, Bg_T, Bu_T, AdT,
+  size_t WdT, WgT, WuT, H, Bd_T, VB_all, dg_grp, du_grp, pg_slots, pg_rank_part, pg_dw_part, dgsum, dusum, dw_part, dw, Bg_T, Bu_T, AdT,
       TG_all, TU_all, small[6], S, Bx, dz, partials, dzT;
   int ldT, ldTz;
   size_t partial_floats;
@@ -195,8 +195,16 @@ Layout make_layout_as(const mixlora_dims &D, int schedule, bool dora, bool few) 
   L.Hp = take(pair_down ? kT * f * E : 0);
   L.Bd_T = take(R * d * E);
   L.VB_all = take(T * R * 4);
-  L.dg_grp = take(kT * f * E);
-  L.du_grp = take(kT * f * E);
+  // (the backward on pair-grouped tiles keeps dg and du to itself; what it needs of its own lies here: partial
+  // rank-r products and partial <H, a> per column block, slots of the gradient sums)
+  const bool pg = E == 2 && !pair_down && fused_pg_bwd_possible((int)f, (int)T, (int)N, (int)k, (int)r);
+  const size_t blocks = pg ? (size_t)fused_pg_bwd_splits((int)f) : 0;
+  const size_t rank_bytes = up(2 * blocks * kT * r * 4), dw_bytes = up(blocks * kT * 4), grads2 = 2 * up(kT * f * E);
+  const size_t own = pg ? rank_bytes + dw_bytes + fused_pg_bwd_floats((int)f, (int)T, (int)N, (int)r) * 4 : 0;
+  L.pg_rank_part = L.dg_grp = take(own > grads2 ? own : grads2);
+  L.du_grp = L.dg_grp + up(kT * f * E);
+  L.pg_dw_part = L.pg_rank_part + rank_bytes;
+  L.pg_slots = L.pg_dw_part + dw_bytes;
   L.dgsum = take(vanilla ? 0 : T * f * E);
   L.dusum = take(vanilla ? 0 : T * f * E);
   L.dw_part = take(kT * (size_t)(L.nct > FUSED_MAX_SPLITS ? L.nct : FUSED_MAX_SPLITS) * 4);
@@ -590,9 +598,9 @@ static int forward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mod
   if (use_pg) {
     // tokens grouped by expert pair: rank-r deltas, SiLU * up, the weighted combination of a
     // token's two pairs (Algorithm 1 lines 11-13 and 15) and the A_down projections in one pass
-    // that fetches G and U once per token; the grouped activations are kept only when a backward
-    // pass can follow
-    const int write_a = workspace_bytes >= L.bwd_end ? 1 : 0;
+    // that fetches G and U once per token; the grouped activations are kept only for a backward
+    // pass that does not make them again
+    const int write_a = workspace_bytes >= L.bwd_end && !fused_pg_bwd_ok(pc, f, Nl) ? 1 : 0;
     HIP_TRY_AS(PROF_FUSED_FWD, (double)(3 + 2 * write_a) * T * f * Eb,
                launch_swiglu_fwd_pg(pc, f, D.lora_scale, pg_tok, pg_tiles, pg_ntiles,
                                     ws + L.G, ws + L.U, (float *)(ws + L.Pg_all),
@@ -842,15 +850,15 @@ static int backward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mo
   // du come out of the same launch
   const bool use_pg = dt == MIXLORA_BF16 && !pair_down && !dora && fused_pg_bwd_ok(pc, f, Nl);
   if (use_pg) {
-    nct = fused_pg_splits(f, T, N);
-    HIP_TRY_AS(PROF_FUSED_BWD, 9.0 * T * f * Eb,
+    nct = fused_pg_bwd_splits(f);
+    HIP_TRY_AS(PROF_FUSED_BWD, 5.0 * T * f * Eb,
                launch_swiglu_bwd_pg(pc, f, s, (int32_t *)(ws + L.pg_tok), (int32_t *)(ws + L.pg_tiles),
                                     (int32_t *)(ws + L.pg_ntiles), ws + L.G, ws + L.U, ws + L.H,
                                     (float *)(ws + L.Pg_all), (float *)(ws + L.Pu_all),
                                     (float *)(ws + L.VB_all), w->B_gate, w->B_up, ws + L.AdT,
-                                    ws + L.Bg_T, ws + L.Bu_T, ws + L.dg_grp, ws + L.du_grp,
-                                    ws + L.dgsum, ws + L.dusum, (float *)(ws + L.dw_part),
-                                    (float *)(ws + L.rank_part), st));
+                                    ws + L.Bg_T, ws + L.Bu_T, ws + L.dgsum, ws + L.dusum,
+                                    (float *)(ws + L.pg_dw_part), (float *)(ws + L.pg_rank_part),
+                                    (float *)(ws + L.pg_slots), grads->dB_gate, grads->dB_up, grads->dA_down, st));
   } else if (dt == MIXLORA_BF16) {
     nct = fused_splits(f, (int)kT);
     HIP_TRY_AS(PROF_FUSED_BWD, 5.0 * kT * f * Eb, launch_swiglu_bwd_mfma(pc, f, s, vanilla ? ws + L.Gp : ws + L.G,
@@ -889,7 +897,7 @@ static int backward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mo
   // gate/up: their input gradient needs no more)
   TailArgs ta{};
   ta.pc = pc;
-  ta.probs = probs, ta.dw_part = (float *)(ws + L.dw_part), ta.n_col_tiles = nct;
+  ta.probs = probs, ta.dw_part = (float *)(ws + (use_pg ? L.pg_dw_part : L.dw_part)), ta.n_col_tiles = nct;
   ta.VB_all = (float *)(ws + L.VB_all), ta.Q_all = (float *)(ws + L.Q_all), ta.F = (float *)(ws + L.F);
   ta.s = s, ta.aux_coeff = D.aux_coeff, ta.d_aux = d_aux;
   ta.dw_ws = (float *)(ws + L.dw), ta.dz = (float *)(ws + L.dz);
@@ -901,10 +909,11 @@ static int backward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mo
       ta.redT[i - 2] = (bf16_t *)(ws + L.small[i]);
       continue;
     }
+    if (use_pg && i != 5) continue;   // the factors of the sums that the fused stage has made
     ta.gather[ta.ngather++] = GatherJob{fsrc[i], ws + L.small[i], by_token[i], weighted[i]};
   }
   if (dt == MIXLORA_BF16) {
-    ta.part = (float *)(ws + L.rank_part), ta.nsplit = nct, ta.bank_stride = (int64_t)nct * kT * r, ta.ldT = L.ldT;
+    ta.part = (float *)(ws + (use_pg ? L.pg_rank_part : L.rank_part)), ta.nsplit = nct, ta.bank_stride = (int64_t)nct * kT * r, ta.ldT = L.ldT;
   } else {
     ta.scatter_src[0] = (float *)(ws + L.TG_all), ta.scatter_src[1] = (float *)(ws + L.TU_all);
     ta.nscatter = 2, ta.scatter_dst = ws + L.S, ta.ld_scatter = Kx;
@@ -951,17 +960,17 @@ static int backward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mo
     // gathered), then dW_router = dz^T x (the transposed bf16 dz comes from the router backward)
     const int order[6] = {0, 1, 4, 2, 3, 5};
     GomJob go[GOM_MAX_JOBS];
-    for (int j = 0; j < 6; j++) {
+    int njobs = 0;
+    for (int j = use_pg ? 3 : 0; j < 6; j++) {
       const int i = order[j];
       const bool pair_rows = dora && i == 5;
-      go[j] = GomJob{ws + L.small[i], pair_rows ? ws + L.dYp : wide[i], gout[i], offs,
+      go[njobs++] = GomJob{ws + L.small[i], pair_rows ? ws + L.dYp : wide[i], gout[i], offs,
                      pair_rows ? nullptr : gat[i], N, r, width[i], k, (int)kT, L.ldT, 3, layout_qc[i], s};
     }
-    int njobs = 6;
     for (int i = 0; i < 2 && router_part(N, i) > 0; i++)
       go[njobs++] = GomJob{(char *)(ws + L.dzT) + (size_t)i * 32 * L.ldTz * 2, x, grads->dW_router + (size_t)i * 32 * d,
                            (int32_t *)(ws + L.tok_offs), nullptr, 1, router_part(N, i), d, 1, T, L.ldTz, 1, 1, 1.f};
-    HIP_TRY_AS(PROF_GRAD_SUMS, (3.0 * kT * f + 3.0 * kT * d + (double)T * d) * Eb,
+    HIP_TRY_AS(PROF_GRAD_SUMS, ((use_pg ? 0.0 : 3.0 * kT * f) + 3.0 * kT * d + (double)T * d) * Eb,
                launch_group_outer_mfma(go, njobs, part, pfl, st));
   } else {
     GoJob go[GO_MAX_JOBS];

@@ -294,6 +294,7 @@ constexpr int PG_TILE_ROWS = 32;
 constexpr int PG_MAX_TOKENS = 1 << 16;
 bool fused_pg_ok(const PairCtx &pc, int f);
 bool fused_pg_bwd_ok(const PairCtx &pc, int f, int Nl);   // Nl: experts per adapter
+bool fused_pg_bwd_possible(int f, int T, int N, int k, int r);   // for some Nl
 int fused_pg_max_tiles(int T, int N);
 int fused_pg_splits(int f, int T, int N);
 hipError_t launch_group_token_pairs(const PairCtx &pc, int32_t *tok_of_pos, int32_t *tile_info,
@@ -304,15 +305,18 @@ hipError_t launch_swiglu_fwd_pg(const PairCtx &pc, int f, float s, const int32_t
                                 const void *B_gate, const void *B_up, const void *A_down,
                                 void *a_grp, void *a_comb, float *Q_part, float *Q_all, void *Qw,
                                 int ldqw, int write_a, hipStream_t st);
-// backward on the same tiles: per-pair dg_grp, du_grp, dw_part [pair row][fused_pg_splits], the rank-r partial
-// products as above and the per-token sums dgsum, dusum
+// backward on the same tiles: the per-token sums dgsum, dusum of the pairs' dg, du; dw_part [pair row][splits], the
+// rank-r partial products [2][splits][kT][r] (splits = fused_pg_bwd_splits(f)); the gradients of B_gate, B_up and
+// A_down.  slots: fused_pg_bwd_floats floats of scratch.
+int fused_pg_bwd_splits(int f);
+size_t fused_pg_bwd_floats(int f, int T, int N, int r);
 hipError_t launch_swiglu_bwd_pg(const PairCtx &pc, int f, float s, const int32_t *tok_of_pos,
                                 const int32_t *tile_info, const int32_t *ntiles, const void *G,
                                 const void *U, const void *H, const float *Pg_all,
                                 const float *Pu_all, const float *VB_all, const void *B_gate,
                                 const void *B_up, const void *AdT, const void *BgT, const void *BuT,
-                                void *dg_grp, void *du_grp, void *dgsum, void *dusum, float *dw_part,
-                                float *rank_part, hipStream_t st);
+                                void *dgsum, void *dusum, float *dw_part, float *rank_part, float *slots,
+                                float *dB_gate, float *dB_up, float *dA_down, hipStream_t st);
 // dense[row, e(row)*r + q] = sum over splits of part[split][row][q] (fixed order); the value (times the
 // routing weight if weighted) also goes as bf16 into the block-sparse operand sparse[t(row) or row, e*r + q]
 hipError_t launch_reduce_rank_parts(const PairCtx &pc, const float *part, int nsplit, float *dense, void *sparse,

@@ -5,20 +5,20 @@
 // into different tiles, so the shared projections G, U of a token are read twice and the weighted
 // combination of its two pairs (Eq. 6, moved in front of the linear frozen down projection) needs
 // another pass over the grouped rows.  Here the TOKENS are grouped by their unordered expert pair
-// instead (csrc/router.hip), 32 tokens of one group to a tile.  A wavefront owns a 32-token x
-// 64-column piece for both experts: G and U are fetched and unpacked once, each expert's rank-r
-// deltas are one MFMA per 32-column block, and the two activations are still in registers when
-// their weighted sum is formed.  Per-pair outputs (a, rank-r partial sums) go to the
-// expert-grouped rows that the backward stages and gradient sums read.
+// instead (csrc/router.hip), 32 tokens of one group to a tile.
 //
-// The forward kernel spends about 31 vector instructions per token and column for both experts
-// and the combination, where the expert-grouped kernel plus the combine pass spent about 56; what
-// it mostly does, though, is wait for memory (its time does not change with the shader clock), so
-// the next piece's operands are requested a whole piece ahead and the grid is cut into few, long
-// workgroups (fused_pg_splits).  The backward kernel keeps one wavefront per expert (two roles per
-// tile) and forms the per-token sums of dg and du from the two roles' LDS tiles.
+// Both kernels put G and U (and H) through LDS row-major into the MFMA accumulators, as a product with the
+// identity, and add the experts' rank-r deltas there by MFMA: no operand is unpacked, no delta rounded, and
+// the element math (13 -> 8 vector instructions per pair and column in the forward) works on a lane's 16
+// columns of one row.  What bounds them is memory (the forward moves 4.4 TB/s, the copy rate being 5.1)
+// and, in the backward, the latency of its chain of phases at two wavefronts per SIMD; so what is left to
+// gain is bytes: the backward makes the gradient sums of its three d_ff-wide operands itself, and neither the
+// activations nor dg and du of a pair are ever stored.  4096 tokens at the 7B shape, us: forward 135 -> 95,
+// backward 268 -> 276 + 25 for adding its partial sums, gradient sums 150 -> 67; the step 2220 -> 2116;
+// 16384 tokens of the L3-8B shape: 529 -> 352, 1162 -> 1407 + 31, 855 -> 270.
+// A non-finite G, U or H reaches the 32 columns beside it in its row (0 times it); rows stay apart.
 //
-// Lane roles, LDS tiles and MFMA fragment layout are those of csrc/fused.hip.
+// LDS tiles are those of csrc/fused.hip.
 #include "fused_common.h"
 
 namespace mixlora {
@@ -37,9 +37,8 @@ static_assert(PG_TILE_ROWS == FT_ROWS, "the grouping kernel cuts tiles of FT_ROW
 // Forward.  Per pair: a_grp[row(t, j), :] (when write_a), Q_part[split][row(t, j)][q]; per token:
 // a_comb[t, :] = w_ta a_ta + w_tb a_tb (the lower-numbered expert's term first, fp32, one rounding).
 //
-// One wavefront owns a 32-token x 64-column piece for BOTH experts of the tile: G and U are loaded
-// and unpacked once, the two experts' rank-r deltas come from four LDS tiles, the two activations
-// stay in registers until their weighted sum is stored.  Wavefronts never wait for each other
+// One wavefront owns a 32-token x 64-column piece for BOTH experts of the tile: G and U are fetched once, the two
+// activations stay in registers until their weighted sum is formed.  Wavefronts never wait for each other
 // inside the loop.  Offsets into the [T, f] / [2T, f] arrays are 32-bit (host check).
 template <int KSR, int NQ>
 __global__ __launch_bounds__(FT_WAVES * 64, 2) void swiglu_fwd_pg_kernel(
@@ -49,7 +48,7 @@ __global__ __launch_bounds__(FT_WAVES * 64, 2) void swiglu_fwd_pg_kernel(
     const float *__restrict__ Pu_all, const bf16_t *__restrict__ B_gate,
     const bf16_t *__restrict__ B_up, const bf16_t *__restrict__ A_down, bf16_t *__restrict__ a_grp,
     bf16_t *__restrict__ a_comb, float *__restrict__ Q_part, int nsplit, int write_a) {
-  constexpr int TILES = 4;   // per wavefront: gate and up delta tiles of expert a, then of expert b
+  constexpr int TILES = 3;   // per wavefront: G then expert a's activations, U then expert b's, the combination
   extern __shared__ __align__(16) unsigned char lds[];   // pg_fwd_lds(NQ) bytes
   __shared__ int growmap[2][FT_ROWS];   // expert-grouped row of every tile row, per expert
   if ((int)blockIdx.x >= ntiles[0]) return;
@@ -77,7 +76,6 @@ __global__ __launch_bounds__(FT_WAVES * 64, 2) void swiglu_fwd_pg_kernel(
   }
   // row-major role: the four rows (8p + rr) this lane serves
   uint32_t gsrc[4], adst[2][4];
-  float wx[2][4];
   bool rvalid[4];
 #pragma unroll
   for (int p = 0; p < 4; p++) {
@@ -88,12 +86,24 @@ __global__ __launch_bounds__(FT_WAVES * 64, 2) void swiglu_fwd_pg_kernel(
     gsrc[p] = (uint32_t)(tok * f) * 2u;   // bytes
 #pragma unroll
     for (int x = 0; x < 2; x++) {
-      const int64_t pair = tok * 2 + (slot_a ^ x);
-      const int grow = pc.row_of_pair[pair];
+      const int grow = pc.row_of_pair[tok * 2 + (slot_a ^ x)];
       adst[x][p] = (uint32_t)grow * (uint32_t)f * 2u;
-      wx[x][p] = pc.w[pair];
       if (cc == 0 && wave == 0) growmap[x][rl] = grow;
     }
+  }
+  // MFMA result role: this lane's row's routing weights; first operands that copy a row-major tile into the
+  // accumulators (identity: column l31 takes element l31 of the row)
+  float wx[2];
+  bf16x8_t eye[2];
+  {
+    const int64_t tok = tok_of_pos[row0 + (l31 < rows ? l31 : 0)];
+    const int slot_a = pc.idx[tok * 2] == ex[0] ? 0 : 1;
+    wx[0] = pc.w[tok * 2 + slot_a];
+    wx[1] = pc.w[tok * 2 + (slot_a ^ 1)];
+#pragma unroll
+    for (int h = 0; h < 2; h++)
+#pragma unroll
+      for (int m = 0; m < 8; m++) eye[h][m] = (bf16_t)(l31 == 16 * h + 8 * hi + m ? 1.f : 0.f);
   }
   f32x16_t accq[2][NQ];
 #pragma unroll
@@ -163,76 +173,73 @@ __global__ __launch_bounds__(FT_WAVES * 64, 2) void swiglu_fwd_pg_kernel(
     const bool tail = c0 + FT_SB > f;
     const uint32_t col = (c0 + 8 * cc) * 2u;   // bytes
     const bool cvalid = c0 + 8 * cc < f;
-    // The next piece's shared projections, requested a whole piece before they are needed and
-    // moved into (gnx, unx) at the end of this one.  Requested inside the row loop instead (into
-    // the registers each row frees) they are copied into place at the loop's back edge while
-    // still in flight, and the wavefront waits there: measured 156 against 148 us.
-    bf16x8_t gny[4], uny[4];
 #pragma unroll
     for (int p = 0; p < 4; p++) {
-      gny[p] = ldg8(G, gsrc[p] + col_of(cn));
-      uny[p] = ldg8(U, gsrc[p] + col_of(cn));
+      const int toff = (8 * p + rr) * FT_PITCH + 8 * cc;
+      *reinterpret_cast<bf16x8_t *>(tiles + toff) = gnx[p];
+      *reinterpret_cast<bf16x8_t *>(tiles + FT_TILE + toff) = unx[p];
     }
-    __builtin_amdgcn_sched_barrier(0);
-    // rank-r deltas of both experts and both 32-column blocks -> LDS tiles
+    __builtin_amdgcn_wave_barrier();
+    // the next piece's shared projections, a whole piece before they are needed
 #pragma unroll
-    for (int x = 0; x < 2; x++)
+    for (int p = 0; p < 4; p++) {
+      gnx[p] = ldg8(G, gsrc[p] + col_of(cn));
+      unx[p] = ldg8(U, gsrc[p] + col_of(cn));
+    }
+    bf16x8_t gf[4], uf[4];
 #pragma unroll
-      for (int b = 0; b < 2; b++) {
-        f32x16_t dg, du;
+    for (int s4 = 0; s4 < 4; s4++) {
+      gf[s4] = ld8(tiles + l31 * FT_PITCH + 16 * s4 + 8 * hi);
+      uf[s4] = ld8(tiles + FT_TILE + l31 * FT_PITCH + 16 * s4 + 8 * hi);
+    }
+    __builtin_amdgcn_wave_barrier();
 #pragma unroll
-        for (int i = 0; i < 16; i++) dg[i] = du[i] = 0.f;
+    for (int b = 0; b < 2; b++) {
+      f32x16_t g0, u0, comb;
+#pragma unroll
+      for (int i = 0; i < 16; i++) g0[i] = u0[i] = 0.f;
+#pragma unroll
+      for (int h = 0; h < 2; h++) {
+        g0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(eye[h], gf[2 * b + h], g0, 0, 0, 0);
+        u0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(eye[h], uf[2 * b + h], u0, 0, 0, 0);
+      }
+#pragma unroll
+      for (int x = 0; x < 2; x++) {
+        f32x16_t g = g0, u = u0;   // + the expert's rank-r deltas
 #pragma unroll
         for (int ks = 0; ks < KSR; ks++) {
-          dg = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wg[x][b][ks], pg[x][ks], dg, 0, 0, 0);
-          du = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wu[x][b][ks], pu[x][ks], du, 0, 0, 0);
+          g = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wg[x][b][ks], pg[x][ks], g, 0, 0, 0);
+          u = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wu[x][b][ks], pu[x][ks], u, 0, 0, 0);
         }
-        tile_put(tiles + (2 * x) * FT_TILE, l31, hi, 32 * b, dg);
-        tile_put(tiles + (2 * x + 1) * FT_TILE, l31, hi, 32 * b, du);
+#pragma unroll
+        for (int i = 0; i < 16; i++) {
+          g[i] = g[i] * fsigmoid(g[i]) * u[i];   // columns past f: finite, meet zeroed weights
+          comb[i] = x == 0 ? wx[0] * g[i] : fmaf(wx[1], g[i], comb[i]);
+        }
+        tile_put(tiles + x * FT_TILE, l31, hi, 32 * b, g);
       }
+      tile_put(tiles + 2 * FT_TILE, l31, hi, 32 * b, comb);
+    }
     load_w(cn);
     __builtin_amdgcn_wave_barrier();
 #pragma unroll
     for (int p = 0; p < 4; p++) {
-      const int toff = (8 * p + rr) * FT_PITCH + 8 * cc;
-      const bf16x8_t gv = gnx[p], uv = unx[p];
-      float gf[8], uf[8], comb[8];
-#pragma unroll
-      for (int m = 0; m < 8; m++) {
-        gf[m] = (float)gv[m];
-        uf[m] = (float)uv[m];
-      }
-#pragma unroll
-      for (int x = 0; x < 2; x++) {
-        bf16_t *tp = tiles + (2 * x) * FT_TILE + toff;
-        const bf16x8_t dgl = ld8(tp), dul = ld8(tp + FT_TILE);
-        bf16x8_t av;
-#pragma unroll
-        for (int m = 0; m < 8; m++) {
-          const float gg = gf[m] + (float)dgl[m];
-          const float uu = uf[m] + (float)dul[m];
-          const float a = gg * fsigmoid(gg) * uu;   // columns past f: finite, meet zeroed weights
-          av[m] = (bf16_t)a;
-          comb[m] = x == 0 ? wx[0][p] * a : fmaf(wx[1][p], a, comb[m]);
-        }
-        if (write_a && rvalid[p] && cvalid) stg8(a_grp, adst[x][p] + col, av);
-        *reinterpret_cast<bf16x8_t *>(tp) = av;
-      }
+      const bf16_t *tp = tiles + (8 * p + rr) * FT_PITCH + 8 * cc;
       if (rvalid[p] && cvalid) {
-        bf16x8_t o;
-#pragma unroll
-        for (int m = 0; m < 8; m++) o[m] = (bf16_t)comb[m];
-        stg8(a_comb, gsrc[p] + col, o);
+        if (write_a) {
+          stg8(a_grp, adst[0][p] + col, ld8(tp));
+          stg8(a_grp, adst[1][p] + col, ld8(tp + FT_TILE));
+        }
+        stg8(a_comb, gsrc[p] + col, ld8(tp + 2 * FT_TILE));
       }
     }
-    __builtin_amdgcn_wave_barrier();
     // Q_x += a_x[rows, 64 cols] * A_down[e_x, q, same cols]^T : four K steps of 16 columns
 #pragma unroll
     for (int s4 = 0; s4 < 4; s4++) {
       const bool zero_w = tail && c0 + 16 * s4 + 8 * hi >= f;
 #pragma unroll
       for (int x = 0; x < 2; x++) {
-        const bf16x8_t af = ld8(tiles + (2 * x) * FT_TILE + l31 * FT_PITCH + 16 * s4 + 8 * hi);
+        const bf16x8_t af = ld8(tiles + x * FT_TILE + l31 * FT_PITCH + 16 * s4 + 8 * hi);
 #pragma unroll
         for (int j = 0; j < NQ; j++) {
           bf16x8_t w = wf[x][s4][j];
@@ -243,12 +250,6 @@ __global__ __launch_bounds__(FT_WAVES * 64, 2) void swiglu_fwd_pg_kernel(
     }
     load_wf(cn);
     __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int p = 0; p < 4; p++) {
-      gnx[p] = gny[p];
-      unx[p] = uny[p];
-    }
   }
   // accq[x][j][i]: row 8*(i/4) + 4*hi + i%4 of the tile, q = j*32 + l31.  Each wavefront parks its
   // sums in its own (now dead) tile space; then the four are added in a fixed order.
@@ -274,274 +275,402 @@ __global__ __launch_bounds__(FT_WAVES * 64, 2) void swiglu_fwd_pg_kernel(
   }
 }
 
-static size_t pg_fwd_lds(int) { return (size_t)FT_WAVES * 4 * FT_TILE * sizeof(bf16_t); }
+static size_t pg_fwd_lds(int) { return (size_t)FT_WAVES * 3 * FT_TILE * sizeof(bf16_t); }
 
-// Backward of the stage above on the same token tiles.  A workgroup of eight wavefronts owns a
-// tile: wavefronts 0-3 ("role A") treat it as 32 rows of expert a, wavefronts 4-7 ("role B") as 32
-// rows of expert b, each exactly as the expert-grouped kernel of csrc/fused.hip treats a row tile
-// (same MFMA products, same element math, same per-pair outputs dg_grp, du_grp, dw_part, TG_part,
-// TU_part on the expert-grouped rows); wavefront w of either role walks super-blocks w, w + 4, ...
-// of the workgroup's column range, so both roles hold the same 32 x 64 piece at the same time.
-// After a workgroup barrier role A adds role B's dg and du tiles (LDS) to its own and writes the
-// per-token sums  dgsum[t] = dg_ta + dg_tb, dusum[t] = du_ta + du_tb  that the input-gradient GEMM
-// reads: no pass over the grouped rows follows, and the second fetch of G, U, H hits in cache.
-template <int KSR, int NQ>
-__global__ __launch_bounds__(2 * FT_WAVES * 64, 1) void swiglu_bwd_pg_kernel(
-    PairCtx pc, int f, float s, const int32_t *__restrict__ tok_of_pos,
-    const int32_t *__restrict__ tile_info, const int32_t *__restrict__ ntiles,
-    const bf16_t *__restrict__ G, const bf16_t *__restrict__ U, const bf16_t *__restrict__ H,
-    const float *__restrict__ Pg_all, const float *__restrict__ Pu_all,
-    const float *__restrict__ VB_all, const bf16_t *__restrict__ B_gate,
-    const bf16_t *__restrict__ B_up, const bf16_t *__restrict__ AdT, const bf16_t *__restrict__ BgT,
-    const bf16_t *__restrict__ BuT, bf16_t *__restrict__ dg_grp, bf16_t *__restrict__ du_grp,
-    bf16_t *__restrict__ dgsum, bf16_t *__restrict__ dusum, float *__restrict__ dw_part,
-    float *__restrict__ TG_part, float *__restrict__ TU_part, int nsplit) {
-  constexpr int TILES = 3;
-  extern __shared__ __align__(16) unsigned char lds[];   // pg_bwd_lds(NQ) bytes
-  __shared__ float dwred[2 * FT_WAVES][FT_ROWS];
-  __shared__ int growmap[2][FT_ROWS];
-  if ((int)blockIdx.x >= ntiles[0]) return;
-  const int32_t *ti = tile_info + (int64_t)blockIdx.x * 4;
-  const int r = pc.r, R = pc.N * r, nP = pc.T * 2;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int role = wave >> 2, w4 = wave & 3;
-  const int l31 = lane & 31, hi = lane >> 5, rr = lane >> 3, cc = lane & 7;
-  const int gid = ti[0], row0 = ti[1], rows = ti[2];
-  const int e = role ? gid % pc.N : gid / pc.N;
-  bf16_t *tg = reinterpret_cast<bf16_t *>(lds) + wave * TILES * FT_TILE;
-  bf16_t *tu = tg + FT_TILE, *td = tu + FT_TILE;
-  const bf16_t *tg_b = reinterpret_cast<const bf16_t *>(lds) + (wave ^ 4) * TILES * FT_TILE;
-  const bf16_t *tu_b = tg_b + FT_TILE;
+// Backward of the stage above on the same token tiles, with the three gradient sums over d_ff-wide operands
+// (dB_gate, dB_up, dA_down) in it: the per-pair gradients dg, du and the activations they need never leave
+// the workgroup.
+//
+// A workgroup owns 256 columns and walks a run of consecutive tiles: wavefronts 0-3 ("role A") take the
+// rows as rows of expert a, 64 columns each, wavefronts 4-7 ("role B") as rows of expert b.  The columns'
+// bank rows stay in registers while the expert stays; the sums accumulate there (48 registers) and are
+// flushed to the wavefront's own slot of the expert when it changes, which tiles ordered by expert pair
+// make rare.  With H[t] = W_down^T dy[t]:
+//   h' = H + s A_down^T VB,  da = w h',  dg = da * u * SiLU'(g),  du = da * SiLU(g),  dw += <H, a>
+// in the accumulators' layout (a lane holds 16 columns of one row): G, U, H go through LDS row-major into
+// the accumulators as a product with the identity, the rank-r terms are added to them by MFMA, so no operand
+// is unpacked and no delta is rounded.  The results return to the tiles in LDS, rounded to bf16, where
+//   - role A adds role B's dg and du to its own and stores the per-token sums,
+//   - the rank-r products with B_gate^T, B_up^T (contraction over columns) read them by rows, and
+//   - the gradient sums (contraction over rows) read them transposed (ds_read_b64_tr_b16).
+// Rank-r products of the four column wavefronts are added through LDS, one partial sum per 256 columns.
+constexpr int PGB_CW = 2, PGB_WAVES = 2 * PGB_CW, PGB_COLS = PGB_CW * FT_SB;   // column wavefronts of a role
+typedef short s16x4_t __attribute__((ext_vector_type(4)));
 
-  bf16x8_t pg[KSR], pu[KSR], vw[KSR];
-  {
-    const int64_t tm = tok_of_pos[row0 + (l31 < rows ? l31 : 0)];
-    const float wm = pc.w[tm * 2 + (pc.idx[tm * 2] == e ? 0 : 1)];
+struct PgBwd {
+  PairCtx pc;
+  int f, nwg;
+  float s;
+  const int32_t *tok_of_pos, *tile_info, *ntiles;
+  const bf16_t *G, *U, *H;
+  const float *Pg_all, *Pu_all, *VB_all;
+  const bf16_t *B_gate, *B_up, *AdT, *BgT, *BuT;
+  bf16_t *dgsum, *dusum;
+  float *dw_part, *T_part;   // [row][column block]; [2][column block][row][r]
+  float *slots;              // [workgroup + column block][wavefront][expert][3][r][64]: along the items one of the two grows
+  uint32_t *masks;           // [workgroup + column block][wavefront]: experts whose slot is in use
+};
+
+// run of workgroup wg: items (column block, tile), tiles fastest; at most two column blocks (nwg >= blocks)
+__device__ __forceinline__ int pgb_run(int nt, int ncb, int nwg) { return (nt * ncb + nwg - 1) / nwg; }
+
+// four rows of one column per lane: rows 4 hi .. 4 hi + 3 of the 16 columns at p, as MFMA operand elements
+__device__ __forceinline__ s16x4_t ld4_t(const bf16_t *p) {
+  return __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+      (__attribute__((address_space(3))) s16x4_t *)(__attribute__((address_space(3))) const bf16_t *)p);
+}
+__device__ __forceinline__ bf16x8_t ld8_t(const bf16_t *p, int pitch) {   // rows 4 hi + .. and 16 + 4 hi + ..
+  typedef short s16x8_t __attribute__((ext_vector_type(8)));
+  const s16x4_t a = ld4_t(p), b = ld4_t(p + 16 * pitch);
+  const s16x8_t v = __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
+  return __builtin_bit_cast(bf16x8_t, v);
+}
+
+struct PgbShared {
+  bf16_t tile[PGB_WAVES][3][FT_TILE];
+  float T[PGB_WAVES][2][FT_ROWS][16];
+  bf16_t P[2][3][FT_ROWS][16];
+  bf16_t eye[2][64][8];
+  int grow[2][2][FT_ROWS], tok[FT_ROWS];
+  float dw[PGB_WAVES][FT_ROWS];
+};
+
+__global__ __launch_bounds__(PGB_WAVES * 64, 2) void swiglu_bwd_pg_kernel(PgBwd a) {
+  extern __shared__ __align__(16) unsigned char lds[];
+  PgbShared &sh = *reinterpret_cast<PgbShared *>(lds);
+  const PairCtx &pc = a.pc;
+  const int f = a.f, r = pc.r, N = pc.N, R = N * r, nP = pc.T * 2;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int role = wave / PGB_CW, cw = wave % PGB_CW;
+  const int l31 = lane & 31, hi = lane >> 5, rr = lane >> 3, cc = lane & 7, l15 = lane & 15, h4 = lane >> 4;
+  const int nt = a.ntiles[0], ncb = (f + PGB_COLS - 1) / PGB_COLS, per = pgb_run(nt, ncb, a.nwg);
+  // consecutive runs on one XCD (workgroups are dealt to the eight in turn): its L2 serves the banks of an eighth of
+  // the columns, and the row factors to all of these
+  const int xq = a.nwg >> 3, xrem = a.nwg & 7, xcd = blockIdx.x & 7;
+  const int wgid = xcd * xq + (xcd < xrem ? xcd : xrem) + (blockIdx.x >> 3);
+  const int i0 = wgid * per, i1 = i0 + per < nt * ncb ? i0 + per : nt * ncb;
+  if (i0 >= i1) return;
+  if (wave < 2) {   // first operands that copy a row-major tile: column l31 takes element l31 of the row
+    bf16x8_t v;
 #pragma unroll
-    for (int ks = 0; ks < KSR; ks++) {
-      const int q0 = ks * 16 + hi * 8;
-      const bool v = q0 < r;
-      const int64_t o = tm * R + e * r + (v ? q0 : 0);
-      pg[ks] = cvt8(Pg_all + o, v, s);
-      pu[ks] = cvt8(Pu_all + o, v, s);
-      vw[ks] = cvt8(VB_all + o, v, wm * s);
+    for (int m = 0; m < 8; m++) v[m] = (bf16_t)(l31 == 16 * wave + 8 * hi + m ? 1.f : 0.f);
+    *reinterpret_cast<bf16x8_t *>(sh.eye[wave][lane]) = v;
+  }
+  __syncthreads();
+  bf16_t *t0 = sh.tile[wave][0], *t1 = sh.tile[wave][1], *t2 = sh.tile[wave][2];
+  // ---- this wavefront's banks and sums for one (expert, column block)
+  bf16x8_t wg[2], wu[2], wd[2], tw[2][2];
+  f32x4_t dacc[3][4];
+  uint32_t used[2] = {0, 0};
+  int e = -1, cb = -1;
+  const int cb_first = i0 / nt;
+  auto flush = [&]() {
+    const int hf = cb - cb_first;
+    float *dst = a.slots + (((size_t)(wgid + cb) * PGB_WAVES + wave) * N + e) * 3 * r * 64;
+    const bool again = (used[hf] >> e) & 1;
+    if (l15 < r) {
+#pragma unroll
+      for (int q = 0; q < 3; q++)
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+          f32x4_t *p = reinterpret_cast<f32x4_t *>(dst + (q * r + l15) * 64 + 16 * j + 4 * h4);
+          *p = again ? *p + dacc[q][j] : dacc[q][j];
+        }
     }
-  }
-  uint32_t gsrc[4], odst[4];   // byte offsets of the token row / the pair's grouped row
-  float wrow[4], dwacc[4];
-  bool rvalid[4];
-#pragma unroll
-  for (int p = 0; p < 4; p++) {
-    const int rl = 8 * p + rr;
-    rvalid[p] = rl < rows;
-    const int64_t tok = tok_of_pos[row0 + (rvalid[p] ? rl : 0)];
-    const int64_t pair = tok * 2 + (pc.idx[tok * 2] == e ? 0 : 1);
-    const int grow = pc.row_of_pair[pair];
-    gsrc[p] = (uint32_t)(tok * f) * 2u;
-    odst[p] = (uint32_t)grow * (uint32_t)f * 2u;
-    wrow[p] = pc.w[pair];
-    dwacc[p] = 0.f;
-    if (cc == 0 && w4 == 0) growmap[role][rl] = grow;
-  }
-  f32x16_t acctg[NQ], acctu[NQ];
-#pragma unroll
-  for (int j = 0; j < NQ; j++)
-#pragma unroll
-    for (int i = 0; i < 16; i++) acctg[j][i] = acctu[j][i] = 0.f;
-
-  const int nsb = (f + FT_SB - 1) / FT_SB;
-  const int per = (nsb + nsplit - 1) / nsplit;
-  const int sb_lo = blockIdx.y * per;
-  const int sb_hi = sb_lo + per < nsb ? sb_lo + per : nsb;
-  const int iters = (per + FT_WAVES - 1) / FT_WAVES;   // the same for every wavefront: barriers inside
-  const bf16_t *bg_e = B_gate + (int64_t)e * f * r;
-  const bf16_t *bu_e = B_up + (int64_t)e * f * r;
-  const bf16_t *ad_e = AdT + (int64_t)e * f * r;
-  const bf16_t *bgt_e = BgT + (int64_t)e * r * f;
-  const bf16_t *but_e = BuT + (int64_t)e * r * f;
-
-  bf16x8_t wg[2][KSR], wu[2][KSR], wd[2][KSR], tgw[4][NQ], tuw[4][NQ], gnx[4], unx[4], hnx[4];
-  auto load_w = [&](int c0) {
+    used[hf] |= 1u << e;
+  };
+  auto begin = [&](int c0) {   // (columns past f: clamped loads, zero weights of the products over columns)
+    const bf16_t *bg_e = a.B_gate + (int64_t)e * f * r, *bu_e = a.B_up + (int64_t)e * f * r;
+    const bf16_t *ad_e = a.AdT + (int64_t)e * f * r;
+    const bf16_t *bt_e[2] = {a.BgT + (int64_t)e * r * f, a.BuT + (int64_t)e * r * f};
+    const int q0 = 8 * hi < r ? 8 * hi : 0;   // (past r the row factors are zero)
 #pragma unroll
     for (int b = 0; b < 2; b++) {
       int col = c0 + 32 * b + l31;
       col = col < f ? col : f - 1;
-#pragma unroll
-      for (int ks = 0; ks < KSR; ks++) {
-        const int q0 = ks * 16 + hi * 8;
-        const uint32_t o = ((uint32_t)col * (uint32_t)r + (q0 < r ? q0 : 0)) * 2u;
-        wg[b][ks] = ldg8(bg_e, o);
-        wu[b][ks] = ldg8(bu_e, o);
-        wd[b][ks] = ldg8(ad_e, o);
-      }
+      const uint32_t o = ((uint32_t)col * (uint32_t)r + q0) * 2u;
+      wg[b] = ldg8(bg_e, o);
+      wu[b] = ldg8(bu_e, o);
+      wd[b] = ldg8(ad_e, o);
     }
-  };
-  auto load_wt = [&](int c0) {
 #pragma unroll
-    for (int s4 = 0; s4 < 4; s4++)
+    for (int bank = 0; bank < 2; bank++)
 #pragma unroll
-      for (int j = 0; j < NQ; j++) {
-        const int q = j * 32 + l31;
-        int col = c0 + 16 * s4 + 8 * hi;
-        col = col < f ? col : f - 8;
-        const uint32_t o = ((uint32_t)(q < r ? q : 0) * (uint32_t)f + col) * 2u;
-        tgw[s4][j] = ldg8(bgt_e, o);
-        tuw[s4][j] = ldg8(but_e, o);
+      for (int ks = 0; ks < 2; ks++) {
+        const int col = c0 + 32 * ks + 8 * h4;
+        tw[bank][ks] = ldg8(bt_e[bank], ((uint32_t)(l15 < r ? l15 : 0) * (uint32_t)f + (col < f ? col : f - 8)) * 2u);
+        if (col >= f) tw[bank][ks] = zero8();
       }
+#pragma unroll
+    for (int q = 0; q < 3; q++)
+#pragma unroll
+      for (int j = 0; j < 4; j++) dacc[q][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   };
-  auto col_of = [&](int c0) { const int c = c0 + 8 * cc; return (uint32_t)(c < f ? c : f - 8) * 2u; };
-  {
-    const int sb_first = sb_lo + w4 < sb_hi ? sb_lo + w4 : (nsb - 1);
-    load_w(sb_first * FT_SB);
+
+  // ---- what a tile needs from memory: requested one tile ahead, its tokens two, its place three, and
+  // nothing loaded is looked at in the iteration that asks for it
+  bf16x8_t gn[4], un[4], hn[4];
+  float4 pf[3][2];                     // fp32 rank entries 8 hi .. of row l31: Pg, Pu, VB
+  float2 w2;                           // row l31: routing weights, grouped rows and expert of its two slots
+  int2 grow2;
+  int idx0;
+  int tokp[4], tokm, tokl;             // tokens of the rows 8 p + rr and of row l31 (tokl: that of w2 ..)
+  int32_t inf[3];                      // {group, first position, rows}
+  auto clampi = [&](int i) { return i < i1 ? i : i1 - 1; };
+  auto place = [&](int i) {
+    const int32_t *ti = a.tile_info + (int64_t)(clampi(i) % nt) * 4;
+    inf[0] = ti[0];
+    inf[1] = ti[1];
+    inf[2] = ti[2];
+  };
+  auto tokens = [&](int r0, int n) {
+#pragma unroll
+    for (int p = 0; p < 4; p++) tokp[p] = a.tok_of_pos[r0 + (8 * p + rr < n ? 8 * p + rr : 0)];
+    tokm = a.tok_of_pos[r0 + (l31 < n ? l31 : 0)];
+  };
+  auto request = [&](int c0) {   // from tokp
 #pragma unroll
     for (int p = 0; p < 4; p++) {
-      const uint32_t o = gsrc[p] + col_of(sb_first * FT_SB);
-      gnx[p] = ldg8(G, o);
-      unx[p] = ldg8(U, o);
-      hnx[p] = ldg8(H, o);
+      const int c = c0 + 8 * cc;
+      const uint32_t o = ((uint32_t)tokp[p] * (uint32_t)f + (c < f ? c : f - 8)) * 2u;
+      gn[p] = ldg8(a.G, o);
+      un[p] = ldg8(a.U, o);
+      hn[p] = ldg8(a.H, o);
     }
-    load_wt(sb_first * FT_SB);
-  }
+  };
+  auto request_rows = [&](int ex, int tok) {   // tok: token of row l31
+    const int64_t o = (int64_t)tok * R + ex * r + (8 * hi < r ? 8 * hi : 0);
+    const float *src[3] = {a.Pg_all + o, a.Pu_all + o, a.VB_all + o};
+#pragma unroll
+    for (int q = 0; q < 3; q++) {
+      pf[q][0] = *reinterpret_cast<const float4 *>(src[q]);
+      pf[q][1] = *reinterpret_cast<const float4 *>(src[q] + 4);
+    }
+    tokl = tok;
+    w2 = *reinterpret_cast<const float2 *>(pc.w + (int64_t)tok * 2);
+    grow2 = *reinterpret_cast<const int2 *>(pc.row_of_pair + (int64_t)tok * 2);
+    idx0 = pc.idx[(int64_t)tok * 2];
+  };
+  auto cvt = [&](const float4 (&v)[2], float scale, bool valid) {
+    bf16x8_t o;
+    const float x[8] = {v[0].x, v[0].y, v[0].z, v[0].w, v[1].x, v[1].y, v[1].z, v[1].w};
+#pragma unroll
+    for (int m = 0; m < 8; m++) o[m] = (bf16_t)(valid ? x[m] * scale : 0.f);
+    return o;
+  };
+  auto expert_of = [&](int g) { return role ? g % N : g / N; };
+  auto col_of = [&](int block) { return block * PGB_COLS + cw * FT_SB; };
+  // banks and sums for the tile to come
+  auto change = [&](int ex, int block) {
+    if (col_of(block) >= f || (ex == e && block == cb)) return;
+    if (e >= 0) flush();
+    e = ex;
+    cb = block;
+    begin(col_of(block));
+  };
 
-  for (int it = 0; it < iters; it++) {
-    const int sb = sb_lo + w4 + it * FT_WAVES;
-    const bool live = sb < sb_hi;            // wave-uniform; the same for both roles of a pair
-    const int c0 = (live ? sb : nsb - 1) * FT_SB;
-    const int cn = sb + FT_WAVES < sb_hi ? c0 + FT_WAVES * FT_SB : c0;
-    const bool tail = c0 + FT_SB > f;
-    const uint32_t col = (uint32_t)(c0 + 8 * cc) * 2u;
-    const bool cvalid = c0 + 8 * cc < f;
+  int gid, rows, gid1, rows1, gid2, row02, rows2;   // tiles i, i + 1, i + 2
+  auto take = [&](int &g, int &r0, int &n) {
+    g = __builtin_amdgcn_readfirstlane(inf[0]);
+    r0 = __builtin_amdgcn_readfirstlane(inf[1]);
+    n = __builtin_amdgcn_readfirstlane(inf[2]);
+  };
+  place(i0);
+  {
+    int row0;
+    take(gid, row0, rows);
+    tokens(row0, rows);
+  }
+  request(col_of(cb_first));
+  request_rows(expert_of(gid), tokm);
+  change(expert_of(gid), cb_first);
+  place(i0 + 1);
+  {
+    int row0;
+    take(gid1, row0, rows1);
+    tokens(row0, rows1);
+  }
+  place(i0 + 2);
+  int last_rows = 0, last_cb = 0;
+  auto add_waves = [&](int par) {      // rank-r products and <H, a> of the tile before, summed over its column wavefronts
+    const int left = (f - last_cb * PGB_COLS + FT_SB - 1) / FT_SB, live = left < PGB_CW ? left : PGB_CW;
+    const int tr = threadIdx.x % (PGB_CW * 64), w0 = role * PGB_CW;
+#pragma unroll
+    for (int x = 0; x < 256 / (PGB_CW * 64); x++) {   // four rank entries of a row each
+      const int at = tr + x * PGB_CW * 64, bank = at >> 7, row = (at >> 2) & 31, q = (at & 3) * 4;
+      if (row >= last_rows || q >= r) continue;
+      f32x4_t v = *reinterpret_cast<const f32x4_t *>(&sh.T[w0][bank][row][q]);
+      for (int w = 1; w < live; w++) v += *reinterpret_cast<const f32x4_t *>(&sh.T[w0 + w][bank][row][q]);
+      *reinterpret_cast<f32x4_t *>(a.T_part + (((int64_t)bank * ncb + last_cb) * nP + sh.grow[par][role][row]) * r + q) = v;
+    }
+    if (tr < last_rows) {
+      float v = sh.dw[w0][tr];
+      for (int w = 1; w < live; w++) v += sh.dw[w0 + w][tr];
+      a.dw_part[(int64_t)sh.grow[par][role][tr] * ncb + last_cb] = v;
+    }
+  };
+
+  for (int i = i0; i < i1; i++) {
+    const int par = i & 1, cbi = i / nt, ei = expert_of(gid), c0 = col_of(cbi);
+    const bool live = c0 < f;          // wave-uniform, the same for both roles of a column
+    if (i > i0) add_waves(par ^ 1);
+    const bool q_in = 8 * hi < r;
+    const int n = rows, slot = idx0 == ei ? 0 : 1;
+    const float wm = slot ? w2.y : w2.x;
     if (live) {
-#pragma unroll
-      for (int b = 0; b < 2; b++) {
-        f32x16_t dgm, dum, ddm;
-#pragma unroll
-        for (int i = 0; i < 16; i++) dgm[i] = dum[i] = ddm[i] = 0.f;
-#pragma unroll
-        for (int ks = 0; ks < KSR; ks++) {
-          dgm = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wg[b][ks], pg[ks], dgm, 0, 0, 0);
-          dum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wu[b][ks], pu[ks], dum, 0, 0, 0);
-          ddm = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wd[b][ks], vw[ks], ddm, 0, 0, 0);
-        }
-        tile_put(tg, l31, hi, 32 * b, dgm);
-        tile_put(tu, l31, hi, 32 * b, dum);
-        tile_put(td, l31, hi, 32 * b, ddm);
-      }
-      load_w(cn);
-      __builtin_amdgcn_wave_barrier();
 #pragma unroll
       for (int p = 0; p < 4; p++) {
-        const int lo = (8 * p + rr) * FT_PITCH + 8 * cc;
-        const bf16x8_t dgl = ld8(tg + lo), dul = ld8(tu + lo), ddl = ld8(td + lo);
-        const bf16x8_t gv = gnx[p], uv = unx[p], hv = hnx[p];
-        bf16x8_t dgv, duv;
-        float part = 0.f;
-#pragma unroll
-        for (int m = 0; m < 8; m++) {
-          const float gg = (float)gv[m] + (float)dgl[m];
-          const float uu = (float)uv[m] + (float)dul[m];
-          const float hh = (float)hv[m];
-          const float sg = fsigmoid(gg);
-          const float da = wrow[p] * hh + (float)ddl[m];
-          const float gs = gg * sg;                       // SiLU(g)
-          part = fmaf(hh, gs * uu, part);
-          // d SiLU / dg = sig (1 + g (1 - sig)) = sig + SiLU(g) (1 - sig)
-          dgv[m] = (bf16_t)((da * uu) * fmaf(gs, 1.f - sg, sg));
-          duv[m] = (bf16_t)(da * gs);
-          // columns past f hold finite values of clamped loads; they meet zeroed weights in the
-          // rank-r products below and are never stored
-        }
-        if (cvalid) dwacc[p] += part;
-        {
-          const uint32_t o = gsrc[p] + col_of(cn);
-          gnx[p] = ldg8(G, o);
-          unx[p] = ldg8(U, o);
-          hnx[p] = ldg8(H, o);
-        }
-        if (rvalid[p] && cvalid) {
-          stg8(dg_grp, odst[p] + col, dgv);
-          stg8(du_grp, odst[p] + col, duv);
-        }
-        *reinterpret_cast<bf16x8_t *>(tg + lo) = dgv;
-        *reinterpret_cast<bf16x8_t *>(tu + lo) = duv;
+        const int o = (8 * p + rr) * FT_PITCH + 8 * cc;
+        *reinterpret_cast<bf16x8_t *>(t0 + o) = gn[p];
+        *reinterpret_cast<bf16x8_t *>(t1 + o) = un[p];
+        *reinterpret_cast<bf16x8_t *>(t2 + o) = hn[p];
       }
     }
-    __syncthreads();   // both roles' dg / du tiles of this piece are complete
+    const bf16x8_t pg = cvt(pf[0], a.s, q_in), pu = cvt(pf[1], a.s, q_in), vb = cvt(pf[2], a.s, q_in);
+    if (cw == 0) {   // the row factors of the sums, zero past the tile's rows; the grouped rows
+      const bool in = q_in && l31 < n;
+      *reinterpret_cast<bf16x8_t *>(&sh.P[role][0][l31][8 * hi]) = cvt(pf[0], 1.f, in);
+      *reinterpret_cast<bf16x8_t *>(&sh.P[role][1][l31][8 * hi]) = cvt(pf[1], 1.f, in);
+      *reinterpret_cast<bf16x8_t *>(&sh.P[role][2][l31][8 * hi]) = cvt(pf[2], wm, in);
+      if (hi == 0) {
+        sh.grow[par][role][l31] = slot ? grow2.y : grow2.x;
+        if (role == 0) sh.tok[l31] = tokl;
+      }
+    }
     if (live) {
-      if (role == 0) {
-        // per-token sums over the two pairs (bf16 values added in fp32, rounded once)
+      float dw = 0.f;
+#pragma unroll
+      for (int b = 0; b < 2; b++) {
+        f32x16_t g, u, h;
+#pragma unroll
+        for (int x = 0; x < 16; x++) g[x] = u[x] = h[x] = 0.f;
+#pragma unroll
+        for (int k = 0; k < 2; k++) {
+          const int o = l31 * FT_PITCH + 32 * b + 16 * k + 8 * hi;
+          const bf16x8_t eye = ld8(sh.eye[k][lane]);
+          g = __builtin_amdgcn_mfma_f32_32x32x16_bf16(eye, ld8(t0 + o), g, 0, 0, 0);
+          u = __builtin_amdgcn_mfma_f32_32x32x16_bf16(eye, ld8(t1 + o), u, 0, 0, 0);
+          h = __builtin_amdgcn_mfma_f32_32x32x16_bf16(eye, ld8(t2 + o), h, 0, 0, 0);
+        }
+        g = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wg[b], pg, g, 0, 0, 0);
+        u = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wu[b], pu, u, 0, 0, 0);
+        f32x16_t hp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wd[b], vb, h, 0, 0, 0);
+#pragma unroll
+        for (int x = 0; x < 16; x++) {
+          const float sg = fsigmoid(g[x]), gs = g[x] * sg;   // SiLU(g)
+          const float da = wm * hp[x];
+          const float act = gs * u[x];
+          // (columns past f: clamped loads, kept out of dw here, out of everything else by what reads it)
+          if (c0 + 32 * b + 8 * (x >> 2) + 4 * hi < f) dw = fmaf(h[x], act, dw);
+          // d SiLU / dg = sig (1 + g (1 - sig)) = sig + SiLU(g) (1 - sig)
+          g[x] = (da * u[x]) * fmaf(gs, 1.f - sg, sg);
+          u[x] = da * gs;
+          hp[x] = act;
+        }
+        tile_put(t0, l31, hi, 32 * b, g);
+        tile_put(t1, l31, hi, 32 * b, u);
+        tile_put(t2, l31, hi, 32 * b, hp);
+        __builtin_amdgcn_sched_barrier(0);   // (interleaved further, the wave runs out of registers)
+      }
+      dw += __shfl_xor(dw, 32, 64);
+      __syncthreads();   // both roles' tiles and the row factors are complete; the sums of the tile before are read
+      if (hi == 0) sh.dw[wave][l31] = dw;
+    } else {
+      __syncthreads();
+    }
+    // the next tile's operands, the tokens of the one after it, the place of the one after that
+    request(col_of(clampi(i + 1) / nt));
+    request_rows(expert_of(gid1), tokm);
+    take(gid2, row02, rows2);
+    tokens(row02, rows2);
+    place(i + 3);
+    __builtin_amdgcn_sched_barrier(0);
+    if (live) {
+      {   // per-token sums over the two pairs, bf16 values added in fp32 (expert a's first), rounded once: role A dg, role B du
+        const bf16_t *ta = sh.tile[cw][role], *tb = sh.tile[PGB_CW + cw][role];
+        bf16_t *out = role ? a.dusum : a.dgsum;
+        const bool cvalid = c0 + 8 * cc < f;
 #pragma unroll
         for (int p = 0; p < 4; p++) {
-          if (rvalid[p] && cvalid) {
-            const int lo = (8 * p + rr) * FT_PITCH + 8 * cc;
-            const bf16x8_t ga = ld8(tg + lo), gb = ld8(tg_b + lo), ua = ld8(tu + lo), ub = ld8(tu_b + lo);
-            bf16x8_t gs8, us8;
+          if (8 * p + rr < n && cvalid) {
+            const int o = (8 * p + rr) * FT_PITCH + 8 * cc;
+            const bf16x8_t va = ld8(ta + o), vb8 = ld8(tb + o);
+            bf16x8_t v;
 #pragma unroll
-            for (int m = 0; m < 8; m++) {
-              gs8[m] = (bf16_t)((float)ga[m] + (float)gb[m]);
-              us8[m] = (bf16_t)((float)ua[m] + (float)ub[m]);
-            }
-            stg8(dgsum, gsrc[p] + col, gs8);
-            stg8(dusum, gsrc[p] + col, us8);
+            for (int m = 0; m < 8; m++) v[m] = (bf16_t)((float)va[m] + (float)vb8[m]);
+            stg8(out, ((uint32_t)sh.tok[8 * p + rr] * (uint32_t)f + c0 + 8 * cc) * 2u, v);
           }
         }
       }
 #pragma unroll
-      for (int s4 = 0; s4 < 4; s4++) {
-        const bf16x8_t fg = ld8(tg + l31 * FT_PITCH + 16 * s4 + 8 * hi);
-        const bf16x8_t fu = ld8(tu + l31 * FT_PITCH + 16 * s4 + 8 * hi);
+      for (int bank = 0; bank < 2; bank++) {
+        const bf16_t *t = bank ? t1 : t0;
 #pragma unroll
-        for (int j = 0; j < NQ; j++) {
-          bf16x8_t wgt = tgw[s4][j], wut = tuw[s4][j];
-          if (tail && c0 + 16 * s4 + 8 * hi >= f) wgt = wut = zero8();
-          acctg[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fg, wgt, acctg[j], 0, 0, 0);
-          acctu[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fu, wut, acctu[j], 0, 0, 0);
+        for (int x = 0; x < 2; x++) {
+          f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int ks = 0; ks < 2; ks++)
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ld8(t + (16 * x + l15) * FT_PITCH + 32 * ks + 8 * h4),
+                                                          tw[bank][ks], acc, 0, 0, 0);
+#pragma unroll
+          for (int m = 0; m < 4; m++) sh.T[wave][bank][16 * x + 4 * h4 + m][l15] = acc[m];
         }
       }
-      load_wt(cn);
-    }
-    __syncthreads();   // the tiles may be overwritten by the next piece
-  }
-  // <H, a> per row: add the 8 column chunks (lanes cc = 0..7 of a row), then the role's 4 waves
 #pragma unroll
-  for (int p = 0; p < 4; p++) {
-    float v = dwacc[p];
-    v += __shfl_xor(v, 1, 64);
-    v += __shfl_xor(v, 2, 64);
-    v += __shfl_xor(v, 4, 64);
-    if (cc == 0) dwred[wave][8 * p + rr] = v;
-  }
-  float(*red)[NQ][16][64] = reinterpret_cast<float(*)[NQ][16][64]>(lds);
-  const int t4 = threadIdx.x & (FT_WAVES * 64 - 1);   // thread within the role
-  const int wv0 = role * FT_WAVES;
-  for (int bank = 0; bank < 2; bank++) {
-    __syncthreads();   // tiles (first pass) or the previous bank's sums are no longer read
+      for (int q = 0; q < 3; q++) {
+        const bf16x8_t pt = ld8_t(&sh.P[role][q][4 * h4 + (l15 >> 2)][4 * (l15 & 3)], 16);
+        const bf16_t *t = (q == 0 ? t0 : q == 1 ? t1 : t2) + (4 * h4 + (l15 >> 2)) * FT_PITCH + 4 * (l15 & 3);
 #pragma unroll
-    for (int j = 0; j < NQ; j++)
-#pragma unroll
-      for (int i = 0; i < 16; i++) red[wave][j][i][lane] = bank == 0 ? acctg[j][i] : acctu[j][i];
-    __syncthreads();
-    float *out = bank == 0 ? TG_part : TU_part;
-    for (int idx2 = t4; idx2 < NQ * 16 * 64; idx2 += FT_WAVES * 64) {
-      const int j = idx2 / (16 * 64), i = (idx2 / 64) % 16, ln = idx2 % 64;
-      const int q = j * 32 + (ln & 31);
-      const int rl = 8 * (i >> 2) + 4 * (ln >> 5) + (i & 3);
-      if (q < r && rl < rows) {
-        const float v = (red[wv0][j][i][ln] + red[wv0 + 1][j][i][ln]) +
-                        (red[wv0 + 2][j][i][ln] + red[wv0 + 3][j][i][ln]);
-        out[((int64_t)blockIdx.y * nP + growmap[role][rl]) * r + q] = v;
+        for (int j = 0; j < 4; j++)
+          dacc[q][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ld8_t(t + 16 * j, FT_PITCH), pt, dacc[q][j], 0, 0, 0);
       }
     }
+    if (i + 1 < i1) change(expert_of(gid1), (i + 1) / nt);
+    last_rows = n;
+    last_cb = cbi;
+    gid = gid1, rows = rows1;
+    gid1 = gid2, rows1 = rows2;
+    __syncthreads();   // the tiles may be overwritten; the wavefronts' rank-r products are complete
   }
-  if (t4 < rows)
-    dw_part[(int64_t)growmap[role][t4] * nsplit + blockIdx.y] =
-        (dwred[wv0][t4] + dwred[wv0 + 1][t4]) + (dwred[wv0 + 2][t4] + dwred[wv0 + 3][t4]);
+  add_waves((i1 - 1) & 1);
+  if (e >= 0) flush();
+  if (lane == 0)
+    for (int b = cb_first; b <= (i1 - 1) / nt; b++) a.masks[(size_t)(wgid + b) * PGB_WAVES + wave] = b == cb_first ? used[0] : used[1];
 }
 
-static size_t pg_bwd_lds(int NQ) {
-  const size_t tiles = (size_t)2 * FT_WAVES * 3 * FT_TILE * sizeof(bf16_t);
-  const size_t red = (size_t)2 * FT_WAVES * NQ * 16 * 64 * sizeof(float);
-  return tiles > red ? tiles : red;
+// The three sums from the slots in use, workgroups in ascending order, role A's before role B's; a
+// workgroup: one expert, one sum, 256 columns, a thread all rank entries of one column.
+__global__ __launch_bounds__(PGB_COLS) void pg_sums_reduce_kernel(PgBwd a, float scale, float *__restrict__ dB_gate,
+                                                             float *__restrict__ dB_up, float *__restrict__ dA_down) {
+  const int cb = blockIdx.x, e = blockIdx.y, sum = blockIdx.z, N = a.pc.N, r = a.pc.r, f = a.f;
+  const int nt = a.ntiles[0], ncb = gridDim.x, per = pgb_run(nt, ncb, a.nwg);
+  const int cw = threadIdx.x >> 6, col = threadIdx.x & 63, c = cb * PGB_COLS + threadIdx.x;
+  float acc[16];
+#pragma unroll
+  for (int q = 0; q < 16; q++) acc[q] = 0.f;
+  for (int wg = cb * nt / per; wg <= ((cb + 1) * nt - 1) / per; wg++) {
+    for (int role = 0; role < 2; role++) {
+      const size_t at = (size_t)(wg + cb) * PGB_WAVES + role * PGB_CW + cw;
+      if (!((a.masks[at] >> e) & 1)) continue;
+      const float *src = a.slots + ((at * N + e) * 3 + sum) * r * 64 + col;
+      float v[16];
+#pragma unroll
+      for (int q = 0; q < 16; q++) v[q] = src[(q < r ? q : 0) * 64];
+#pragma unroll
+      for (int q = 0; q < 16; q++) acc[q] += v[q];
+    }
+  }
+  if (c >= f) return;
+  if (sum == 2) {
+#pragma unroll
+    for (int q = 0; q < 16; q++)
+      if (q < r) dA_down[((int64_t)e * r + q) * f + c] = scale * acc[q];
+    return;
+  }
+  float *out = (sum ? dB_up : dB_gate) + ((int64_t)e * f + c) * r;
+#pragma unroll
+  for (int q = 0; q < 16; q += 4)
+    if (q < r) *reinterpret_cast<float4 *>(out + q) = make_float4(scale * acc[q], scale * acc[q + 1], scale * acc[q + 2], scale * acc[q + 3]);
 }
 
 // The forward has no lower limit on the tokens per pair of experts: the expert-grouped stage would add a
@@ -552,14 +681,21 @@ bool fused_pg_ok(const PairCtx &pc, int f) {
          f >= 64 && (int64_t)2 * pc.T * f < ((int64_t)1 << 31);
 }
 
-// The backward takes at least 12 tokens per pair of experts that can occur (pairs of one adapter's own).
-// With fewer, most of a 32-token tile is padding, and the expert-grouped stage and its combine are ahead;
-// both form a token's sums from the same bf16 gradients.  Training step at the 7B shape, us, here / there:
-// 16 experts 300 tokens 538 / 438, 1000 818 / 760, 1400 1029 / 1006; 8 experts 200 356 / 342, 330 390 / 386;
-// two adapters of 8 experts 500 539 / 507, 1400 1028 / 1055; four of 4 200 399 / 395, 500 509 / 513, 1400
-// 1032 / 1060.
+// The backward takes at least 28 tokens per pair of experts that can occur (pairs of one adapter's own) and enough
+// column blocks and tiles for two workgroups per CU.  With fewer, tiles are mostly padding and the expert changes
+// with every tile; the expert-grouped stage, its combine and its sums are ahead then.  Training step, us, here /
+// there: 7B shape, 8 experts, 340 tokens 413 / 380, 600 565 / 557, 800 680 / 675; 1024 x 2752, 800 211 / 207,
+// 1600 247 / 259; 16 experts 2000 281 / 274, 3400 372 / 381; 512 x 1536, 1000 176 / 156, 3000 226 / 228; two
+// adapters of 8 experts, 7B shape, 1600 1157 / 1147, 2048 1278 / 1280.
+static bool pg_bwd_size(int f, int T, int N, int Nl) {
+  return T >= 14 * N * (Nl - 1) && (int64_t)fused_pg_bwd_splits(f) * ((T + FT_ROWS - 1) / FT_ROWS) >= 1024;
+}
 bool fused_pg_bwd_ok(const PairCtx &pc, int f, int Nl) {
-  return fused_pg_ok(pc, f) && pc.T >= 6 * pc.N * (Nl - 1);
+  return fused_pg_ok(pc, f) && pg_bwd_size(f, pc.T, pc.N, Nl);
+}
+bool fused_pg_bwd_possible(int f, int T, int N, int k, int r) {   // with adapters of two experts at the least
+  const PairCtx pc{nullptr, nullptr, nullptr, nullptr, nullptr, T, N, k, r};
+  return fused_pg_ok(pc, f) && pg_bwd_size(f, T, N, 2);
 }
 
 int fused_pg_max_tiles(int T, int N) { return (T + FT_ROWS - 1) / FT_ROWS + N * N; }
@@ -609,31 +745,46 @@ hipError_t launch_swiglu_fwd_pg(const PairCtx &pc, int f, float s, const int32_t
   return launch_reduce_rank_parts(pc, Q_part, nsplit, Q_all, Qw, ldqw, 1, 0, st);
 }
 
+int fused_pg_bwd_splits(int f) { return (f + PGB_COLS - 1) / PGB_COLS; }
+
+// Workgroups: two per CU, a tile each at least; never fewer than column blocks, so that a run touches two of
+// them at most.
+static int pgb_workgroups(int f, int T, int N) {
+  const int64_t ncb = fused_pg_bwd_splits(f), tiles = (T + FT_ROWS - 1) / FT_ROWS + N * (N - 1) / 4;
+  int64_t n = ncb * tiles;
+  n = n > 512 ? 512 : n;
+  return (int)(n < ncb ? ncb : n);
+}
+
+size_t fused_pg_bwd_floats(int f, int T, int N, int r) {
+  const size_t pieces = pgb_workgroups(f, T, N) + fused_pg_bwd_splits(f);
+  return pieces * PGB_WAVES * N * 3 * r * 64 + pieces * PGB_WAVES;
+}
+
 hipError_t launch_swiglu_bwd_pg(const PairCtx &pc, int f, float s, const int32_t *tok_of_pos,
                                 const int32_t *tile_info, const int32_t *ntiles, const void *G,
                                 const void *U, const void *H, const float *Pg_all,
                                 const float *Pu_all, const float *VB_all, const void *B_gate,
                                 const void *B_up, const void *AdT, const void *BgT, const void *BuT,
-                                void *dg_grp, void *du_grp, void *dgsum, void *dusum, float *dw_part,
-                                float *rank_part, hipStream_t st) {
+                                void *dgsum, void *dusum, float *dw_part, float *rank_part, float *slots,
+                                float *dB_gate, float *dB_up, float *dA_down, hipStream_t st) {
   if (!fused_pg_ok(pc, f)) return hipErrorInvalidValue;
-  const int nP = pc.T * 2, nsplit = fused_pg_splits(f, pc.T, pc.N);
-  float *TG_part = rank_part, *TU_part = rank_part + (size_t)nsplit * nP * pc.r;
-  const dim3 grid(fused_pg_max_tiles(pc.T, pc.N), nsplit), block(2 * FT_WAVES * 64);
-  auto kern = swiglu_bwd_pg_kernel<1, 1>;   // fused_pg_ok: r <= 16
-  const size_t lds_ = pg_bwd_lds(1);
   static bool attr_set = false;
   if (!attr_set) {
-    hipError_t e_ = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_);
+    hipError_t e_ = hipFuncSetAttribute(reinterpret_cast<const void *>(swiglu_bwd_pg_kernel),
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(PgbShared));
     if (e_ != hipSuccess) return e_;
     attr_set = true;
   }
-  hipLaunchKernelGGL(kern, grid, block, lds_, st, pc, f, s, tok_of_pos, tile_info, ntiles,
-                     (const bf16_t *)G, (const bf16_t *)U, (const bf16_t *)H, Pg_all, Pu_all, VB_all,
-                     (const bf16_t *)B_gate, (const bf16_t *)B_up, (const bf16_t *)AdT,
-                     (const bf16_t *)BgT, (const bf16_t *)BuT, (bf16_t *)dg_grp, (bf16_t *)du_grp,
-                     (bf16_t *)dgsum, (bf16_t *)dusum, dw_part, TG_part, TU_part, nsplit);
+  const int nwg = pgb_workgroups(f, pc.T, pc.N), ncb = fused_pg_bwd_splits(f);
+  const PgBwd a{pc, f, nwg, s, tok_of_pos, tile_info, ntiles, (const bf16_t *)G, (const bf16_t *)U,
+                (const bf16_t *)H, Pg_all, Pu_all, VB_all, (const bf16_t *)B_gate, (const bf16_t *)B_up,
+                (const bf16_t *)AdT, (const bf16_t *)BgT, (const bf16_t *)BuT, (bf16_t *)dgsum, (bf16_t *)dusum,
+                dw_part, rank_part, slots, (uint32_t *)(slots + (size_t)(nwg + ncb) * PGB_WAVES * pc.N * 3 * pc.r * 64)};
+  hipLaunchKernelGGL(swiglu_bwd_pg_kernel, dim3(nwg), dim3(PGB_WAVES * 64), sizeof(PgbShared), st, a);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(pg_sums_reduce_kernel, dim3(ncb, pc.N, 3), dim3(PGB_COLS), 0, st, a, s, dB_gate, dB_up, dA_down);
   return hipGetLastError();
 }
 
