@@ -186,13 +186,6 @@ __global__ __launch_bounds__(FT_WAVES * 64, 2) void swiglu_fwd_pg_kernel(
       gnx[p] = ldg8(G, gsrc[p] + col_of(cn));
       unx[p] = ldg8(U, gsrc[p] + col_of(cn));
     }
-    bf16x8_t gf[4], uf[4];
-#pragma unroll
-    for (int s4 = 0; s4 < 4; s4++) {
-      gf[s4] = ld8(tiles + l31 * FT_PITCH + 16 * s4 + 8 * hi);
-      uf[s4] = ld8(tiles + FT_TILE + l31 * FT_PITCH + 16 * s4 + 8 * hi);
-    }
-    __builtin_amdgcn_wave_barrier();
 #pragma unroll
     for (int b = 0; b < 2; b++) {
       f32x16_t g0, u0, comb;
@@ -200,8 +193,9 @@ __global__ __launch_bounds__(FT_WAVES * 64, 2) void swiglu_fwd_pg_kernel(
       for (int i = 0; i < 16; i++) g0[i] = u0[i] = 0.f;
 #pragma unroll
       for (int h = 0; h < 2; h++) {
-        g0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(eye[h], gf[2 * b + h], g0, 0, 0, 0);
-        u0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(eye[h], uf[2 * b + h], u0, 0, 0, 0);
+        const bf16_t *p = tiles + l31 * FT_PITCH + 32 * b + 16 * h + 8 * hi;   // (block b overwrites its own columns only)
+        g0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(eye[h], ld8(p), g0, 0, 0, 0);
+        u0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(eye[h], ld8(p + FT_TILE), u0, 0, 0, 0);
       }
 #pragma unroll
       for (int x = 0; x < 2; x++) {
@@ -219,6 +213,7 @@ __global__ __launch_bounds__(FT_WAVES * 64, 2) void swiglu_fwd_pg_kernel(
         tile_put(tiles + x * FT_TILE, l31, hi, 32 * b, g);
       }
       tile_put(tiles + 2 * FT_TILE, l31, hi, 32 * b, comb);
+      __builtin_amdgcn_sched_barrier(0);   // (interleaved, the blocks run out of registers)
     }
     load_w(cn);
     __builtin_amdgcn_wave_barrier();
