@@ -103,7 +103,8 @@ inline bool few_shapes(const mixlora_dims &D, int schedule, bool dora) {
 
 // Buffers a schedule does not use get size 0 (per-token G, U in the unshared schedule, the
 // combined activations where the down projection runs per pair, ...).
-Layout make_layout_as(const mixlora_dims &D, int schedule, bool dora, bool few) {
+// No smaller than `at_least` up to base_end.
+Layout make_layout_as(const mixlora_dims &D, int schedule, bool dora, bool few, size_t at_least = 0) {
   Layout L{};
   L.few = few;
   const bool pair_down = schedule != MIXLORA_SCHEDULE_LINEAR_DOWN;
@@ -175,6 +176,7 @@ Layout make_layout_as(const mixlora_dims &D, int schedule, bool dora, bool few) 
     const size_t per_tile = E == 2 && large && slices >= 2 ? GEMM_SCRATCH_FLOATS / 256 : 0;
     L.gemm_floats = per_tile * (tiles < 256 ? tiles : 256);
     L.joint_floats = per_tile * (tiles_T < 256 ? tiles_T : 256);
+    if (o < at_least) o = at_least;
     L.base_end = o;
     L.gemm_part = take(L.gemm_floats * 4);
     L.fwd_end = o;
@@ -242,16 +244,15 @@ Layout make_layout_as(const mixlora_dims &D, int schedule, bool dora, bool few) 
 
 // The few-token stage keeps a partial sum per column block, the grouped stages one per split: where only
 // the latter's workspace fits the library's own array, they run (the layout and with it the path depend on the
-// dims alone, whichever entry point is called).
+// dims alone, whichever entry point is called).  The few-token layout is no smaller than the grouped one, so the
+// calls that the array takes are those whose grouped workspace fits it.
 Layout make_layout(const mixlora_dims &D, int schedule = MIXLORA_SCHEDULE_LINEAR_DOWN,
                    bool dora = false) {
-  const bool few = few_shapes(D, schedule, dora);
-  const Layout L = make_layout_as(D, schedule, dora, few);
-  if (few && L.base_end > (size_t)MIXLORA_STATIC_SCRATCH_BYTES) {
-    const Layout G = make_layout_as(D, schedule, dora, false);
-    if (G.base_end <= (size_t)MIXLORA_STATIC_SCRATCH_BYTES) return G;
-  }
-  return L;
+  const Layout G = make_layout_as(D, schedule, dora, false);
+  if (!few_shapes(D, schedule, dora)) return G;
+  const Layout L = make_layout_as(D, schedule, dora, true, G.base_end);
+  const size_t limit = MIXLORA_STATIC_SCRATCH_BYTES;
+  return L.base_end > limit && G.base_end <= limit ? G : L;
 }
 
 int check_dims(const mixlora_dims *D) {

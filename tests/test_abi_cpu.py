@@ -104,6 +104,20 @@ def test_forward_static_argument_errors(lib):
     assert m and int(m.group(1)) * 1024 * 1024 == B.STATIC_SCRATCH_BYTES
 
 
+def test_static_scratch_limit_of_few_tokens(lib):
+    """The array takes the calls whose grouped workspace fits it, also where the few-token stage's is smaller
+    (each of these is beyond it grouped and within it with the few-token stage's own buffers)."""
+    for d, f, N, k, r, T in ((5120, 10880, 8, 2, 1, 128), (6976, 13440, 16, 2, 8, 128), (8128, 18368, 16, 2, 16, 96),
+                             (7872, 11968, 16, 4, 4, 64)):
+        dm = dims(T=T, d=d, d_ff=f, N=N, k=k, r=r)
+        assert B.mixlora_workspace_bytes(dm, False) > B.STATIC_SCRATCH_BYTES
+        a = fwd_args()
+        a.pop("workspace"), a.pop("workspace_bytes")
+        with pytest.raises(B.MixLoraError) as ei:
+            B.mixlora_ffn_forward_static(dm, fake_weights(), stream=0, **a)
+        assert ei.value.code == -7
+
+
 def test_backward_argument_errors(lib):
     g = B.make_grads({n: FAKE for n in B.GRAD_FIELDS})
 
