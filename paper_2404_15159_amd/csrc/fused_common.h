@@ -80,4 +80,16 @@ __device__ __forceinline__ void tile_put(bf16_t *tile, int l31, int hi, int cb32
   }
 }
 
+// the reverse: a block of a tile in the accumulators' layout
+__device__ __forceinline__ f32x16_t tile_get(const bf16_t *tile, int l31, int hi, int cb32) {
+  f32x16_t d;
+#pragma unroll
+  for (int g = 0; g < 4; g++) {
+    const bf16x4_t v = *reinterpret_cast<const bf16x4_t *>(tile + l31 * FT_PITCH + cb32 + 8 * g + 4 * hi);
+#pragma unroll
+    for (int m = 0; m < 4; m++) d[g * 4 + m] = (float)v[m];
+  }
+  return d;
+}
+
 }  // namespace mixlora

@@ -7,16 +7,17 @@
 // another pass over the grouped rows.  Here the TOKENS are grouped by their unordered expert pair
 // instead (csrc/router.hip), 32 tokens of one group to a tile.
 //
-// Both kernels put G and U (and H) through LDS row-major into the MFMA accumulators, as a product with the
-// identity, and add the experts' rank-r deltas there by MFMA: no operand is unpacked, no delta rounded, and
-// the element math (13 -> 8 vector instructions per pair and column in the forward) works on a lane's 16
-// columns of one row.  What bounds them is memory (the forward moves 4.4 TB/s, the copy rate being 5.1)
+// Both kernels put G and U (and H) through LDS row-major into the accumulators' layout and add the experts'
+// rank-r deltas there by MFMA: no delta is rounded, and the element math (13 -> 9 vector instructions per
+// pair and column in the forward) works on a lane's 16 columns of one row.  A lane reads its own columns and unpacks
+// them; as a product with the identity that is 10-15 % fewer vector instructions and the same time (step at the 7B
+// shape 2047 us, read 2044), but a non-finite element then makes NaN of the 31 columns beside it.  What bounds them is memory (the forward moves 4.4 TB/s, the copy rate being 5.1)
 // and, in the backward, the latency of its chain of phases at two wavefronts per SIMD; so what is left to
 // gain is bytes: the backward makes the gradient sums of its three d_ff-wide operands itself, and neither the
 // activations nor dg and du of a pair are ever stored.  4096 tokens at the 7B shape, us: forward 135 -> 95,
 // backward 268 -> 276 + 25 for adding its partial sums, gradient sums 150 -> 67; the step 2220 -> 2116;
 // 16384 tokens of the L3-8B shape: 529 -> 352, 1162 -> 1407 + 31, 855 -> 270.
-// A non-finite G, U or H reaches the 32 columns beside it in its row (0 times it); rows stay apart.
+// A non-finite G, U or H stays in its column, and in its row but for the row's own rank-r products.
 //
 // LDS tiles are those of csrc/fused.hip.
 #include "fused_common.h"
@@ -91,19 +92,13 @@ __global__ __launch_bounds__(FT_WAVES * 64, 2) void swiglu_fwd_pg_kernel(
       if (cc == 0 && wave == 0) growmap[x][rl] = grow;
     }
   }
-  // MFMA result role: this lane's row's routing weights; first operands that copy a row-major tile into the
-  // accumulators (identity: column l31 takes element l31 of the row)
+  // MFMA result role: this lane's row's routing weights
   float wx[2];
-  bf16x8_t eye[2];
   {
     const int64_t tok = tok_of_pos[row0 + (l31 < rows ? l31 : 0)];
     const int slot_a = pc.idx[tok * 2] == ex[0] ? 0 : 1;
     wx[0] = pc.w[tok * 2 + slot_a];
     wx[1] = pc.w[tok * 2 + (slot_a ^ 1)];
-#pragma unroll
-    for (int h = 0; h < 2; h++)
-#pragma unroll
-      for (int m = 0; m < 8; m++) eye[h][m] = (bf16_t)(l31 == 16 * h + 8 * hi + m ? 1.f : 0.f);
   }
   f32x16_t accq[2][NQ];
 #pragma unroll
@@ -188,15 +183,9 @@ __global__ __launch_bounds__(FT_WAVES * 64, 2) void swiglu_fwd_pg_kernel(
     }
 #pragma unroll
     for (int b = 0; b < 2; b++) {
-      f32x16_t g0, u0, comb;
-#pragma unroll
-      for (int i = 0; i < 16; i++) g0[i] = u0[i] = 0.f;
-#pragma unroll
-      for (int h = 0; h < 2; h++) {
-        const bf16_t *p = tiles + l31 * FT_PITCH + 32 * b + 16 * h + 8 * hi;   // (block b overwrites its own columns only)
-        g0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(eye[h], ld8(p), g0, 0, 0, 0);
-        u0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(eye[h], ld8(p + FT_TILE), u0, 0, 0, 0);
-      }
+      // (block b overwrites its own columns only)
+      const f32x16_t g0 = tile_get(tiles, l31, hi, 32 * b), u0 = tile_get(tiles + FT_TILE, l31, hi, 32 * b);
+      f32x16_t comb;
 #pragma unroll
       for (int x = 0; x < 2; x++) {
         f32x16_t g = g0, u = u0;   // + the expert's rank-r deltas
@@ -281,10 +270,9 @@ static size_t pg_fwd_lds(int) { return (size_t)FT_WAVES * 3 * FT_TILE * sizeof(b
 // bank rows stay in registers while the expert stays; the sums accumulate there (48 registers) and are
 // flushed to the wavefront's own slot of the expert when it changes, which tiles ordered by expert pair
 // make rare.  With H[t] = W_down^T dy[t]:
-//   h' = H + s A_down^T VB,  da = w h',  dg = da * u * SiLU'(g),  du = da * SiLU(g),  dw += <H, a>
-// in the accumulators' layout (a lane holds 16 columns of one row): G, U, H go through LDS row-major into
-// the accumulators as a product with the identity, the rank-r terms are added to them by MFMA, so no operand
-// is unpacked and no delta is rounded.  The results return to the tiles in LDS, rounded to bf16, where
+//   da = w H + A_down^T (w s VB),  dg = da * u * SiLU'(g),  du = da * SiLU(g),  dw += <H, a>
+// in the accumulators' layout (a lane holds 16 columns of one row): G, U, H go through LDS row-major, the
+// rank-r terms are added to them by MFMA, so no delta is rounded.  The results return to the tiles in LDS, rounded to bf16, where
 //   - role A adds role B's dg and du to its own and stores the per-token sums,
 //   - the rank-r products with B_gate^T, B_up^T (contraction over columns) read them by rows, and
 //   - the gradient sums (contraction over rows) read them transposed (ds_read_b64_tr_b16).
@@ -325,7 +313,6 @@ struct PgbShared {
   bf16_t tile[PGB_WAVES][3][FT_TILE];
   float T[PGB_WAVES][2][FT_ROWS][16];
   bf16_t P[2][3][FT_ROWS][16];
-  bf16_t eye[2][64][8];
   int grow[2][2][FT_ROWS], tok[FT_ROWS];
   float dw[PGB_WAVES][FT_ROWS];
 };
@@ -345,13 +332,6 @@ __global__ __launch_bounds__(PGB_WAVES * 64, 2) void swiglu_bwd_pg_kernel(PgBwd 
   const int wgid = xcd * xq + (xcd < xrem ? xcd : xrem) + (blockIdx.x >> 3);
   const int i0 = wgid * per, i1 = i0 + per < nt * ncb ? i0 + per : nt * ncb;
   if (i0 >= i1) return;
-  if (wave < 2) {   // first operands that copy a row-major tile: column l31 takes element l31 of the row
-    bf16x8_t v;
-#pragma unroll
-    for (int m = 0; m < 8; m++) v[m] = (bf16_t)(l31 == 16 * wave + 8 * hi + m ? 1.f : 0.f);
-    *reinterpret_cast<bf16x8_t *>(sh.eye[wave][lane]) = v;
-  }
-  __syncthreads();
   bf16_t *t0 = sh.tile[wave][0], *t1 = sh.tile[wave][1], *t2 = sh.tile[wave][2];
   // ---- this wavefront's banks and sums for one (expert, column block)
   bf16x8_t wg[2], wu[2], wd[2], tw[2][2];
@@ -521,7 +501,7 @@ __global__ __launch_bounds__(PGB_WAVES * 64, 2) void swiglu_bwd_pg_kernel(PgBwd 
         *reinterpret_cast<bf16x8_t *>(t2 + o) = hn[p];
       }
     }
-    const bf16x8_t pg = cvt(pf[0], a.s, q_in), pu = cvt(pf[1], a.s, q_in), vb = cvt(pf[2], a.s, q_in);
+    const bf16x8_t pg = cvt(pf[0], a.s, q_in), pu = cvt(pf[1], a.s, q_in), vb = cvt(pf[2], wm * a.s, q_in);
     if (cw == 0) {   // the row factors of the sums, zero past the tile's rows; the grouped rows
       const bool in = q_in && l31 < n;
       *reinterpret_cast<bf16x8_t *>(&sh.P[role][0][l31][8 * hi]) = cvt(pf[0], 1.f, in);
@@ -536,35 +516,28 @@ __global__ __launch_bounds__(PGB_WAVES * 64, 2) void swiglu_bwd_pg_kernel(PgBwd 
       float dw = 0.f;
 #pragma unroll
       for (int b = 0; b < 2; b++) {
-        f32x16_t g, u, h;
-#pragma unroll
-        for (int x = 0; x < 16; x++) g[x] = u[x] = h[x] = 0.f;
-#pragma unroll
-        for (int k = 0; k < 2; k++) {
-          const int o = l31 * FT_PITCH + 32 * b + 16 * k + 8 * hi;
-          const bf16x8_t eye = ld8(sh.eye[k][lane]);
-          g = __builtin_amdgcn_mfma_f32_32x32x16_bf16(eye, ld8(t0 + o), g, 0, 0, 0);
-          u = __builtin_amdgcn_mfma_f32_32x32x16_bf16(eye, ld8(t1 + o), u, 0, 0, 0);
-          h = __builtin_amdgcn_mfma_f32_32x32x16_bf16(eye, ld8(t2 + o), h, 0, 0, 0);
-        }
+        f32x16_t g = tile_get(t0, l31, hi, 32 * b), u = tile_get(t1, l31, hi, 32 * b);
+        const f32x16_t h = tile_get(t2, l31, hi, 32 * b);
         g = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wg[b], pg, g, 0, 0, 0);
         u = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wu[b], pu, u, 0, 0, 0);
-        f32x16_t hp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wd[b], vb, h, 0, 0, 0);
+        f32x16_t da;
+#pragma unroll
+        for (int x = 0; x < 16; x++) da[x] = wm * h[x];
+        da = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wd[b], vb, da, 0, 0, 0);
 #pragma unroll
         for (int x = 0; x < 16; x++) {
           const float sg = fsigmoid(g[x]), gs = g[x] * sg;   // SiLU(g)
-          const float da = wm * hp[x];
           const float act = gs * u[x];
           // (columns past f: clamped loads, kept out of dw here, out of everything else by what reads it)
           if (c0 + 32 * b + 8 * (x >> 2) + 4 * hi < f) dw = fmaf(h[x], act, dw);
           // d SiLU / dg = sig (1 + g (1 - sig)) = sig + SiLU(g) (1 - sig)
-          g[x] = (da * u[x]) * fmaf(gs, 1.f - sg, sg);
-          u[x] = da * gs;
-          hp[x] = act;
+          g[x] = (da[x] * u[x]) * fmaf(gs, 1.f - sg, sg);
+          u[x] = da[x] * gs;
+          da[x] = act;
         }
         tile_put(t0, l31, hi, 32 * b, g);
         tile_put(t1, l31, hi, 32 * b, u);
-        tile_put(t2, l31, hi, 32 * b, hp);
+        tile_put(t2, l31, hi, 32 * b, da);
         __builtin_amdgcn_sched_barrier(0);   // (interleaved further, the wave runs out of registers)
       }
       dw += __shfl_xor(dw, 32, 64);

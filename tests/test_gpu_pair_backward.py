@@ -2,7 +2,7 @@
 A_down itself: token counts on both sides of its limit, column blocks that end inside a wavefront's columns
 or leave a wavefront without any, ranks of one and two 8-entry pieces, runs that cross column blocks, experts
 that come back after others, every token at one pair, several adapters.  Against the oracle, bf16 tolerance
-(2e-2)."""
+(2e-2).  And, with a lower limit on neither, what a non-finite value of one feature or one token may reach."""
 import numpy as np
 import pytest
 
@@ -63,3 +63,52 @@ def test_pair_backward_of_several_adapters(T, M, N):
     host["W_router"] = synth._store(host["W_router"] * 8.0, cfg.dtype)
     res, fw, bw, tm = run_multi(cfg, host, "uneven")
     compare_multi(res, fw, bw, cfg, tm)
+
+
+# (the second: pair-grouped forward, expert-grouped backward)
+@pytest.mark.parametrize("T,f", [(1000, 4648), (300, 776)])
+@pytest.mark.parametrize("name", ["W_gate", "W_up", "W_down"])
+def test_non_finite_feature_stays_to_itself(T, f, name):
+    """One infinite element of a frozen matrix makes one feature (a column of G, U or dy W_down) non-finite for every
+    token: the gradients of every other feature are those of a clean pass, bit for bit."""
+    cfg = synth.scaled(BASE, name="pair_bwd_inf", T=T, d=64, d_ff=f, N=8, k=2, r=16)
+    host = synth.make_inputs(cfg)
+    c = f // 2 + 5
+    out = []
+    for v in (0.0, np.inf):
+        W = host[name].copy()
+        W[(7, c) if name == "W_down" else (c, 7)] = v
+        print(f"case T={T} f={f} {name} {v}", flush=True)
+        m = MixLoraFFN(cfg, dict(host, **{name: W}))
+        m.workspace.fill_(0xFF)
+        m.forward()
+        m.backward(d_aux=0.0)
+        out.append(m.results())
+    rest = np.delete(np.arange(f), c)
+    for n in ("dB_gate", "dB_up"):
+        assert not np.isfinite(out[1][n][:, c]).all() or (n, name) == ("dB_up", "W_up"), n
+        assert np.array_equal(out[0][n][:, rest], out[1][n][:, rest]), n
+    assert np.array_equal(out[0]["dA_down"][:, :, rest], out[1]["dA_down"][:, :, rest])
+
+
+@pytest.mark.parametrize("T,f", [(1000, 4648), (300, 776)])
+def test_non_finite_tokens_stay_to_themselves(T, f):
+    cfg = synth.scaled(BASE, name="pair_bwd_nan", T=T, d=64, d_ff=f, N=8, k=2, r=16)
+    host = synth.make_inputs(cfg)
+    bad = {5: np.nan, T // 2: np.inf, T - 1: -np.inf}
+    rest = np.setdiff1d(np.arange(T), list(bad))
+    clean, dirty = host["x"].copy(), host["x"].copy()
+    for t, v in bad.items():
+        clean[t] = 0.0
+        dirty[t, 3] = v
+    out = []
+    for x in (clean, dirty):
+        print(f"case T={T} f={f} tokens", flush=True)
+        m = MixLoraFFN(cfg, dict(host, x=x))
+        m.workspace.fill_(0xFF)
+        m.forward()
+        m.backward(d_aux=0.0)
+        out.append(m.results())
+    assert not np.isfinite(out[1]["y"][list(bad)]).all()
+    for n in ("topk_idx", "topk_w", "y", "dx"):
+        assert np.array_equal(out[0][n][rest], out[1][n][rest]), n
