@@ -421,6 +421,7 @@ static int forward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mod
     add_seg(p[2], x, d, w->A_gate, d, d);
     add_seg(p[3], x, d, w->A_up, d, d);
     add_seg(p[4], x, d, w->W_router, d, d);
+    p[4].by_rows = dt == MIXLORA_F32;
     add_seg(p[5], w->W_gate, d, w->A_gate, d, d);
     add_seg(p[6], w->W_up, d, w->A_up, d, d);
     add_seg(p[7], w->W_down, f, w->A_down, f, f);

@@ -64,6 +64,7 @@ struct GemmProblem {
   void *C;
   int64_t ldc;
   int c_f32;  // 1: C is float32 regardless of the storage dtype
+  int by_rows;   // fp32 storage, one segment: waves per row, each sum over 64 lanes (the router's logits)
 };
 // Enqueue up to GEMM_MAX_PROBLEMS independent problems in one launch (N and the output type may
 // differ per problem; M too when the launch qualifies for the large-tile bf16 kernel, i.e. every

@@ -897,11 +897,60 @@ __global__ __launch_bounds__(GEMV_WAVES * 64) void gemm_bf16_rows_kernel(GemmBat
 // waves on a 32 x 32 tile walk K in an eighth of the steps and cover the chip with tiles, where a
 // 64 x 64 tile staged through LDS left most of it idle (256 x 128 x 824: 64 -> 11 us).  Where 64 x 64
 // tiles are many enough for every CU, they halve the loads per product.
-template <int TB, int NWV>
+//
+// A problem marked by_rows takes a wave per row and two columns instead: lane l sums the 8-wide pieces l, l + 64, .. of the
+// row, a butterfly adds the lanes.  Its chains are K / 64 long, not K / 8: the routing weights, which exponentiate
+// these sums, are 1.2e-7 from 64 bits at K = 4096, and 3.1e-7 on the tiles.
+__device__ __forceinline__ void f32_rows(const GemmProblem &P, int first, int step) {
+  constexpr int NC = 2;   // columns of an item (with four the kernel's registers cost a workgroup per CU)
+  const int lane = threadIdx.x & 63, groups = (P.N + NC - 1) / NC;
+  const GemmSeg &S = P.seg[0];
+  for (int64_t item = first; item < (int64_t)P.M * groups; item += step) {
+    const int64_t row = item / groups;
+    const int n0 = (int)(item - row * groups) * NC;
+    const float *a = reinterpret_cast<const float *>(S.A) + row * S.lda;
+    float acc[NC];
+#pragma unroll
+    for (int n = 0; n < NC; n++) acc[n] = 0.f;
+    for (int c = lane * 8; c < S.K; c += 64 * 8) {   // K % 8 == 0
+      Vec8<float> av;
+      av.load(a + c);
+#pragma unroll
+      for (int n = 0; n < NC; n++) {
+        Vec8<float> bv;
+        bv.load(reinterpret_cast<const float *>(S.B) + (int64_t)(n0 + n < P.N ? n0 + n : P.N - 1) * S.ldb + c);
+#pragma unroll
+        for (int i = 0; i < 8; i++) acc[n] = fmaf(av.get(i), bv.get(i), acc[n]);
+      }
+    }
+#pragma unroll
+    for (int n = 0; n < NC; n++) {
+      float v = acc[n];
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+      if (lane == n && n0 + n < P.N) reinterpret_cast<float *>(P.C)[row * P.ldc + n0 + n] = v;
+    }
+  }
+}
+
+__global__ __launch_bounds__(256) void f32_rows_kernel(GemmBatch args) {
+  f32_rows(args.p[0], blockIdx.x * 4 + (threadIdx.x >> 6), gridDim.x * 4);
+}
+
+// ROWS: the launch has such a problem (an instance of its own: the branch changes the compiler's schedule of
+// the tiles, a tenth more time where 64 x 64 tiles cover the chip, which therefore have the rows in a launch
+// behind them)
+template <int TB, int NWV, bool ROWS>
 __global__ __launch_bounds__(NWV * 64) void gemm_f32_kernel(GemmBatch args) {
   constexpr int NB = TB / 16;
   __shared__ float red[NWV][TB][TB + (TB == 64 ? 0 : 4)];   // 64 KB at most
   const GemmProblem &P = args.p[blockIdx.z];
+  if constexpr (ROWS) {
+    if (P.by_rows) {   // workgroup-uniform
+      f32_rows(P, blockIdx.x * NWV + (threadIdx.x >> 6), gridDim.x * NWV);
+      return;
+    }
+  }
   const int M = P.M, N = P.N;
   const int tiles_m = (M + TB - 1) / TB, tiles_n = (N + TB - 1) / TB;
   if ((int)blockIdx.x >= tiles_m * tiles_n) return;   // problems of one launch may differ in shape
@@ -1293,19 +1342,33 @@ hipError_t launch_gemm(int dtype, const GemmProblem *probs, int nprob, hipStream
     for (int i = 0; i < GEMM_MAX_PROBLEMS; i++) l.p[i] = probs[only];
   const int nl = only >= 0 ? 1 : nprob;
   if (dtype == MIXLORA_F32) {
-    int t32 = 0, t64 = 0, all64 = 0;
+    int t32 = 0, t64 = 0, all64 = 0, rows = -1;
     for (int i = 0; i < nprob; i++) {
       if (probs[i].M <= 0 || probs[i].N <= 0) return hipErrorInvalidValue;
+      if (probs[i].by_rows) {
+        if (rows >= 0 || i + 1 != nprob || only >= 0 || probs[i].nseg != 1) return hipErrorInvalidValue;
+        rows = i;
+        continue;
+      }
       const int a = ((probs[i].M + 31) / 32) * ((probs[i].N + 31) / 32);
       const int c = ((probs[i].M + 63) / 64) * ((probs[i].N + 63) / 64);
       t32 = a > t32 ? a : t32;
       t64 = c > t64 ? c : t64;
       all64 += c;
     }
-    if (all64 >= 512)   // two tiles of 64 x 64 per CU
-      hipLaunchKernelGGL((gemm_f32_kernel<64, 4>), dim3(t64, 1, nl), dim3(256), 0, st, l);
-    else
-      hipLaunchKernelGGL((gemm_f32_kernel<32, 8>), dim3(t32, 1, nl), dim3(512), 0, st, l);
+    if (all64 >= 512 || (rows >= 0 && nprob == 1)) {   // two tiles of 64 x 64 per CU
+      if (nl > (rows >= 0))
+        hipLaunchKernelGGL((gemm_f32_kernel<64, 4, false>), dim3(t64, 1, nl - (rows >= 0)), dim3(256), 0, st, l);
+      if (rows >= 0) {
+        l.p[0] = probs[rows];
+        const int64_t blocks = ((int64_t)l.p[0].M * ((l.p[0].N + 1) / 2) + 3) / 4;
+        hipLaunchKernelGGL(f32_rows_kernel, dim3((unsigned)(blocks < 4096 ? blocks : 4096)), dim3(256), 0, st, l);
+      }
+    } else if (rows >= 0) {
+      hipLaunchKernelGGL((gemm_f32_kernel<32, 8, true>), dim3(t32, 1, nl), dim3(512), 0, st, l);
+    } else {
+      hipLaunchKernelGGL((gemm_f32_kernel<32, 8, false>), dim3(t32, 1, nl), dim3(512), 0, st, l);
+    }
     return hipGetLastError();
   }
   const int M = probs[0].M, N = probs[0].N;
