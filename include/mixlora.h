@@ -113,9 +113,7 @@ MIXLORA_API size_t mixlora_workspace_bytes(const mixlora_dims *dims, int for_bac
  *      expert_counts [N] int32 = number of pairs routed to each expert;
  *      aux_loss [1] float32 (device) = Eq. 8 with dims.aux_coeff / dims.aux_mode.
  * workspace: scratch, and the activations the backward needs; pass the same buffer,
- *      untouched, to mixlora_ffn_backward.  A workspace_bytes below the for_backward = 1 size
- *      says that no backward pass follows: activations that only it reads are then not kept.
- *      Calls sharing a workspace must not overlap. */
+ *      untouched, to mixlora_ffn_backward.  Calls sharing a workspace must not overlap. */
 MIXLORA_API int mixlora_ffn_forward(const mixlora_dims *dims, const mixlora_weights *w, const void *x,
                         void *y, int32_t *topk_idx, float *topk_w, int32_t *expert_counts,
                         float *aux_loss, void *workspace, size_t workspace_bytes,

@@ -476,7 +476,6 @@ static int forward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mod
     fs.B_gate = (const bf16_t *)w->B_gate, fs.B_up = (const bf16_t *)w->B_up, fs.A_down = (const bf16_t *)w->A_down;
     fs.Pg_all = (const float *)(ws + L.Pg_all), fs.Pu_all = (const float *)(ws + L.Pu_all);
     fs.a_comb = (bf16_t *)(ws + L.a_comb);
-    fs.a_grp = workspace_bytes >= L.bwd_end ? (bf16_t *)(ws + L.a_grp) : nullptr;
     fs.Q_part = (float *)(ws + L.rank_part);
     fs.probs = probs, fs.w_out = topk_w, fs.w_ws = wts, fs.loss = aux_loss;
     fs.F = (float *)(ws + L.F), fs.P = (float *)(ws + L.P);
@@ -600,15 +599,13 @@ static int forward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mod
   if (use_pg) {
     // tokens grouped by expert pair: rank-r deltas, SiLU * up, the weighted combination of a
     // token's two pairs (Algorithm 1 lines 11-13 and 15) and the A_down projections in one pass
-    // that fetches G and U once per token; the grouped activations are kept only for a backward
-    // pass that does not make them again
-    const int write_a = workspace_bytes >= L.bwd_end && !fused_pg_bwd_ok(pc, f, Nl) ? 1 : 0;
-    HIP_TRY_AS(PROF_FUSED_FWD, (double)(3 + 2 * write_a) * T * f * Eb,
+    // that fetches G and U once per token; the backward pass makes the pairs' activations again
+    HIP_TRY_AS(PROF_FUSED_FWD, 3.0 * T * f * Eb,
                launch_swiglu_fwd_pg(pc, f, D.lora_scale, pg_tok, pg_tiles, pg_ntiles,
                                     ws + L.G, ws + L.U, (float *)(ws + L.Pg_all),
                                     (float *)(ws + L.Pu_all), w->B_gate, w->B_up, w->A_down,
-                                    ws + L.a_grp, ws + L.a_comb, (float *)(ws + L.rank_part),
-                                    (float *)(ws + L.Q_all), ws + L.Qw, R, write_a, st));
+                                    ws + L.a_comb, (float *)(ws + L.rank_part),
+                                    (float *)(ws + L.Q_all), ws + L.Qw, R, st));
     GemmProblem p = problem(T, d, y, d, 0);
     add_seg(p, ws + L.a_comb, f, w->W_down, f, f);
     add_seg(p, ws + L.Qw, R, ws + L.Bd_cat, R, R);
@@ -863,13 +860,16 @@ static int backward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mo
                                     (float *)(ws + L.pg_slots), grads->dB_gate, grads->dB_up, grads->dA_down, st));
   } else if (dt == MIXLORA_BF16) {
     nct = fused_splits(f, (int)kT);
-    HIP_TRY_AS(PROF_FUSED_BWD, 5.0 * kT * f * Eb, launch_swiglu_bwd_mfma(pc, f, s, vanilla ? ws + L.Gp : ws + L.G,
+    // (the forward stages that end in the weighted combination have not stored the pairs' activations)
+    const bool make_a = !pair_down && !dora && (L.few || fused_pg_ok(pc, f));
+    HIP_TRY_AS(PROF_FUSED_BWD, (make_a ? 6.0 : 5.0) * kT * f * Eb, launch_swiglu_bwd_mfma(pc, f, s, vanilla ? ws + L.Gp : ws + L.G,
                                    vanilla ? ws + L.Up : ws + L.U, pair_down ? ws + L.Hp : ws + L.H,
                                    (float *)(ws + L.Pg_all),
                                    (float *)(ws + L.Pu_all), (float *)(ws + L.VB_all), w->B_gate,
                                    w->B_up, ws + L.AdT, ws + L.Bg_T, ws + L.Bu_T, ws + L.dg_grp,
                                    ws + L.du_grp, (float *)(ws + L.dw_part),
-                                   (float *)(ws + L.rank_part), st, rows_mode, dora ? &dargs : nullptr));
+                                   (float *)(ws + L.rank_part), make_a ? ws + L.a_grp : nullptr, st, rows_mode,
+                                   dora ? &dargs : nullptr));
   } else {
     HIP_TRY_AS(PROF_FUSED_BWD, 5.0 * kT * f * Eb, launch_swiglu_bwd(pc, f, s, ws + L.G, ws + L.U, (float *)(ws + L.Pg_all),
                               (float *)(ws + L.Pu_all), w->B_gate, w->B_up, ws + L.H,

@@ -129,7 +129,7 @@ struct FewStage {
   int mode;
   const bf16_t *G, *U, *B_gate, *B_up, *A_down;
   const float *Pg_all, *Pu_all;
-  bf16_t *a_comb, *a_grp;   // a_grp may be NULL
+  bf16_t *a_comb;
   float *Q_part;
   float *probs, *w_out, *w_ws, *loss, *F, *P;
   int32_t *idx_out, *idx_ws, *counts, *counts_out, *offs, *row_of_pair, *pair_of_row, *tok_offs, *model_tokens;
@@ -275,12 +275,12 @@ constexpr int ROWS_GU = 1, ROWS_H = 2, ROWS_SPARSE = 4;
 // bf16 MFMA backward of the same stage: dg_grp, du_grp, dw_part[row][split]
 // (split count = fused_splits(f, kT)), and per split the rank-r partial products of dg with B_gate and of du
 // with B_up, [2][split][kT][r] at rank_part.  AdT = A_down re-laid [N, f, r]; BgT / BuT = B banks re-laid
-// [N, r, f].
+// [N, r, f].  a_grp != NULL (r <= 16, not weight-decomposed): the pairs' activations as well.
 hipError_t launch_swiglu_bwd_mfma(const PairCtx &pc, int f, float s, const void *G, const void *U,
                                   const void *H, const float *Pg_all, const float *Pu_all,
                                   const float *VB_all, const void *B_gate, const void *B_up,
                                   const void *AdT, const void *BgT, const void *BuT, void *dg_grp,
-                                  void *du_grp, float *dw_part, float *rank_part, hipStream_t st,
+                                  void *du_grp, float *dw_part, float *rank_part, void *a_grp, hipStream_t st,
                                   int rows_mode = 0, const DoraArgs *dora = nullptr);
 // Pair-grouped token tiles (csrc/fused_pg.hip) for top-2 routing, N <= PG_MAX_EXPERTS, 128 < T <=
 // PG_MAX_TOKENS, r <= 16: tokens are grouped by their unordered expert pair, a workgroup handles
@@ -304,8 +304,8 @@ hipError_t launch_swiglu_fwd_pg(const PairCtx &pc, int f, float s, const int32_t
                                 const int32_t *tile_info, const int32_t *ntiles, const void *G,
                                 const void *U, const float *Pg_all, const float *Pu_all,
                                 const void *B_gate, const void *B_up, const void *A_down,
-                                void *a_grp, void *a_comb, float *Q_part, float *Q_all, void *Qw,
-                                int ldqw, int write_a, hipStream_t st);
+                                void *a_comb, float *Q_part, float *Q_all, void *Qw,
+                                int ldqw, hipStream_t st);
 // backward on the same tiles: the per-token sums dgsum, dusum of the pairs' dg, du; dw_part [pair row][splits], the
 // rank-r partial products [2][splits][kT][r] (splits = fused_pg_bwd_splits(f)); the gradients of B_gate, B_up and
 // A_down.  slots: fused_pg_bwd_floats floats of scratch.

@@ -210,7 +210,9 @@ __global__ __launch_bounds__(FT_WAVES * 64, KSR == 1 ? 3 : 1) void swiglu_fwd_mf
 // DORA: g = cg * (G + delta), u = cu * (U + delta); the gradients written (and used for TG / TU)
 // are those of the unscaled projections, cg * dg and cu * du; the sums over the tile's rows of
 // dg * (G + delta) and du * (U + delta) go to dm_part_g / dm_part_u [tile][column].
-template <int KSR, int NQ, bool DORA>
+// MAKE_A: the activations go to a_grp as well, for the sum of A_down's gradient (behind forward stages that do
+// not store them).
+template <int KSR, int NQ, bool DORA, bool MAKE_A = false>
 __global__ __launch_bounds__(FT_WAVES * 64, (KSR == 1 && !DORA) ? 2 : 1) void swiglu_bwd_mfma_kernel(
     PairCtx pc, int f, float s, const bf16_t *__restrict__ G, const bf16_t *__restrict__ U,
     const bf16_t *__restrict__ H, const float *__restrict__ Pg_all,
@@ -218,8 +220,8 @@ __global__ __launch_bounds__(FT_WAVES * 64, (KSR == 1 && !DORA) ? 2 : 1) void sw
     const bf16_t *__restrict__ B_gate, const bf16_t *__restrict__ B_up,
     const bf16_t *__restrict__ AdT, const bf16_t *__restrict__ BgT, const bf16_t *__restrict__ BuT,
     bf16_t *__restrict__ dg_grp, bf16_t *__restrict__ du_grp, float *__restrict__ dw_part,
-    float *__restrict__ TG_part, float *__restrict__ TU_part, int nsplit, int rows_mode,
-    DoraArgs dora) {
+    float *__restrict__ TG_part, float *__restrict__ TU_part, bf16_t *__restrict__ a_grp, int nsplit,
+    int rows_mode, DoraArgs dora) {
   constexpr int TILES = 3;
   constexpr int LDS_BYTES = FT_WAVES * TILES * FT_TILE * 2 > FT_WAVES * NQ * 16 * 64 * 4
                                 ? FT_WAVES * TILES * FT_TILE * 2 : FT_WAVES * NQ * 16 * 64 * 4;
@@ -358,7 +360,7 @@ __global__ __launch_bounds__(FT_WAVES * 64, (KSR == 1 && !DORA) ? 2 : 1) void sw
       const int lo = (8 * p + rr) * FT_PITCH + 8 * cc;
       const bf16x8_t dgl = ld8(tg + lo), dul = ld8(tu + lo), ddl = ld8(td + lo);
       const bf16x8_t gv = gnx[p], uv = unx[p], hv = hnx[p];
-      bf16x8_t dgv, duv;
+      bf16x8_t dgv, duv, av;
       float part = 0.f;
 #pragma unroll
       for (int m = 0; m < 8; m++) {
@@ -371,6 +373,7 @@ __global__ __launch_bounds__(FT_WAVES * 64, (KSR == 1 && !DORA) ? 2 : 1) void sw
         const float da = wrow[p] * hh + (float)ddl[m];
         const float gs = gg * sg;                       // SiLU(g)
         part = fmaf(hh, gs * uu, part);
+        if constexpr (MAKE_A) av[m] = (bf16_t)(gs * uu);
         // d SiLU / dg = sig (1 + g (1 - sig)) = sig + SiLU(g) (1 - sig)
         float dgr = (da * uu) * fmaf(gs, 1.f - sg, sg);
         float dur = da * gs;
@@ -394,6 +397,7 @@ __global__ __launch_bounds__(FT_WAVES * 64, (KSR == 1 && !DORA) ? 2 : 1) void sw
       if (rvalid[p] && cvalid) {
         *reinterpret_cast<bf16x8_t *>(dg_grp + odst[p] + col) = dgv;
         *reinterpret_cast<bf16x8_t *>(du_grp + odst[p] + col) = duv;
+        if constexpr (MAKE_A) *reinterpret_cast<bf16x8_t *>(a_grp + odst[p] + col) = av;
       }
       *reinterpret_cast<bf16x8_t *>(tg + lo) = dgv;
       *reinterpret_cast<bf16x8_t *>(tu + lo) = duv;
@@ -545,24 +549,26 @@ hipError_t launch_swiglu_bwd_mfma(const PairCtx &pc, int f, float s, const void 
                                   const void *H, const float *Pg_all, const float *Pu_all,
                                   const float *VB_all, const void *B_gate, const void *B_up,
                                   const void *AdT, const void *BgT, const void *BuT, void *dg_grp,
-                                  void *du_grp, float *dw_part, float *rank_part, hipStream_t st, int rows_mode,
-                                  const DoraArgs *dora) {
+                                  void *du_grp, float *dw_part, float *rank_part, void *a_grp, hipStream_t st,
+                                  int rows_mode, const DoraArgs *dora) {
+  if (a_grp && (dora || pc.r > 16)) return hipErrorInvalidValue;   // (such forward stages store them)
   const int nP = pc.T * pc.k, nsplit = fused_splits(f, nP);
   float *TG_part = rank_part, *TU_part = rank_part + (size_t)nsplit * nP * pc.r;
   const dim3 grid((nP + FT_ROWS - 1) / FT_ROWS + pc.N, nsplit), block(FT_WAVES * 64);
   const DoraArgs da = dora ? *dora : DoraArgs{};
-#define MIXLORA_BWD(KSR_, NQ_, DORA_)                                                            \
-  hipLaunchKernelGGL((swiglu_bwd_mfma_kernel<KSR_, NQ_, DORA_>), grid, block, 0, st, pc, f, s,    \
+#define MIXLORA_BWD(...)                                                                         \
+  hipLaunchKernelGGL((swiglu_bwd_mfma_kernel<__VA_ARGS__>), grid, block, 0, st, pc, f, s,         \
                      (const bf16_t *)G, (const bf16_t *)U, (const bf16_t *)H, Pg_all, Pu_all,      \
                      VB_all, (const bf16_t *)B_gate, (const bf16_t *)B_up, (const bf16_t *)AdT,    \
                      (const bf16_t *)BgT, (const bf16_t *)BuT, (bf16_t *)dg_grp, (bf16_t *)du_grp, \
-                     dw_part, TG_part, TU_part, nsplit, rows_mode, da)
+                     dw_part, TG_part, TU_part, (bf16_t *)a_grp, nsplit, rows_mode, da)
   if (dora) {
     if (pc.r <= 16) MIXLORA_BWD(1, 1, true);
     else if (pc.r <= 32) MIXLORA_BWD(2, 1, true);
     else MIXLORA_BWD(4, 2, true);
   } else {
-    if (pc.r <= 16) MIXLORA_BWD(1, 1, false);
+    if (a_grp) MIXLORA_BWD(1, 1, false, true);
+    else if (pc.r <= 16) MIXLORA_BWD(1, 1, false);
     else if (pc.r <= 32) MIXLORA_BWD(2, 1, false);
     else MIXLORA_BWD(4, 2, false);
   }

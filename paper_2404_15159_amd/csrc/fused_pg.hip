@@ -35,7 +35,7 @@ __device__ __forceinline__ void stg8(bf16_t *base, uint32_t byte_off, const bf16
 
 static_assert(PG_TILE_ROWS == FT_ROWS, "the grouping kernel cuts tiles of FT_ROWS tokens");
 
-// Forward.  Per pair: a_grp[row(t, j), :] (when write_a), Q_part[split][row(t, j)][q]; per token:
+// Forward.  Per pair: Q_part[split][row(t, j)][q]; per token:
 // a_comb[t, :] = w_ta a_ta + w_tb a_tb (the lower-numbered expert's term first, fp32, one rounding).
 //
 // One wavefront owns a 32-token x 64-column piece for BOTH experts of the tile: G and U are fetched once, the two
@@ -47,8 +47,8 @@ __global__ __launch_bounds__(FT_WAVES * 64, 2) void swiglu_fwd_pg_kernel(
     const int32_t *__restrict__ tile_info, const int32_t *__restrict__ ntiles,
     const bf16_t *__restrict__ G, const bf16_t *__restrict__ U, const float *__restrict__ Pg_all,
     const float *__restrict__ Pu_all, const bf16_t *__restrict__ B_gate,
-    const bf16_t *__restrict__ B_up, const bf16_t *__restrict__ A_down, bf16_t *__restrict__ a_grp,
-    bf16_t *__restrict__ a_comb, float *__restrict__ Q_part, int nsplit, int write_a) {
+    const bf16_t *__restrict__ B_up, const bf16_t *__restrict__ A_down,
+    bf16_t *__restrict__ a_comb, float *__restrict__ Q_part, int nsplit) {
   constexpr int TILES = 3;   // per wavefront: G then expert a's activations, U then expert b's, the combination
   extern __shared__ __align__(16) unsigned char lds[];   // pg_fwd_lds(NQ) bytes
   __shared__ int growmap[2][FT_ROWS];   // expert-grouped row of every tile row, per expert
@@ -76,7 +76,7 @@ __global__ __launch_bounds__(FT_WAVES * 64, 2) void swiglu_fwd_pg_kernel(
       }
   }
   // row-major role: the four rows (8p + rr) this lane serves
-  uint32_t gsrc[4], adst[2][4];
+  uint32_t gsrc[4];
   bool rvalid[4];
 #pragma unroll
   for (int p = 0; p < 4; p++) {
@@ -88,7 +88,6 @@ __global__ __launch_bounds__(FT_WAVES * 64, 2) void swiglu_fwd_pg_kernel(
 #pragma unroll
     for (int x = 0; x < 2; x++) {
       const int grow = pc.row_of_pair[tok * 2 + (slot_a ^ x)];
-      adst[x][p] = (uint32_t)grow * (uint32_t)f * 2u;
       if (cc == 0 && wave == 0) growmap[x][rl] = grow;
     }
   }
@@ -209,13 +208,7 @@ __global__ __launch_bounds__(FT_WAVES * 64, 2) void swiglu_fwd_pg_kernel(
 #pragma unroll
     for (int p = 0; p < 4; p++) {
       const bf16_t *tp = tiles + (8 * p + rr) * FT_PITCH + 8 * cc;
-      if (rvalid[p] && cvalid) {
-        if (write_a) {
-          stg8(a_grp, adst[0][p] + col, ld8(tp));
-          stg8(a_grp, adst[1][p] + col, ld8(tp + FT_TILE));
-        }
-        stg8(a_comb, gsrc[p] + col, ld8(tp + 2 * FT_TILE));
-      }
+      if (rvalid[p] && cvalid) stg8(a_comb, gsrc[p] + col, ld8(tp + 2 * FT_TILE));
     }
     // Q_x += a_x[rows, 64 cols] * A_down[e_x, q, same cols]^T : four K steps of 16 columns
 #pragma unroll
@@ -685,8 +678,8 @@ hipError_t launch_swiglu_fwd_pg(const PairCtx &pc, int f, float s, const int32_t
                                 const int32_t *tile_info, const int32_t *ntiles, const void *G,
                                 const void *U, const float *Pg_all, const float *Pu_all,
                                 const void *B_gate, const void *B_up, const void *A_down,
-                                void *a_grp, void *a_comb, float *Q_part, float *Q_all, void *Qw,
-                                int ldqw, int write_a, hipStream_t st) {
+                                void *a_comb, float *Q_part, float *Q_all, void *Qw,
+                                int ldqw, hipStream_t st) {
   if (!fused_pg_ok(pc, f)) return hipErrorInvalidValue;
   const int nsplit = fused_pg_splits(f, pc.T, pc.N);
   const dim3 grid(fused_pg_max_tiles(pc.T, pc.N), nsplit), block(FT_WAVES * 64);
@@ -704,7 +697,7 @@ hipError_t launch_swiglu_fwd_pg(const PairCtx &pc, int f, float s, const int32_t
     hipLaunchKernelGGL(kern, grid, block, lds_, st, pc, f, s, tok_of_pos, tile_info, ntiles,      \
                        (const bf16_t *)G, (const bf16_t *)U, Pg_all, Pu_all,                      \
                        (const bf16_t *)B_gate, (const bf16_t *)B_up, (const bf16_t *)A_down,      \
-                       (bf16_t *)a_grp, (bf16_t *)a_comb, Q_part, nsplit, write_a);               \
+                       (bf16_t *)a_comb, Q_part, nsplit);                                         \
   } while (0)
   MIXLORA_PGF(1, 1);
 #undef MIXLORA_PGF

@@ -6,7 +6,7 @@ import pytest
 import torch
 
 from oracle import mixlora_oracle as orc
-from paper_2404_15159_amd import synth
+from paper_2404_15159_amd import binding as B, synth
 from paper_2404_15159_amd.runner import MixLoraFFN
 
 import parity_utils as pu
@@ -124,3 +124,24 @@ def test_capture_and_replay():
         g.replay()
         torch.cuda.synchronize()
         assert np.array_equal(m.results()["y"], ref["y"])
+
+
+@pytest.mark.parametrize("T,f", [(2, 512), (40, 768), (128, 512), (300, 768), (1000, 4648)])
+def test_backward_does_not_depend_on_the_size_named_to_the_forward(T, f):
+    """The forward may be told of the forward's own workspace size: in the same (larger) buffer it leaves all that a
+    backward pass reads, also beside the two stages above that end in the weighted combination."""
+    cfg = synth.scaled(BASE, name="few_ws", T=T, d=64, d_ff=f, N=8, k=2, r=16)
+    host = synth.make_inputs(cfg)
+    out = []
+    for size in (B.mixlora_workspace_bytes(MixLoraFFN(cfg, host).dims, True),
+                 B.mixlora_workspace_bytes(MixLoraFFN(cfg, host).dims, False)):
+        print(f"case T={T} f={f} size={size}", flush=True)
+        m = MixLoraFFN(cfg, host)
+        m.workspace.fill_(0xFF)
+        whole, m.ws_bytes = m.ws_bytes, size
+        m.forward()
+        m.ws_bytes = whole
+        m.backward(d_aux=1.0)
+        out.append(m.results())
+    for n in ("dx",) + pu.GRAD_NAMES:
+        assert np.isfinite(out[1][n]).all() and np.array_equal(out[0][n], out[1][n]), n
