@@ -32,7 +32,8 @@ struct Layout {
   size_t G, U, Pg_all, Pu_all, a_grp, Q_all;
   // forward scratch
   size_t a_comb, Qw, Bd_cat, rank_part, splitk, gp_scratch, gemm_part;
-  bool few;   // the few-token stage of csrc/fused_few.hip runs (its partial sums are rank_part)
+  bool few;   // the few-token stage of csrc/fused_few.hip runs
+  size_t few_part;   // its partial sums
   size_t gemm_floats;   // floats at gemm_part: partial tiles of GEMM launches cut along K
   size_t joint_floats;  // those that the default schedule would have
   size_t base_end;      // forward workspace without them
@@ -103,8 +104,8 @@ inline bool few_shapes(const mixlora_dims &D, int schedule, bool dora) {
 
 // Buffers a schedule does not use get size 0 (per-token G, U in the unshared schedule, the
 // combined activations where the down projection runs per pair, ...).
-// No smaller than `at_least` up to base_end.
-Layout make_layout_as(const mixlora_dims &D, int schedule, bool dora, bool few, size_t at_least = 0) {
+// No smaller than `at_least` up to base_end.  Nl: experts per adapter (D.N: of all).
+Layout make_layout_as(const mixlora_dims &D, int Nl, int schedule, bool dora, bool few, size_t at_least = 0) {
   Layout L{};
   L.few = few;
   const bool pair_down = schedule != MIXLORA_SCHEDULE_LINEAR_DOWN;
@@ -136,7 +137,9 @@ Layout make_layout_as(const mixlora_dims &D, int schedule, bool dora, bool few, 
   L.U = take(vanilla ? 0 : T * f * E);
   L.Pg_all = take(T * R * 4);
   L.Pu_all = take(T * R * 4);
-  L.a_grp = take(kT * f * E);
+  // (the few-token stage's partial sums share these bytes: only the backward pass stores activations then)
+  const size_t cols = few ? up(few_part_floats((int)f, (int)kT, (int)r) * 4) + T * FEW_RANK_SUMS * 4 : 0;
+  L.few_part = L.a_grp = take(cols > kT * f * E ? cols : kT * f * E);
   L.Q_all = take(kT * R * 4);
   L.a_comb = take(pair_down ? 0 : T * f * E);
   L.Qw = take(pair_down ? 0 : T * R * E);
@@ -159,9 +162,7 @@ Layout make_layout_as(const mixlora_dims &D, int schedule, bool dora, bool few, 
   L.Bd_cat = take(d * R * E);
   {   // per-split rank-r partial sums (two banks), for the grouped and the token-major stages
     const size_t sp_g = (size_t)fused_splits((int)f, (int)kT), sp_t = (size_t)fused_pg_splits((int)f, (int)T, (int)(N <= PG_MAX_EXPERTS ? N : 1));
-    const size_t grouped = 2 * (sp_g > sp_t ? sp_g : sp_t) * kT * r * 4;
-    const size_t cols = few ? up(few_part_floats((int)f, (int)kT, (int)r) * 4) + T * FEW_RANK_SUMS * 4 : 0;
-    L.rank_part = take(cols > grouped ? cols : grouped);
+    L.rank_part = take(2 * (sp_g > sp_t ? sp_g : sp_t) * kT * r * 4);
   }
   // few tokens (decode-shaped calls): partial outputs of the K-split down projection
   L.splitk = take(T <= SPLITK_MAX_ROWS ? (size_t)(few ? down_slices((int)d, (int)f).n : GEMM_MAX_PROBLEMS) * T * d * 4 : 0);
@@ -199,7 +200,8 @@ Layout make_layout_as(const mixlora_dims &D, int schedule, bool dora, bool few, 
   L.VB_all = take(T * R * 4);
   // (the backward on pair-grouped tiles keeps dg and du to itself; what it needs of its own lies here: partial
   // rank-r products and partial <H, a> per column block, slots of the gradient sums)
-  const bool pg = E == 2 && !pair_down && fused_pg_bwd_possible((int)f, (int)T, (int)N, (int)k, (int)r);
+  const PairCtx pc{nullptr, nullptr, nullptr, nullptr, nullptr, (int)T, (int)N, (int)k, (int)r};
+  const bool pg = E == 2 && !pair_down && fused_pg_bwd_ok(pc, (int)f, Nl);
   const size_t blocks = pg ? (size_t)fused_pg_bwd_splits((int)f) : 0;
   const size_t rank_bytes = up(2 * blocks * kT * r * 4), dw_bytes = up(blocks * kT * 4), grads2 = 2 * up(kT * f * E);
   const size_t own = pg ? rank_bytes + dw_bytes + fused_pg_bwd_floats((int)f, (int)T, (int)N, (int)r) * 4 : 0;
@@ -242,15 +244,14 @@ Layout make_layout_as(const mixlora_dims &D, int schedule, bool dora, bool few, 
   return L;
 }
 
-// The few-token stage keeps a partial sum per column block, the grouped stages one per split: where only
-// the latter's workspace fits the library's own array, they run (the layout and with it the path depend on the
-// dims alone, whichever entry point is called).  The few-token layout is no smaller than the grouped one, so the
-// calls that the array takes are those whose grouped workspace fits it.
-Layout make_layout(const mixlora_dims &D, int schedule = MIXLORA_SCHEDULE_LINEAR_DOWN,
+// The few-token layout is the grouped one's size, so the calls that the library's own array takes are those whose
+// grouped workspace fits it; where it is larger (one or two tokens of a few dozen columns) and does not fit,
+// the grouped stages run (the layout and with it the path depend on the dims alone, whichever entry point is called).
+Layout make_layout(const mixlora_dims &D, int Nl, int schedule = MIXLORA_SCHEDULE_LINEAR_DOWN,
                    bool dora = false) {
-  const Layout G = make_layout_as(D, schedule, dora, false);
+  const Layout G = make_layout_as(D, Nl, schedule, dora, false);
   if (!few_shapes(D, schedule, dora)) return G;
-  const Layout L = make_layout_as(D, schedule, dora, true, G.base_end);
+  const Layout L = make_layout_as(D, Nl, schedule, dora, true, G.base_end);
   const size_t limit = MIXLORA_STATIC_SCRATCH_BYTES;
   return L.base_end > limit && G.base_end <= limit ? G : L;
 }
@@ -328,7 +329,7 @@ int mixlora_version(void) { return 100; }
 
 size_t mixlora_workspace_bytes(const mixlora_dims *dims, int for_backward) {
   if (check_dims(dims) != MIXLORA_OK) return 0;
-  const Layout L = make_layout(*dims);
+  const Layout L = make_layout(*dims, dims->N);
   return for_backward ? L.bwd_end : L.fwd_end;
 }
 
@@ -379,7 +380,7 @@ static int forward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mod
                         int schedule = MIXLORA_SCHEDULE_LINEAR_DOWN,
                         const mixlora_dora *dora = nullptr,
                         float *gemm_part = nullptr) {   // partial tiles elsewhere than in the workspace
-  const Layout L = make_layout(Du, schedule, dora != nullptr);
+  const Layout L = make_layout(Du, Nl, schedule, dora != nullptr);
   const bool pair_down = schedule != MIXLORA_SCHEDULE_LINEAR_DOWN;   // down projection per pair
   const bool vanilla = schedule == MIXLORA_SCHEDULE_VANILLA;         // gate/up per pair as well
   if (workspace_bytes < (gemm_part ? L.base_end : L.fwd_end)) return MIXLORA_E_WORKSPACE;
@@ -476,7 +477,7 @@ static int forward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mod
     fs.B_gate = (const bf16_t *)w->B_gate, fs.B_up = (const bf16_t *)w->B_up, fs.A_down = (const bf16_t *)w->A_down;
     fs.Pg_all = (const float *)(ws + L.Pg_all), fs.Pu_all = (const float *)(ws + L.Pu_all);
     fs.a_comb = (bf16_t *)(ws + L.a_comb);
-    fs.Q_part = (float *)(ws + L.rank_part);
+    fs.Q_part = (float *)(ws + L.few_part);
     fs.probs = probs, fs.w_out = topk_w, fs.w_ws = wts, fs.loss = aux_loss;
     fs.F = (float *)(ws + L.F), fs.P = (float *)(ws + L.P);
     fs.idx_out = topk_idx, fs.idx_ws = idx, fs.counts = (int32_t *)(ws + L.counts), fs.counts_out = expert_counts;
@@ -484,8 +485,8 @@ static int forward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mod
     fs.pair_of_row = pair_of_row, fs.tok_offs = (int32_t *)(ws + L.tok_offs);
     fs.model_tokens = (int32_t *)(ws + L.model_tokens);
     HIP_TRY_AS(PROF_FUSED_FWD, 3.0 * T * f * Eb, launch_few_stage(fs, st));
-    const FewRank rk{(const float *)(ws + L.rank_part), wts, idx, row_of_pair, (const bf16_t *)w->B_down,
-                     (float *)(ws + L.Q_all), (float *)(ws + L.rank_part + up(few_part_floats(f, kT, r) * 4)),
+    const FewRank rk{(const float *)(ws + L.few_part), wts, idx, row_of_pair, (const bf16_t *)w->B_down,
+                     (float *)(ws + L.Q_all), (float *)(ws + L.few_part + up(few_part_floats(f, kT, r) * 4)),
                      T, N, k, r, few_column_blocks(f), D.lora_scale};
     if (gemm_rows_ok(dt, T, f + R)) {
       GemmProblem p = problem(T, d, y, d, 0);
@@ -715,7 +716,9 @@ size_t mixlora_multi_workspace_bytes(const mixlora_dims *dims, int32_t M, int fo
   if (!dims || M < 1 || (int64_t)M * dims->N > 64 || dims->k > dims->N) return 0;
   mixlora_dims all = *dims;
   all.N = M * dims->N;
-  return mixlora_workspace_bytes(&all, for_backward);
+  if (check_dims(&all) != MIXLORA_OK) return 0;
+  const Layout L = make_layout(all, dims->N);
+  return for_backward ? L.bwd_end : L.fwd_end;
 }
 
 int mixlora_multi_forward(const mixlora_dims *dims, const mixlora_multi *multi,
@@ -758,7 +761,7 @@ static int backward_impl(const mixlora_dims &Du, int Nl, const int32_t *token_mo
                          int schedule = MIXLORA_SCHEDULE_LINEAR_DOWN,
                          const mixlora_dora *dora = nullptr,
                          const mixlora_dora_grads *dgrads = nullptr) {
-  const Layout L = make_layout(Du, schedule, dora != nullptr);
+  const Layout L = make_layout(Du, Nl, schedule, dora != nullptr);
   const bool pair_down = schedule != MIXLORA_SCHEDULE_LINEAR_DOWN;
   const bool vanilla = schedule == MIXLORA_SCHEDULE_VANILLA;
   if (workspace_bytes < L.bwd_end) return MIXLORA_E_WORKSPACE;
@@ -1033,7 +1036,7 @@ static int check_schedule(const mixlora_dims *dims, int32_t schedule) {
 size_t mixlora_schedule_workspace_bytes(const mixlora_dims *dims, int32_t schedule,
                                         int for_backward) {
   if (check_dims(dims) != MIXLORA_OK || check_schedule(dims, schedule) != MIXLORA_OK) return 0;
-  const Layout L = make_layout(*dims, schedule);
+  const Layout L = make_layout(*dims, dims->N, schedule);
   return for_backward ? L.bwd_end : L.fwd_end;
 }
 
@@ -1078,7 +1081,7 @@ static int check_dora(const mixlora_dims *dims, const mixlora_dora *dora) {
 
 size_t mixlora_dora_workspace_bytes(const mixlora_dims *dims, int for_backward) {
   if (check_dims(dims) != MIXLORA_OK || dims->dtype != MIXLORA_BF16) return 0;
-  const Layout L = make_layout(*dims, MIXLORA_SCHEDULE_SHARED, true);
+  const Layout L = make_layout(*dims, dims->N, MIXLORA_SCHEDULE_SHARED, true);
   return for_backward ? L.bwd_end : L.fwd_end;
 }
 
@@ -1151,7 +1154,7 @@ int mixlora_ffn_forward_static(const mixlora_dims *dims, const mixlora_weights *
   const int rc = check_forward_args(dims, w, x, y, topk_idx, topk_w, expert_counts, aux_loss,
                                     reinterpret_cast<const void *>(uintptr_t{256}));
   if (rc) return rc;
-  const Layout L = make_layout(*dims);
+  const Layout L = make_layout(*dims, dims->N);
   if (L.base_end > (size_t)MIXLORA_STATIC_SCRATCH_BYTES) return MIXLORA_E_SCRATCH;
   void *ws = static_scratch_ptr();
   if (!ws) return MIXLORA_E_HIP;

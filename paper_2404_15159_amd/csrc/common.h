@@ -295,7 +295,6 @@ constexpr int PG_TILE_ROWS = 32;
 constexpr int PG_MAX_TOKENS = 1 << 16;
 bool fused_pg_ok(const PairCtx &pc, int f);
 bool fused_pg_bwd_ok(const PairCtx &pc, int f, int Nl);   // Nl: experts per adapter
-bool fused_pg_bwd_possible(int f, int T, int N, int k, int r);   // for some Nl
 int fused_pg_max_tiles(int T, int N);
 int fused_pg_splits(int f, int T, int N);
 hipError_t launch_group_token_pairs(const PairCtx &pc, int32_t *tok_of_pos, int32_t *tile_info,

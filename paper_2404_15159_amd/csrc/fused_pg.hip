@@ -654,10 +654,6 @@ static bool pg_bwd_size(int f, int T, int N, int Nl) {
 bool fused_pg_bwd_ok(const PairCtx &pc, int f, int Nl) {
   return fused_pg_ok(pc, f) && pg_bwd_size(f, pc.T, pc.N, Nl);
 }
-bool fused_pg_bwd_possible(int f, int T, int N, int k, int r) {   // with adapters of two experts at the least
-  const PairCtx pc{nullptr, nullptr, nullptr, nullptr, nullptr, T, N, k, r};
-  return fused_pg_ok(pc, f) && pg_bwd_size(f, T, N, 2);
-}
 
 int fused_pg_max_tiles(int T, int N) { return (T + FT_ROWS - 1) / FT_ROWS + N * N; }
 

@@ -118,6 +118,21 @@ def test_static_scratch_limit_of_few_tokens(lib):
         assert ei.value.code == -7
 
 
+def test_workspace_holds_no_stage_that_does_not_run(lib):
+    """Slots of the pair-grouped backward are reserved where its rule (tokens per pair of experts of ONE adapter) takes
+    the call, and few tokens' partial sums lie where the activations would: sizes of the expert-grouped stages alone."""
+    def mib(T, N, M=1, d=4096, f=11008, r=16):
+        return B.mixlora_multi_workspace_bytes(dims(T=T, d=d, d_ff=f, N=N, k=2, r=r), M, True) / 2.0 ** 20
+
+    assert mib(800, 16) < 565 and mib(2000, 16) < 905 and mib(500, 8) < 470
+    assert mib(1000, 8, M=2) < 620 and mib(1003, 16, d=1792, f=4096) < 227
+    # the same experts as one adapter or as two differ by the slots alone: at 2500 tokens only adapters of 8 take the stage
+    assert abs(mib(300, 16) - mib(300, 8, M=2)) < 0.1 and mib(2500, 8, M=2) > mib(2500, 16) + 200
+    for T, d, f, N, k, r, grouped in ((5, 128, 14528, 16, 3, 16, 1056512), (51, 192, 6144, 8, 3, 16, 4589824),
+                                      (3, 64, 5056, 24, 4, 16, 327168), (30, 448, 10432, 4, 2, 16, 3902208)):
+        assert B.mixlora_workspace_bytes(dims(T=T, d=d, d_ff=f, N=N, k=k, r=r), False) <= grouped
+
+
 def test_backward_argument_errors(lib):
     g = B.make_grads({n: FAKE for n in B.GRAD_FIELDS})
 
