@@ -462,7 +462,7 @@ struct TailArgs {
   int ncombine, width, comb_weighted;
 };
 struct TailBlocks {   // workgroups of each part (of one bank, job, token)
-  int router, reduce, gather, scatter, combine;
+  int router, reduce, gather, scatter, combine, total;
 };
 hipError_t launch_tail(int dtype, const TailArgs &a, hipStream_t st);
 

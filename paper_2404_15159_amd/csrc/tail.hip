@@ -155,10 +155,15 @@ __device__ __forceinline__ void scatter_body(const TailArgs &a, int bank, int bl
   reinterpret_cast<float *>(a.scatter_dst)[(int64_t)t * a.ld_scatter + bank * R + er] = v;
 }
 
+// Workgroups in rows of TAIL_GRID_X: a grid dimension holds less than 2^32 threads, and millions of tokens of a
+// narrow block need more workgroups than that in one.
+constexpr int TAIL_GRID_X = 1 << 16;
+
 template <typename E>
 __global__ __launch_bounds__(256) void tail_kernel(TailArgs a, TailBlocks n) {
   __shared__ bf16_t tile[256 + 64];
-  int b = blockIdx.x;   // all branches are workgroup-uniform
+  int b = blockIdx.y * TAIL_GRID_X + blockIdx.x;   // all branches are workgroup-uniform
+  if (b >= n.total) return;
   if (b < n.router) {
     router_bwd_body<E>(a, b);
     return;
@@ -202,9 +207,12 @@ hipError_t launch_tail(int dtype, const TailArgs &a, hipStream_t st) {
     return hipErrorInvalidValue;
   const int64_t blocks = n.router + 2ll * n.reduce + (int64_t)a.ngather * n.gather + (int64_t)a.nscatter * n.scatter +
                          (int64_t)a.ncombine * n.combine * pc.T;
-  if (blocks < 1 || blocks >= (1ll << 31)) return hipErrorInvalidValue;
-  if (dtype == MIXLORA_BF16) hipLaunchKernelGGL(tail_kernel<bf16_t>, dim3((unsigned)blocks), dim3(256), 0, st, a, n);
-  else hipLaunchKernelGGL(tail_kernel<float>, dim3((unsigned)blocks), dim3(256), 0, st, a, n);
+  static_assert((int64_t)TAIL_GRID_X * 256 < (1ll << 32) && (1ll << 31) / TAIL_GRID_X < 65536, "grid limits");
+  if (blocks < 1 || blocks >= (1ll << 31) - TAIL_GRID_X) return hipErrorInvalidValue;
+  n.total = (int)blocks;
+  const dim3 grid(blocks < TAIL_GRID_X ? (unsigned)blocks : TAIL_GRID_X, (unsigned)((blocks + TAIL_GRID_X - 1) / TAIL_GRID_X));
+  if (dtype == MIXLORA_BF16) hipLaunchKernelGGL(tail_kernel<bf16_t>, grid, dim3(256), 0, st, a, n);
+  else hipLaunchKernelGGL(tail_kernel<float>, grid, dim3(256), 0, st, a, n);
   return hipGetLastError();
 }
 

@@ -1,6 +1,6 @@
 """GPU parity of the row-wise steps that share one launch behind the fused backward stage: ranks whose rows
 do not fill a 256-thread block evenly, pair counts that end inside one, with and without the sums over a
-token's pairs (top-2 on pair-grouped tiles makes them itself).  Against the oracle, usual tolerances."""
+token's pairs (top-2 on pair-grouped tiles makes them itself); more workgroups than a grid row holds.  Against the oracle, usual tolerances."""
 import pytest
 
 from oracle import mixlora_oracle as orc
@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("base,T,N,k,r", [("llama2_7b", 37, 5, 3, 24), ("llama2_7b", 150, 8, 2, 40),
                                           ("llama2_7b", 131, 8, 1, 56), ("llama2_7b", 401, 8, 2, 8),
                                           ("llama2_7b", 203, 7, 4, 64), ("tiny_f32", 77, 5, 3, 24),
-                                          ("tiny_f32", 131, 4, 2, 40)])
+                                          ("tiny_f32", 131, 4, 2, 40), ("llama2_7b", 36001, 4, 2, 24)])
 def test_backward_rows_match_oracle(base, T, N, k, r):
     cfg = synth.scaled(synth.CONFIGS[base], name="tail", T=T, d=128, d_ff=344, N=N, k=k, r=r, alpha=2.0 * r)
     print(f"case {base} T={T} N={N} k={k} r={r}", flush=True)
