@@ -509,7 +509,9 @@ template <int NMAX> struct Counters {
 
 template <typename E, int NMAX, bool ROUTE>
 __global__ __launch_bounds__(RG_WAVES * 64) void route_group_kernel(RouteGroup a, RelayoutBatch batch, int rblocks) {
-  __shared__ uint16_t tok[ROUTE_GROUP_MAX_PAIRS];            // kept experts, 4 bits a slot; or the pair's group
+  // kept experts, 4 bits a slot; or the pair's group; or a partial sum (a float) per thread
+  __shared__ __align__(16) uint16_t tok[ROUTE_GROUP_MAX_PAIRS];
+  static_assert(sizeof(tok) >= RG_WAVES * 64 * sizeof(float), "partial sums fit");
   __shared__ int cnt[RG_WAVES][PG_GROUPS];
   __shared__ int wtot[2][RG_WAVES];
   if constexpr (ROUTE) {
