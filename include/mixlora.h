@@ -246,7 +246,8 @@ typedef struct {
   const float *d_aux;
 } mixlora_multi;
 
-/* Workspace bytes of the multi-adapter calls (0 for invalid dims or M). */
+/* Workspace bytes of the multi-adapter calls (0 for invalid dims or M; not always those of one adapter
+ * with M*N experts). */
 MIXLORA_API size_t mixlora_multi_workspace_bytes(const mixlora_dims *dims, int32_t M,
                                                  int for_backward);
 

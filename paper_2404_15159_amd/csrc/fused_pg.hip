@@ -642,17 +642,23 @@ bool fused_pg_ok(const PairCtx &pc, int f) {
          f >= 64 && (int64_t)2 * pc.T * f < ((int64_t)1 << 31);
 }
 
-// The backward takes at least 28 tokens per pair of experts that can occur (pairs of one adapter's own) and enough
-// column blocks and tiles for two workgroups per CU.  With fewer, tiles are mostly padding and the expert changes
-// with every tile; the expert-grouped stage, its combine and its sums are ahead then.  Training step, us, here /
-// there: 7B shape, 8 experts, 340 tokens 413 / 380, 600 565 / 557, 800 680 / 675; 1024 x 2752, 800 211 / 207,
-// 1600 247 / 259; 16 experts 2000 281 / 274, 3400 372 / 381; 512 x 1536, 1000 176 / 156, 3000 226 / 228; two
-// adapters of 8 experts, 7B shape, 1600 1157 / 1147, 2048 1278 / 1280.
-static bool pg_bwd_size(int f, int T, int N, int Nl) {
-  return T >= 14 * N * (Nl - 1) && (int64_t)fused_pg_bwd_splits(f) * ((T + FT_ROWS - 1) / FT_ROWS) >= 1024;
+// The backward takes at least 24 (rank 8) or 36 (rank 16) tokens per pair of experts that can occur (pairs of one
+// adapter's own), or 3400 in all: with fewer, tiles are mostly padding and the expert, with it r columns of sums to flush, changes with
+// every tile; the expert-grouped stage, its combine and its sums are ahead then.  Training step, us, here / there, rank
+// 16: 7B shape, 8 experts, 784 tokens 675 / 671, 1000 733 / 719, 1050 802 / 801, 1300 963 / 972; 12 experts 2000
+// 1236 / 1225, 2400 1558 / 1560; 16 experts 3000 1824 / 1799, 3400 1980 / 1983, 4200 2406 / 2409; two adapters of 8, 1900 1275 / 1252, 2048
+// 1274 / 1283.  Rank 8: 7B shape, 8 experts, 600 532 / 530, 784 640 / 643; 16 experts 2200 1516 / 1489, 3000
+// 1742 / 1767.  (d_ff of 4096 to 8192, where the other form's sums fill the chip badly, would gain 3 to 6 % from 600
+// tokens on.)  Below 1024 items, column blocks times tiles, two workgroups per CU have one each: 1024 x 2752, 1000
+// tokens 224 / 211, 1500 230 / 235; 512 x 1536, 1800 187 / 179, 3000 216 / 218.  And few column blocks leave
+// pg_sums_reduce_kernel a long chain of runs: 256 x 512, 10000 tokens 288 / 263, 20000 411 / 419; x 704, 7000 252 / 235,
+// 14000 359 / 375; x 1024, 5000 241 / 235, 7000 281 / 284.
+static bool pg_bwd_size(int f, int T, int N, int Nl, int r) {
+  const int64_t blocks = fused_pg_bwd_splits(f), items = blocks * ((T + FT_ROWS - 1) / FT_ROWS);
+  return (4ll * T >= (24ll + 3 * r) * N * (Nl - 1) || T >= 3400) && items >= 1024 && items * blocks >= 12000;
 }
 bool fused_pg_bwd_ok(const PairCtx &pc, int f, int Nl) {
-  return fused_pg_ok(pc, f) && pg_bwd_size(f, pc.T, pc.N, Nl);
+  return fused_pg_ok(pc, f) && pg_bwd_size(f, pc.T, pc.N, Nl, pc.r);
 }
 
 int fused_pg_max_tiles(int T, int N) { return (T + FT_ROWS - 1) / FT_ROWS + N * N; }

@@ -126,7 +126,7 @@ def test_capture_and_replay():
         assert np.array_equal(m.results()["y"], ref["y"])
 
 
-@pytest.mark.parametrize("T,f", [(2, 512), (40, 768), (128, 512), (300, 768), (1000, 4648)])
+@pytest.mark.parametrize("T,f", [(2, 512), (40, 768), (128, 512), (300, 768), (1100, 4648)])
 def test_backward_does_not_depend_on_the_size_named_to_the_forward(T, f):
     """The forward may be told of the forward's own workspace size: in the same (larger) buffer it leaves all that a
     backward pass reads, also beside the two stages above that end in the weighted combination."""

@@ -18,7 +18,9 @@ BASE = synth.CONFIGS["llama2_7b"]
 
 
 @pytest.mark.parametrize("T,f,N,r", [(783, 5632, 8, 16), (784, 5632, 8, 16), (1000, 4648, 8, 8), (1100, 4168, 3, 16),
-                                     (3400, 1288, 16, 8), (900, 4688, 2, 4), (2048, 2064, 7, 12)])
+                                     (3400, 1288, 16, 8), (900, 4688, 2, 4), (2048, 2064, 7, 12), (1007, 5632, 8, 16),
+                                     (1008, 5632, 8, 16), (671, 6912, 8, 8), (672, 6912, 8, 8), (3399, 1408, 16, 16), (3400, 1408, 16, 16), (3808, 1280, 4, 16),
+                                     (3840, 1280, 4, 16)])
 def test_pair_backward_matches_oracle(T, f, N, r):
     cfg = synth.scaled(BASE, name="pair_bwd", T=T, d=64, d_ff=f, N=N, k=2, r=r, alpha=2.0 * r)
     print(f"case T={T} f={f} N={N} r={r}", flush=True)
@@ -66,7 +68,7 @@ def test_pair_backward_of_several_adapters(T, M, N):
 
 
 # (the second: pair-grouped forward, expert-grouped backward)
-@pytest.mark.parametrize("T,f", [(1000, 4648), (300, 776)])
+@pytest.mark.parametrize("T,f", [(1100, 4648), (300, 776)])
 @pytest.mark.parametrize("name", ["W_gate", "W_up", "W_down"])
 def test_non_finite_feature_stays_to_itself(T, f, name):
     """One infinite element of a frozen matrix makes one feature (a column of G, U or dy W_down) non-finite for every
@@ -91,7 +93,7 @@ def test_non_finite_feature_stays_to_itself(T, f, name):
     assert np.array_equal(out[0]["dA_down"][:, :, rest], out[1]["dA_down"][:, :, rest])
 
 
-@pytest.mark.parametrize("T,f", [(1000, 4648), (300, 776)])
+@pytest.mark.parametrize("T,f", [(1100, 4648), (300, 776)])
 def test_non_finite_tokens_stay_to_themselves(T, f):
     cfg = synth.scaled(BASE, name="pair_bwd_nan", T=T, d=64, d_ff=f, N=8, k=2, r=16)
     host = synth.make_inputs(cfg)
