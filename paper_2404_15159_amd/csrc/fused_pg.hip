@@ -41,7 +41,6 @@ static_assert(PG_TILE_ROWS == FT_ROWS, "the grouping kernel cuts tiles of FT_ROW
 // One wavefront owns a 32-token x 64-column piece for BOTH experts of the tile: G and U are fetched once, the two
 // activations stay in registers until their weighted sum is formed.  Wavefronts never wait for each other
 // inside the loop.  Offsets into the [T, f] / [2T, f] arrays are 32-bit (host check).
-template <int KSR, int NQ>
 __global__ __launch_bounds__(FT_WAVES * 64, 2) void swiglu_fwd_pg_kernel(
     PairCtx pc, int f, float s, const int32_t *__restrict__ tok_of_pos,
     const int32_t *__restrict__ tile_info, const int32_t *__restrict__ ntiles,
@@ -50,7 +49,7 @@ __global__ __launch_bounds__(FT_WAVES * 64, 2) void swiglu_fwd_pg_kernel(
     const bf16_t *__restrict__ B_up, const bf16_t *__restrict__ A_down,
     bf16_t *__restrict__ a_comb, float *__restrict__ Q_part, int nsplit) {
   constexpr int TILES = 3;   // per wavefront: G then expert a's activations, U then expert b's, the combination
-  extern __shared__ __align__(16) unsigned char lds[];   // pg_fwd_lds(NQ) bytes
+  __shared__ __align__(16) bf16_t lds[FT_WAVES * TILES * FT_TILE];
   __shared__ int growmap[2][FT_ROWS];   // expert-grouped row of every tile row, per expert
   if ((int)blockIdx.x >= ntiles[0]) return;
   const int32_t *ti = tile_info + (int64_t)blockIdx.x * 4;
@@ -59,21 +58,20 @@ __global__ __launch_bounds__(FT_WAVES * 64, 2) void swiglu_fwd_pg_kernel(
   const int l31 = lane & 31, hi = lane >> 5, rr = lane >> 3, cc = lane & 7;
   const int gid = ti[0], row0 = ti[1], rows = ti[2];
   const int ex[2] = {gid / pc.N, gid % pc.N};
-  bf16_t *tiles = reinterpret_cast<bf16_t *>(lds) + wave * TILES * FT_TILE;
+  bf16_t *tiles = lds + wave * TILES * FT_TILE;
+  const int q0 = hi * 8;
+  const bool q_in = q0 < r;   // r <= 16: one MFMA step over the rank
 
   // MFMA role: second-operand fragments of this lane's row (token), per expert
-  bf16x8_t pg[2][KSR], pu[2][KSR];
+  bf16x8_t pg[2], pu[2];
   {
     const int64_t tm = tok_of_pos[row0 + (l31 < rows ? l31 : 0)];
 #pragma unroll
-    for (int x = 0; x < 2; x++)
-#pragma unroll
-      for (int ks = 0; ks < KSR; ks++) {
-        const int q0 = ks * 16 + hi * 8;
-        const bool v = q0 < r;
-        pg[x][ks] = cvt8(Pg_all + tm * R + ex[x] * r + (v ? q0 : 0), v, s);
-        pu[x][ks] = cvt8(Pu_all + tm * R + ex[x] * r + (v ? q0 : 0), v, s);
-      }
+    for (int x = 0; x < 2; x++) {
+      const int64_t o = tm * R + ex[x] * r + (q_in ? q0 : 0);
+      pg[x] = cvt8(Pg_all + o, q_in, s);
+      pu[x] = cvt8(Pu_all + o, q_in, s);
+    }
   }
   // row-major role: the four rows (8p + rr) this lane serves
   uint32_t gsrc[4];
@@ -99,13 +97,11 @@ __global__ __launch_bounds__(FT_WAVES * 64, 2) void swiglu_fwd_pg_kernel(
     wx[0] = pc.w[tok * 2 + slot_a];
     wx[1] = pc.w[tok * 2 + (slot_a ^ 1)];
   }
-  f32x16_t accq[2][NQ];
+  f32x16_t accq[2];
 #pragma unroll
   for (int x = 0; x < 2; x++)
 #pragma unroll
-    for (int j = 0; j < NQ; j++)
-#pragma unroll
-      for (int i = 0; i < 16; i++) accq[x][j][i] = 0.f;
+    for (int i = 0; i < 16; i++) accq[x][i] = 0.f;
 
   const int nsb = (f + FT_SB - 1) / FT_SB;
   const int per = (nsb + nsplit - 1) / nsplit;
@@ -119,36 +115,29 @@ __global__ __launch_bounds__(FT_WAVES * 64, 2) void swiglu_fwd_pg_kernel(
     ad_e[x] = A_down + (int64_t)ex[x] * r * f;
   }
 
-  bf16x8_t wg[2][2][KSR], wu[2][2][KSR], wf[2][4][NQ], gnx[4], unx[4];
+  bf16x8_t wg[2][2], wu[2][2], wf[2][4], gnx[4], unx[4];
   auto load_w = [&](int c0) {
 #pragma unroll
     for (int b = 0; b < 2; b++) {
       int col = c0 + 32 * b + l31;
       col = col < f ? col : f - 1;
+      const uint32_t o = ((uint32_t)col * (uint32_t)r + (q_in ? q0 : 0)) * 2u;
 #pragma unroll
-      for (int ks = 0; ks < KSR; ks++) {
-        const int q0 = ks * 16 + hi * 8;
-        const uint32_t o = ((uint32_t)col * (uint32_t)r + (q0 < r ? q0 : 0)) * 2u;
-#pragma unroll
-        for (int x = 0; x < 2; x++) {
-          wg[x][b][ks] = ldg8(bg_e[x], o);
-          wu[x][b][ks] = ldg8(bu_e[x], o);
-        }
+      for (int x = 0; x < 2; x++) {
+        wg[x][b] = ldg8(bg_e[x], o);
+        wu[x][b] = ldg8(bu_e[x], o);
       }
     }
   };
   auto load_wf = [&](int c0) {
 #pragma unroll
-    for (int s4 = 0; s4 < 4; s4++)
+    for (int s4 = 0; s4 < 4; s4++) {
+      int col = c0 + 16 * s4 + 8 * hi;
+      col = col < f ? col : f - 8;
+      const uint32_t o = ((uint32_t)(l31 < r ? l31 : 0) * (uint32_t)f + col) * 2u;
 #pragma unroll
-      for (int j = 0; j < NQ; j++) {
-        const int q = j * 32 + l31;
-        int col = c0 + 16 * s4 + 8 * hi;
-        col = col < f ? col : f - 8;
-        const uint32_t o = ((uint32_t)(q < r ? q : 0) * (uint32_t)f + col) * 2u;
-#pragma unroll
-        for (int x = 0; x < 2; x++) wf[x][s4][j] = ldg8(ad_e[x], o);
-      }
+      for (int x = 0; x < 2; x++) wf[x][s4] = ldg8(ad_e[x], o);
+    }
   };
   auto col_of = [&](int c0) { const int c = c0 + 8 * cc; return (uint32_t)(c < f ? c : f - 8) * 2u; };   // bytes
   if (sb_lo + wave < sb_hi) {
@@ -188,11 +177,8 @@ __global__ __launch_bounds__(FT_WAVES * 64, 2) void swiglu_fwd_pg_kernel(
 #pragma unroll
       for (int x = 0; x < 2; x++) {
         f32x16_t g = g0, u = u0;   // + the expert's rank-r deltas
-#pragma unroll
-        for (int ks = 0; ks < KSR; ks++) {
-          g = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wg[x][b][ks], pg[x][ks], g, 0, 0, 0);
-          u = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wu[x][b][ks], pu[x][ks], u, 0, 0, 0);
-        }
+        g = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wg[x][b], pg[x], g, 0, 0, 0);
+        u = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wu[x][b], pu[x], u, 0, 0, 0);
 #pragma unroll
         for (int i = 0; i < 16; i++) {
           g[i] = g[i] * fsigmoid(g[i]) * u[i];   // columns past f: finite, meet zeroed weights
@@ -217,33 +203,28 @@ __global__ __launch_bounds__(FT_WAVES * 64, 2) void swiglu_fwd_pg_kernel(
 #pragma unroll
       for (int x = 0; x < 2; x++) {
         const bf16x8_t af = ld8(tiles + x * FT_TILE + l31 * FT_PITCH + 16 * s4 + 8 * hi);
-#pragma unroll
-        for (int j = 0; j < NQ; j++) {
-          bf16x8_t w = wf[x][s4][j];
-          if (zero_w) w = zero8();
-          accq[x][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af, w, accq[x][j], 0, 0, 0);
-        }
+        bf16x8_t w = wf[x][s4];
+        if (zero_w) w = zero8();
+        accq[x] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af, w, accq[x], 0, 0, 0);
       }
     }
     load_wf(cn);
     __builtin_amdgcn_wave_barrier();
   }
-  // accq[x][j][i]: row 8*(i/4) + 4*hi + i%4 of the tile, q = j*32 + l31.  Each wavefront parks its
+  // accq[x][i]: row 8*(i/4) + 4*hi + i%4 of the tile, q = l31.  Each wavefront parks its
   // sums in its own (now dead) tile space; then the four are added in a fixed order.
-  static_assert(sizeof(float) * 2 * NQ * 16 * 64 <= sizeof(bf16_t) * TILES * FT_TILE, "reduction space");
+  static_assert(sizeof(float) * 2 * 16 * 64 <= sizeof(bf16_t) * TILES * FT_TILE, "reduction space");
   float *mine = reinterpret_cast<float *>(tiles);
 #pragma unroll
   for (int x = 0; x < 2; x++)
 #pragma unroll
-    for (int j = 0; j < NQ; j++)
-#pragma unroll
-      for (int i = 0; i < 16; i++) mine[((x * NQ + j) * 16 + i) * 64 + lane] = accq[x][j][i];
+    for (int i = 0; i < 16; i++) mine[(x * 16 + i) * 64 + lane] = accq[x][i];
   __syncthreads();
   const int wstride = TILES * FT_TILE / 2;   // floats between two wavefronts' spaces
   const float *base = reinterpret_cast<const float *>(lds);
-  for (int idx2 = threadIdx.x; idx2 < 2 * NQ * 16 * 64; idx2 += FT_WAVES * 64) {
-    const int x = idx2 / (NQ * 16 * 64), j = (idx2 / (16 * 64)) % NQ, i = (idx2 / 64) % 16, ln = idx2 % 64;
-    const int q = j * 32 + (ln & 31);
+  for (int idx2 = threadIdx.x; idx2 < 2 * 16 * 64; idx2 += FT_WAVES * 64) {
+    const int x = idx2 / (16 * 64), i = (idx2 / 64) % 16, ln = idx2 % 64;
+    const int q = ln & 31;
     const int rl = 8 * (i >> 2) + 4 * (ln >> 5) + (i & 3);
     if (q < r && rl < rows) {
       const float v = (base[idx2] + base[wstride + idx2]) + (base[2 * wstride + idx2] + base[3 * wstride + idx2]);
@@ -252,25 +233,24 @@ __global__ __launch_bounds__(FT_WAVES * 64, 2) void swiglu_fwd_pg_kernel(
   }
 }
 
-static size_t pg_fwd_lds(int) { return (size_t)FT_WAVES * 3 * FT_TILE * sizeof(bf16_t); }
-
 // Backward of the stage above on the same token tiles, with the three gradient sums over d_ff-wide operands
 // (dB_gate, dB_up, dA_down) in it: the per-pair gradients dg, du and the activations they need never leave
 // the workgroup.
 //
-// A workgroup owns 256 columns and walks a run of consecutive tiles: wavefronts 0-3 ("role A") take the
-// rows as rows of expert a, 64 columns each, wavefronts 4-7 ("role B") as rows of expert b.  The columns'
+// A workgroup owns 128 columns (PGB_COLS) and walks a run of consecutive tiles: wavefronts 0 and 1 ("role A")
+// take the rows as rows of expert a, 64 columns each, wavefronts 2 and 3 ("role B") as rows of expert b.  The columns'
 // bank rows stay in registers while the expert stays; the sums accumulate there (48 registers) and are
 // flushed to the wavefront's own slot of the expert when it changes, which tiles ordered by expert pair
 // make rare.  With H[t] = W_down^T dy[t]:
 //   da = w H + A_down^T (w s VB),  dg = da * u * SiLU'(g),  du = da * SiLU(g),  dw += <H, a>
 // in the accumulators' layout (a lane holds 16 columns of one row): G, U, H go through LDS row-major, the
-// rank-r terms are added to them by MFMA, so no delta is rounded.  The results return to the tiles in LDS, rounded to bf16, where
-//   - role A adds role B's dg and du to its own and stores the per-token sums,
+// rank-r terms are added to them by MFMA, so no delta is rounded.  The results return to the tiles in LDS,
+// rounded to bf16, where
+//   - the two roles add each other's to their own and store the per-token sums, role A those of dg, role B of du,
 //   - the rank-r products with B_gate^T, B_up^T (contraction over columns) read them by rows, and
 //   - the gradient sums (contraction over rows) read them transposed (ds_read_b64_tr_b16).
-// Rank-r products of the four column wavefronts are added through LDS, one partial sum per 256 columns.
-constexpr int PGB_CW = 2, PGB_WAVES = 2 * PGB_CW, PGB_COLS = PGB_CW * FT_SB;   // column wavefronts of a role
+// Rank-r products of a role's wavefronts are added through LDS, one partial sum per PGB_COLS columns.
+constexpr int PGB_CW = 2, PGB_WAVES = 2 * PGB_CW, PGB_COLS = PGB_CW * FT_SB;   // PGB_CW: wavefronts of a role
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
 
 struct PgBwd {
@@ -600,7 +580,7 @@ __global__ __launch_bounds__(PGB_WAVES * 64, 2) void swiglu_bwd_pg_kernel(PgBwd 
 }
 
 // The three sums from the slots in use, workgroups in ascending order, role A's before role B's; a
-// workgroup: one expert, one sum, 256 columns, a thread all rank entries of one column.
+// workgroup: one expert, one sum, PGB_COLS columns, a thread all rank entries of one column.
 __global__ __launch_bounds__(PGB_COLS) void pg_sums_reduce_kernel(PgBwd a, float scale, float *__restrict__ dB_gate,
                                                              float *__restrict__ dB_up, float *__restrict__ dA_down) {
   const int cb = blockIdx.x, e = blockIdx.y, sum = blockIdx.z, N = a.pc.N, r = a.pc.r, f = a.f;
@@ -685,24 +665,9 @@ hipError_t launch_swiglu_fwd_pg(const PairCtx &pc, int f, float s, const int32_t
   if (!fused_pg_ok(pc, f)) return hipErrorInvalidValue;
   const int nsplit = fused_pg_splits(f, pc.T, pc.N);
   const dim3 grid(fused_pg_max_tiles(pc.T, pc.N), nsplit), block(FT_WAVES * 64);
-#define MIXLORA_PGF(KSR_, NQ_)                                                                    \
-  do {                                                                                            \
-    auto kern = swiglu_fwd_pg_kernel<KSR_, NQ_>;                                                  \
-    const size_t lds_ = pg_fwd_lds(NQ_);                                                          \
-    static bool attr_set = false;                                                                 \
-    if (!attr_set) {                                                                              \
-      hipError_t e_ = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),                   \
-                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_); \
-      if (e_ != hipSuccess) return e_;                                                            \
-      attr_set = true;                                                                            \
-    }                                                                                             \
-    hipLaunchKernelGGL(kern, grid, block, lds_, st, pc, f, s, tok_of_pos, tile_info, ntiles,      \
-                       (const bf16_t *)G, (const bf16_t *)U, Pg_all, Pu_all,                      \
-                       (const bf16_t *)B_gate, (const bf16_t *)B_up, (const bf16_t *)A_down,      \
-                       (bf16_t *)a_comb, Q_part, nsplit);                                         \
-  } while (0)
-  MIXLORA_PGF(1, 1);
-#undef MIXLORA_PGF
+  hipLaunchKernelGGL(swiglu_fwd_pg_kernel, grid, block, 0, st, pc, f, s, tok_of_pos, tile_info, ntiles,
+                     (const bf16_t *)G, (const bf16_t *)U, Pg_all, Pu_all, (const bf16_t *)B_gate,
+                     (const bf16_t *)B_up, (const bf16_t *)A_down, (bf16_t *)a_comb, Q_part, nsplit);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   return launch_reduce_rank_parts(pc, Q_part, nsplit, Q_all, Qw, ldqw, 1, 0, st);
