@@ -81,21 +81,17 @@ __global__ __launch_bounds__(FT_WAVES * 64, 2) void swiglu_fwd_pg_kernel(
     const int rl = 8 * p + rr;
     rvalid[p] = rl < rows;
     const int64_t tok = tok_of_pos[row0 + (rvalid[p] ? rl : 0)];
-    const int slot_a = pc.idx[tok * 2] == ex[0] ? 0 : 1;   // expert a's slot of this token
     gsrc[p] = (uint32_t)(tok * f) * 2u;   // bytes
-#pragma unroll
-    for (int x = 0; x < 2; x++) {
-      const int grow = pc.row_of_pair[tok * 2 + (slot_a ^ x)];
-      if (cc == 0 && wave == 0) growmap[x][rl] = grow;
-    }
   }
-  // MFMA result role: this lane's row's routing weights
+  // MFMA result role: this lane's row's routing weights, and its grouped row with expert hi
   float wx[2];
+  int grow;
   {
     const int64_t tok = tok_of_pos[row0 + (l31 < rows ? l31 : 0)];
-    const int slot_a = pc.idx[tok * 2] == ex[0] ? 0 : 1;
+    const int slot_a = pc.idx[tok * 2] == ex[0] ? 0 : 1;   // expert a's slot of this token
     wx[0] = pc.w[tok * 2 + slot_a];
     wx[1] = pc.w[tok * 2 + (slot_a ^ 1)];
+    grow = pc.row_of_pair[tok * 2 + (slot_a ^ hi)];
   }
   f32x16_t accq[2];
 #pragma unroll
@@ -150,6 +146,7 @@ __global__ __launch_bounds__(FT_WAVES * 64, 2) void swiglu_fwd_pg_kernel(
     }
     load_wf(cf);
   }
+  growmap[hi][l31] = grow;   // every wavefront the same (under a condition the load waits for its turn there)
   for (int sb = sb_lo + wave; sb < sb_hi; sb += FT_WAVES) {
     const int c0 = sb * FT_SB;
     const int cn = sb + FT_WAVES < sb_hi ? c0 + FT_WAVES * FT_SB : c0;   // next (or again this)
