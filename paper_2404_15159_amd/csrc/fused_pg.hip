@@ -11,13 +11,14 @@
 // rank-r deltas there by MFMA: no delta is rounded, and the element math (13 -> 9 vector instructions per
 // pair and column in the forward) works on a lane's 16 columns of one row.  A lane reads its own columns and unpacks
 // them; as a product with the identity that is 10-15 % fewer vector instructions and the same time (step at the 7B
-// shape 2047 us, read 2044), but a non-finite element then makes NaN of the 31 columns beside it.  What bounds them is memory (the forward moves 4.4 TB/s, the copy rate being 5.1)
-// and, in the backward, the latency of its chain of phases at two wavefronts per SIMD; so what is left to
-// gain is bytes: the backward makes the gradient sums of its three d_ff-wide operands itself, and neither the
-// activations nor dg and du of a pair are ever stored.  4096 tokens at the 7B shape, us: forward 135 -> 95,
-// backward 268 -> 276 + 25 for adding its partial sums, gradient sums 150 -> 67; the step 2220 -> 2116;
-// 16384 tokens of the L3-8B shape: 529 -> 352, 1162 -> 1407 + 31, 855 -> 270.
-// A non-finite G, U or H stays in its column, and in its row but for the row's own rank-r products.
+// shape 2047 us, read 2044), but a non-finite element then makes NaN of the 31 columns beside it.  (As it is, it
+// reaches its own column and what is formed from its whole row.)
+// What bounds them is memory (the forward moves 4.4 TB/s, the copy rate being 5.1) and, in the backward, the
+// latency of its chain of phases at two wavefronts per SIMD; so what is left to gain is bytes: the backward
+// makes the gradient sums of its three d_ff-wide operands itself, and neither the activations nor dg and du of a
+// pair are ever stored.  4096 tokens at the 7B shape, us, against the two kernels that stored all three: forward 135 ->
+// 91, backward 268 -> 258 + 26 for adding its partial sums, gradient sums 150 -> 65; the step 2146 -> 2055.
+// 16384 tokens of the L3-8B shape: 529 -> 337, 1162 -> 1363 + 38, 855 -> 271; 10716 -> 10340.
 //
 // LDS tiles are those of csrc/fused.hip.
 #include "fused_common.h"
@@ -619,20 +620,24 @@ bool fused_pg_ok(const PairCtx &pc, int f) {
          f >= 64 && (int64_t)2 * pc.T * f < ((int64_t)1 << 31);
 }
 
-// The backward takes at least 24 (rank 8) or 36 (rank 16) tokens per pair of experts that can occur (pairs of one
-// adapter's own), or 3400 in all: with fewer, tiles are mostly padding and the expert, with it r columns of sums to flush, changes with
-// every tile; the expert-grouped stage, its combine and its sums are ahead then.  Training step, us, here / there, rank
-// 16: 7B shape, 8 experts, 784 tokens 675 / 671, 1000 733 / 719, 1050 802 / 801, 1300 963 / 972; 12 experts 2000
-// 1236 / 1225, 2400 1558 / 1560; 16 experts 3000 1824 / 1799, 3400 1980 / 1983, 4200 2406 / 2409; two adapters of 8, 1900 1275 / 1252, 2048
-// 1274 / 1283.  Rank 8: 7B shape, 8 experts, 600 532 / 530, 784 640 / 643; 16 experts 2200 1516 / 1489, 3000
-// 1742 / 1767.  (d_ff of 4096 to 8192, where the other form's sums fill the chip badly, would gain 3 to 6 % from 600
-// tokens on.)  Below 1024 items, column blocks times tiles, two workgroups per CU have one each: 1024 x 2752, 1000
-// tokens 224 / 211, 1500 230 / 235; 512 x 1536, 1800 187 / 179, 3000 216 / 218.  And few column blocks leave
-// pg_sums_reduce_kernel a long chain of runs: 256 x 512, 10000 tokens 288 / 263, 20000 411 / 419; x 704, 7000 252 / 235,
-// 14000 359 / 375; x 1024, 5000 241 / 235, 7000 281 / 284.
+// The backward takes at least 24 (rank 8) or 36 (rank 16) tokens per pair of experts that can occur (pairs of
+// one adapter's own), or 3400 in all: with fewer, tiles are mostly padding and the expert, with it r columns of
+// sums to flush, changes with every tile; the expert-grouped stage, its combine and its sums are ahead then.
+// Where those sums are cut into row slices, which costs them another 15 us, 28 are enough at rank 16. Training
+// step, us, here / there, rank 16: 7B shape, 8 experts, 784 tokens 675 / 671, 1000 733 / 719, 1050 802 / 801,
+// 1300 963 / 972; 12 experts 2000 1236 / 1225, 2400 1558 / 1560; 16 experts 3000 1824 / 1799, 3400 1980 / 1983,
+// 4200 2406 / 2409; two adapters of 8, 1900 1275 / 1252, 2048 1274 / 1283; sums cut: 2048 x 5504 784 311 / 332,
+// 2048 x 8192 784 385 / 402, 6 experts of the 7B shape 420 446 / 465. Rank 8: 7B shape, 8 experts, 600 532 /
+// 530, 784 640 / 643; 16 experts 2200 1516 / 1489, 3000 1742 / 1767. Below 1024 items, column blocks times
+// tiles, two workgroups per CU have one each: 1024 x 2752, 1000 tokens 224 / 211, 1500 230 / 235; 512 x 1536,
+// 1800 187 / 179, 3000 216 / 218. And few column blocks leave pg_sums_reduce_kernel a long chain of runs: 256 x
+// 512, 10000 tokens 288 / 263, 20000 411 / 419; x 704, 7000 252 / 235, 14000 359 / 375; x 1024, 5000 241 / 235,
+// 7000 281 / 284.
 static bool pg_bwd_size(int f, int T, int N, int Nl, int r) {
+  const bool cut = group_outer_mfma_partial_floats(N, r, f, 2 * T, 3) > 0;
   const int64_t blocks = fused_pg_bwd_splits(f), items = blocks * ((T + FT_ROWS - 1) / FT_ROWS);
-  return (4ll * T >= (24ll + 3 * r) * N * (Nl - 1) || T >= 3400) && items >= 1024 && items * blocks >= 12000;
+  const int64_t half_pair = r <= 8 ? 12 : cut ? 14 : 18;
+  return (T >= half_pair * N * (Nl - 1) || T >= 3400) && items >= 1024 && items * blocks >= 12000;
 }
 bool fused_pg_bwd_ok(const PairCtx &pc, int f, int Nl) {
   return fused_pg_ok(pc, f) && pg_bwd_size(f, pc.T, pc.N, Nl, pc.r);

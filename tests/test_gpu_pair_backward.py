@@ -18,8 +18,8 @@ BASE = synth.CONFIGS["llama2_7b"]
 
 
 @pytest.mark.parametrize("T,f,N,r", [(783, 5632, 8, 16), (784, 5632, 8, 16), (1000, 4648, 8, 8), (1100, 4168, 3, 16),
-                                     (3400, 1288, 16, 8), (900, 4688, 2, 4), (2048, 2064, 7, 12), (1007, 5632, 8, 16),
-                                     (1008, 5632, 8, 16), (671, 6912, 8, 8), (672, 6912, 8, 8), (3399, 1408, 16, 16), (3400, 1408, 16, 16), (3808, 1280, 4, 16),
+                                     (3400, 1288, 16, 8), (900, 4688, 2, 4), (2048, 2064, 7, 12), (1007, 10304, 8, 16),
+                                     (1008, 10304, 8, 16), (671, 6912, 8, 8), (672, 6912, 8, 8), (3399, 1408, 16, 16), (3400, 1408, 16, 16), (3808, 1280, 4, 16),
                                      (3840, 1280, 4, 16)])
 def test_pair_backward_matches_oracle(T, f, N, r):
     cfg = synth.scaled(BASE, name="pair_bwd", T=T, d=64, d_ff=f, N=N, k=2, r=r, alpha=2.0 * r)
