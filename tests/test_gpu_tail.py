@@ -1,6 +1,7 @@
 """GPU parity of the row-wise steps that share one launch behind the fused backward stage: ranks whose rows
 do not fill a 256-thread block evenly, pair counts that end inside one, with and without the sums over a
-token's pairs (top-2 on pair-grouped tiles makes them itself); more workgroups than a grid row holds.  Against the oracle, usual tolerances."""
+token's pairs (top-2 on pair-grouped tiles makes them itself); more workgroups than a grid row
+holds.  Against the oracle, usual tolerances."""
 import pytest
 
 from oracle import mixlora_oracle as orc
